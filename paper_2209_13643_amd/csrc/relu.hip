@@ -27,6 +27,8 @@
 
 #include <atomic>
 #include "msb_pack.h"
+#include "relu_fused.h"
+#include "relu_steps.h"
 
 namespace {
 
@@ -35,8 +37,6 @@ constexpr int kMaxChunks = 64;
 // chunk size picked when the caller passes n_chunks = 0 and the lane sets none (mpc_ctx_set_relu_chunk)
 constexpr size_t kAutoChunkElems = (size_t)1 << 20;
 constexpr size_t kAutoChunkElemsPacked = (size_t)1 << 22;   // the packed path: a third of the bytes per element
-
-struct alignas(16) u64x2 { u64 a, b; };
 
 // Everything one party's kernels may touch.
 struct ReluParty {
@@ -55,66 +55,6 @@ struct ReluParty {
     u64* y; u8* s_bit; u64* s_arith;
     size_t n;       // total elements (stride of the [12][n] / [4][n] arrays)
 };
-
-template <int V> struct Pack;
-template <> struct Pack<1> {
-    u64 v[1];
-    __device__ static Pack ld(const u64* p, size_t i) { Pack r; r.v[0] = p[i]; return r; }
-    __device__ void st(u64* p, size_t i) const { p[i] = v[0]; }
-};
-template <> struct Pack<2> {
-    u64 v[2];
-    __device__ static Pack ld(const u64* p, size_t i)
-    {
-        const u64x2 t = *reinterpret_cast<const u64x2*>(p + i);
-        Pack r; r.v[0] = t.a; r.v[1] = t.b; return r;
-    }
-    __device__ void st(u64* p, size_t i) const
-    {
-        u64x2 t; t.a = v[0]; t.b = v[1];
-        *reinterpret_cast<u64x2*>(p + i) = t;
-    }
-};
-
-template <> struct Pack<4> {
-    u64 v[4];
-    __device__ static Pack ld(const u64* p, size_t i)
-    {
-        const u64x2 t = *reinterpret_cast<const u64x2*>(p + i), u = *reinterpret_cast<const u64x2*>(p + i + 2);
-        Pack r; r.v[0] = t.a; r.v[1] = t.b; r.v[2] = u.a; r.v[3] = u.b; return r;
-    }
-    __device__ void st(u64* p, size_t i) const
-    {
-        u64x2 t, u; t.a = v[0]; t.b = v[1]; u.a = v[2]; u.b = v[3];
-        *reinterpret_cast<u64x2*>(p + i) = t; *reinterpret_cast<u64x2*>(p + i + 2) = u;
-    }
-};
-
-// V consecutive bytes (one per element): a single 16- or 32-bit access when V is 2 or 4
-template <int V> __device__ __forceinline__ void ld_bytes(const u8* p, size_t i, u8 (&out)[V])
-{
-    if constexpr (V == 4) { const uint32_t w = *reinterpret_cast<const uint32_t*>(p + i);
-                            out[0] = (u8)w; out[1] = (u8)(w >> 8); out[2] = (u8)(w >> 16); out[3] = (u8)(w >> 24); }
-    else if constexpr (V == 2) { const uint16_t w = *reinterpret_cast<const uint16_t*>(p + i);
-                                 out[0] = (u8)w; out[1] = (u8)(w >> 8); }
-    else out[0] = p[i];
-}
-template <int V> __device__ __forceinline__ void st_bytes(u8* p, size_t i, const u8 (&in)[V])
-{
-    if constexpr (V == 4) *reinterpret_cast<uint32_t*>(p + i) = (uint32_t)in[0] | ((uint32_t)in[1] << 8) | ((uint32_t)in[2] << 16) | ((uint32_t)in[3] << 24);
-    else if constexpr (V == 2) *reinterpret_cast<uint16_t*>(p + i) = (uint16_t)((uint16_t)in[0] | ((uint16_t)in[1] << 8));
-    else p[i] = in[0];
-}
-
-// Beaver AND, one party's side (Eq. 4; Alg. 4 for the party that adds d & g):
-// d, g are the opened masked operands, (a, b, c) this party's triple words.
-template <int PARTY>
-__device__ __forceinline__ u64 and_finish(u64 d, u64 g, u64 a, u64 b, u64 c)
-{
-    u64 t = c ^ (d & b) ^ (g & a);
-    if (PARTY == 0) t ^= d & g;
-    return t;
-}
 
 #define FOR_ELEMS(V)                                                                         \
     const size_t stride_ = (size_t)gridDim.x * blockDim.x * V;                               \
@@ -149,34 +89,11 @@ __device__ __forceinline__ void b_first(const ReluParty& p, size_t lo, size_t hi
     }
 }
 
-// ---- adder topologies -----------------------------------------------------------
-// TOPO 0: Kogge-Stone, level l combines every position p with p - 2^l.
-// TOPO 1: the prefix tree of the listing in Sec. 4.2, level l joins blocks of
-// 2^l bits: the upper half of each 2^(l+1)-bit block (om) combines with the top
-// bit of its lower half (im), copied over the upper half by a multiply (mu).
-constexpr u64 tree_im(int l) { u64 m = 0; for (int b = 0; b < 64; b += 2 << l) m |= (u64)1 << (b + (1 << l) - 1); return m; }
-constexpr u64 tree_om(int l)
-{
-    const int half = 1 << l; u64 m = 0;
-    for (int b = 0; b < 64; b += 2 * half) m |= (half == 64 ? ~(u64)0 : (((u64)1 << half) - 1)) << (b + half);
-    return m;
-}
-constexpr u64 tree_mu(int l) { u64 m = 0; for (int k = 1; k <= (1 << l); ++k) m |= (u64)1 << k; return m; }
-// left operand of a level's ANDs, from P
-template <int TOPO, int L> __device__ __forceinline__ u64 op_x(u64 P) { if constexpr (TOPO) return P & tree_om(L); else return P; }
-// right operand, from G (first AND) or P (second AND)
-template <int TOPO, int L> __device__ __forceinline__ u64 op_y(u64 w)
-{
-    if constexpr (TOPO) return (w & tree_im(L)) * tree_mu(L); else return w << (1 << L);
-}
-// the part of P a level leaves untouched
-template <int TOPO, int L> __device__ __forceinline__ u64 keep_p(u64 P) { if constexpr (TOPO) return P & ~tree_om(L); else return 0; }
-
 // ---- K_level ------------------------------------------------------------------
 // LEVEL 0 finishes G = U & V (triple 0, own masked words re-read from the send
 // buffer); LEVEL l > 0 finishes the two ANDs of level l-1 from the carried
 // (G, P).  Then masks the operands of level LEVEL.
-template <int PARTY, int LEVEL, int V, int TOPO, bool PUT>
+template <int PARTY, int LEVEL, int V, int TOPO>
 __device__ __forceinline__ void b_level(const ReluParty& p, size_t lo, size_t hi)
 {
     const size_t n = p.n;
@@ -186,19 +103,7 @@ __device__ __forceinline__ void b_level(const ReluParty& p, size_t lo, size_t hi
             const Pack<V> rd = Pack<V>::ld(p.recv, i), rg = Pack<V>::ld(p.recv + n, i);
             const Pack<V> a = Pack<V>::ld(p.ta, i), b = Pack<V>::ld(p.tb, i), c = Pack<V>::ld(p.tc, i);
             P = Pack<V>::ld(p.P, i);
-            Pack<V> sd, sg;
-            if constexpr (PUT) {
-                // own masked words of G = U & V, re-formed: the own word of the pair (U, V) is x ^ r, the other P ^ it
-                const Pack<V> x = Pack<V>::ld(p.x, i), r = Pack<V>::ld(p.r, i);
-#pragma unroll
-                for (int k = 0; k < V; ++k) {
-                    const u64 own = x.v[k] ^ r.v[k], other = P.v[k] ^ own;
-                    sd.v[k] = (PARTY == 0 ? own : other) ^ a.v[k];
-                    sg.v[k] = (PARTY == 0 ? other : own) ^ b.v[k];
-                }
-            } else {
-                sd = Pack<V>::ld(p.send, i); sg = Pack<V>::ld(p.send + n, i);
-            }
+            const Pack<V> sd = Pack<V>::ld(p.send, i), sg = Pack<V>::ld(p.send + n, i);
 #pragma unroll
             for (int k = 0; k < V; ++k)
                 G.v[k] = and_finish<PARTY>(sd.v[k] ^ rd.v[k], sg.v[k] ^ rg.v[k], a.v[k], b.v[k], c.v[k]);
@@ -229,24 +134,20 @@ __device__ __forceinline__ void b_level(const ReluParty& p, size_t lo, size_t hi
         Pack<V> d1, g1;
 #pragma unroll
         for (int k = 0; k < V; ++k) { d1.v[k] = op_x<TOPO, LEVEL>(P.v[k]) ^ na1.v[k]; g1.v[k] = op_y<TOPO, LEVEL>(G.v[k]) ^ nb1.v[k]; }
-        // The next stage recomputes this party's own masked words from the carried (G, P), so with the
-        // exchange by remote store they go to the peer only; the copy exchange needs them in the send buffer.
-        if constexpr (PUT) { d1.st(p.put, i); g1.st(p.put + n, i); }
-        else               { d1.st(p.send, i); g1.st(p.send + n, i); }
+        d1.st(p.send, i); g1.st(p.send + n, i);
         if constexpr (LEVEL < 5) {
             const Pack<V> na2 = Pack<V>::ld(p.ta + u2 * n, i), nb2 = Pack<V>::ld(p.tb + u2 * n, i);
             Pack<V> d2, g2;
 #pragma unroll
             for (int k = 0; k < V; ++k) { d2.v[k] = op_x<TOPO, LEVEL>(P.v[k]) ^ na2.v[k]; g2.v[k] = op_y<TOPO, LEVEL>(P.v[k]) ^ nb2.v[k]; }
-            if constexpr (PUT) { d2.st(p.put + 2 * n, i); g2.st(p.put + 3 * n, i); }
-            else               { d2.st(p.send + 2 * n, i); g2.st(p.send + 3 * n, i); }
+            d2.st(p.send + 2 * n, i); g2.st(p.send + 3 * n, i);
         }
         G.st(p.G, i); P.st(p.P, i);
     }
 }
 
 // ---- K_sign -------------------------------------------------------------------
-template <int PARTY, int V, int TOPO, bool PUT>
+template <int PARTY, int V, int TOPO>
 __device__ __forceinline__ void b_sign(const ReluParty& p, size_t lo, size_t hi)
 {
     const size_t n = p.n;
@@ -269,7 +170,6 @@ __device__ __forceinline__ void b_sign(const ReluParty& p, size_t lo, size_t hi)
         }
         if (p.s_bit) st_bytes<V>(p.s_bit, i, sb);
         st_bytes<V>(p.sendb, i, mb);
-        if constexpr (PUT) st_bytes<V>(p.putb, i, mb);
     }
 }
 
@@ -557,8 +457,9 @@ struct ReluWs {
     u64 *send[2], *recv[2];     // [4][n]
     u8 *sendb[2], *recvb[2];
     u64 *G[2], *P[2]; u8* p63[2];
-    u64* recv2[2];                          // second receive buffer (exchange by remote store alternates)
+    u64* recv2[2];                          // packed chain: second receive buffer (exchange by remote store alternates)
     u64 *sendL[2], *recvL[2], *gsel[2];     // packed levels only
+    u64* box;                               // all of it: the receive buffers of the one-launch chain
     size_t bytes; bool ok;
 };
 
@@ -571,8 +472,9 @@ ReluWs carve_relu(u8* base, size_t cap, size_t n)
         r.sendb[i] = w.take<u8>(n); r.recvb[i] = w.take<u8>(n);
         r.G[i] = w.take<u64>(n); r.P[i] = w.take<u64>(n); r.p63[i] = w.take<u8>(n);
     }
-    for (int i = 0; i < 2; ++i) r.recv2[i] = w.take<u64>(4 * n);      // only touched by the remote-store exchange
-    r.bytes = w.off; r.ok = w.ok;
+    r.box = reinterpret_cast<u64*>(base);
+    const size_t box = relu_fused_box_bytes(n);
+    r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
     return r;
 }
 
@@ -596,40 +498,32 @@ enum Stage { ST_FIRST = 0, ST_LEVEL0 = 1, ST_SIGN = 7, ST_B2A = 8, ST_SELECT = 9
 
 // One launch runs a protocol stage for both parties (blockIdx.y = party) or,
 // when the parties live on different streams, for party `only` alone.
-template <int STAGE, int PARTY, int V, int TOPO, bool PUT>
+template <int STAGE, int PARTY, int V, int TOPO>
 __device__ __forceinline__ void stage_body(const ReluParty& p, size_t lo, size_t hi)
 {
-    if constexpr (STAGE == 0) b_first<PARTY, V, PUT>(p, lo, hi);
-    else if constexpr (STAGE >= 1 && STAGE <= 6) b_level<PARTY, STAGE - 1, V, TOPO, PUT>(p, lo, hi);
-    else if constexpr (STAGE == 7) b_sign<PARTY, V, TOPO, PUT>(p, lo, hi);
-    else if constexpr (STAGE == 8) b_b2a<PARTY, V, PUT>(p, lo, hi);
-    else b_select<PARTY, V, PUT>(p, lo, hi);
+    if constexpr (STAGE == 0) b_first<PARTY, V, false>(p, lo, hi);
+    else if constexpr (STAGE >= 1 && STAGE <= 6) b_level<PARTY, STAGE - 1, V, TOPO>(p, lo, hi);
+    else if constexpr (STAGE == 7) b_sign<PARTY, V, TOPO>(p, lo, hi);
+    else if constexpr (STAGE == 8) b_b2a<PARTY, V, false>(p, lo, hi);
+    else b_select<PARTY, V, false>(p, lo, hi);
 }
 
-template <int STAGE, int V, int TOPO, bool PUT>
+template <int STAGE, int V, int TOPO>
 __global__ __launch_bounds__(kThreads) void k_relu_stage(ReluParty p0, ReluParty p1, int only, size_t lo, size_t hi)
 {
     const int party = only >= 0 ? only : (int)blockIdx.y;
-    if (party == 0) stage_body<STAGE, 0, V, TOPO, PUT>(p0, lo, hi);
-    else            stage_body<STAGE, 1, V, TOPO, PUT>(p1, lo, hi);
+    if (party == 0) stage_body<STAGE, 0, V, TOPO>(p0, lo, hi);
+    else            stage_body<STAGE, 1, V, TOPO>(p1, lo, hi);
 }
 
 template <int STAGE, int V>
 void launch_stage_t(hipStream_t st, const ReluParty& p0, const ReluParty& p1, int only, size_t lo, size_t hi, int topo)
 {
     const dim3 grid(grid_for((hi - lo + V - 1) / V), only >= 0 ? 1 : 2), block(kThreads);
-    // only the carry-network stages depend on the topology; the last stage sends nothing, but with the exchange
-    // by remote store it re-forms its own masked words instead of reading them back
+    // only the carry-network stages depend on the topology
     constexpr int T1 = (STAGE >= 1 && STAGE <= 7) ? 1 : 0;
-    constexpr bool P1 = true;
-    const bool put = p0.put != nullptr && P1;
-    if (topo && T1) {
-        if (put) hipLaunchKernelGGL((k_relu_stage<STAGE, V, T1, P1>), grid, block, 0, st, p0, p1, only, lo, hi);
-        else     hipLaunchKernelGGL((k_relu_stage<STAGE, V, T1, false>), grid, block, 0, st, p0, p1, only, lo, hi);
-    } else {
-        if (put) hipLaunchKernelGGL((k_relu_stage<STAGE, V, 0, P1>), grid, block, 0, st, p0, p1, only, lo, hi);
-        else     hipLaunchKernelGGL((k_relu_stage<STAGE, V, 0, false>), grid, block, 0, st, p0, p1, only, lo, hi);
-    }
+    if (topo && T1) hipLaunchKernelGGL((k_relu_stage<STAGE, V, T1>), grid, block, 0, st, p0, p1, only, lo, hi);
+    else            hipLaunchKernelGGL((k_relu_stage<STAGE, V, 0>), grid, block, 0, st, p0, p1, only, lo, hi);
 }
 
 template <int V>
@@ -740,9 +634,17 @@ int wire_words(mpc_ctx* c, const u64* src0, u64* dst0, const u64* src1, u64* dst
 // The protocol on n elements whose buffers are described by parties[2].  With
 // `geom` the carry chain runs on packed words (mpc_relu_msb), without it on
 // whole words.
-int relu_run(mpc_ctx* c, ReluParty (&pp)[2], size_t n, int n_chunks, const MsbGeom* geom = nullptr)
+int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, const MsbGeom* geom = nullptr)
 {
     const bool one_queue = c->s[0] == c->s[1] && c->s[1] == c->s[2];   // in-order queue: no events needed
+    if (one_queue && c->exchange_put && !geom) {
+        FusedRelu q{};
+        for (int i = 0; i < 2; ++i)
+            q.p[i] = FusedReluParty{ pp[i].x, pp[i].r, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].rb, pp[i].ra,
+                                     pp[i].ma, pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_bit, pp[i].s_arith };
+        q.box = box; q.n = n;
+        return launch_relu_fused(c, c->s[0], q, c->adder);
+    }
     // chunk boundaries: multiples of four elements, and of 256 on the packed path
     // (four whole words of the deepest level)
     const size_t align = geom ? 256 : 4;
@@ -961,7 +863,7 @@ int relu_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat, mpc_share
     ReluParty pp[2];
     for (int i = 0; i < 2; ++i)
         fill_party(pp[i], i, x.p[i], mat, w, y.p[i], s_bit ? s_bit[i] : nullptr, s_arith ? s_arith[i] : nullptr, n);
-    MPC_TRY(relu_run(c, pp, n, n_chunks, packed ? &g : nullptr));
+    MPC_TRY(relu_run(c, pp, w.box, n, n_chunks, packed ? &g : nullptr));
     if (pi >= 0) {      // the region ends when both parties' last kernels are done
         MPC_TRY(chain(c, c->s[1], c->s[0]));
         prof_end(c, MPC_PROF_RELU, pi, c->s[0]);
@@ -1016,7 +918,7 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
         fill_party(pp[i], i, d1[i], mat1, w1, r1[i], nullptr, s1 ? s1[i] : nullptr, 2 * n_out);
     }
     MPC_TRY(lane_join(c));
-    MPC_TRY(relu_run(c, pp, 2 * n_out, n_chunks, packed ? &g1 : nullptr));
+    MPC_TRY(relu_run(c, pp, w1.box, 2 * n_out, n_chunks, packed ? &g1 : nullptr));
     // second level: max of the two winners; out = v + ReLU(u - v)
     for (int i = 0; i < 2; ++i) {
         hipLaunchKernelGGL(k_pool_l2, grid, block, 0, c->s[i], x.p[i], r1[i], v[i], d2[i], B, H, W, C);
@@ -1024,7 +926,7 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
         fill_party(pp[i], i, d2[i], mat2, w2, y.p[i], nullptr, s2 ? s2[i] : nullptr, n_out);
     }
     MPC_TRY(lane_join(c));
-    MPC_TRY(relu_run(c, pp, n_out, n_chunks, packed ? &g2 : nullptr));
+    MPC_TRY(relu_run(c, pp, w2.box, n_out, n_chunks, packed ? &g2 : nullptr));
     for (int i = 0; i < 2; ++i)
         MPC_TRY(launch_add(c, c->s[i], y.p[i], v[i], y.p[i], n_out));
     return MPC_OK;
@@ -1034,12 +936,11 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
 // Its rounds exchange and carry state through a fixed array in the code object
 // instead of the caller's workspace.  Layout and size are those carve_relu gives
 // for kStaticMaxN elements: per party 2 x [4][n] words (sent / received), 2 x n
-// bytes, G, P (n words each), n bytes; then the two alternate receive buffers.
+// bytes, G, P (n words each), n bytes (the one-launch chain needs a third of that).
 constexpr size_t kStaticMaxN = 65536;
 constexpr size_t static_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 constexpr size_t kStaticBytes =
-    2 * (2 * static_up(32 * kStaticMaxN) + 2 * static_up(kStaticMaxN) + 2 * static_up(8 * kStaticMaxN) + static_up(kStaticMaxN)) +
-    2 * static_up(32 * kStaticMaxN);
+    2 * (2 * static_up(32 * kStaticMaxN) + 2 * static_up(kStaticMaxN) + 2 * static_up(8 * kStaticMaxN) + static_up(kStaticMaxN));
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 // Device address of `scratch` per device (every device holds its own copy of the

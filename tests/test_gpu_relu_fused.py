@@ -1,0 +1,55 @@
+"""GPU parity of the secure ReLU as one launch (single-queue lanes, exchange by remote store) against the CPU oracle at
+the sizes where its tiling can go wrong: fewer elements than a wave, ragged last tiles, the change from one to two
+elements per thread (65 536 | 65 537), several tiles per workgroup, and an output that overwrites the input."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2209_13643_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mpc():
+    from paper_2209_13643_amd import mpc as m
+    return m
+
+
+@pytest.fixture()
+def lane(mpc):
+    ln = mpc.Lane(0, single_queue=True)
+    ln.set_exchange("put")
+    yield ln
+    ln.sync()
+    ln.close()
+
+
+def dev(mpc, pair):
+    return tuple(mpc.to_device(p) for p in pair)
+
+
+def equal(mpc, got, want, what):
+    for i, w in enumerate(want):
+        g = mpc.to_host(got[i]).reshape(w.shape)
+        assert np.array_equal(g, w), f"{what}: party {i} differs at {np.argwhere(g != w)[:3].tolist()} of {w.size}"
+
+
+SIZES = [1, 2, 3, 63, 64, 65, 127, 65535, 65536, 65537, 131072, 131073, 262144 + 130]
+
+
+@pytest.mark.parametrize("adder", ["kogge-stone", "tree"])
+@pytest.mark.parametrize("n", SIZES)
+def test_one_launch_relu(mpc, lane, n, adder):
+    print(f"one-launch relu n={n} {adder}", flush=True)
+    rng = np.random.default_rng(n)
+    xs = synth.share_additive(rng, synth.normal_fixed(rng, n, 4.0))
+    mat = synth.deal_relu_material(rng, n)
+    want = oracle.relu(xs, mat, adder=adder)
+    lane.set_adder(adder)
+    x = dev(mpc, xs)
+    y, sb, sa = lane.relu(x, mpc.material_to_device(mat), want_sign=True, out=x if n % 2 else None)
+    lane.sync()
+    equal(mpc, y, want.y, "output")
+    equal(mpc, sb, want.s_bit, "sign bit share")
+    equal(mpc, sa, want.s_arith, "sign arithmetic share")
