@@ -156,8 +156,8 @@ int mpc_graph_destroy(mpc_graph* graph);
  *   two devices); the next round starts when that kernel has ended.  One launch
  *   per round instead of two and one traversal less per exchanged word.  Takes
  *   effect on lanes whose three streams are one queue; elsewhere the copy
- *   kernels are used.  Results are identical.  mpc_relu and mpc_maxpool2x2
- *   run all rounds in one launch in this mode: a round ends when the waves of
+ *   kernels are used.  Results are identical.  mpc_relu,
+ *   mpc_relu_msb and the max-pool calls run all rounds in one launch in this mode: a round ends when the waves of
  *   both parties that hold the same elements have stored their words
  *   (n_chunks then has nothing to cut).  The three-party ReLU and
  *   max-pool calls honour it on every lane (they use one stream): each stage

@@ -41,3 +41,30 @@ inline size_t msb_level_words(size_t n, int l)
     const size_t n64 = (n + 63) / 64 * 64;
     return ((n64 >> (l + 1)) + 3) / 4 * 4;
 }
+
+// Word counts and offsets of the packed arrays for n elements.
+struct MsbGeom {
+    size_t n;
+    size_t pw[6];      // words of level l's packed arrays: ceil64(n) / 2^(l+1), rounded up to 4
+    size_t toff[12];   // offset of triple t inside a packed and_a / and_b / and_c buffer
+    size_t loff[6];    // offset of level l's [4][pw] block inside sendL / recvL
+    size_t goff[6];    // offset of level l's words inside gsel
+    size_t words_triples, words_level_blocks, words_gsel;
+};
+
+inline MsbGeom msb_geom(size_t n)
+{
+    MsbGeom g{};
+    g.n = n;
+    size_t lo = 0, go = 0;
+    for (int l = 0; l < 6; ++l) {
+        g.pw[l] = msb_level_words(n, l);
+        g.loff[l] = lo; lo += 4 * g.pw[l];
+        g.goff[l] = go; go += g.pw[l];
+    }
+    g.toff[0] = 0;
+    size_t to = (n + 3) / 4 * 4;
+    for (int t = 1; t < 12; ++t) { g.toff[t] = to; to += g.pw[(t - 1) / 2]; }
+    g.words_triples = to; g.words_level_blocks = lo; g.words_gsel = go;
+    return g;
+}

@@ -48,8 +48,6 @@ struct ReluParty {
     const u64* recv;   // [4][n] words received from the other party
     u8* sendb; const u8* recvb;    // byte exchange (B2A)
     u64* G; u64* P; u8* p63;       // carried state
-    u64* put; u8* putb; u64* putL; // exchange by remote store: the peer's receive buffers (null: copy kernels)
-    u64* recv_alt;                 // second receive buffer, alternating with recv from stage to stage in that mode
     u64* sendL; const u64* recvL;  // packed levels (mpc_relu_msb): per level a [4][pw] block
     u64* gsel;                     // packed levels: the G bits a level keeps
     u64* y; u8* s_bit; u64* s_arith;
@@ -61,7 +59,7 @@ struct ReluParty {
     for (size_t i = lo + ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * V; i < hi; i += stride_)
 
 // ---- K_first ------------------------------------------------------------------
-template <int PARTY, int V, bool PUT>
+template <int PARTY, int V>
 __device__ __forceinline__ void b_first(const ReluParty& p, size_t lo, size_t hi)
 {
     const size_t n = p.n;
@@ -80,10 +78,7 @@ __device__ __forceinline__ void b_first(const ReluParty& p, size_t lo, size_t hi
             P.v[k] = U ^ Vv;
             top[k] = (u8)(P.v[k] >> 63);
         }
-        // with the exchange by remote store the next stage re-forms this party's own masked words from x, r and P
-        // (U or V is the own x ^ r, the other one P ^ that), so they go to the peer only
-        if constexpr (PUT) { d.st(p.put, i); g.st(p.put + n, i); }
-        else               { d.st(p.send, i); g.st(p.send + n, i); }
+        d.st(p.send, i); g.st(p.send + n, i);
         P.st(p.P, i);
         st_bytes<V>(p.p63, i, top);
     }
@@ -174,7 +169,7 @@ __device__ __forceinline__ void b_sign(const ReluParty& p, size_t lo, size_t hi)
 }
 
 // ---- K_b2a --------------------------------------------------------------------
-template <int PARTY, int V, bool PUT>
+template <int PARTY, int V>
 __device__ __forceinline__ void b_b2a(const ReluParty& p, size_t lo, size_t hi)
 {
     const size_t n = p.n;
@@ -193,37 +188,20 @@ __device__ __forceinline__ void b_b2a(const ReluParty& p, size_t lo, size_t hi)
             e.v[k] = x.v[k] - ma.v[k];
             f.v[k] = m - mb.v[k];
         }
-        // with the exchange by remote store the select stage re-forms this party's own masked words: peer only
-        if constexpr (PUT) { e.st(p.put, i); f.st(p.put + n, i); }
-        else               { e.st(p.send, i); f.st(p.send + n, i); }
+        e.st(p.send, i); f.st(p.send + n, i);
         if (p.s_arith) sa.st(p.s_arith, i);
     }
 }
 
 // ---- K_select -----------------------------------------------------------------
-template <int PARTY, int V, bool PUT>
+template <int PARTY, int V>
 __device__ __forceinline__ void b_select(const ReluParty& p, size_t lo, size_t hi)
 {
     const size_t n = p.n;
     FOR_ELEMS(V) {
         const Pack<V> re = Pack<V>::ld(p.recv, i), rf = Pack<V>::ld(p.recv + n, i);
         const Pack<V> ma = Pack<V>::ld(p.ma, i), mb = Pack<V>::ld(p.mb, i), mc = Pack<V>::ld(p.mc, i);
-        Pack<V> se, sf;
-        if constexpr (PUT) {
-            // own masked words of the select product, re-formed as the B2A stage formed them
-            const Pack<V> x = Pack<V>::ld(p.x, i), ra = Pack<V>::ld(p.ra, i);
-            u8 own[V], got[V];
-            ld_bytes<V>(p.sendb, i, own); ld_bytes<V>(p.recvb, i, got);
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const u64 v = (u64)(own[k] ^ got[k]);
-                const u64 sa = ra.v[k] - 2 * v * ra.v[k] + (PARTY == 0 ? v : 0);
-                se.v[k] = x.v[k] - ma.v[k];
-                sf.v[k] = ((PARTY == 0 ? (u64)1 : (u64)0) - sa) - mb.v[k];
-            }
-        } else {
-            se = Pack<V>::ld(p.send, i); sf = Pack<V>::ld(p.send + n, i);
-        }
+        const Pack<V> se = Pack<V>::ld(p.send, i), sf = Pack<V>::ld(p.send + n, i);
         Pack<V> y;
 #pragma unroll
         for (int k = 0; k < V; ++k) {
@@ -237,33 +215,6 @@ __device__ __forceinline__ void b_select(const ReluParty& p, size_t lo, size_t h
 }
 
 // ---- MSB-only carry chain on packed words (bit geometry: msb_pack.h) -----------
-// Word counts and offsets of the packed arrays for n elements.
-struct MsbGeom {
-    size_t n;
-    size_t pw[6];      // words of level l's packed arrays: ceil64(n) / 2^(l+1), rounded up to 4
-    size_t toff[12];   // offset of triple t inside a packed and_a / and_b / and_c buffer
-    size_t loff[6];    // offset of level l's [4][pw] block inside sendL / recvL
-    size_t goff[6];    // offset of level l's words inside gsel
-    size_t words_triples, words_level_blocks, words_gsel;
-};
-
-MsbGeom msb_geom(size_t n)
-{
-    MsbGeom g{};
-    g.n = n;
-    size_t lo = 0, go = 0;
-    for (int l = 0; l < 6; ++l) {
-        g.pw[l] = msb_level_words(n, l);
-        g.loff[l] = lo; lo += 4 * g.pw[l];
-        g.goff[l] = go; go += g.pw[l];
-    }
-    g.toff[0] = 0;
-    size_t to = (n + 3) / 4 * 4;
-    for (int t = 1; t < 12; ++t) { g.toff[t] = to; to += g.pw[(t - 1) / 2]; }
-    g.words_triples = to; g.words_level_blocks = lo; g.words_gsel = go;
-    return g;
-}
-
 template <int V> __device__ __forceinline__ Pack<V> ld_upto(const u64* p, size_t i, size_t n)
 {
     if constexpr (V == 4) return Pack<4>::ld(p, i);      // the caller guarantees i + 3 < n
@@ -275,7 +226,7 @@ template <int V> __device__ __forceinline__ Pack<V> ld_upto(const u64* p, size_t
 
 // Stage 1 + LEVEL of the packed chain: finish the previous round's ANDs for the
 // 2 W input words behind W output words, regroup, and mask this level's operands.
-template <int PARTY, int LEVEL, int W, bool PUT>
+template <int PARTY, int LEVEL, int W>
 __device__ __forceinline__ void b_plevel(const ReluParty& p, const MsbGeom& g, size_t lo, size_t hi)
 {
     constexpr int d = 1 << LEVEL, s = 2 * d;
@@ -289,19 +240,7 @@ __device__ __forceinline__ void b_plevel(const ReluParty& p, const MsbGeom& g, s
             const Pack<2 * W> rd = ld_upto<2 * W>(p.recv, e, n), rg = ld_upto<2 * W>(p.recv + n, e, n);
             const Pack<2 * W> a = ld_upto<2 * W>(p.ta, e, n), b = ld_upto<2 * W>(p.tb, e, n), c = ld_upto<2 * W>(p.tc, e, n);
             P = ld_upto<2 * W>(p.P, e, n);
-            Pack<2 * W> sd, sg;
-            if constexpr (PUT) {
-                // own masked words of G = U & V, re-formed as in the whole-word level-0 stage
-                const Pack<2 * W> x = ld_upto<2 * W>(p.x, e, n), r = ld_upto<2 * W>(p.r, e, n);
-#pragma unroll
-                for (int k = 0; k < 2 * W; ++k) {
-                    const u64 own = x.v[k] ^ r.v[k], other = P.v[k] ^ own;
-                    sd.v[k] = (PARTY == 0 ? own : other) ^ a.v[k];
-                    sg.v[k] = (PARTY == 0 ? other : own) ^ b.v[k];
-                }
-            } else {
-                sd = ld_upto<2 * W>(p.send, e, n); sg = ld_upto<2 * W>(p.send + n, e, n);
-            }
+            const Pack<2 * W> sd = ld_upto<2 * W>(p.send, e, n), sg = ld_upto<2 * W>(p.send + n, e, n);
 #pragma unroll
             for (int k = 0; k < 2 * W; ++k)
                 G.v[k] = and_finish<PARTY>(sd.v[k] ^ rd.v[k], sg.v[k] ^ rg.v[k], a.v[k], b.v[k], c.v[k]);
@@ -341,16 +280,13 @@ __device__ __forceinline__ void b_plevel(const ReluParty& p, const MsbGeom& g, s
         Pack<W> d1, g1;
 #pragma unroll
         for (int k = 0; k < W; ++k) { d1.v[k] = X.v[k] ^ na1.v[k]; g1.v[k] = Y1.v[k] ^ nb1.v[k]; }
-        u64* po = PUT ? p.putL + g.loff[LEVEL] : nullptr;
         d1.st(so, j); g1.st(so + pl, j);
-        if constexpr (PUT) { d1.st(po, j); g1.st(po + pl, j); }
         if constexpr (LEVEL < 5) {
             const Pack<W> na2 = Pack<W>::ld(p.ta + g.toff[u2], j), nb2 = Pack<W>::ld(p.tb + g.toff[u2], j);
             Pack<W> d2, g2;
 #pragma unroll
             for (int k = 0; k < W; ++k) { d2.v[k] = X.v[k] ^ na2.v[k]; g2.v[k] = Y2.v[k] ^ nb2.v[k]; }
             d2.st(so + 2 * pl, j); g2.st(so + 3 * pl, j);
-            if constexpr (PUT) { d2.st(po + 2 * pl, j); g2.st(po + 3 * pl, j); }
         }
         Gk.st(p.gsel + g.goff[LEVEL], j);
     }
@@ -358,7 +294,7 @@ __device__ __forceinline__ void b_plevel(const ReluParty& p, const MsbGeom& g, s
 
 // Packed K_sign: finish level 5; element i's carry into bit 63 sits at bit
 // (62 + i) mod 64 of word i / 64.
-template <int PARTY, int V, bool PUT>
+template <int PARTY, int V>
 __device__ __forceinline__ void b_psign(const ReluParty& p, const MsbGeom& g, size_t lo, size_t hi)
 {
     const size_t p5 = g.pw[5];
@@ -381,7 +317,6 @@ __device__ __forceinline__ void b_psign(const ReluParty& p, const MsbGeom& g, si
         }
         if (p.s_bit) st_bytes<V>(p.s_bit, i, sb);
         st_bytes<V>(p.sendb, i, mb);
-        if constexpr (PUT) st_bytes<V>(p.putb, i, mb);
     }
 }
 
@@ -457,7 +392,6 @@ struct ReluWs {
     u64 *send[2], *recv[2];     // [4][n]
     u8 *sendb[2], *recvb[2];
     u64 *G[2], *P[2]; u8* p63[2];
-    u64* recv2[2];                          // packed chain: second receive buffer (exchange by remote store alternates)
     u64 *sendL[2], *recvL[2], *gsel[2];     // packed levels only
     u64* box;                               // all of it: the receive buffers of the one-launch chain
     size_t bytes; bool ok;
@@ -489,8 +423,9 @@ ReluWs carve_relu_msb(u8* base, size_t cap, size_t n, const MsbGeom& g)
         r.sendL[i] = w.take<u64>(g.words_level_blocks); r.recvL[i] = w.take<u64>(g.words_level_blocks);
         r.gsel[i] = w.take<u64>(g.words_gsel);
     }
-    for (int i = 0; i < 2; ++i) r.recv2[i] = w.take<u64>(2 * n);
-    r.bytes = w.off; r.ok = w.ok;
+    r.box = reinterpret_cast<u64*>(base);
+    const size_t box = relu_fused_msb_box_bytes(n);
+    r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
     return r;
 }
 
@@ -501,11 +436,11 @@ enum Stage { ST_FIRST = 0, ST_LEVEL0 = 1, ST_SIGN = 7, ST_B2A = 8, ST_SELECT = 9
 template <int STAGE, int PARTY, int V, int TOPO>
 __device__ __forceinline__ void stage_body(const ReluParty& p, size_t lo, size_t hi)
 {
-    if constexpr (STAGE == 0) b_first<PARTY, V, false>(p, lo, hi);
+    if constexpr (STAGE == 0) b_first<PARTY, V>(p, lo, hi);
     else if constexpr (STAGE >= 1 && STAGE <= 6) b_level<PARTY, STAGE - 1, V, TOPO>(p, lo, hi);
     else if constexpr (STAGE == 7) b_sign<PARTY, V, TOPO>(p, lo, hi);
-    else if constexpr (STAGE == 8) b_b2a<PARTY, V, false>(p, lo, hi);
-    else b_select<PARTY, V, false>(p, lo, hi);
+    else if constexpr (STAGE == 8) b_b2a<PARTY, V>(p, lo, hi);
+    else b_select<PARTY, V>(p, lo, hi);
 }
 
 template <int STAGE, int V, int TOPO>
@@ -545,24 +480,24 @@ void launch_stage(int stage, hipStream_t st, const ReluParty& p0, const ReluPart
 }
 
 // The packed chain: stages 1..7 work on packed words, the others are shared.
-template <int STAGE, int PARTY, int V, bool PUT>
+template <int STAGE, int PARTY, int V>
 __device__ __forceinline__ void stage_body_msb(const ReluParty& p, const MsbGeom& g, size_t lo, size_t hi)
 {
-    if constexpr (STAGE == 0) b_first<PARTY, V, PUT>(p, lo, hi);
-    else if constexpr (STAGE == 1) b_plevel<PARTY, 0, (V == 4 ? 2 : 1), PUT>(p, g, lo, hi);
-    else if constexpr (STAGE >= 2 && STAGE <= 6) b_plevel<PARTY, STAGE - 1, 2, PUT>(p, g, lo, hi);
-    else if constexpr (STAGE == 7) b_psign<PARTY, V, PUT>(p, g, lo, hi);
-    else if constexpr (STAGE == 8) b_b2a<PARTY, V, PUT>(p, lo, hi);
-    else b_select<PARTY, V, PUT>(p, lo, hi);
+    if constexpr (STAGE == 0) b_first<PARTY, V>(p, lo, hi);
+    else if constexpr (STAGE == 1) b_plevel<PARTY, 0, (V == 4 ? 2 : 1)>(p, g, lo, hi);
+    else if constexpr (STAGE >= 2 && STAGE <= 6) b_plevel<PARTY, STAGE - 1, 2>(p, g, lo, hi);
+    else if constexpr (STAGE == 7) b_psign<PARTY, V>(p, g, lo, hi);
+    else if constexpr (STAGE == 8) b_b2a<PARTY, V>(p, lo, hi);
+    else b_select<PARTY, V>(p, lo, hi);
 }
 
-template <int STAGE, int V, bool PUT>
+template <int STAGE, int V>
 __global__ __launch_bounds__(kThreads) void k_relu_msb_stage(ReluParty p0, ReluParty p1, MsbGeom g, int only,
                                                              size_t lo, size_t hi)
 {
     const int party = only >= 0 ? only : (int)blockIdx.y;
-    if (party == 0) stage_body_msb<STAGE, 0, V, PUT>(p0, g, lo, hi);
-    else            stage_body_msb<STAGE, 1, V, PUT>(p1, g, lo, hi);
+    if (party == 0) stage_body_msb<STAGE, 0, V>(p0, g, lo, hi);
+    else            stage_body_msb<STAGE, 1, V>(p1, g, lo, hi);
 }
 
 template <int STAGE, int V>
@@ -578,9 +513,7 @@ void launch_msb_stage_t(hipStream_t st, const ReluParty& p0, const ReluParty& p1
         threads = (hi - lo + V - 1) / V;
     }
     const dim3 grid(grid_for(threads), only >= 0 ? 1 : 2), block(kThreads);
-    constexpr bool P1 = true;
-    if (p0.put != nullptr && P1) hipLaunchKernelGGL((k_relu_msb_stage<STAGE, V, P1>), grid, block, 0, st, p0, p1, g, only, lo, hi);
-    else                         hipLaunchKernelGGL((k_relu_msb_stage<STAGE, V, false>), grid, block, 0, st, p0, p1, g, only, lo, hi);
+    hipLaunchKernelGGL((k_relu_msb_stage<STAGE, V>), grid, block, 0, st, p0, p1, g, only, lo, hi);
 }
 
 template <int V>
@@ -637,13 +570,13 @@ int wire_words(mpc_ctx* c, const u64* src0, u64* dst0, const u64* src1, u64* dst
 int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, const MsbGeom* geom = nullptr)
 {
     const bool one_queue = c->s[0] == c->s[1] && c->s[1] == c->s[2];   // in-order queue: no events needed
-    if (one_queue && c->exchange_put && !geom) {
+    if (one_queue && c->exchange_put) {
         FusedRelu q{};
         for (int i = 0; i < 2; ++i)
             q.p[i] = FusedReluParty{ pp[i].x, pp[i].r, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].rb, pp[i].ra,
                                      pp[i].ma, pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_bit, pp[i].s_arith };
         q.box = box; q.n = n;
-        return launch_relu_fused(c, c->s[0], q, c->adder);
+        return geom ? launch_relu_fused_msb(c, c->s[0], q, *geom) : launch_relu_fused(c, c->s[0], q, c->adder);
     }
     // chunk boundaries: multiples of four elements, and of 256 on the packed path
     // (four whole words of the deepest level)
@@ -677,21 +610,18 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
     hipEvent_t got[kMaxChunks];
 
     // stage `stage` on elements [l, h): both parties in one launch (only = -1) or party `only`
-    auto launch_with = [&](const ReluParty (&q)[2], int stage, hipStream_t st, int only, size_t l, size_t h) -> int {
+    auto launch = [&](int stage, hipStream_t st, int only, size_t l, size_t h) -> int {
         if (geom) {
-            if (vec4)     launch_msb_stage<4>(stage, st, q[0], q[1], *geom, only, l, h);
-            else if (vec) launch_msb_stage<2>(stage, st, q[0], q[1], *geom, only, l, h);
-            else          launch_msb_stage<1>(stage, st, q[0], q[1], *geom, only, l, h);
+            if (vec4)     launch_msb_stage<4>(stage, st, pp[0], pp[1], *geom, only, l, h);
+            else if (vec) launch_msb_stage<2>(stage, st, pp[0], pp[1], *geom, only, l, h);
+            else          launch_msb_stage<1>(stage, st, pp[0], pp[1], *geom, only, l, h);
         } else {
-            if (vec4)     launch_stage<4>(stage, st, q[0], q[1], only, l, h, c->adder);
-            else if (vec) launch_stage<2>(stage, st, q[0], q[1], only, l, h, c->adder);
-            else          launch_stage<1>(stage, st, q[0], q[1], only, l, h, c->adder);
+            if (vec4)     launch_stage<4>(stage, st, pp[0], pp[1], only, l, h, c->adder);
+            else if (vec) launch_stage<2>(stage, st, pp[0], pp[1], only, l, h, c->adder);
+            else          launch_stage<1>(stage, st, pp[0], pp[1], only, l, h, c->adder);
         }
         MPC_HIP(c, hipGetLastError());
         return MPC_OK;
-    };
-    auto launch = [&](int stage, hipStream_t st, int only, size_t l, size_t h) -> int {
-        return launch_with(pp, stage, st, only, l, h);
     };
     // the exchange that follows `stage` (-1: the A2B masks); *sent = false if the stage sends nothing
     auto exchange = [&](int stage, size_t l, size_t h, bool* sent) -> int {
@@ -730,22 +660,6 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
             if (hi[m] <= lo[m]) continue;
             MPC_TRY(exchange(-1, lo[m], hi[m], &sent));
             for (int stage = 0; stage < ST_COUNT; ++stage) {
-                if (c->exchange_put) {
-                    // Exchange by remote store: the stage kernel writes its masked words into the
-                    // peer's receive buffer as well; the word buffers alternate so that a stage
-                    // never stores where the peer's same stage still reads.
-                    ReluParty q[2] = { pp[0], pp[1] };
-                    for (int i = 0; i < 2; ++i) {
-                        u64* mine[2] = { const_cast<u64*>(pp[i].recv), pp[i].recv_alt };
-                        u64* peer[2] = { const_cast<u64*>(pp[1 - i].recv), pp[1 - i].recv_alt };
-                        q[i].recv = mine[stage & 1];
-                        q[i].put = peer[(stage + 1) & 1];
-                        q[i].putb = const_cast<u8*>(pp[1 - i].recvb);
-                        q[i].putL = const_cast<u64*>(pp[1 - i].recvL);
-                    }
-                    MPC_TRY(launch_with(q, stage, P[0], -1, lo[m], hi[m]));
-                    continue;
-                }
                 MPC_TRY(launch(stage, P[0], -1, lo[m], hi[m]));
                 MPC_TRY(exchange(stage, lo[m], hi[m], &sent));
             }
@@ -795,7 +709,6 @@ void fill_party(ReluParty& p, int i, const u64* x, const mpc_relu_material* m, c
     p.rb = m->rb[i]; p.ra = m->ra.p[i];
     p.ma = m->ma.p[i]; p.mb = m->mb.p[i]; p.mc = m->mc.p[i];
     p.send = w.send[i]; p.recv = w.recv[i]; p.sendb = w.sendb[i]; p.recvb = w.recvb[i];
-    p.put = nullptr; p.putb = nullptr; p.putL = nullptr; p.recv_alt = w.recv2[i];
     p.G = w.G[i]; p.P = w.P[i]; p.p63 = w.p63[i];
     p.sendL = w.sendL[i]; p.recvL = w.recvL[i]; p.gsel = w.gsel[i];
     p.y = y; p.s_bit = s_bit; p.s_arith = s_arith; p.n = n;

@@ -1,6 +1,7 @@
 // Interface of the one-launch secure ReLU (relu_fused.hip) to the entry points (relu.hip).
 #pragma once
 #include "common.h"
+#include "msb_pack.h"
 
 struct FusedReluParty {
     const u64 *x, *r;                    // input share, A2B mask
@@ -17,3 +18,6 @@ struct FusedRelu {
 };
 size_t relu_fused_box_bytes(size_t n);
 int launch_relu_fused(mpc_ctx* c, hipStream_t st, FusedRelu q, int topo);
+// the sign-only chain; triples in the packed layout of `g`
+size_t relu_fused_msb_box_bytes(size_t n);
+int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, FusedRelu q, const MsbGeom& g);

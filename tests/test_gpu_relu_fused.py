@@ -53,3 +53,20 @@ def test_one_launch_relu(mpc, lane, n, adder):
     equal(mpc, y, want.y, "output")
     equal(mpc, sb, want.s_bit, "sign bit share")
     equal(mpc, sa, want.s_arith, "sign arithmetic share")
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 4097, 131072, 131073, 131072 + 128 + 65, 524288 + 3])
+def test_one_launch_sign_only_relu(mpc, lane, n):
+    """The packed chain changes from one to two elements per lane at 131 072 | 131 073; beyond it the last n mod 128
+    elements run one per lane."""
+    print(f"one-launch sign-only relu n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    xs = synth.share_additive(rng, synth.normal_fixed(rng, n, 4.0))
+    mat = synth.deal_relu_material(rng, n)
+    want = oracle.relu(xs, mat)
+    x = dev(mpc, xs)
+    y, sb, sa = lane.relu(x, lane.pack_material(mpc.material_to_device(mat)), want_sign=True, packed=True, out=x if n % 2 else None)
+    lane.sync()
+    equal(mpc, y, want.y, "output")
+    equal(mpc, sb, want.s_bit, "sign bit share")
+    equal(mpc, sa, want.s_arith, "sign arithmetic share")
