@@ -407,7 +407,7 @@ ReluWs carve_relu(u8* base, size_t cap, size_t n)
         r.G[i] = w.take<u64>(n); r.P[i] = w.take<u64>(n); r.p63[i] = w.take<u8>(n);
     }
     r.box = reinterpret_cast<u64*>(base);
-    const size_t box = relu_fused_box_bytes(n);
+    const size_t box = relu_fused_box_bytes(2, n);
     r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
     return r;
 }
@@ -424,7 +424,7 @@ ReluWs carve_relu_msb(u8* base, size_t cap, size_t n, const MsbGeom& g)
         r.gsel[i] = w.take<u64>(g.words_gsel);
     }
     r.box = reinterpret_cast<u64*>(base);
-    const size_t box = relu_fused_msb_box_bytes(n);
+    const size_t box = relu_fused_msb_box_bytes(2, n);
     r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
     return r;
 }
@@ -573,10 +573,13 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
     if (one_queue && c->exchange_put) {
         FusedRelu q{};
         for (int i = 0; i < 2; ++i)
-            q.p[i] = FusedReluParty{ pp[i].x, pp[i].r, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].rb, pp[i].ra,
+            q.p[i] = FusedReluParty{ pp[i].x, pp[i].r, nullptr, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].rb, pp[i].ra,
                                      pp[i].ma, pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_bit, pp[i].s_arith };
         q.box = box; q.n = n;
-        return geom ? launch_relu_fused_msb(c, c->s[0], q, *geom) : launch_relu_fused(c, c->s[0], q, c->adder);
+        if (!geom) return launch_relu_fused(c, c->s[0], 2, q, c->adder);
+        PackedTriples g{};
+        for (int k = 0; k < 12; ++k) g.off[k] = geom->toff[k];
+        return launch_relu_fused_msb(c, c->s[0], 2, q, g);
     }
     // chunk boundaries: multiples of four elements, and of 256 on the packed path
     // (four whole words of the deepest level)
@@ -594,7 +597,7 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
     // four elements per thread additionally need n % 4 == 0 and 4-byte aligned byte arrays
     bool vec = (n % 2 == 0);
     for (int i = 0; i < 2 && vec; ++i) {
-        const void* ptrs[] = { pp[i].x, pp[i].r, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].ra, pp[i].ma,
+        const void* ptrs[] = { pp[i].x, pp[i].r, nullptr, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].ra, pp[i].ma,
                                pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_arith };
         for (const void* q : ptrs) if (q && ((uintptr_t)q & 15)) vec = false;
     }

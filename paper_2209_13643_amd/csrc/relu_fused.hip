@@ -1,9 +1,9 @@
 // Secure ReLU, all rounds in one launch (exchange by remote store on a single-queue lane).
 //
-// A workgroup is one wave per party, and both waves work on the same elements.  A party's wave reads its own share,
-// its own material and what it has received; a round's masked words are stored into the peer's receive buffer in
-// device memory, and the workgroup barrier that follows is the round: nothing but the two waves of a workgroup
-// depends on each other, so no wave ever waits for another workgroup.  Between rounds (G, P) stay in registers, and a
+// A workgroup is one wave per party (two or three), and its waves work on the same elements.  A party's wave reads its
+// own share, its own material and what it has received; a round's masked words are stored into the peers' receive
+// buffers in device memory, and the workgroup barrier that follows is the round: nothing but the waves of a workgroup
+// depend on each other, so no wave ever waits for another workgroup.  Between rounds (G, P) stay in registers, and a
 // receive buffer holds one round of one workgroup's elements, so what streams from HBM is the input, the offline
 // material and the output, each once: 690 bytes per element of both parties instead of the 2498 that one launch per
 // round moves.  2 097 152 elements: 0.95 ms as ten launches, 0.323 ms here (4.5 TB/s of compulsory bytes).
@@ -15,6 +15,7 @@
 // workgroups, they are 8 MB, and four lanes converting at once still fit (batch-128 VGG16 on four lanes: 11.7 ms with
 // two buffers, 11.2 ms with one).  The material is read once, hence the non-temporal loads (0.376 -> 0.345 ms).
 #include "common.h"
+#include "msb_pack.h"
 #include "relu_steps.h"
 #include "relu_fused.h"
 
@@ -58,24 +59,174 @@ template <> struct ByteWord<4> { typedef uint32_t type __attribute__((aligned(1)
 template <int V> __device__ __forceinline__ unsigned ld_flags(const u8* p) { return *reinterpret_cast<const typename ByteWord<V>::type*>(p); }
 template <int V> __device__ __forceinline__ void st_flags(u8* p, unsigned w) { *reinterpret_cast<typename ByteWord<V>::type*>(p) = (typename ByteWord<V>::type)w; }
 
-template <int V, int TOPO>
-__global__ __launch_bounds__(2 * kWave, 4) void k_relu_fused(FusedRelu q)
+// The receive buffers of a workgroup, one per ordered pair of parties: party i's buffer s holds what party
+// (i + 1 + s) mod NP sent last.  `box_words` words each.
+template <int NP>
+struct Wire {
+    u8* in; u8* out[NP - 1]; size_t step;
+    __device__ __forceinline__ Wire(u64* box, int party, size_t box_words)
+    {
+        step = box_words * 8;
+        u8* const wg = reinterpret_cast<u8*>(box) + (size_t)blockIdx.x * (NP * (NP - 1)) * step;
+        in = wg + (size_t)party * (NP - 1) * step;
+#pragma unroll
+        for (int s = 0; s < NP - 1; ++s) {
+            int to = party + NP - 1 - s; if (to >= NP) to -= NP;             // the party whose buffer s is filled from here
+            out[s] = wg + ((size_t)to * (NP - 1) + s) * step;
+        }
+    }
+    template <int W> __device__ __forceinline__ void put_to(int s, unsigned off, const Pack<W>& w) const { w.st(reinterpret_cast<u64*>(out[s] + off), 0); }
+    template <int W> __device__ __forceinline__ void put(unsigned off, const Pack<W>& w) const
+    {
+#pragma unroll
+        for (int s = 0; s < NP - 1; ++s) put_to(s, off, w);
+    }
+    template <int W> __device__ __forceinline__ Pack<W> from(int s, unsigned off) const { return Pack<W>::ld(reinterpret_cast<const u64*>(in + s * step + off), 0); }
+    // what the peers sent, added up (XOR shares / additive shares)
+    template <int W> __device__ __forceinline__ Pack<W> xored(unsigned off) const
+    {
+        Pack<W> r = from<W>(0, off);
+        if constexpr (NP == 3) {
+            const Pack<W> t = from<W>(1, off);
+#pragma unroll
+            for (int k = 0; k < W; ++k) r.v[k] ^= t.v[k];
+        }
+        return r;
+    }
+    template <int W> __device__ __forceinline__ Pack<W> summed(unsigned off) const
+    {
+        Pack<W> r = from<W>(0, off);
+        if constexpr (NP == 3) {
+            const Pack<W> t = from<W>(1, off);
+#pragma unroll
+            for (int k = 0; k < W; ++k) r.v[k] += t.v[k];
+        }
+        return r;
+    }
+    template <int V> __device__ __forceinline__ void put_flags(unsigned off, unsigned w) const
+    {
+#pragma unroll
+        for (int s = 0; s < NP - 1; ++s) st_flags<V>(out[s] + off, w);
+    }
+    template <int V> __device__ __forceinline__ unsigned flags(unsigned off) const
+    {
+        unsigned w = ld_flags<V>(in + off);
+        if constexpr (NP == 3) w ^= ld_flags<V>(in + step + off);
+        return w;
+    }
+    __device__ __forceinline__ static void opened() { __syncthreads(); }      // every wave has stored its words of the round
+    __device__ __forceinline__ static void drained() { __syncthreads(); }     // every wave holds the words of the last round: the buffers are free
+};
+
+// One party's side of a Beaver AND; m0: all ones for the party that adds the product of the opened words.
+__device__ __forceinline__ u64 fin(u64 d, u64 g, u64 a, u64 b, u64 c, u64 m0) { return c ^ (d & b) ^ (g & a) ^ (d & g & m0); }
+
+template <int V> struct Operands { Pack<V> P, G; u64 top[V]; };         // top: bit 63 of P
+
+// Alg. 2 on a wave's elements, up to P = U ^ V and G = U & V of the two words the prefix network adds.  Two parties:
+// the words x_0, x_1; three: the carry-save sum of x_0, x_1, x_2 and its majority shifted up.  row: loads the
+// wave's words of an array; t1: offset of triple 1; whole: bytes between two rows of the receive buffers; before_last:
+// loads to issue ahead of the last wait.
+template <int NP, int V, typename Row, typename Next>
+__device__ __forceinline__ Operands<V> a2b(const FusedReluParty& p, const Wire<NP>& wire, int party, u64 m0, const Pack<V>& x,
+                                           unsigned slot, unsigned whole, Row&& row, size_t t1, Next&& before_last)
+{
+    Operands<V> o;
+    const Pack<V> r = row(p.r);
+    Pack<V> a = row(p.ta), b = row(p.tb), c = row(p.tc), d, g;
+    if constexpr (NP == 2) {
+        wire.drained();
+        wire.put(slot, r);                                               // the mask half of the own word
+        wire.opened();
+        const Pack<V> rr = wire.template from<V>(0, slot);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const u64 own = x.v[k] ^ r.v[k], U = party == 0 ? own : rr.v[k], Vv = party == 0 ? rr.v[k] : own;
+            d.v[k] = U ^ a.v[k]; g.v[k] = Vv ^ b.v[k];
+            o.P.v[k] = U ^ Vv; o.top[k] = o.P.v[k] >> 63;
+        }
+    } else {
+        const Pack<V> r1 = row(p.r1);
+        wire.drained();
+        wire.put_to(0, slot, r1); wire.put_to(1, slot, r);               // r1 to party + 2, r to party + 1
+        const Pack<V> na = row(p.ta + t1), nb = row(p.tb + t1), nc = row(p.tc + t1);
+        wire.opened();
+        const Pack<V> w1 = wire.template from<V>(0, slot), w2 = wire.template from<V>(1, slot);      // words of party + 1, party + 2
+        Pack<V> S, Wd;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const u64 own = x.v[k] ^ r.v[k] ^ r1.v[k];
+            const u64 U = party == 0 ? own : party == 1 ? w2.v[k] : w1.v[k];
+            const u64 Vv = party == 1 ? own : party == 2 ? w2.v[k] : w1.v[k];
+            Wd.v[k] = party == 2 ? own : party == 0 ? w2.v[k] : w1.v[k];
+            S.v[k] = U ^ Vv ^ Wd.v[k];
+            d.v[k] = U ^ Wd.v[k] ^ a.v[k]; g.v[k] = Vv ^ Wd.v[k] ^ b.v[k];
+        }
+        wire.drained();
+        wire.put(slot, d); wire.put(slot + whole, g);
+        wire.opened();
+        const Pack<V> rd = wire.template xored<V>(slot), rg = wire.template xored<V>(slot + whole);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const u64 K = (fin(d.v[k] ^ rd.v[k], g.v[k] ^ rg.v[k], a.v[k], b.v[k], c.v[k], m0) ^ Wd.v[k]) << 1;
+            o.P.v[k] = S.v[k] ^ K; o.top[k] = o.P.v[k] >> 63;
+            d.v[k] = S.v[k] ^ na.v[k]; g.v[k] = K ^ nb.v[k];
+        }
+        a = na; b = nb; c = nc;
+    }
+    wire.drained();
+    wire.put(slot, d); wire.put(slot + whole, g);
+    before_last();
+    wire.opened();
+    const Pack<V> rd = wire.template xored<V>(slot), rg = wire.template xored<V>(slot + whole);
+#pragma unroll
+    for (int k = 0; k < V; ++k) o.G.v[k] = fin(d.v[k] ^ rd.v[k], g.v[k] ^ rg.v[k], a.v[k], b.v[k], c.v[k], m0);
+    return o;
+}
+
+// B2A of the sign share and the select product.  s: the share, one byte per element; y and the additive share out.
+template <int NP, int V>
+__device__ __forceinline__ void select(const Wire<NP>& wire, u64 m0, unsigned lane, unsigned slot, unsigned whole, unsigned masked,
+                                       const Pack<V>& x, const Pack<V>& ra, const Pack<V>& ma, const Pack<V>& mb, const Pack<V>& mc,
+                                       Pack<V>& y, Pack<V>& sa)
+{
+    wire.drained();
+    wire.template put_flags<V>(lane * V, masked);
+    wire.opened();
+    const unsigned v = masked ^ wire.template flags<V>(lane * V);
+    Pack<V> e, f;
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        // s = v xor rb = v + rb - 2 v rb on additive shares of rb
+        const u64 vk = (v >> (8 * k)) & 1;
+        sa.v[k] = (vk ? (u64)0 - ra.v[k] : ra.v[k]) + (vk & m0);
+        e.v[k] = x.v[k] - ma.v[k];
+        f.v[k] = (m0 & 1) - sa.v[k] - mb.v[k];
+    }
+    wire.drained();
+    wire.put(slot, e); wire.put(slot + whole, f);
+    wire.opened();
+    const Pack<V> re = wire.template summed<V>(slot), rf = wire.template summed<V>(slot + whole);
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        const u64 eo = e.v[k] + re.v[k], fo = f.v[k] + rf.v[k];
+        y.v[k] = mc.v[k] + eo * (mb.v[k] + (fo & m0)) + ma.v[k] * fo;
+    }
+}
+
+template <int W> struct LevelTriples { Pack<W> a1, b1, c1, a2, b2, c2; };
+
+template <int NP, int V, int TOPO>
+__global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused(FusedRelu q)
 {
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int lane = threadIdx.x % kWave;
     const FusedReluParty& p = q.p[party];
     const size_t n = q.n;
-    const u64 m0 = party == 0 ? ~(u64)0 : 0;             // the party that adds the product of the opened words
-    constexpr size_t kBox = (size_t)kRows * kWave * V;
-    u64* const in = q.box + ((size_t)blockIdx.x * 2 + party) * kBox;
-    u64* const out = q.box + ((size_t)blockIdx.x * 2 + (party ^ 1)) * kBox;
+    const u64 m0 = party == 0 ? ~(u64)0 : 0;
+    const Wire<NP> wire(q.box, party, (size_t)kRows * kWave * V);
+    constexpr unsigned whole = kWave * V * 8u;
     unsigned slot = lane * V * 8u;
-    // row `row` of this round's words, into the peer's receive buffer / out of the own one
-    auto put = [&](int row, const Pack<V>& w) { w.st(reinterpret_cast<u64*>(reinterpret_cast<u8*>(out) + (slot + row * kWave * V * 8u)), 0); };
-    auto get = [&](int row) { return Pack<V>::ld(reinterpret_cast<const u64*>(reinterpret_cast<const u8*>(in) + (slot + row * kWave * V * 8u)), 0); };
-    auto opened = [] { __syncthreads(); };      // both waves have stored their words of the round
-    auto drained = [] { __syncthreads(); };     // both waves hold the words of the last round: the buffers are free
-    auto fin = [&](u64 d, u64 g, u64 a, u64 b, u64 c) { return c ^ (d & b) ^ (g & a) ^ (d & g & m0); };
 
     for (size_t tile = blockIdx.x; tile < q.tiles; tile += gridDim.x) {
         // the wave's elements: base + off .. ; a ragged last tile takes the last 64 V elements and stores its own only
@@ -83,98 +234,58 @@ __global__ __launch_bounds__(2 * kWave, 4) void k_relu_fused(FusedRelu q)
         const size_t base = first + kWave * V <= n ? first : n >= kWave * V ? n - kWave * V : 0;
         const unsigned rest = n < kWave * V ? (unsigned)n - V : kWave * V - V;
         unsigned off = lane * V < rest ? lane * V : rest;
-        // opaque per tile: otherwise the addresses of all 43 rows are formed ahead of the loop and spilled
+        // opaque per tile: otherwise the addresses of all rows are formed ahead of the loop and spilled
         asm volatile("" : "+v"(off), "+v"(slot));
         auto row = [&](const u64* t) { return ld_once<V>(t + base, off * 8u); };
-        auto tri = [&](const u64* t, int k) { return row(t + (size_t)k * n); };
+        auto triples = [&](auto tag) {
+            constexpr int L = decltype(tag)::value, t = NP - 1 + 2 * L;
+            LevelTriples<V> r;
+            r.a1 = row(p.ta + t * n); r.b1 = row(p.tb + t * n); r.c1 = row(p.tc + t * n);
+            if constexpr (L < 5) { r.a2 = row(p.ta + (t + 1) * n); r.b2 = row(p.tb + (t + 1) * n); r.c2 = row(p.tc + (t + 1) * n); }
+            return r;
+        };
 
-        const Pack<V> x = row(p.x), r = row(p.r);
-        Pack<V> a1 = tri(p.ta, 0), b1 = tri(p.tb, 0), c1 = tri(p.tc, 0), a2, b2, c2;
-        drained();
-        put(0, r);                                                     // Alg. 2: the mask half of the own word
-        opened();
-        Pack<V> P, G, sd, sg;
-        u64 top[V];
-        {
-            const Pack<V> rr = get(0);
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const u64 o = x.v[k] ^ r.v[k], U = party == 0 ? o : rr.v[k], Vv = party == 0 ? rr.v[k] : o;
-                sd.v[k] = U ^ a1.v[k]; sg.v[k] = Vv ^ b1.v[k];
-                P.v[k] = U ^ Vv; top[k] = P.v[k] >> 63;
-            }
-            drained();
-            put(0, sd); put(1, sg);
-        }
-        Pack<V> na1 = tri(p.ta, 1), nb1 = tri(p.tb, 1), nc1 = tri(p.tc, 1);
-        Pack<V> na2 = tri(p.ta, 2), nb2 = tri(p.tb, 2), nc2 = tri(p.tc, 2);
-        opened();
-        {
-            const Pack<V> rd = get(0), rg = get(1);
-#pragma unroll
-            for (int k = 0; k < V; ++k) G.v[k] = fin(sd.v[k] ^ rd.v[k], sg.v[k] ^ rg.v[k], a1.v[k], b1.v[k], c1.v[k]);
-        }
+        const Pack<V> x = row(p.x);
+        LevelTriples<V> next;
+        Operands<V> o = a2b<NP, V>(p, wire, party, m0, x, slot, whole, row, n, [&] { next = triples(std::integral_constant<int, 0>{}); });
+        Pack<V>&P = o.P, &G = o.G;
         // prefix levels: mask and send level L's operands, fetch the next level's triples, open, finish
         auto level = [&](auto tag) {
             constexpr int L = decltype(tag)::value;
-            a1 = na1; b1 = nb1; c1 = nc1; a2 = na2; b2 = nb2; c2 = nc2;
+            const LevelTriples<V> t = next;
             Pack<V> d1, g1, d2, g2;
 #pragma unroll
             for (int k = 0; k < V; ++k) {
                 const u64 X = op_x<TOPO, L>(P.v[k]);
-                d1.v[k] = X ^ a1.v[k]; g1.v[k] = op_y<TOPO, L>(G.v[k]) ^ b1.v[k];
-                if constexpr (L < 5) { d2.v[k] = X ^ a2.v[k]; g2.v[k] = op_y<TOPO, L>(P.v[k]) ^ b2.v[k]; }
+                d1.v[k] = X ^ t.a1.v[k]; g1.v[k] = op_y<TOPO, L>(G.v[k]) ^ t.b1.v[k];
+                if constexpr (L < 5) { d2.v[k] = X ^ t.a2.v[k]; g2.v[k] = op_y<TOPO, L>(P.v[k]) ^ t.b2.v[k]; }
             }
-            drained();
-            put(0, d1); put(1, g1);
-            if constexpr (L < 5) { put(2, d2); put(3, g2); }
-            if constexpr (L < 5) { na1 = tri(p.ta, 3 + 2 * L); nb1 = tri(p.tb, 3 + 2 * L); nc1 = tri(p.tc, 3 + 2 * L); }
-            if constexpr (L < 4) { na2 = tri(p.ta, 4 + 2 * L); nb2 = tri(p.tb, 4 + 2 * L); nc2 = tri(p.tc, 4 + 2 * L); }
-            opened();
-            const Pack<V> rd1 = get(0), rg1 = get(1);
+            wire.drained();
+            wire.put(slot, d1); wire.put(slot + whole, g1);
+            if constexpr (L < 5) { wire.put(slot + 2 * whole, d2); wire.put(slot + 3 * whole, g2); }
+            if constexpr (L < 5) next = triples(std::integral_constant<int, L + 1>{});
+            wire.opened();
+            const Pack<V> rd1 = wire.template xored<V>(slot), rg1 = wire.template xored<V>(slot + whole);
             Pack<V> rd2, rg2;
-            if constexpr (L < 5) { rd2 = get(2); rg2 = get(3); }
+            if constexpr (L < 5) { rd2 = wire.template xored<V>(slot + 2 * whole); rg2 = wire.template xored<V>(slot + 3 * whole); }
 #pragma unroll
             for (int k = 0; k < V; ++k) {
-                G.v[k] ^= fin(d1.v[k] ^ rd1.v[k], g1.v[k] ^ rg1.v[k], a1.v[k], b1.v[k], c1.v[k]);
+                G.v[k] ^= fin(d1.v[k] ^ rd1.v[k], g1.v[k] ^ rg1.v[k], t.a1.v[k], t.b1.v[k], t.c1.v[k], m0);
                 if constexpr (L < 5)
-                    P.v[k] = keep_p<TOPO, L>(P.v[k]) ^ fin(d2.v[k] ^ rd2.v[k], g2.v[k] ^ rg2.v[k], a2.v[k], b2.v[k], c2.v[k]);
+                    P.v[k] = keep_p<TOPO, L>(P.v[k]) ^ fin(d2.v[k] ^ rd2.v[k], g2.v[k] ^ rg2.v[k], t.a2.v[k], t.b2.v[k], t.c2.v[k], m0);
             }
         };
         level(std::integral_constant<int, 0>{}); level(std::integral_constant<int, 1>{}); level(std::integral_constant<int, 2>{});
         level(std::integral_constant<int, 3>{}); level(std::integral_constant<int, 4>{}); level(std::integral_constant<int, 5>{});
 
-        // sign share = bit 63 of U ^ V xor the carry out of bits 0..62; masked with the random bit and opened
+        // sign share = bit 63 of the sum's half-add xor the carry out of bits 0..62; an element's bits are bytes of s
         const Pack<V> ra = row(p.ra), ma = row(p.ma), mb = row(p.mb), mc = row(p.mc);
         const unsigned rb = ld_flags<V>(p.rb + base + off);
-        unsigned s = 0;                                                // the bits of an element are bytes of s
+        unsigned s = 0;
 #pragma unroll
-        for (int k = 0; k < V; ++k) s |= (unsigned)(top[k] ^ ((G.v[k] >> 62) & 1)) << (8 * k);
-        drained();
-        st_flags<V>(reinterpret_cast<u8*>(out) + lane * V, s ^ rb);
-        opened();
-        const unsigned v = s ^ rb ^ ld_flags<V>(reinterpret_cast<const u8*>(in) + lane * V);
-        Pack<V> sa, e, f;
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            // s = v xor rb = v + rb - 2 v rb on additive shares of rb
-            const u64 vk = (v >> (8 * k)) & 1;
-            sa.v[k] = (vk ? (u64)0 - ra.v[k] : ra.v[k]) + (vk & m0);
-            e.v[k] = x.v[k] - ma.v[k];
-            f.v[k] = (m0 & 1) - sa.v[k] - mb.v[k];
-        }
-        drained();
-        put(0, e); put(1, f);
-        opened();
-        Pack<V> y;
-        {
-            const Pack<V> re = get(0), rf = get(1);
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const u64 eo = e.v[k] + re.v[k], fo = f.v[k] + rf.v[k];
-                y.v[k] = mc.v[k] + eo * (mb.v[k] + (fo & m0)) + ma.v[k] * fo;
-            }
-        }
+        for (int k = 0; k < V; ++k) s |= (unsigned)(o.top[k] ^ ((G.v[k] >> 62) & 1)) << (8 * k);
+        Pack<V> y, sa;
+        select<NP, V>(wire, m0, lane, slot, whole, s ^ rb, x, ra, ma, mb, mc, y, sa);
         if (base + off >= first) {
             st_words<V>(p.y + base, off * 8u, y);
             if (p.s_bit) st_flags<V>(p.s_bit + base + off, s);
@@ -201,78 +312,41 @@ __device__ __forceinline__ u64 from_lane_xor(u64 v, int mask)
     return ((u64)hi << 32) | lo;
 }
 
-struct MsbTile {
-    const FusedReluParty& p; const MsbGeom& g;
-    u64 *in, *out;
-    int party, lane;
-    u64 m0;
-};
-
-template <int W> struct LevelTriples { Pack<W> a1, b1, c1, a2, b2, c2; };
-
-template <int V>
-__device__ __forceinline__ void msb_tile(const MsbTile& t, size_t base, size_t n)
+template <int NP, int V>
+__device__ __forceinline__ void msb_tile(const FusedReluParty& p, const PackedTriples& g, const Wire<NP>& wire, int party, size_t base, size_t n)
 {
-    const FusedReluParty& p = t.p;
-    const u64 m0 = t.m0;
+    const u64 m0 = party == 0 ? ~(u64)0 : 0;
+    unsigned lane = threadIdx.x % kWave;
     const unsigned rest = V == 1 && n - base < kWave ? (unsigned)(n - base) - 1 : kWave * V - V;
-    unsigned off = t.lane * V < rest ? t.lane * V : rest;         // V > 1: the caller passes whole tiles only
-    unsigned lane = t.lane;
+    unsigned off = lane * V < rest ? lane * V : rest;             // V > 1: the caller passes whole tiles only
     asm volatile("" : "+v"(off), "+v"(lane));
     auto row = [&](const u64* q) { return ld_once<V>(q + base, off * 8u); };
-    auto opened = [] { __syncthreads(); };
-    auto drained = [] { __syncthreads(); };
-    auto fin = [&](u64 d, u64 g, u64 a, u64 b, u64 c) { return c ^ (d & b) ^ (g & a) ^ (d & g & m0); };
-    // words at word index `w` of the peer's / the own receive buffer; rows of whole words and of packed words
-    constexpr unsigned kWhole = kWave * V, kPacked = kWave * V / 2;
-    auto put = [&](unsigned w, const auto& v) { v.st(reinterpret_cast<u64*>(reinterpret_cast<u8*>(t.out) + w * 8u), 0); };
-    auto get = [&](unsigned w, auto tag) {
-        return Pack<decltype(tag)::value>::ld(reinterpret_cast<const u64*>(reinterpret_cast<const u8*>(t.in) + w * 8u), 0);
-    };
-    typedef std::integral_constant<int, V> VT;
-
+    // rows of whole words and of packed words in the receive buffers
+    constexpr unsigned whole = kWave * V * 8u, packed = kWave * V / 2 * 8u;
+    const unsigned slot = lane * V * 8u;
     // level L: a lane forms words(L) words, at word index at(L) of the tile
     auto at = [&](auto tag) { constexpr int L = decltype(tag)::value; return (2 << L) <= V ? lane * (V >> (L + 1)) : (lane * V) >> (L + 1); };
     auto triples = [&](auto tag) {
-        constexpr int L = decltype(tag)::value, W = (2 << L) <= V ? V >> (L + 1) : 1;
-        const unsigned w = at(tag);
-        auto tri = [&](const u64* q, int k) { return ld_once<W>(q + t.g.toff[k] + (base >> (L + 1)), w * 8u); };
+        constexpr int L = decltype(tag)::value, W = (2 << L) <= V ? V >> (L + 1) : 1, t = NP - 1 + 2 * L;
+        const unsigned w = at(tag) * 8u;
+        auto tri = [&](const u64* q, int k) { return ld_once<W>(q + g.off[k] + (base >> (L + 1)), w); };
         LevelTriples<W> r;
-        r.a1 = tri(p.ta, 1 + 2 * L); r.b1 = tri(p.tb, 1 + 2 * L); r.c1 = tri(p.tc, 1 + 2 * L);
-        if constexpr (L < 5) { r.a2 = tri(p.ta, 2 + 2 * L); r.b2 = tri(p.tb, 2 + 2 * L); r.c2 = tri(p.tc, 2 + 2 * L); }
+        r.a1 = tri(p.ta, t); r.b1 = tri(p.tb, t); r.c1 = tri(p.tc, t);
+        if constexpr (L < 5) { r.a2 = tri(p.ta, t + 1); r.b2 = tri(p.tb, t + 1); r.c2 = tri(p.tc, t + 1); }
         return r;
     };
 
-    const Pack<V> x = row(p.x), r = row(p.r), a0 = row(p.ta), b0 = row(p.tb), c0 = row(p.tc);
-    drained();
-    put(lane * V, r);
-    opened();
-    Pack<V> P, G, sd, sg;
+    const Pack<V> x = row(p.x);
     LevelTriples<V == 1 ? 1 : V / 2> t0;
-    u64 top = 0;                                                  // bit k: bit 63 of U ^ V of element k
-    {
-        const Pack<V> rr = get(lane * V, VT{});
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            const u64 o = x.v[k] ^ r.v[k], U = t.party == 0 ? o : rr.v[k], Vv = t.party == 0 ? rr.v[k] : o;
-            sd.v[k] = U ^ a0.v[k]; sg.v[k] = Vv ^ b0.v[k];
-            P.v[k] = U ^ Vv; top |= (P.v[k] >> 63) << k;
-        }
-        drained();
-        put(lane * V, sd); put(lane * V + kWhole, sg);
-        t0 = triples(std::integral_constant<int, 0>{});
-        opened();
-        const Pack<V> rd = get(lane * V, VT{}), rg = get(lane * V + kWhole, VT{});
-#pragma unroll
-        for (int k = 0; k < V; ++k) G.v[k] = fin(sd.v[k] ^ rd.v[k], sg.v[k] ^ rg.v[k], a0.v[k], b0.v[k], c0.v[k]);
-    }
+    Operands<V> o = a2b<NP, V>(p, wire, party, m0, x, slot, whole, row, g.off[1], [&] { t0 = triples(std::integral_constant<int, 0>{}); });
+    Pack<V>&P = o.P, &G = o.G;
     // mask and send, fetch the next level's triples (returned), open and finish
     auto level = [&](auto tag, const auto& tr) {
         constexpr int L = decltype(tag)::value, d = 1 << L;
         constexpr u64 A = sel_mask(L), B = low_mask(L);
         constexpr bool inlane = (2 << L) <= V;
         constexpr int W = inlane ? V >> (L + 1) : 1;
-        const unsigned w = at(tag);
+        const unsigned w = at(tag) * 8u;
         Pack<W> d1, g1, d2, g2, Gk;
 #pragma unroll
         for (int k = 0; k < W; ++k) {
@@ -293,21 +367,20 @@ __device__ __forceinline__ void msb_tile(const MsbTile& t, size_t base, size_t n
                 g2.v[k] = (rotl<d>(Plo & B) | rotl<2 * d>(Phi & B)) ^ tr.b2.v[k];   // P[p - d] moved to p
             }
         }
-        drained();
-        put(w, d1); put(w + kPacked, g1);
-        if constexpr (L < 5) { put(w + 2 * kPacked, d2); put(w + 3 * kPacked, g2); }
+        wire.drained();
+        wire.put(w, d1); wire.put(w + packed, g1);
+        if constexpr (L < 5) { wire.put(w + 2 * packed, d2); wire.put(w + 3 * packed, g2); }
         constexpr int W1 = (4 << L) <= V ? V >> (L + 2) : 1;
         LevelTriples<W1> next;
         if constexpr (L < 5) next = triples(std::integral_constant<int, L + 1>{});
-        opened();
-        typedef std::integral_constant<int, W> WT;
-        const Pack<W> rd1 = get(w, WT{}), rg1 = get(w + kPacked, WT{});
+        wire.opened();
+        const Pack<W> rd1 = wire.template xored<W>(w), rg1 = wire.template xored<W>(w + packed);
         Pack<W> rd2, rg2;
-        if constexpr (L < 5) { rd2 = get(w + 2 * kPacked, WT{}); rg2 = get(w + 3 * kPacked, WT{}); }
+        if constexpr (L < 5) { rd2 = wire.template xored<W>(w + 2 * packed); rg2 = wire.template xored<W>(w + 3 * packed); }
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            G.v[k] = Gk.v[k] ^ fin(d1.v[k] ^ rd1.v[k], g1.v[k] ^ rg1.v[k], tr.a1.v[k], tr.b1.v[k], tr.c1.v[k]);
-            if constexpr (L < 5) P.v[k] = fin(d2.v[k] ^ rd2.v[k], g2.v[k] ^ rg2.v[k], tr.a2.v[k], tr.b2.v[k], tr.c2.v[k]);
+            G.v[k] = Gk.v[k] ^ fin(d1.v[k] ^ rd1.v[k], g1.v[k] ^ rg1.v[k], tr.a1.v[k], tr.b1.v[k], tr.c1.v[k], m0);
+            if constexpr (L < 5) P.v[k] = fin(d2.v[k] ^ rd2.v[k], g2.v[k] ^ rg2.v[k], tr.a2.v[k], tr.b2.v[k], tr.c2.v[k], m0);
         }
         return next;
     };
@@ -320,36 +393,13 @@ __device__ __forceinline__ void msb_tile(const MsbTile& t, size_t base, size_t n
     const auto t5 = level(std::integral_constant<int, 4>{}, t4);
     level(std::integral_constant<int, 5>{}, t5);
 
-    // element i's carry into bit 63 sits at bit (62 + i) mod 64 of word i / 64; the bits of an element are bytes of s
+    // element i's carry into bit 63 sits at bit (62 + i) mod 64 of word i / 64; an element's bits are bytes of s
     const unsigned rb = ld_flags<V>(p.rb + base + off);
     unsigned s = 0;
 #pragma unroll
-    for (int k = 0; k < V; ++k) s |= (unsigned)(((top >> k) ^ (G.v[0] >> ((62 + lane * V + k) & 63))) & 1) << (8 * k);
-    drained();
-    st_flags<V>(reinterpret_cast<u8*>(t.out) + lane * V, s ^ rb);
-    opened();
-    const unsigned v = s ^ rb ^ ld_flags<V>(reinterpret_cast<const u8*>(t.in) + lane * V);
-    Pack<V> sa, e, f;
-#pragma unroll
-    for (int k = 0; k < V; ++k) {
-        // s = v xor rb = v + rb - 2 v rb on additive shares of rb
-        const u64 vk = (v >> (8 * k)) & 1;
-        sa.v[k] = (vk ? (u64)0 - ra.v[k] : ra.v[k]) + (vk & m0);
-        e.v[k] = x.v[k] - ma.v[k];
-        f.v[k] = (m0 & 1) - sa.v[k] - mb.v[k];
-    }
-    drained();
-    put(lane * V, e); put(lane * V + kWhole, f);
-    opened();
-    Pack<V> y;
-    {
-        const Pack<V> re = get(lane * V, VT{}), rf = get(lane * V + kWhole, VT{});
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            const u64 eo = e.v[k] + re.v[k], fo = f.v[k] + rf.v[k];
-            y.v[k] = mc.v[k] + eo * (mb.v[k] + (fo & m0)) + ma.v[k] * fo;
-        }
-    }
+    for (int k = 0; k < V; ++k) s |= (unsigned)((o.top[k] ^ (G.v[0] >> ((62 + lane * V + k) & 63))) & 1) << (8 * k);
+    Pack<V> y, sa;
+    select<NP, V>(wire, m0, lane, slot, whole, s ^ rb, x, ra, ma, mb, mc, y, sa);
     if (off != lane * V) return;              // past the end: a lane that worked on the last element again, at another bit position
     st_words<V>(p.y + base, off * 8u, y);
     if (p.s_bit) st_flags<V>(p.s_bit + base + off, s);
@@ -359,70 +409,79 @@ __device__ __forceinline__ void msb_tile(const MsbTile& t, size_t base, size_t n
 // tiles 0 .. wide-1: 128 elements each, two per lane; the others 64 elements, one per lane (the last one ragged)
 constexpr int kMsbV = 2;
 constexpr size_t kMsbBox = 2 * kWave * kMsbV;      // words: two rows of whole words, or four of level 0
-__global__ __launch_bounds__(2 * kWave, 4) void k_relu_fused_msb(FusedRelu q, MsbGeom g, unsigned wide)
+template <int NP>
+__global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused_msb(FusedRelu q, PackedTriples g, unsigned wide)
 {
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    constexpr size_t kBox = kMsbBox;
-    const MsbTile t{ q.p[party], g, q.box + ((size_t)blockIdx.x * 2 + party) * kBox, q.box + ((size_t)blockIdx.x * 2 + (party ^ 1)) * kBox,
-                     party, (int)(threadIdx.x % kWave), party == 0 ? ~(u64)0 : 0 };
+    const Wire<NP> wire(q.box, party, kMsbBox);
     for (unsigned tile = blockIdx.x; tile < q.tiles; tile += gridDim.x) {
-        if (tile < wide) msb_tile<kMsbV>(t, (size_t)tile * kWave * kMsbV, q.n);
-        else             msb_tile<1>(t, ((size_t)wide * kMsbV + (tile - wide)) * kWave, q.n);
+        if (tile < wide) msb_tile<NP, kMsbV>(q.p[party], g, wire, party, (size_t)tile * kWave * kMsbV, q.n);
+        else             msb_tile<NP, 1>(q.p[party], g, wire, party, ((size_t)wide * kMsbV + (tile - wide)) * kWave, q.n);
     }
 }
 
-constexpr int kFusedBlocks = 1024;      // two waves per SIMD; 512 and 2048 workgroups are 4 and 2 % slower
+// Workgroups of a launch, [parties - 2]: as many as their receive buffers fit the L2 of their XCD (a three-party
+// workgroup has six of them).  Whole words, 2 097 152 elements: two parties 512 / 1024 / 2048 workgroups 0.335 / 0.323 /
+// 0.331 ms; three parties 256 / 512 / 768 / 1024 workgroups 0.73 / 0.65 / 0.71 / 0.75 ms (2.12 ms as eleven launches).
+// Sign-only: two parties 1024 / 2048 workgroups 0.145 / 0.141 ms; three parties 1024 / 1536 / 2048 workgroups 0.369 /
+// 0.360 / 0.365 ms (0.99 ms as eleven launches).
+constexpr unsigned kBlocks[2] = { 1024, 512 }, kMsbBlocks[2] = { 2048, 1536 };
+constexpr int kMaxBlockPairs[2] = { 2, 6 };        // ordered pairs of parties: receive buffers per workgroup
 
-template <int V> unsigned fused_tiles(size_t n) { return (unsigned)((n + kWave * V - 1) / (kWave * V)); }
 // two elements per thread (16-byte accesses) once one element per thread would need a second round of workgroups
-inline int fused_width(size_t n) { return n > (size_t)kFusedBlocks * kWave ? 2 : 1; }
-
-template <int V>
-int launch(mpc_ctx* c, hipStream_t st, FusedRelu& q, int topo)
+int width(size_t n, unsigned blocks) { return n > (size_t)blocks * kWave ? 2 : 1; }
+unsigned tiles_of(size_t n, int v) { return (unsigned)((n + kWave * v - 1) / (kWave * v)); }
+unsigned wide_tiles(size_t n, unsigned blocks) { return width(n, blocks) == kMsbV ? (unsigned)(n / (kWave * kMsbV)) : 0; }
+unsigned msb_tiles(size_t n, unsigned blocks)
 {
-    q.tiles = fused_tiles<V>(q.n);
-    const dim3 grid(q.tiles < (unsigned)kFusedBlocks ? q.tiles : kFusedBlocks), block(2 * kWave);
-    if (topo) hipLaunchKernelGGL((k_relu_fused<V, 1>), grid, block, 0, st, q);
-    else      hipLaunchKernelGGL((k_relu_fused<V, 0>), grid, block, 0, st, q);
-    MPC_HIP(c, hipGetLastError());
-    return MPC_OK;
+    const unsigned wide = wide_tiles(n, blocks);
+    return wide + tiles_of(n - (size_t)wide * kWave * kMsbV, 1);
+}
+unsigned least(unsigned a, unsigned b) { return a < b ? a : b; }
+
+template <int NP, int V>
+void launch(hipStream_t st, const FusedRelu& q, int topo)
+{
+    const dim3 grid(least(q.tiles, kBlocks[NP - 2])), block(NP * kWave);
+    if constexpr (NP == 2)
+        if (topo) { hipLaunchKernelGGL((k_relu_fused<NP, V, 1>), grid, block, 0, st, q); return; }
+    hipLaunchKernelGGL((k_relu_fused<NP, V, 0>), grid, block, 0, st, q);
 }
 
 }  // namespace
 
-size_t relu_fused_box_bytes(size_t n)
+size_t relu_fused_box_bytes(int parties, size_t n)
 {
-    const int v = fused_width(n);
-    const size_t tiles = v == 2 ? fused_tiles<2>(n) : fused_tiles<1>(n);
-    return (tiles < kFusedBlocks ? tiles : kFusedBlocks) * 2 * (kRows * kWave * v) * sizeof(u64);
+    const unsigned blocks = kBlocks[parties - 2];
+    const int v = width(n, blocks);
+    return (size_t)least(tiles_of(n, v), blocks) * kMaxBlockPairs[parties - 2] * (kRows * kWave * v) * sizeof(u64);
 }
 
-int launch_relu_fused(mpc_ctx* c, hipStream_t st, FusedRelu q, int topo)
+int launch_relu_fused(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, int topo)
 {
     if (q.n == 0 || q.n >= ((size_t)1 << 37)) return MPC_EINVAL;
-    return fused_width(q.n) == 2 ? launch<2>(c, st, q, topo) : launch<1>(c, st, q, topo);
+    const int v = width(q.n, kBlocks[parties - 2]);
+    q.tiles = tiles_of(q.n, v);
+    if (parties == 2) { if (v == 2) launch<2, 2>(st, q, topo); else launch<2, 1>(st, q, topo); }
+    else              { if (v == 2) launch<3, 2>(st, q, 0);    else launch<3, 1>(st, q, 0); }
+    MPC_HIP(c, hipGetLastError());
+    return MPC_OK;
 }
 
-constexpr int kMsbBlocks = 2048;
-// two elements per lane once one per lane would need a second round of workgroups
-static unsigned msb_wide_tiles(size_t n) { return n > (size_t)kMsbBlocks * kWave ? (unsigned)(n / (kWave * kMsbV)) : 0; }
-static unsigned msb_tiles(size_t n)
+size_t relu_fused_msb_box_bytes(int parties, size_t n)
 {
-    const unsigned wide = msb_wide_tiles(n);
-    return wide + (unsigned)((n - (size_t)wide * kWave * kMsbV + kWave - 1) / kWave);
+    const unsigned blocks = kMsbBlocks[parties - 2];
+    return (size_t)least(msb_tiles(n, blocks), blocks) * kMaxBlockPairs[parties - 2] * kMsbBox * sizeof(u64);
 }
 
-size_t relu_fused_msb_box_bytes(size_t n)
-{
-    const size_t tiles = msb_tiles(n);
-    return (tiles < kMsbBlocks ? tiles : kMsbBlocks) * 2 * kMsbBox * sizeof(u64);
-}
-
-int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, FusedRelu q, const MsbGeom& g)
+int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, const PackedTriples& g)
 {
     if (q.n == 0 || q.n >= ((size_t)1 << 37)) return MPC_EINVAL;
-    q.tiles = msb_tiles(q.n);
-    hipLaunchKernelGGL(k_relu_fused_msb, dim3(q.tiles < kMsbBlocks ? q.tiles : kMsbBlocks), dim3(2 * kWave), 0, st, q, g, msb_wide_tiles(q.n));
+    const unsigned blocks = kMsbBlocks[parties - 2], wide = wide_tiles(q.n, blocks);
+    q.tiles = msb_tiles(q.n, blocks);
+    const dim3 grid(least(q.tiles, blocks));
+    if (parties == 2) hipLaunchKernelGGL(k_relu_fused_msb<2>, grid, dim3(2 * kWave), 0, st, q, g, wide);
+    else              hipLaunchKernelGGL(k_relu_fused_msb<3>, grid, dim3(3 * kWave), 0, st, q, g, wide);
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }

@@ -5,10 +5,11 @@
 // and the element-wise steps of the backward pass (Sec. 5.3).  Everything here
 // is bound by HBM; all launches go to the lane's first stream, one launch per
 // step for all three parties (blockIdx.y = party), and every exchange is a copy
-// kernel or, on request, a remote store by the stage kernel itself.  The linear
+// kernel or, on request, a remote store (the ReLU then runs as one launch: relu_fused.hip).  The linear
 // layers with three parties live in linear.hip.
 #include "common.h"
 #include "msb_pack.h"
+#include "relu_fused.h"
 
 namespace {
 
@@ -67,14 +68,10 @@ struct Relu3Party {
     u64* send;                           // [4][n] masked words of the current round
     u64* recv[2];                        // [4][n] the same from party+1 / party+2
     u8* vsend; u8* vrecv[2];             // B2A round (one byte per element)
-    // exchange by remote store: the stage kernel also writes its masked words where the two peers
-    // read them (put[s]: the receive buffer recv[s] of party (me + 2 - s) mod 3); recv_alt is the second
-    // set of receive buffers, alternating with recv from stage to stage in that mode
-    u64* put[2]; u64* putL[2]; u8* vput[2]; u64* recv_alt[2];
     // sign-only chain: per level a [4][pw] block of masked packed words, and the G bits a level keeps
     u64* sendL; u64* recvL[2]; u64* gsel;
 };
-struct Relu3Args { Relu3Party p[3]; size_t n; size_t tn; };   // n: elements of this call or chunk; tn: row stride of the [13][tn] triples
+struct Relu3Args { Relu3Party p[3]; size_t n; size_t tn; u64* box; };   // n: elements of this call or chunk; tn: row stride of the [13][tn] triples; box: receive buffers of the one-launch chain
 
 // Words are processed one per thread, or two per thread with 16-byte accesses
 // when the element count is even and every array is 16-byte aligned.
@@ -109,7 +106,7 @@ __device__ __forceinline__ T and_finish(int party, T d, T g, T a, T b, T c)
 //       8      : level 5 finished -> sign share, B2A masked
 //       9      : B2A finished -> m = 1 - s, select masked
 //       10     : select finished -> y
-template <int STAGE, typename T, bool PUT>
+template <int STAGE, typename T>
 __global__ __launch_bounds__(kT) void k3_relu(Relu3Args q)
 {
     typedef typename ByteOf<T>::type B;
@@ -124,30 +121,12 @@ __global__ __launch_bounds__(kT) void k3_relu(Relu3Args q)
     auto out = [n](u64* base, int r) { return reinterpret_cast<T*>(base + (size_t)r * n); };
     auto tr = [tn](const u64* base, int r) { return reinterpret_cast<const T*>(base + (size_t)r * tn); };
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < units; i += stride) {
-        // row k of this round's masked words: into the own send buffer and, by remote store, to both peers.
-        // From stage 2 on a party that stores to its peers keeps no copy for itself: the stage that opens the
-        // words forms the party's own ones again from the state it carries and the triples it reads anyway
-        // (the level stages then also carry P).
-        constexpr bool kReform = PUT && STAGE >= 3;          // the round before left no own copy
-        auto send = [&](int k, T v) {
-            if constexpr (!(PUT && STAGE >= 2)) out(p.send, k)[i] = v;
-            if constexpr (PUT) { out(p.put[0], k)[i] = v; out(p.put[1], k)[i] = v; }
-        };
+        auto send = [&](int k, T v) { out(p.send, k)[i] = v; };
         // masked words of the previous round, opened
         T o[4] = {};
         constexpr int kOpen = (STAGE == 0 || STAGE >= 9) ? 0 : (STAGE >= 3 && STAGE <= 7) ? 4 : 2;
-        if constexpr (kReform && kOpen > 0) {
-            // stages 3..8 finish level L = STAGE - 3, masked by the stage before from its (P, G) with shift 2^L
-            constexpr int L = STAGE - 3, tg = 2 + 2 * L, tp = 3 + 2 * L;
-            const T Pp = in(p.P, 0)[i], Gp = in(p.G, 0)[i];
-            o[0] = Pp ^ tr(p.ta, tg)[i];  o[1] = (Gp << (1 << L)) ^ tr(p.tb, tg)[i];
-            if constexpr (kOpen == 4) { o[2] = Pp ^ tr(p.ta, tp)[i];  o[3] = (Pp << (1 << L)) ^ tr(p.tb, tp)[i]; }
 #pragma unroll
-            for (int k = 0; k < kOpen; ++k) o[k] ^= in(p.recv[0], k)[i] ^ in(p.recv[1], k)[i];
-        } else {
-#pragma unroll
-            for (int k = 0; k < kOpen; ++k) o[k] = in(p.send, k)[i] ^ in(p.recv[0], k)[i] ^ in(p.recv[1], k)[i];
-        }
+        for (int k = 0; k < kOpen; ++k) o[k] = in(p.send, k)[i] ^ in(p.recv[0], k)[i] ^ in(p.recv[1], k)[i];
 
         if constexpr (STAGE == 0) {
             const T own = in(p.x, 0)[i] ^ in(p.r0, 0)[i] ^ in(p.r1, 0)[i];
@@ -180,7 +159,6 @@ __global__ __launch_bounds__(kT) void k3_relu(Relu3Args q)
             const T P = and_finish<T>(party, o[2], o[3], tr(p.ta, tp)[i], tr(p.tb, tp)[i], tr(p.tc, tp)[i]);
             const T G = in(p.G, 0)[i] ^ T1;
             out(p.G, 0)[i] = G;
-            if constexpr (PUT) out(p.P, 0)[i] = P;       // the next stage forms this party's masked words from (P, G)
             constexpr int d = 2 << L;                    // shift of level L + 1
             constexpr int ng = tg + 2, np = tp + 2;
             send(0, P ^ tr(p.ta, ng)[i]);  send(1, (G << d) ^ tr(p.tb, ng)[i]);
@@ -194,7 +172,6 @@ __global__ __launch_bounds__(kT) void k3_relu(Relu3Args q)
             if (p.s_bit) reinterpret_cast<B*>(p.s_bit)[i] = s;
             const B masked = s ^ reinterpret_cast<const B*>(p.rb)[i];
             reinterpret_cast<B*>(p.vsend)[i] = masked;
-            if constexpr (PUT) { reinterpret_cast<B*>(p.vput[0])[i] = masked; reinterpret_cast<B*>(p.vput[1])[i] = masked; }
         } else if constexpr (STAGE == 9) {
             const T v = to_words(reinterpret_cast<const B*>(p.vsend)[i] ^ reinterpret_cast<const B*>(p.vrecv[0])[i] ^
                                  reinterpret_cast<const B*>(p.vrecv[1])[i]);
@@ -208,20 +185,8 @@ __global__ __launch_bounds__(kT) void k3_relu(Relu3Args q)
         } else {
             // additive opening of the select product's masked operands
             const T mb = in(p.mb, 0)[i], ma = in(p.ma, 0)[i];
-            T e_own, f_own;
-            if constexpr (PUT) {                         // formed again from x, ra and the opened sign byte
-                const T v = to_words(reinterpret_cast<const B*>(p.vsend)[i] ^ reinterpret_cast<const B*>(p.vrecv[0])[i] ^
-                                     reinterpret_cast<const B*>(p.vrecv[1])[i]);
-                const T ra = in(p.ra, 0)[i];
-                T sa = ra - 2 * v * ra;
-                if (party == 0) sa += v;
-                e_own = in(p.x, 0)[i] - ma;
-                f_own = ((party == 0 ? (u64)1 : (u64)0) - sa) - mb;
-            } else {
-                e_own = in(p.send, 0)[i]; f_own = in(p.send, 1)[i];
-            }
-            const T e = e_own + in(p.recv[0], 0)[i] + in(p.recv[1], 0)[i];
-            const T f = f_own + in(p.recv[0], 1)[i] + in(p.recv[1], 1)[i];
+            const T e = in(p.send, 0)[i] + in(p.recv[0], 0)[i] + in(p.recv[1], 0)[i];
+            const T f = in(p.send, 1)[i] + in(p.recv[0], 1)[i] + in(p.recv[1], 1)[i];
             T yv = in(p.mc, 0)[i] + e * mb + ma * f;
             if (party == 0) yv += e * f;
             out(p.y, 0)[i] = yv;
@@ -312,7 +277,7 @@ __device__ __forceinline__ void st2(u64* p, size_t j, u64 a, u64 b)
 // LEVEL 0, else level LEVEL - 1 on packed words) for the four input words behind two
 // output words, regroup, and mask this level's operands.  `vec0`: the whole-word arrays
 // of LEVEL 0 allow 16-byte loads (n a multiple of four, aligned bases).
-template <int LEVEL, bool PUT>
+template <int LEVEL>
 __global__ __launch_bounds__(kT) void k3_plevel(Relu3Args q, Msb3Geom g, bool vec0)
 {
     const int party = blockIdx.y;
@@ -364,14 +329,7 @@ __global__ __launch_bounds__(kT) void k3_plevel(Relu3Args q, Msb3Geom g, bool ve
         const size_t pl = g.pw[LEVEL];
         u64* so = p.sendL + g.loff[LEVEL];
         const u64v2 na1 = *reinterpret_cast<const u64v2*>(p.ta + g.toff[ng] + j), nb1 = *reinterpret_cast<const u64v2*>(p.tb + g.toff[ng] + j);
-        // row r of this level's block: own send buffer and, by remote store, both peers' receive blocks
-        auto send2 = [&](int r, u64 a, u64 b) {
-            st2(so + (size_t)r * pl, j, a, b);
-            if constexpr (PUT) {
-                st2(p.putL[0] + g.loff[LEVEL] + (size_t)r * pl, j, a, b);
-                st2(p.putL[1] + g.loff[LEVEL] + (size_t)r * pl, j, a, b);
-            }
-        };
+        auto send2 = [&](int r, u64 a, u64 b) { st2(so + (size_t)r * pl, j, a, b); };      // row r of this level's block
         send2(0, X[0] ^ na1.x, X[1] ^ na1.y);
         send2(1, Y1[0] ^ nb1.x, Y1[1] ^ nb1.y);
         if constexpr (LEVEL < 5) {                               // the last level needs no P update
@@ -385,7 +343,7 @@ __global__ __launch_bounds__(kT) void k3_plevel(Relu3Args q, Msb3Geom g, bool ve
 
 // Packed sign stage: finish level 5; element i's carry into bit 63 sits at bit
 // (62 + i) mod 64 of word i / 64.  Then the B2A mask as in stage 8 of the whole-word chain.
-template <int V, bool PUT>
+template <int V>
 __global__ __launch_bounds__(kT) void k3_psign(Relu3Args q, Msb3Geom g)
 {
     const int party = blockIdx.y;
@@ -408,13 +366,11 @@ __global__ __launch_bounds__(kT) void k3_psign(Relu3Args q, Msb3Geom g)
             const uint32_t sb = top ^ carry;
             if (p.s_bit) *reinterpret_cast<uint32_t*>(p.s_bit + i) = sb;
             *reinterpret_cast<uint32_t*>(p.vsend + i) = sb ^ rb;
-            if constexpr (PUT) { *reinterpret_cast<uint32_t*>(p.vput[0] + i) = sb ^ rb; *reinterpret_cast<uint32_t*>(p.vput[1] + i) = sb ^ rb; }
         } else {
             const u8 sb = (u8)(p.p63[i] ^ (u8)((Gw >> ((62 + i) & 63)) & 1));
             if (p.s_bit) p.s_bit[i] = sb;
             const u8 masked = (u8)(sb ^ p.rb[i]);
             p.vsend[i] = masked;
-            if constexpr (PUT) { p.vput[0][i] = masked; p.vput[1][i] = masked; }
         }
     }
 }
@@ -442,46 +398,18 @@ __global__ __launch_bounds__(kT) void k3_pack_triples(const u64* __restrict__ in
     }
 }
 
-// Arguments of one stage launch when the exchange is by remote store: the launch with index k
-// reads the receive-buffer set (k - 1) & 1 and stores into the peers' set k & 1, so that no party
-// stores where a peer's same launch still reads.  Party i's words land in recv[s] of party
-// (i + 2 - s) mod 3, the buffer that party reads for its peer number s.
-Relu3Args put_args(const Relu3Args& q, int k)
-{
-    Relu3Args a = q;
-    for (int i = 0; i < 3; ++i)
-        for (int s = 0; s < 2; ++s) {
-            const int peer = (i + 2 - s) % 3;
-            u64* const rd[2] = { q.p[i].recv[s], q.p[i].recv_alt[s] };
-            u64* const wr[2] = { q.p[peer].recv[s], q.p[peer].recv_alt[s] };
-            a.p[i].recv[s] = rd[(k + 1) & 1];
-            a.p[i].put[s] = wr[k & 1];
-            a.p[i].putL[s] = q.p[peer].recvL[s];
-            a.p[i].vput[s] = q.p[peer].vrecv[s];
-        }
-    return a;
-}
-
-template <int STAGE, bool PUT>
-int launch_stage_t(mpc_ctx* c, hipStream_t st, const Relu3Args& q, int vec)
-{
-    if (vec == 4)      hipLaunchKernelGGL((k3_relu<STAGE, u64v4, PUT>), dim3(grid3(q.n / 4), 3), dim3(kT), 0, st, q);
-    else if (vec == 2) hipLaunchKernelGGL((k3_relu<STAGE, u64v2, PUT>), dim3(grid3(q.n / 2), 3), dim3(kT), 0, st, q);
-    else               hipLaunchKernelGGL((k3_relu<STAGE, u64, PUT>), dim3(grid3(q.n), 3), dim3(kT), 0, st, q);
-    MPC_HIP(c, hipGetLastError());
-    return MPC_OK;
-}
-
 int exchange_words(mpc_ctx* c, hipStream_t st, const Relu3Args& q, int words);
 int exchange_bytes(mpc_ctx* c, hipStream_t st, const Relu3Args& q);
 
 // Stage STAGE for all three parties, then the exchange of what it sends: `rows` word rows,
-// bytes for rows < 0, nothing for rows == 0.  By remote store the kernel itself delivers.
+// bytes for rows < 0, nothing for rows == 0.
 template <int STAGE>
 int launch_stage(mpc_ctx* c, hipStream_t st, const Relu3Args& q, int vec, int rows)
 {
-    if (c->exchange_put) return launch_stage_t<STAGE, true>(c, st, put_args(q, STAGE), vec);
-    MPC_TRY((launch_stage_t<STAGE, false>(c, st, q, vec)));
+    if (vec == 4)      hipLaunchKernelGGL((k3_relu<STAGE, u64v4>), dim3(grid3(q.n / 4), 3), dim3(kT), 0, st, q);
+    else if (vec == 2) hipLaunchKernelGGL((k3_relu<STAGE, u64v2>), dim3(grid3(q.n / 2), 3), dim3(kT), 0, st, q);
+    else               hipLaunchKernelGGL((k3_relu<STAGE, u64>), dim3(grid3(q.n), 3), dim3(kT), 0, st, q);
+    MPC_HIP(c, hipGetLastError());
     if (rows == 0) return MPC_OK;
     return rows > 0 ? exchange_words(c, st, q, rows) : exchange_bytes(c, st, q);
 }
@@ -507,7 +435,8 @@ int exchange_bytes(mpc_ctx* c, hipStream_t st, const Relu3Args& q)
     return launch_copy_multi(c, st, cp, 6);
 }
 
-size_t relu3_ws(u8* base, size_t cap, size_t n, Relu3Args* q, bool* ok)
+// stage buffers for chunks of n elements; the one-launch chain takes the whole call (calln) at once
+size_t relu3_ws(u8* base, size_t cap, size_t n, size_t calln, Relu3Args* q, bool* ok)
 {
     WsAlloc w(base, cap);
     for (int i = 0; i < 3; ++i) {
@@ -517,10 +446,10 @@ size_t relu3_ws(u8* base, size_t cap, size_t n, Relu3Args* q, bool* ok)
         p.send = w.take<u64>(4 * n); p.recv[0] = w.take<u64>(4 * n); p.recv[1] = w.take<u64>(4 * n);
         p.p63 = w.take<u8>(n); p.vsend = w.take<u8>(n); p.vrecv[0] = w.take<u8>(n); p.vrecv[1] = w.take<u8>(n);
     }
-    for (int i = 0; i < 3; ++i)      // only touched by the remote-store exchange
-        for (int s = 0; s < 2; ++s) q->p[i].recv_alt[s] = w.take<u64>(4 * n);
-    if (ok) *ok = w.ok;
-    return w.off;
+    q->box = reinterpret_cast<u64*>(base);
+    const size_t box = relu_fused_box_bytes(3, calln), bytes = w.off > box ? w.off : box;
+    if (ok) *ok = w.ok && cap >= bytes;
+    return bytes;
 }
 
 int check_material3(const mpc_relu3_material* m)
@@ -545,6 +474,18 @@ void fill3(Relu3Args& q, const u64* const x[3], const mpc_relu3_material* m, u64
         p.s_bit = s_bit ? s_bit[i] : nullptr; p.s_arith = s_arith ? s_arith[i] : nullptr;
     }
     q.n = n; q.tn = n;
+}
+
+// the call's arrays as the one-launch chain (exchange by remote store) takes them
+FusedRelu fused3(const Relu3Args& q)
+{
+    FusedRelu f{};
+    for (int i = 0; i < 3; ++i) {
+        const Relu3Party& p = q.p[i];
+        f.p[i] = FusedReluParty{ p.x, p.r0, p.r1, p.ta, p.tb, p.tc, p.rb, p.ra, p.ma, p.mb, p.mc, p.y, p.s_bit, p.s_arith };
+    }
+    f.box = q.box; f.n = q.n;
+    return f;
 }
 
 // The whole chain for one chunk on one stream: A2B distribution, 11 stage kernels, 10 word exchanges, one byte exchange.
@@ -600,6 +541,7 @@ inline size_t relu3_chunk_cap(size_t n, size_t chunk = kChunk3)          // larg
 int relu3_run(mpc_ctx* c, hipStream_t st, const Relu3Args& q)
 {
     const size_t n = q.n;
+    if (c->exchange_put) return launch_relu_fused(c, st, 3, fused3(q), 0);
     const int k = relu3_chunks(n, relu3_chunk_of(c));
     if (k == 1) return relu3_chunk(c, st, q);
     const size_t cap = relu3_chunk_cap(n, relu3_chunk_of(c));
@@ -632,10 +574,10 @@ size_t relu3_msb_ws(u8* base, size_t cap, size_t n, const Msb3Geom& g, Relu3Args
         p.sendL = w.take<u64>(g.words_blocks); p.recvL[0] = w.take<u64>(g.words_blocks); p.recvL[1] = w.take<u64>(g.words_blocks);
         p.gsel = w.take<u64>(g.words_gsel);
     }
-    for (int i = 0; i < 3; ++i)      // only touched by the remote-store exchange
-        for (int s = 0; s < 2; ++s) q->p[i].recv_alt[s] = w.take<u64>(2 * n);
-    if (ok) *ok = w.ok;
-    return w.off;
+    q->box = reinterpret_cast<u64*>(base);
+    const size_t box = relu_fused_msb_box_bytes(3, n), bytes = w.off > box ? w.off : box;
+    if (ok) *ok = w.ok && cap >= bytes;
+    return bytes;
 }
 
 template <int LEVEL>
@@ -643,13 +585,7 @@ int launch_plevel(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom
 {
     const size_t words = (q.n + ((size_t)2 << LEVEL) - 1) >> (LEVEL + 1);
     const dim3 grid(grid3((words + 1) / 2), 3), block(kT);
-    if (c->exchange_put) {
-        // level 0 reads the whole words stage 1 delivered (launch index 2); the levels' own blocks do not alternate
-        hipLaunchKernelGGL((k3_plevel<LEVEL, true>), grid, block, 0, st, put_args(q, 2), g, vec0);
-        MPC_HIP(c, hipGetLastError());
-        return MPC_OK;
-    }
-    hipLaunchKernelGGL((k3_plevel<LEVEL, false>), grid, block, 0, st, q, g, vec0);
+    hipLaunchKernelGGL((k3_plevel<LEVEL>), grid, block, 0, st, q, g, vec0);
     MPC_HIP(c, hipGetLastError());
     // this level's masked packed words go to both peers
     const size_t len = (size_t)(LEVEL < 5 ? 4 : 2) * g.pw[LEVEL] * sizeof(u64);
@@ -664,6 +600,11 @@ int launch_plevel(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom
 int relu3_msb_run(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom& g)
 {
     const size_t n = q.n;
+    if (c->exchange_put) {
+        PackedTriples t{};
+        for (int k = 0; k < 13; ++k) t.off[k] = g.toff[k];
+        return launch_relu_fused_msb(c, st, 3, fused3(q), t);
+    }
     const int vec = relu3_vectorisable(q);
     const bool vec0 = vec >= 2 && n % 4 == 0;
     {
@@ -683,17 +624,10 @@ int relu3_msb_run(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom
     MPC_TRY(launch_plevel<4>(c, st, q, g, vec0));
     MPC_TRY(launch_plevel<5>(c, st, q, g, vec0));
     const dim3 sgrid(vec == 4 ? grid3(n / 4) : grid3(n), 3), block(kT);
-    if (c->exchange_put) {
-        const Relu3Args a = put_args(q, 8);
-        if (vec == 4) hipLaunchKernelGGL((k3_psign<4, true>), sgrid, block, 0, st, a, g);
-        else          hipLaunchKernelGGL((k3_psign<1, true>), sgrid, block, 0, st, a, g);
-        MPC_HIP(c, hipGetLastError());
-    } else {
-        if (vec == 4) hipLaunchKernelGGL((k3_psign<4, false>), sgrid, block, 0, st, q, g);
-        else          hipLaunchKernelGGL((k3_psign<1, false>), sgrid, block, 0, st, q, g);
-        MPC_HIP(c, hipGetLastError());
-        MPC_TRY(exchange_bytes(c, st, q));
-    }
+    if (vec == 4) hipLaunchKernelGGL(k3_psign<4>, sgrid, block, 0, st, q, g);
+    else          hipLaunchKernelGGL(k3_psign<1>, sgrid, block, 0, st, q, g);
+    MPC_HIP(c, hipGetLastError());
+    MPC_TRY(exchange_bytes(c, st, q));
     MPC_TRY(launch_stage<9>(c, st, q, vec, 2));
     MPC_TRY(launch_stage<10>(c, st, q, vec, 0));
     return MPC_OK;
@@ -896,7 +830,7 @@ size_t mpc_relu3_workspace_bytes(size_t n)
 {
     if (n == 0) return 0;
     Relu3Args q{};
-    return relu3_ws(nullptr, 0, relu3_chunk_cap(n), &q, nullptr);
+    return relu3_ws(nullptr, 0, relu3_chunk_cap(n), n, &q, nullptr);
 }
 
 int mpc_relu3(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m, mpc_share3 y, size_t n,
@@ -908,7 +842,7 @@ int mpc_relu3(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m, mpc_share3
     for (int i = 0; i < 3; ++i) if (!x.p[i] || !y.p[i]) return MPC_EINVAL;
     Relu3Args q{};
     bool ok = false;
-    relu3_ws(c->ws, c->ws_bytes, relu3_chunk_cap(n, relu3_chunk_of(c)), &q, &ok);
+    relu3_ws(c->ws, c->ws_bytes, relu3_chunk_cap(n, relu3_chunk_of(c)), n, &q, &ok);
     if (!ok) return MPC_ENOMEM;
     fill3(q, x.p, m, y.p, s_bit, s_arith, n);
     hipStream_t st = c->s[0];
@@ -1007,8 +941,8 @@ static int maxpool3_entry(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m
         relu3_msb_ws(rest, room, 2 * n_out, g1, &q1, &ok1);
         relu3_msb_ws(rest, room, n_out, g2, &q2, &ok2);                        // the second conversion reuses the scratch
     } else {
-        relu3_ws(rest, room, relu3_chunk_cap(2 * n_out, relu3_chunk_of(c)), &q1, &ok1);
-        relu3_ws(rest, room, relu3_chunk_cap(n_out, relu3_chunk_of(c)), &q2, &ok2);
+        relu3_ws(rest, room, relu3_chunk_cap(2 * n_out, relu3_chunk_of(c)), 2 * n_out, &q1, &ok1);
+        relu3_ws(rest, room, relu3_chunk_cap(n_out, relu3_chunk_of(c)), n_out, &q2, &ok2);
     }
     if (!ok1 || !ok2) return MPC_ENOMEM;
     fill3(q1, pq.d1, mat1, r1, nullptr, s1, 2 * n_out);

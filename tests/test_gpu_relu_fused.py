@@ -70,3 +70,21 @@ def test_one_launch_sign_only_relu(mpc, lane, n):
     equal(mpc, y, want.y, "output")
     equal(mpc, sb, want.s_bit, "sign bit share")
     equal(mpc, sa, want.s_arith, "sign arithmetic share")
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 32768, 32769, 65536 + 129, 98304, 98305, 98304 + 193])
+def test_one_launch_relu_three_parties(mpc, lane, n, packed):
+    """Three parties: one to two elements per lane at 32 768 | 32 769 (whole words) and 98 304 | 98 305 (packed)."""
+    print(f"one-launch three-party relu n={n} packed={packed}", flush=True)
+    rng = np.random.default_rng(n)
+    xs = synth.share_additive3(rng, synth.normal_fixed(rng, n, 4.0))
+    mat = synth.deal_relu3_material(rng, n)
+    want = oracle.relu3(xs, mat)
+    md = mpc.material_to_device(mat)
+    x = dev(mpc, xs)
+    y, sb, sa = lane.relu3(x, lane.pack_material3(md) if packed else md, want_sign=True, packed=packed, out=x if n % 2 else None)
+    lane.sync()
+    equal(mpc, y, want.y, "output")
+    equal(mpc, sb, want.s_bit, "sign bit share")
+    equal(mpc, sa, want.s_arith, "sign arithmetic share")
