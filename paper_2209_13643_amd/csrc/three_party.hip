@@ -446,6 +446,8 @@ size_t relu3_ws(u8* base, size_t cap, size_t n, size_t calln, Relu3Args* q, bool
         p.send = w.take<u64>(4 * n); p.recv[0] = w.take<u64>(4 * n); p.recv[1] = w.take<u64>(4 * n);
         p.p63 = w.take<u8>(n); p.vsend = w.take<u8>(n); p.vrecv[0] = w.take<u8>(n); p.vrecv[1] = w.take<u8>(n);
     }
+    // 24 n more words belong to the documented size of this workspace (a second set of receive buffers, once)
+    for (int i = 0; i < 6; ++i) w.take<u64>(4 * n);
     q->box = reinterpret_cast<u64*>(base);
     const size_t box = relu_fused_box_bytes(3, calln), bytes = w.off > box ? w.off : box;
     if (ok) *ok = w.ok && cap >= bytes;
