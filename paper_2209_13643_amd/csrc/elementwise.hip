@@ -82,20 +82,56 @@ __device__ __forceinline__ u64 balanced_digits(u64 x)
     return (x + h) ^ h;
 }
 
+// The digits of four words, digit by digit: out[d] holds digit d of w[0..3] in bytes 0..3.
+__device__ __forceinline__ void digits_of_4(const u64 (&w)[4], uint32_t (&out)[8])
+{
+    uint32_t h[2][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) { const u64 d = balanced_digits(w[t]); h[0][t] = (uint32_t)d; h[1][t] = (uint32_t)(d >> 32); }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        // a 4 x 4 byte transpose in eight byte permutes
+        const uint32_t x0 = __builtin_amdgcn_perm(h[q][1], h[q][0], 0x05010400), y0 = __builtin_amdgcn_perm(h[q][3], h[q][2], 0x05010400);
+        const uint32_t x1 = __builtin_amdgcn_perm(h[q][1], h[q][0], 0x07030602), y1 = __builtin_amdgcn_perm(h[q][3], h[q][2], 0x07030602);
+        out[4 * q + 0] = __builtin_amdgcn_perm(y0, x0, 0x05040100); out[4 * q + 1] = __builtin_amdgcn_perm(y0, x0, 0x07060302);
+        out[4 * q + 2] = __builtin_amdgcn_perm(y1, x1, 0x05040100); out[4 * q + 3] = __builtin_amdgcn_perm(y1, x1, 0x07060302);
+    }
+}
+
+// 16 consecutive k of one row to the eight planes of one k block
+__device__ __forceinline__ void store_unit(const u64 (&v)[16], u8* out, long long digit_stride)
+{
+    uint32_t w[8][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const u64 four[4] = { v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3] };
+        uint32_t d[8];
+        digits_of_4(four, d);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k][q] = d[k];
+    }
+#pragma unroll
+    for (int d = 0; d < 8; ++d) *reinterpret_cast<uint4*>(out + (size_t)d * digit_stride) = make_uint4(w[d][0], w[d][1], w[d][2], w[d][3]);
+}
+
 // One thread recodes one (row, k-block): 16 ring words in, one 16-byte unit
 // out per digit plane.  Consecutive lanes take consecutive rows so that the
-// plane stores are contiguous.
+// plane stores are contiguous.  The 16 words of every operand are loaded at clamped indices with no branch between
+// them and masked afterwards: with a range check around each word the loads ran one after the other (a recoding of
+// any size took at least 12 us, now 5).
 __device__ __forceinline__ void recode_body(const RecodeArgs& a, int tap /* == ntaps: zero padding block(s) */, int b,
                                             unsigned bx, unsigned nbx)
 {
-    const u64* src = a.src + (size_t)b * a.src_batch_stride;
-    const u64* src2 = a.src2 ? a.src2 + (size_t)b * a.src_batch_stride : nullptr;
-    const u64* src3 = a.src3 ? a.src3 + (size_t)b * a.src_batch_stride : nullptr;
-    const u64* sub = a.sub ? a.sub + (size_t)b * a.src_batch_stride : nullptr;
-    u64* side = a.side ? a.side + (size_t)b * a.src_batch_stride : nullptr;
-    const u64* minuend = (a.minuend && a.side && !a.sub) ? a.minuend + (size_t)b * a.src_batch_stride : nullptr;
-    u8* dst = a.dst + (size_t)b * a.dst_batch_stride;
+    // tap_stride may be negative (filters read in reverse tap order)
     const bool padtap = tap >= a.ntaps;
+    const long long at = (long long)b * a.src_batch_stride + (padtap ? 0 : (long long)tap * a.tap_stride);
+    const u64* src = a.src + at;
+    const u64* src2 = a.src2 ? a.src2 + at : nullptr;
+    const u64* src3 = a.src3 ? a.src3 + at : nullptr;
+    const u64* sub = a.sub ? a.sub + at : nullptr;
+    u64* side = a.side ? a.side + at : nullptr;
+    const u64* minuend = (a.minuend && a.side && !a.sub) ? a.minuend + at : nullptr;
+    u8* dst = a.dst + (size_t)b * a.dst_batch_stride;
     const int kb_count = padtap ? a.KB_total - a.ntaps * a.KB_tap : a.KB_tap;
     const size_t items = (size_t)kb_count * a.plane_rows;
     const size_t stride = (size_t)nbx * blockDim.x;
@@ -103,36 +139,42 @@ __device__ __forceinline__ void recode_body(const RecodeArgs& a, int tap /* == n
         const int kbl = (int)(it / a.plane_rows);
         const int row = (int)(it - (size_t)kbl * a.plane_rows);
         const int kb_out = (padtap ? a.ntaps * a.KB_tap : tap * a.KB_tap) + kbl;
-        u64 dg[16];
+        const int k0 = kbl * 16;
+        // valid words of the unit: k0 .. k0 + have - 1
+        const int have = (padtap || row >= a.rows) ? 0 : a.K - k0 < 16 ? (a.K - k0 > 0 ? a.K - k0 : 0) : 16;
+        const long long base = (long long)(row < a.rows ? row : 0) * a.row_stride + (long long)(k0 < a.K ? k0 : 0) * a.k_stride;
+        auto load = [&](const u64* q, u64 (&w)[16]) {
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            const int k = kbl * 16 + t;
-            u64 v = 0;
-            if (!padtap && k < a.K && row < a.rows) {
-                // tap_stride may be negative (filters read in reverse tap order)
-                const long long idx = (long long)row * a.row_stride + (long long)k * a.k_stride + (long long)tap * a.tap_stride;
-                v = src[idx];
-                if (sub) { v -= sub[idx]; if (side) side[idx] = v; }
-                else if (minuend) side[idx] = minuend[idx] - v;
-                if (src2) v += src2[idx];
-                if (src3) v += src3[idx];
+            for (int t = 0; t < 16; ++t) w[t] = q[base + (long long)(t < have ? t : 0) * a.k_stride];
+        };
+        u64 v[16], w[16];
+        load(src, v);
+        if (sub) {
+            load(sub, w);
+#pragma unroll
+            for (int t = 0; t < 16; ++t) v[t] -= w[t];
+            if (side) {
+#pragma unroll
+                for (int t = 0; t < 16; ++t) if (t < have) side[base + (long long)t * a.k_stride] = v[t];
             }
-            dg[t] = balanced_digits(v);
+        } else if (minuend) {
+            load(minuend, w);
+#pragma unroll
+            for (int t = 0; t < 16; ++t) if (t < have) side[base + (long long)t * a.k_stride] = w[t] - v[t];
         }
-        u8* out = dst + ((size_t)kb_out * a.plane_rows + row) * 16;
+        if (src2) {
+            load(src2, w);
 #pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            uint32_t w[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t v = 0;
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    v |= (uint32_t)((dg[q * 4 + t] >> (8 * d)) & 0xff) << (8 * t);
-                w[q] = v;
-            }
-            *reinterpret_cast<uint4*>(out + (size_t)d * a.digit_stride) = make_uint4(w[0], w[1], w[2], w[3]);
+            for (int t = 0; t < 16; ++t) v[t] += w[t];
         }
+        if (src3) {
+            load(src3, w);
+#pragma unroll
+            for (int t = 0; t < 16; ++t) v[t] += w[t];
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) v[t] = t < have ? v[t] : 0;
+        store_unit(v, dst + ((size_t)kb_out * a.plane_rows + row) * 16, a.digit_stride);
     }
 }
 
@@ -142,84 +184,104 @@ __global__ __launch_bounds__(kThreads) void k_recode(RecodeArgs a)
 }
 
 // Recoding of a matrix whose k index is contiguous in memory (left operands,
-// NHWC activations): a workgroup takes a 64-row x 64-k tile, reads it with
-// lanes along k (coalesced 16-byte loads), scatters the digits into LDS in
+// NHWC activations, filters read with their channel roles swapped): a workgroup takes a 64-row x 64-k tile of one
+// filter tap, reads it with lanes along k (coalesced 16-byte loads), scatters the digits into LDS in
 // plane order, and writes each plane's 16-byte units with lanes along rows
-// (coalesced again).  blockIdx = (row tile, group of 4 k blocks, set*batch).
+// (coalesced again).  bx = row tile, by = (tap, group of 4 k blocks); the loads of an operand are issued together.
+__device__ __forceinline__ int row_groups(const RecodeArgs& a) { return ((a.ntaps == 1 ? a.KB_total : a.KB_tap) + 3) / 4; }
 __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, unsigned bx, unsigned by, uint32_t (*tile)[4][64][4])
 {
-    const int row0 = bx * 64, kb0 = by * 4;
-    if (row0 >= a.plane_rows || kb0 >= a.KB_total) return;      // uniform per workgroup
-    const u64* src = a.src + (size_t)b * a.src_batch_stride;
-    const u64* src2 = a.src2 ? a.src2 + (size_t)b * a.src_batch_stride : nullptr;
-    const u64* src3 = a.src3 ? a.src3 + (size_t)b * a.src_batch_stride : nullptr;
-    const u64* sub = a.sub ? a.sub + (size_t)b * a.src_batch_stride : nullptr;
-    u64* side = a.side ? a.side + (size_t)b * a.src_batch_stride : nullptr;
-    const u64* minuend = (a.minuend && a.side && !a.sub) ? a.minuend + (size_t)b * a.src_batch_stride : nullptr;
+    const int groups = row_groups(a), tap = (int)by / groups;
+    const int row0 = bx * 64, kb0 = ((int)by - tap * groups) * 4;
+    const bool padtap = tap >= a.ntaps;                          // the k blocks behind the last tap: zero
+    const int kb_lim = padtap ? a.KB_total - a.ntaps * a.KB_tap : a.ntaps == 1 ? a.KB_total : a.KB_tap;
+    const int kb_first = tap * a.KB_tap;
+    if (row0 >= a.plane_rows || kb0 >= kb_lim) return;           // uniform per workgroup
+    const long long at = (long long)b * a.src_batch_stride + (padtap ? 0 : (long long)tap * a.tap_stride);
+    const u64* src = a.src + at;
+    const u64* src2 = a.src2 ? a.src2 + at : nullptr;
+    const u64* src3 = a.src3 ? a.src3 + at : nullptr;
+    const u64* sub = a.sub ? a.sub + at : nullptr;
+    u64* side = a.side ? a.side + at : nullptr;
+    const u64* minuend = (a.minuend && a.side && !a.sub) ? a.minuend + at : nullptr;
     u8* dst = a.dst + (size_t)b * a.dst_batch_stride;
-    const bool vec_ok = (a.row_stride % 2 == 0) && (((uintptr_t)src & 15) == 0) &&
-                        (!src2 || ((uintptr_t)src2 & 15) == 0) && (!src3 || ((uintptr_t)src3 & 15) == 0) &&
-                        (!sub || ((uintptr_t)sub & 15) == 0) && (!side || ((uintptr_t)side & 15) == 0) &&
-                        (!minuend || ((uintptr_t)minuend & 15) == 0);
+    const int k_lim = padtap ? 0 : a.K;
+    const bool vec = (a.row_stride % 2 == 0) && (((uintptr_t)src | (uintptr_t)src2 | (uintptr_t)src3 | (uintptr_t)sub |
+                                                  (uintptr_t)side | (uintptr_t)minuend) & 15) == 0;
+    // thread's segments: 4 words each, segment p at row (threadIdx.x + 256 p) / 16 of the tile
+    const int s4 = threadIdx.x & 15, k = kb0 * 16 + s4 * 4;
+    const bool whole = vec && k + 3 < k_lim;                     // 16-byte accesses allowed
+    auto row_of = [&](int p) { return row0 + (int)(threadIdx.x >> 4) + 16 * p; };
+    auto load = [&](const u64* q, u64 (&w)[4][4]) {
+        if (whole) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int seg = threadIdx.x + 256 * p;
-        const int row = seg >> 4, s4 = seg & 15;
-        const int r = row0 + row, k = kb0 * 16 + s4 * 4;
-        u64 v[4] = { 0, 0, 0, 0 };
-        if (r < a.rows && k < a.K) {
-            const size_t idx = (size_t)r * a.row_stride + k;
-            if (vec_ok && k + 3 < a.K) {
-                const u64x2 p0 = *reinterpret_cast<const u64x2*>(src + idx), p1 = *reinterpret_cast<const u64x2*>(src + idx + 2);
-                v[0] = p0.a; v[1] = p0.b; v[2] = p1.a; v[3] = p1.b;
-                if (sub) {
-                    const u64x2 q0 = *reinterpret_cast<const u64x2*>(sub + idx), q1 = *reinterpret_cast<const u64x2*>(sub + idx + 2);
-                    v[0] -= q0.a; v[1] -= q0.b; v[2] -= q1.a; v[3] -= q1.b;
-                    if (side) {
-                        u64x2 s0, s1; s0.a = v[0]; s0.b = v[1]; s1.a = v[2]; s1.b = v[3];
-                        *reinterpret_cast<u64x2*>(side + idx) = s0; *reinterpret_cast<u64x2*>(side + idx + 2) = s1;
-                    }
-                }
-                if (minuend) {
-                    const u64x2 q0 = *reinterpret_cast<const u64x2*>(minuend + idx), q1 = *reinterpret_cast<const u64x2*>(minuend + idx + 2);
-                    u64x2 s0, s1; s0.a = q0.a - v[0]; s0.b = q0.b - v[1]; s1.a = q1.a - v[2]; s1.b = q1.b - v[3];
-                    *reinterpret_cast<u64x2*>(side + idx) = s0; *reinterpret_cast<u64x2*>(side + idx + 2) = s1;
-                }
-                if (src2) { const u64x2 q0 = *reinterpret_cast<const u64x2*>(src2 + idx), q1 = *reinterpret_cast<const u64x2*>(src2 + idx + 2);
-                            v[0] += q0.a; v[1] += q0.b; v[2] += q1.a; v[3] += q1.b; }
-                if (src3) { const u64x2 q0 = *reinterpret_cast<const u64x2*>(src3 + idx), q1 = *reinterpret_cast<const u64x2*>(src3 + idx + 2);
-                            v[0] += q0.a; v[1] += q0.b; v[2] += q1.a; v[3] += q1.b; }
-            } else {
+            for (int p = 0; p < 4; ++p) {
+                const int r = row_of(p);
+                const u64x2* t = reinterpret_cast<const u64x2*>(q + (size_t)(r < a.rows ? r : 0) * a.row_stride + k);
+                const u64x2 lo = t[0], hi = t[1];
+                w[p][0] = lo.a; w[p][1] = lo.b; w[p][2] = hi.a; w[p][3] = hi.b;
+            }
+        } else {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (k + t < a.K) {
-                        v[t] = src[idx + t];
-                        if (sub) { v[t] -= sub[idx + t]; if (side) side[idx + t] = v[t]; }
-                        else if (minuend) side[idx + t] = minuend[idx + t] - v[t];
-                        if (src2) v[t] += src2[idx + t];
-                        if (src3) v[t] += src3[idx + t];
-                    }
+            for (int p = 0; p < 4; ++p) {
+                const int r = row_of(p);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) w[p][t] = q[(size_t)(r < a.rows ? r : 0) * a.row_stride + (k + t < k_lim ? k + t : 0)];
             }
         }
-        u64 dg[4];
+    };
+    auto store = [&](u64* q, const u64 (&w)[4][4]) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) dg[t] = balanced_digits(v[t]);
+        for (int p = 0; p < 4; ++p) {
+            const int r = row_of(p);
+            if (r >= a.rows) continue;
+            u64* o = q + (size_t)r * a.row_stride + k;
+            if (whole) {
+                u64x2 lo, hi; lo.a = w[p][0]; lo.b = w[p][1]; hi.a = w[p][2]; hi.b = w[p][3];
+                reinterpret_cast<u64x2*>(o)[0] = lo; reinterpret_cast<u64x2*>(o)[1] = hi;
+            } else {
 #pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            uint32_t w = 0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) w |= (uint32_t)((dg[t] >> (8 * d)) & 0xff) << (8 * t);
-            tile[d][s4 >> 2][row][s4 & 3] = w;
+                for (int t = 0; t < 4; ++t) if (k + t < k_lim) o[t] = w[p][t];
+            }
         }
+    };
+    auto fold = [&](u64 (&v)[4][4], const u64 (&w)[4][4], bool minus) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[p][t] = minus ? v[p][t] - w[p][t] : v[p][t] + w[p][t];
+    };
+    u64 v[4][4], w[4][4];
+    load(src, v);
+    if (sub) {
+        load(sub, w);
+        fold(v, w, true);
+        if (side) store(side, v);
+    } else if (minuend) {
+        load(minuend, w);
+        fold(w, v, true);
+        store(side, w);
+    }
+    if (src2) { load(src2, w); fold(v, w, false); }
+    if (src3) { load(src3, w); fold(v, w, false); }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const bool row_ok = row_of(p) < a.rows;
+        u64 four[4]; uint32_t d[8];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) four[t] = row_ok && k + t < k_lim ? v[p][t] : 0;
+        digits_of_4(four, d);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) tile[q][s4 >> 2][(threadIdx.x >> 4) + 16 * p][s4 & 3] = d[q];
     }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int u = threadIdx.x + 256 * q;
         const int d = u >> 8, kbl = (u >> 6) & 3, row = u & 63;
-        if (row0 + row < a.plane_rows && kb0 + kbl < a.KB_total) {
+        if (row0 + row < a.plane_rows && kb0 + kbl < kb_lim) {
             const uint4 val = *reinterpret_cast<const uint4*>(&tile[d][kbl][row][0]);
-            *reinterpret_cast<uint4*>(dst + (size_t)d * a.digit_stride + ((size_t)(kb0 + kbl) * a.plane_rows + row0 + row) * 16) = val;
+            *reinterpret_cast<uint4*>(dst + (size_t)d * a.digit_stride + ((size_t)(kb_first + kb0 + kbl) * a.plane_rows + row0 + row) * 16) = val;
         }
     }
 }
@@ -266,38 +328,32 @@ __global__ __launch_bounds__(kThreads) void k_recode_im2col_t(Im2colTBatch bt)
         const int row = (int)(it - (size_t)kb * rows);
         const int tap = row / a.Cin, ci = row - tap * a.Cin;
         const int dy = tap / a.KW, dx = tap - dy * a.KW;
-        long long m = (long long)kb * 16;
+        // loads at clamped pixels with no branch between them, masked afterwards
+        const long long m = (long long)kb * 16;
         int wo = (int)(m % a.Wo); long long t2 = m / a.Wo;
         int ho = (int)(t2 % a.Ho); int b = (int)(t2 / a.Ho);
-        u64 dg[16];
+        size_t idx[16]; unsigned ok = 0;
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
-            u64 v = 0;
-            if (m + t < npix) {
-                const int hi = ho * a.stride + dy - a.pad, wi = wo * a.stride + dx - a.pad;
-                if (hi >= 0 && hi < a.H && wi >= 0 && wi < a.W) {
-                    const size_t idx = (((size_t)b * a.H + hi) * a.W + wi) * a.Cin + ci;
-                    v = a.src[idx];
-                    if (a.src2) v += a.src2[idx];
-                }
-            }
-            dg[t] = balanced_digits(v);
+            const int hi = ho * a.stride + dy - a.pad, wi = wo * a.stride + dx - a.pad;
+            const bool in = m + t < npix && hi >= 0 && hi < a.H && wi >= 0 && wi < a.W;
+            ok |= (unsigned)in << t;
+            idx[t] = in ? (((size_t)b * a.H + hi) * a.W + wi) * a.Cin + ci : 0;
             if (++wo == a.Wo) { wo = 0; if (++ho == a.Ho) { ho = 0; ++b; } }
         }
-        u8* out = a.dst + ((size_t)kb * rows + row) * 16;
+        u64 v[16];
 #pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            uint32_t w[4];
+        for (int t = 0; t < 16; ++t) v[t] = a.src[idx[t]];
+        if (a.src2) {
+            u64 w[16];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t v = 0;
+            for (int t = 0; t < 16; ++t) w[t] = a.src2[idx[t]];
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    v |= (uint32_t)((dg[q * 4 + t] >> (8 * d)) & 0xff) << (8 * t);
-                w[q] = v;
-            }
-            *reinterpret_cast<uint4*>(out + (size_t)d * a.digit_stride) = make_uint4(w[0], w[1], w[2], w[3]);
+            for (int t = 0; t < 16; ++t) v[t] += w[t];
         }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) v[t] = (ok >> t) & 1 ? v[t] : 0;
+        store_unit(v, a.dst + ((size_t)kb * rows + row) * 16, a.digit_stride);
     }
 }
 
@@ -507,23 +563,32 @@ int launch_truncate(mpc_ctx* c, hipStream_t st, u64* z, size_t n, int bits, int 
     return MPC_OK;
 }
 
+// contiguous k, and taps (if any) of at least two whole k blocks: the tile recoder; else one thread per (row, k block)
+static bool rows_form(const RecodeArgs& a) { return a.k_stride == 1 && (a.ntaps == 1 || a.KB_tap >= 2); }
+// (tap, group of four k blocks) pairs of the tile recoder, the padding behind the last tap included
+static unsigned rows_gy(const RecodeArgs& a)
+{
+    const unsigned groups = (unsigned)(((a.ntaps == 1 ? a.KB_total : a.KB_tap) + 3) / 4);
+    return groups * (unsigned)(a.ntaps + (a.ntaps > 1 && a.KB_total > a.ntaps * a.KB_tap ? 1 : 0));
+}
+
 int launch_recode_multi(mpc_ctx* c, hipStream_t st, const RecodeArgs* sets, int count)
 {
     if (count < 1 || count > kMaxRecodeSets) return MPC_EINVAL;
     bool rows_kind = true;          // every set a plain matrix with contiguous k?
     for (int i = 0; i < count; ++i)
-        if (sets[i].k_stride != 1 || sets[i].ntaps != 1 || sets[i].batch != sets[0].batch) rows_kind = false;
+        if (!rows_form(sets[i]) || sets[i].batch != sets[0].batch) rows_kind = false;
     if (rows_kind) {
         RecodeBatch rb{};
-        int rows = 0, kb = 0;
+        int rows = 0; unsigned gy = 0;
         for (int i = 0; i < count; ++i) {
             rb.a[i] = sets[i];
             if (sets[i].plane_rows > rows) rows = sets[i].plane_rows;
-            if (sets[i].KB_total > kb) kb = sets[i].KB_total;
+            if (rows_gy(sets[i]) > gy) gy = rows_gy(sets[i]);
         }
         rb.batch = sets[0].batch;
-        if ((size_t)count * rb.batch > 65535 || (kb + 3) / 4 > 65535) return MPC_EINVAL;
-        dim3 grid((rows + 63) / 64, (kb + 3) / 4, count * rb.batch);
+        if ((size_t)count * rb.batch > 65535 || gy > 65535) return MPC_EINVAL;
+        dim3 grid((rows + 63) / 64, gy, count * rb.batch);
         hipLaunchKernelGGL(k_recode_rows, grid, dim3(kThreads), 0, st, rb);
         MPC_HIP(c, hipGetLastError());
         return MPC_OK;
@@ -555,9 +620,9 @@ int launch_recode_any(mpc_ctx* c, hipStream_t st, const RecodeArgs* sets, int co
     for (int i = 0; i < count; ++i) {
         const RecodeArgs& a = sets[i];
         m.rb.a[i] = a;
-        m.rows_kind[i] = a.k_stride == 1 && a.ntaps == 1;
+        m.rows_kind[i] = rows_form(a);
         if (m.rows_kind[i]) {
-            m.gx[i] = (unsigned)((a.plane_rows + 63) / 64); m.gy[i] = (unsigned)((a.KB_total + 3) / 4);
+            m.gx[i] = (unsigned)((a.plane_rows + 63) / 64); m.gy[i] = rows_gy(a);
         } else {
             m.gx[i] = (unsigned)grid_for((size_t)a.KB_tap * a.plane_rows);
             m.gy[i] = (unsigned)(a.ntaps + (a.KB_total > a.ntaps * a.KB_tap ? 1 : 0));
@@ -654,7 +719,7 @@ int launch_poolbwd_scatter(mpc_ctx* c, hipStream_t st, const PoolBwdArgs& q)
 
 int launch_recode(mpc_ctx* c, hipStream_t st, const RecodeArgs& a)
 {
-    if (a.k_stride == 1 && a.ntaps == 1) return launch_recode_multi(c, st, &a, 1);
+    if (rows_form(a)) return launch_recode_multi(c, st, &a, 1);
     const bool has_pad = a.KB_total > a.ntaps * a.KB_tap;
     const size_t items = (size_t)a.KB_tap * a.plane_rows;
     dim3 grid(grid_for(items), a.ntaps + (has_pad ? 1 : 0), a.batch);
