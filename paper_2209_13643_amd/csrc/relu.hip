@@ -564,6 +564,14 @@ int wire_words(mpc_ctx* c, const u64* src0, u64* dst0, const u64* src1, u64* dst
     return MPC_OK;
 }
 
+PackedTriples packed_triples(const MsbGeom& g)
+{
+    PackedTriples t{};
+    for (int k = 0; k < 12; ++k) t.off[k] = g.toff[k];
+    for (int l = 0; l < 6; ++l) t.words[l] = g.pw[l];
+    return t;
+}
+
 // The protocol on n elements whose buffers are described by parties[2].  With
 // `geom` the carry chain runs on packed words (mpc_relu_msb), without it on
 // whole words.
@@ -577,9 +585,7 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
                                      pp[i].ma, pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_bit, pp[i].s_arith };
         q.box = box; q.n = n;
         if (!geom) return launch_relu_fused(c, c->s[0], 2, q, c->adder);
-        PackedTriples g{};
-        for (int k = 0; k < 12; ++k) g.off[k] = geom->toff[k];
-        return launch_relu_fused_msb(c, c->s[0], 2, q, g);
+        return launch_relu_fused_msb(c, c->s[0], 2, q, packed_triples(*geom));
     }
     // chunk boundaries: multiples of four elements, and of 256 on the packed path
     // (four whole words of the deepest level)
@@ -717,6 +723,12 @@ void fill_party(ReluParty& p, int i, const u64* x, const mpc_relu_material* m, c
     p.y = y; p.s_bit = s_bit; p.s_arith = s_arith; p.n = n;
 }
 
+FusedReluParty fused_party(const mpc_relu_material* m, int i)
+{
+    return FusedReluParty{ nullptr, m->r.p[i], nullptr, m->and_a.p[i], m->and_b.p[i], m->and_c.p[i], m->rb[i], m->ra.p[i],
+                           m->ma.p[i], m->mb.p[i], m->mc.p[i], nullptr, nullptr, nullptr };
+}
+
 // ---- max-pool gathers (local, linear) ----------------------------------------------
 // level 1: d[2o] = p00 - p01, d[2o+1] = p10 - p11 for output index o (NHWC)
 __global__ __launch_bounds__(kThreads) void k_pool_l1(const u64* __restrict__ x, u64* __restrict__ d,
@@ -794,7 +806,8 @@ size_t maxpool_ws(int B, int H, int W, int C, bool packed)
     // per party: d1 (2 n_out), r1 (2 n_out), v (n_out), d2 (n_out); then the ReLU's own scratch
     const size_t relu = packed ? carve_relu_msb(nullptr, 0, 2 * n_out, msb_geom(2 * n_out)).bytes
                                : carve_relu(nullptr, 0, 2 * n_out).bytes;
-    return 2 * (align_up(2 * n_out * 8) * 2 + align_up(n_out * 8) * 2) + relu;
+    const size_t bytes = 2 * (align_up(2 * n_out * 8) * 2 + align_up(n_out * 8) * 2) + relu, box = maxpool_fused_box_bytes(2, packed, n_out);
+    return bytes > box ? bytes : box;
 }
 
 int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const mpc_relu_material* mat2,
@@ -825,6 +838,17 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
     const ReluWs w2 = packed ? carve_relu_msb(c->ws + wa.off, c->ws_bytes - wa.off, n_out, g2) : w1;
     if (!w1.ok || !w2.ok) return MPC_ENOMEM;
     MPC_TRY(lane_join(c));
+    if (c->exchange_put && c->s[0] == c->s[1] && c->s[1] == c->s[2]) {
+        if (c->ws_bytes < maxpool_fused_box_bytes(2, packed, n_out)) return MPC_ENOMEM;
+        FusedPool q{};
+        for (int i = 0; i < 2; ++i) {
+            q.m1[i] = fused_party(mat1, i); q.m2[i] = fused_party(mat2, i);
+            q.x[i] = x.p[i]; q.y[i] = y.p[i]; q.s1[i] = s1 ? s1[i] : nullptr; q.s2[i] = s2 ? s2[i] : nullptr;
+        }
+        q.box = reinterpret_cast<u64*>(c->ws); q.n_out = n_out; q.H = H; q.W = W; q.C = C;
+        const PackedTriples t1 = packed_triples(g1), t2 = packed_triples(g2);
+        return launch_maxpool_fused(c, c->s[0], 2, q, c->adder, packed ? &t1 : nullptr, packed ? &t2 : nullptr);
+    }
     const dim3 grid(grid_for(n_out)), block(kThreads);
     ReluParty pp[2];
     // first tournament level: max(p00, p01) and max(p10, p11)

@@ -17,109 +17,14 @@
 #include "common.h"
 #include "msb_pack.h"
 #include "relu_steps.h"
+#include "wire.h"
 #include "relu_fused.h"
 
 #include <type_traits>
 
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kRows = 4;            // most words an element sends in one round
-
-typedef u64 u64v2u __attribute__((ext_vector_type(2), aligned(8)));
-
-// V consecutive words at scalar base + 32-bit byte offset, any 8-byte aligned address, read once
-template <int V> __device__ __forceinline__ Pack<V> ld_once(const u64* p, unsigned off)
-{
-    const u8* a = reinterpret_cast<const u8*>(p) + off;
-    Pack<V> r;
-    if constexpr (V >= 2) {
-#pragma unroll
-        for (int k = 0; k < V; k += 2) {
-            const u64v2u t = __builtin_nontemporal_load(reinterpret_cast<const u64v2u*>(a + 8 * k));
-            r.v[k] = t.x; r.v[k + 1] = t.y;
-        }
-    }
-    else r.v[0] = __builtin_nontemporal_load(reinterpret_cast<const u64*>(a));
-    return r;
-}
-
-template <int V> __device__ __forceinline__ void st_words(u64* p, unsigned off, const Pack<V>& w)
-{
-    u8* a = reinterpret_cast<u8*>(p) + off;
-    if constexpr (V == 1) *reinterpret_cast<u64*>(a) = w.v[0];
-#pragma unroll
-    for (int k = 0; k + 1 < V; k += 2) *reinterpret_cast<u64v2u*>(a + 8 * k) = u64v2u{ w.v[k], w.v[k + 1] };
-}
-// V consecutive bytes at any address, one per element
-template <int V> struct ByteWord;
-template <> struct ByteWord<1> { typedef u8 type; };
-template <> struct ByteWord<2> { typedef uint16_t type __attribute__((aligned(1))); };
-template <> struct ByteWord<4> { typedef uint32_t type __attribute__((aligned(1))); };
-template <int V> __device__ __forceinline__ unsigned ld_flags(const u8* p) { return *reinterpret_cast<const typename ByteWord<V>::type*>(p); }
-template <int V> __device__ __forceinline__ void st_flags(u8* p, unsigned w) { *reinterpret_cast<typename ByteWord<V>::type*>(p) = (typename ByteWord<V>::type)w; }
-
-// The receive buffers of a workgroup, one per ordered pair of parties: party i's buffer s holds what party
-// (i + 1 + s) mod NP sent last.  `box_words` words each.
-template <int NP>
-struct Wire {
-    u8* in; u8* out[NP - 1]; size_t step;
-    __device__ __forceinline__ Wire(u64* box, int party, size_t box_words)
-    {
-        step = box_words * 8;
-        u8* const wg = reinterpret_cast<u8*>(box) + (size_t)blockIdx.x * (NP * (NP - 1)) * step;
-        in = wg + (size_t)party * (NP - 1) * step;
-#pragma unroll
-        for (int s = 0; s < NP - 1; ++s) {
-            int to = party + NP - 1 - s; if (to >= NP) to -= NP;             // the party whose buffer s is filled from here
-            out[s] = wg + ((size_t)to * (NP - 1) + s) * step;
-        }
-    }
-    template <int W> __device__ __forceinline__ void put_to(int s, unsigned off, const Pack<W>& w) const { w.st(reinterpret_cast<u64*>(out[s] + off), 0); }
-    template <int W> __device__ __forceinline__ void put(unsigned off, const Pack<W>& w) const
-    {
-#pragma unroll
-        for (int s = 0; s < NP - 1; ++s) put_to(s, off, w);
-    }
-    template <int W> __device__ __forceinline__ Pack<W> from(int s, unsigned off) const { return Pack<W>::ld(reinterpret_cast<const u64*>(in + s * step + off), 0); }
-    // what the peers sent, added up (XOR shares / additive shares)
-    template <int W> __device__ __forceinline__ Pack<W> xored(unsigned off) const
-    {
-        Pack<W> r = from<W>(0, off);
-        if constexpr (NP == 3) {
-            const Pack<W> t = from<W>(1, off);
-#pragma unroll
-            for (int k = 0; k < W; ++k) r.v[k] ^= t.v[k];
-        }
-        return r;
-    }
-    template <int W> __device__ __forceinline__ Pack<W> summed(unsigned off) const
-    {
-        Pack<W> r = from<W>(0, off);
-        if constexpr (NP == 3) {
-            const Pack<W> t = from<W>(1, off);
-#pragma unroll
-            for (int k = 0; k < W; ++k) r.v[k] += t.v[k];
-        }
-        return r;
-    }
-    template <int V> __device__ __forceinline__ void put_flags(unsigned off, unsigned w) const
-    {
-#pragma unroll
-        for (int s = 0; s < NP - 1; ++s) st_flags<V>(out[s] + off, w);
-    }
-    template <int V> __device__ __forceinline__ unsigned flags(unsigned off) const
-    {
-        unsigned w = ld_flags<V>(in + off);
-        if constexpr (NP == 3) w ^= ld_flags<V>(in + step + off);
-        return w;
-    }
-    __device__ __forceinline__ static void opened() { __syncthreads(); }      // every wave has stored its words of the round
-    __device__ __forceinline__ static void drained() { __syncthreads(); }     // every wave holds the words of the last round: the buffers are free
-};
-
-// One party's side of a Beaver AND; m0: all ones for the party that adds the product of the opened words.
-__device__ __forceinline__ u64 fin(u64 d, u64 g, u64 a, u64 b, u64 c, u64 m0) { return c ^ (d & b) ^ (g & a) ^ (d & g & m0); }
 
 template <int V> struct Operands { Pack<V> P, G; u64 top[V]; };         // top: bit 63 of P
 
@@ -216,6 +121,65 @@ __device__ __forceinline__ void select(const Wire<NP>& wire, u64 m0, unsigned la
 
 template <int W> struct LevelTriples { Pack<W> a1, b1, c1, a2, b2, c2; };
 
+// y = ReLU(x) on a wave's elements, whole-word adder.  row: loads the wave's words of an array of n; rb: its random
+// bits.  s: the sign bit shares (one byte per element), sa: the additive ones.
+template <int V> struct Converted { Pack<V> y, sa; unsigned s; };
+template <int NP, int V, int TOPO, typename Row>
+__device__ __forceinline__ Converted<V> convert_words(const FusedReluParty& p, const Wire<NP>& wire, int party, unsigned lane, unsigned slot,
+                                                      size_t n, const Pack<V>& x, unsigned rb_at, const u8* rb_base, Row&& row)
+{
+    const u64 m0 = party == 0 ? ~(u64)0 : 0;
+    constexpr unsigned whole = kWave * V * 8u;
+    auto triples = [&](auto tag) {
+        constexpr int L = decltype(tag)::value, t = NP - 1 + 2 * L;
+        LevelTriples<V> r;
+        r.a1 = row(p.ta + t * n); r.b1 = row(p.tb + t * n); r.c1 = row(p.tc + t * n);
+        if constexpr (L < 5) { r.a2 = row(p.ta + (t + 1) * n); r.b2 = row(p.tb + (t + 1) * n); r.c2 = row(p.tc + (t + 1) * n); }
+        return r;
+    };
+    LevelTriples<V> next;
+    Operands<V> o = a2b<NP, V>(p, wire, party, m0, x, slot, whole, row, n, [&] { next = triples(std::integral_constant<int, 0>{}); });
+    Pack<V>&P = o.P, &G = o.G;
+    // prefix levels: mask and send level L's operands, fetch the next level's triples, open, finish
+    auto level = [&](auto tag) {
+        constexpr int L = decltype(tag)::value;
+        const LevelTriples<V> t = next;
+        Pack<V> d1, g1, d2, g2;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const u64 X = op_x<TOPO, L>(P.v[k]);
+            d1.v[k] = X ^ t.a1.v[k]; g1.v[k] = op_y<TOPO, L>(G.v[k]) ^ t.b1.v[k];
+            if constexpr (L < 5) { d2.v[k] = X ^ t.a2.v[k]; g2.v[k] = op_y<TOPO, L>(P.v[k]) ^ t.b2.v[k]; }
+        }
+        wire.drained();
+        wire.put(slot, d1); wire.put(slot + whole, g1);
+        if constexpr (L < 5) { wire.put(slot + 2 * whole, d2); wire.put(slot + 3 * whole, g2); }
+        if constexpr (L < 5) next = triples(std::integral_constant<int, L + 1>{});
+        wire.opened();
+        const Pack<V> rd1 = wire.template xored<V>(slot), rg1 = wire.template xored<V>(slot + whole);
+        Pack<V> rd2, rg2;
+        if constexpr (L < 5) { rd2 = wire.template xored<V>(slot + 2 * whole); rg2 = wire.template xored<V>(slot + 3 * whole); }
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            G.v[k] ^= fin(d1.v[k] ^ rd1.v[k], g1.v[k] ^ rg1.v[k], t.a1.v[k], t.b1.v[k], t.c1.v[k], m0);
+            if constexpr (L < 5)
+                P.v[k] = keep_p<TOPO, L>(P.v[k]) ^ fin(d2.v[k] ^ rd2.v[k], g2.v[k] ^ rg2.v[k], t.a2.v[k], t.b2.v[k], t.c2.v[k], m0);
+        }
+    };
+    level(std::integral_constant<int, 0>{}); level(std::integral_constant<int, 1>{}); level(std::integral_constant<int, 2>{});
+    level(std::integral_constant<int, 3>{}); level(std::integral_constant<int, 4>{}); level(std::integral_constant<int, 5>{});
+
+    // sign share = bit 63 of the sum's half-add xor the carry out of bits 0..62
+    const Pack<V> ra = row(p.ra), ma = row(p.ma), mb = row(p.mb), mc = row(p.mc);
+    const unsigned rb = ld_flags<V>(rb_base + rb_at);
+    Converted<V> r;
+    r.s = 0;
+#pragma unroll
+    for (int k = 0; k < V; ++k) r.s |= (unsigned)(o.top[k] ^ ((G.v[k] >> 62) & 1)) << (8 * k);
+    select<NP, V>(wire, m0, lane, slot, whole, r.s ^ rb, x, ra, ma, mb, mc, r.y, r.sa);
+    return r;
+}
+
 template <int NP, int V, int TOPO>
 __global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused(FusedRelu q)
 {
@@ -223,9 +187,7 @@ __global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused(FusedRelu q)
     const int lane = threadIdx.x % kWave;
     const FusedReluParty& p = q.p[party];
     const size_t n = q.n;
-    const u64 m0 = party == 0 ? ~(u64)0 : 0;
     const Wire<NP> wire(q.box, party, (size_t)kRows * kWave * V);
-    constexpr unsigned whole = kWave * V * 8u;
     unsigned slot = lane * V * 8u;
 
     for (size_t tile = blockIdx.x; tile < q.tiles; tile += gridDim.x) {
@@ -237,63 +199,16 @@ __global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused(FusedRelu q)
         // opaque per tile: otherwise the addresses of all rows are formed ahead of the loop and spilled
         asm volatile("" : "+v"(off), "+v"(slot));
         auto row = [&](const u64* t) { return ld_once<V>(t + base, off * 8u); };
-        auto triples = [&](auto tag) {
-            constexpr int L = decltype(tag)::value, t = NP - 1 + 2 * L;
-            LevelTriples<V> r;
-            r.a1 = row(p.ta + t * n); r.b1 = row(p.tb + t * n); r.c1 = row(p.tc + t * n);
-            if constexpr (L < 5) { r.a2 = row(p.ta + (t + 1) * n); r.b2 = row(p.tb + (t + 1) * n); r.c2 = row(p.tc + (t + 1) * n); }
-            return r;
-        };
-
         const Pack<V> x = row(p.x);
-        LevelTriples<V> next;
-        Operands<V> o = a2b<NP, V>(p, wire, party, m0, x, slot, whole, row, n, [&] { next = triples(std::integral_constant<int, 0>{}); });
-        Pack<V>&P = o.P, &G = o.G;
-        // prefix levels: mask and send level L's operands, fetch the next level's triples, open, finish
-        auto level = [&](auto tag) {
-            constexpr int L = decltype(tag)::value;
-            const LevelTriples<V> t = next;
-            Pack<V> d1, g1, d2, g2;
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const u64 X = op_x<TOPO, L>(P.v[k]);
-                d1.v[k] = X ^ t.a1.v[k]; g1.v[k] = op_y<TOPO, L>(G.v[k]) ^ t.b1.v[k];
-                if constexpr (L < 5) { d2.v[k] = X ^ t.a2.v[k]; g2.v[k] = op_y<TOPO, L>(P.v[k]) ^ t.b2.v[k]; }
-            }
-            wire.drained();
-            wire.put(slot, d1); wire.put(slot + whole, g1);
-            if constexpr (L < 5) { wire.put(slot + 2 * whole, d2); wire.put(slot + 3 * whole, g2); }
-            if constexpr (L < 5) next = triples(std::integral_constant<int, L + 1>{});
-            wire.opened();
-            const Pack<V> rd1 = wire.template xored<V>(slot), rg1 = wire.template xored<V>(slot + whole);
-            Pack<V> rd2, rg2;
-            if constexpr (L < 5) { rd2 = wire.template xored<V>(slot + 2 * whole); rg2 = wire.template xored<V>(slot + 3 * whole); }
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                G.v[k] ^= fin(d1.v[k] ^ rd1.v[k], g1.v[k] ^ rg1.v[k], t.a1.v[k], t.b1.v[k], t.c1.v[k], m0);
-                if constexpr (L < 5)
-                    P.v[k] = keep_p<TOPO, L>(P.v[k]) ^ fin(d2.v[k] ^ rd2.v[k], g2.v[k] ^ rg2.v[k], t.a2.v[k], t.b2.v[k], t.c2.v[k], m0);
-            }
-        };
-        level(std::integral_constant<int, 0>{}); level(std::integral_constant<int, 1>{}); level(std::integral_constant<int, 2>{});
-        level(std::integral_constant<int, 3>{}); level(std::integral_constant<int, 4>{}); level(std::integral_constant<int, 5>{});
-
-        // sign share = bit 63 of the sum's half-add xor the carry out of bits 0..62; an element's bits are bytes of s
-        const Pack<V> ra = row(p.ra), ma = row(p.ma), mb = row(p.mb), mc = row(p.mc);
-        const unsigned rb = ld_flags<V>(p.rb + base + off);
-        unsigned s = 0;
-#pragma unroll
-        for (int k = 0; k < V; ++k) s |= (unsigned)(o.top[k] ^ ((G.v[k] >> 62) & 1)) << (8 * k);
-        Pack<V> y, sa;
-        select<NP, V>(wire, m0, lane, slot, whole, s ^ rb, x, ra, ma, mb, mc, y, sa);
+        const Converted<V> r = convert_words<NP, V, TOPO>(p, wire, party, lane, slot, n, x, off, p.rb + base, row);
         if (base + off >= first) {
-            st_words<V>(p.y + base, off * 8u, y);
-            if (p.s_bit) st_flags<V>(p.s_bit + base + off, s);
-            if (p.s_arith) st_words<V>(p.s_arith + base, off * 8u, sa);
+            st_words<V>(p.y + base, off * 8u, r.y);
+            if (p.s_bit) st_flags<V>(p.s_bit + base + off, r.s);
+            if (p.s_arith) st_words<V>(p.s_arith + base, off * 8u, r.sa);
         } else if (V == 2 && base + off + 1 == first) {                // an odd count: only the second element is the tile's own
-            (p.y + base)[off + 1] = y.v[V - 1];
-            if (p.s_bit) (p.s_bit + base)[off + 1] = (u8)(s >> 8);
-            if (p.s_arith) (p.s_arith + base)[off + 1] = sa.v[V - 1];
+            (p.y + base)[off + 1] = r.y.v[V - 1];
+            if (p.s_bit) (p.s_bit + base)[off + 1] = (u8)(r.s >> 8);
+            if (p.s_arith) (p.s_arith + base)[off + 1] = r.sa.v[V - 1];
         }
     }
 }
@@ -312,15 +227,13 @@ __device__ __forceinline__ u64 from_lane_xor(u64 v, int mask)
     return ((u64)hi << 32) | lo;
 }
 
-template <int NP, int V>
-__device__ __forceinline__ void msb_tile(const FusedReluParty& p, const PackedTriples& g, const Wire<NP>& wire, int party, size_t base, size_t n)
+// y = ReLU(x) on a wave's elements from `base` (a multiple of 64 V) on; lane's elements at lane V.  RAGGED: the tile may
+// reach past the packed words of the call's elements (word indices are clamped then).
+template <int NP, int V, bool RAGGED, typename Row>
+__device__ __forceinline__ Converted<V> convert_packed(const FusedReluParty& p, const PackedTriples& g, const Wire<NP>& wire, int party,
+                                                       unsigned lane, size_t base, const Pack<V>& x, unsigned rb_at, const u8* rb_base, Row&& row)
 {
     const u64 m0 = party == 0 ? ~(u64)0 : 0;
-    unsigned lane = threadIdx.x % kWave;
-    const unsigned rest = V == 1 && n - base < kWave ? (unsigned)(n - base) - 1 : kWave * V - V;
-    unsigned off = lane * V < rest ? lane * V : rest;             // V > 1: the caller passes whole tiles only
-    asm volatile("" : "+v"(off), "+v"(lane));
-    auto row = [&](const u64* q) { return ld_once<V>(q + base, off * 8u); };
     // rows of whole words and of packed words in the receive buffers
     constexpr unsigned whole = kWave * V * 8u, packed = kWave * V / 2 * 8u;
     const unsigned slot = lane * V * 8u;
@@ -328,15 +241,18 @@ __device__ __forceinline__ void msb_tile(const FusedReluParty& p, const PackedTr
     auto at = [&](auto tag) { constexpr int L = decltype(tag)::value; return (2 << L) <= V ? lane * (V >> (L + 1)) : (lane * V) >> (L + 1); };
     auto triples = [&](auto tag) {
         constexpr int L = decltype(tag)::value, W = (2 << L) <= V ? V >> (L + 1) : 1, t = NP - 1 + 2 * L;
-        const unsigned w = at(tag) * 8u;
-        auto tri = [&](const u64* q, int k) { return ld_once<W>(q + g.off[k] + (base >> (L + 1)), w); };
+        unsigned w = at(tag);
+        if constexpr (RAGGED) {
+            const size_t have = g.words[L] - (base >> (L + 1));                 // of this level from the tile's first one on
+            if (w + W > have) w = have < W ? 0 : (unsigned)have - W;
+        }
+        auto tri = [&](const u64* q, int k) { return ld_once<W>(q + g.off[k] + (base >> (L + 1)), w * 8u); };
         LevelTriples<W> r;
         r.a1 = tri(p.ta, t); r.b1 = tri(p.tb, t); r.c1 = tri(p.tc, t);
         if constexpr (L < 5) { r.a2 = tri(p.ta, t + 1); r.b2 = tri(p.tb, t + 1); r.c2 = tri(p.tc, t + 1); }
         return r;
     };
 
-    const Pack<V> x = row(p.x);
     LevelTriples<V == 1 ? 1 : V / 2> t0;
     Operands<V> o = a2b<NP, V>(p, wire, party, m0, x, slot, whole, row, g.off[1], [&] { t0 = triples(std::integral_constant<int, 0>{}); });
     Pack<V>&P = o.P, &G = o.G;
@@ -393,17 +309,30 @@ __device__ __forceinline__ void msb_tile(const FusedReluParty& p, const PackedTr
     const auto t5 = level(std::integral_constant<int, 4>{}, t4);
     level(std::integral_constant<int, 5>{}, t5);
 
-    // element i's carry into bit 63 sits at bit (62 + i) mod 64 of word i / 64; an element's bits are bytes of s
-    const unsigned rb = ld_flags<V>(p.rb + base + off);
-    unsigned s = 0;
+    // element i's carry into bit 63 sits at bit (62 + i) mod 64 of word i / 64
+    const unsigned rb = ld_flags<V>(rb_base + rb_at);
+    Converted<V> r;
+    r.s = 0;
 #pragma unroll
-    for (int k = 0; k < V; ++k) s |= (unsigned)((o.top[k] ^ (G.v[0] >> ((62 + lane * V + k) & 63))) & 1) << (8 * k);
-    Pack<V> y, sa;
-    select<NP, V>(wire, m0, lane, slot, whole, s ^ rb, x, ra, ma, mb, mc, y, sa);
+    for (int k = 0; k < V; ++k) r.s |= (unsigned)((o.top[k] ^ (G.v[0] >> ((62 + lane * V + k) & 63))) & 1) << (8 * k);
+    select<NP, V>(wire, m0, lane, slot, whole, r.s ^ rb, x, ra, ma, mb, mc, r.y, r.sa);
+    return r;
+}
+
+template <int NP, int V>
+__device__ __forceinline__ void msb_tile(const FusedReluParty& p, const PackedTriples& g, const Wire<NP>& wire, int party, size_t base, size_t n)
+{
+    unsigned lane = threadIdx.x % kWave;
+    const unsigned rest = V == 1 && n - base < kWave ? (unsigned)(n - base) - 1 : kWave * V - V;
+    unsigned off = lane * V < rest ? lane * V : rest;             // V > 1: the caller passes whole tiles only
+    asm volatile("" : "+v"(off), "+v"(lane));
+    auto row = [&](const u64* q) { return ld_once<V>(q + base, off * 8u); };
+    const Pack<V> x = row(p.x);
+    const Converted<V> r = convert_packed<NP, V, false>(p, g, wire, party, lane, base, x, off, p.rb + base, row);
     if (off != lane * V) return;              // past the end: a lane that worked on the last element again, at another bit position
-    st_words<V>(p.y + base, off * 8u, y);
-    if (p.s_bit) st_flags<V>(p.s_bit + base + off, s);
-    if (p.s_arith) st_words<V>(p.s_arith + base, off * 8u, sa);
+    st_words<V>(p.y + base, off * 8u, r.y);
+    if (p.s_bit) st_flags<V>(p.s_bit + base + off, r.s);
+    if (p.s_arith) st_words<V>(p.s_arith + base, off * 8u, r.sa);
 }
 
 // tiles 0 .. wide-1: 128 elements each, two per lane; the others 64 elements, one per lane (the last one ragged)
@@ -417,6 +346,54 @@ __global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused_msb(FusedRelu q, P
     for (unsigned tile = blockIdx.x; tile < q.tiles; tile += gridDim.x) {
         if (tile < wide) msb_tile<NP, kMsbV>(q.p[party], g, wire, party, (size_t)tile * kWave * kMsbV, q.n);
         else             msb_tile<NP, 1>(q.p[party], g, wire, party, ((size_t)wide * kMsbV + (tile - wide)) * kWave, q.n);
+    }
+}
+
+constexpr size_t kPoolBox = (size_t)kRows * kWave * 2;        // words: four rows of the first level's pairs
+// ---- 2x2 max-pool: two tournament levels, each max(p, q) = q + ReLU(p - q) ----------------
+// A wave works on 64 outputs: the first level's pair of differences of an output are two elements of one lane, the
+// second level's difference one, so both conversions and the sums around them stay in registers.
+// 32 x 32 x 32 x 64 inputs (524 288 outputs): 0.283 ms as gathers, two one-launch conversions and a sum (eight launches),
+// 0.251 ms here (whole words; 512 workgroups 0.311 ms), sign-only 0.145 -> 0.137 ms; 32 x 8 x 8 x 256: 81 -> 64 us.
+template <int NP, bool PACKED, int TOPO>
+__global__ __launch_bounds__(NP * kWave, 4) void k_maxpool_fused(FusedPool q, PackedTriples g1, PackedTriples g2)
+{
+    const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const Wire<NP> wire(q.box, party, kPoolBox);
+    const FusedReluParty &p1 = q.m1[party], &p2 = q.m2[party];
+    const u64* const x = q.x[party];
+    const unsigned C = (unsigned)q.C, Wo = (unsigned)q.W / 2, Ho = (unsigned)q.H / 2;
+    for (unsigned tile = blockIdx.x; tile < q.tiles; tile += gridDim.x) {
+        const size_t o0 = (size_t)tile * kWave;
+        unsigned lane = threadIdx.x % kWave;
+        const unsigned last = q.n_out - o0 < kWave ? (unsigned)(q.n_out - o0) - 1 : kWave - 1;
+        unsigned at = lane < last ? lane : last;                    // past the end: the last output again, not stored
+        asm volatile("" : "+v"(at), "+v"(lane));
+        size_t t = o0 + at;
+        const unsigned ch = (unsigned)(t % C); t /= C;
+        const unsigned wo = (unsigned)(t % Wo); t /= Wo;
+        const unsigned ho = (unsigned)(t % Ho); const size_t b = t / Ho;
+        const u64* const w = x + ((b * q.H + 2 * ho) * q.W + 2 * wo) * C + ch;
+        const size_t dh = (size_t)q.W * C;
+        const u64 p00 = w[0], p01 = w[C], p10 = w[dh], p11 = w[dh + C];
+        Pack<2> d1;
+        d1.v[0] = p00 - p01; d1.v[1] = p10 - p11;
+        auto row1 = [&](const u64* m) { return ld_once<2>(m + 2 * o0, at * 16u); };
+        Converted<2> r1;
+        if constexpr (PACKED) r1 = convert_packed<NP, 2, true>(p1, g1, wire, party, lane, 2 * o0, d1, 2 * at, p1.rb + 2 * o0, row1);
+        else                  r1 = convert_words<NP, 2, TOPO>(p1, wire, party, lane, lane * 16u, 2 * q.n_out, d1, 2 * at, p1.rb + 2 * o0, row1);
+        const u64 u = p01 + r1.y.v[0], v = p11 + r1.y.v[1];
+        Pack<1> d2;
+        d2.v[0] = u - v;
+        asm volatile("" : "+v"(at), "+v"(lane));
+        auto row2 = [&](const u64* m) { return ld_once<1>(m + o0, at * 8u); };
+        Converted<1> r2;
+        if constexpr (PACKED) r2 = convert_packed<NP, 1, false>(p2, g2, wire, party, lane, o0, d2, at, p2.rb + o0, row2);
+        else                  r2 = convert_words<NP, 1, TOPO>(p2, wire, party, lane, lane * 8u, q.n_out, d2, at, p2.rb + o0, row2);
+        if (at != lane) continue;
+        q.y[party][o0 + at] = v + r2.y.v[0];
+        if (q.s1[party]) st_words<2>(q.s1[party] + 2 * o0, at * 16u, r1.sa);
+        if (q.s2[party]) q.s2[party][o0 + at] = r2.sa.v[0];
     }
 }
 
@@ -482,6 +459,31 @@ int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, 
     const dim3 grid(least(q.tiles, blocks));
     if (parties == 2) hipLaunchKernelGGL(k_relu_fused_msb<2>, grid, dim3(2 * kWave), 0, st, q, g, wide);
     else              hipLaunchKernelGGL(k_relu_fused_msb<3>, grid, dim3(3 * kWave), 0, st, q, g, wide);
+    MPC_HIP(c, hipGetLastError());
+    return MPC_OK;
+}
+
+size_t maxpool_fused_box_bytes(int parties, bool packed, size_t n_out)
+{
+    const unsigned blocks = (packed ? kMsbBlocks : kBlocks)[parties - 2];
+    return (size_t)least(tiles_of(n_out, 1), blocks) * kMaxBlockPairs[parties - 2] * kPoolBox * sizeof(u64);
+}
+
+int launch_maxpool_fused(mpc_ctx* c, hipStream_t st, int parties, FusedPool q, int topo, const PackedTriples* g1, const PackedTriples* g2)
+{
+    if (q.n_out == 0 || q.n_out >= ((size_t)1 << 36)) return MPC_EINVAL;
+    const bool packed = g1 != nullptr;
+    q.tiles = tiles_of(q.n_out, 1);
+    const dim3 grid(least(q.tiles, (packed ? kMsbBlocks : kBlocks)[parties - 2])), block(parties * kWave);
+    const PackedTriples none{};
+    if (parties == 2) {
+        if (packed)    hipLaunchKernelGGL((k_maxpool_fused<2, true, 0>), grid, block, 0, st, q, *g1, *g2);
+        else if (topo) hipLaunchKernelGGL((k_maxpool_fused<2, false, 1>), grid, block, 0, st, q, none, none);
+        else           hipLaunchKernelGGL((k_maxpool_fused<2, false, 0>), grid, block, 0, st, q, none, none);
+    } else {
+        if (packed)    hipLaunchKernelGGL((k_maxpool_fused<3, true, 0>), grid, block, 0, st, q, *g1, *g2);
+        else           hipLaunchKernelGGL((k_maxpool_fused<3, false, 0>), grid, block, 0, st, q, none, none);
+    }
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }

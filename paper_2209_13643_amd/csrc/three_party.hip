@@ -490,6 +490,14 @@ FusedRelu fused3(const Relu3Args& q)
     return f;
 }
 
+PackedTriples packed_triples3(const Msb3Geom& g)
+{
+    PackedTriples t{};
+    for (int k = 0; k < 13; ++k) t.off[k] = g.toff[k];
+    for (int l = 0; l < 6; ++l) t.words[l] = g.pw[l];
+    return t;
+}
+
 // The whole chain for one chunk on one stream: A2B distribution, 11 stage kernels, 10 word exchanges, one byte exchange.
 int relu3_chunk(mpc_ctx* c, hipStream_t st, const Relu3Args& q)
 {
@@ -602,11 +610,7 @@ int launch_plevel(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom
 int relu3_msb_run(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom& g)
 {
     const size_t n = q.n;
-    if (c->exchange_put) {
-        PackedTriples t{};
-        for (int k = 0; k < 13; ++k) t.off[k] = g.toff[k];
-        return launch_relu_fused_msb(c, st, 3, fused3(q), t);
-    }
+    if (c->exchange_put) return launch_relu_fused_msb(c, st, 3, fused3(q), packed_triples3(g));
     const int vec = relu3_vectorisable(q);
     const bool vec0 = vec >= 2 && n % 4 == 0;
     {
@@ -907,8 +911,10 @@ static size_t maxpool3_ws(int B, int H, int W, int C, bool packed)
     if (B <= 0 || H <= 0 || W <= 0 || C <= 0 || (H & 1) || (W & 1)) return 0;
     const size_t n_out = (size_t)B * (H / 2) * (W / 2) * C;
     // per party: d1 (2 n_out), r1 (2 n_out), v (n_out), d2 (n_out); then the larger conversion's scratch
-    return 3 * (2 * align_up(2 * n_out * 8) + 2 * align_up(n_out * 8)) +
-           (packed ? mpc_relu3_msb_workspace_bytes(2 * n_out) : mpc_relu3_workspace_bytes(2 * n_out));
+    const size_t bytes = 3 * (2 * align_up(2 * n_out * 8) + 2 * align_up(n_out * 8)) +
+                         (packed ? mpc_relu3_msb_workspace_bytes(2 * n_out) : mpc_relu3_workspace_bytes(2 * n_out));
+    const size_t box = maxpool_fused_box_bytes(3, packed, n_out);
+    return bytes > box ? bytes : box;
 }
 
 size_t mpc_maxpool3_workspace_bytes(int B, int H, int W, int C) { return maxpool3_ws(B, H, W, C, false); }
@@ -952,6 +958,19 @@ static int maxpool3_entry(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m
     if (packed) { q1.tn = g1.toff[1]; q2.tn = g2.toff[1]; }
     hipStream_t st = c->s[0];
     MPC_TRY(lane_join(c));
+    if (c->exchange_put) {
+        if (c->ws_bytes < maxpool_fused_box_bytes(3, packed, n_out)) return MPC_ENOMEM;
+        FusedPool q{};
+        const FusedRelu f1 = fused3(q1), f2 = fused3(q2);
+        for (int i = 0; i < 3; ++i) {
+            q.m1[i] = f1.p[i]; q.m2[i] = f2.p[i]; q.x[i] = x.p[i]; q.y[i] = y.p[i];
+            q.s1[i] = s1 ? s1[i] : nullptr; q.s2[i] = s2 ? s2[i] : nullptr;
+        }
+        q.box = reinterpret_cast<u64*>(c->ws); q.n_out = n_out; q.H = H; q.W = W; q.C = C;
+        const PackedTriples t1 = packed_triples3(g1), t2 = packed_triples3(g2);
+        MPC_TRY(launch_maxpool_fused(c, st, 3, q, 0, packed ? &t1 : nullptr, packed ? &t2 : nullptr));
+        return lane_fanout(c);
+    }
     MPC_TRY(launch_pool<0>(c, st, pq, n_out));       // first tournament level: max(p00, p01), max(p10, p11)
     MPC_TRY(packed ? relu3_msb_run(c, st, q1, g1) : relu3_run(c, st, q1));
     MPC_TRY(launch_pool<1>(c, st, pq, n_out));       // second level: the two winners

@@ -88,3 +88,33 @@ def test_one_launch_relu_three_parties(mpc, lane, n, packed):
     equal(mpc, y, want.y, "output")
     equal(mpc, sb, want.s_bit, "sign bit share")
     equal(mpc, sa, want.s_arith, "sign arithmetic share")
+
+
+@pytest.mark.parametrize("parties,chain", [(2, "kogge-stone"), (2, "tree"), (2, "packed"), (3, "kogge-stone"), (3, "packed")])
+@pytest.mark.parametrize("shape", [(1, 2, 2, 1), (1, 2, 2, 63), (1, 2, 2, 64), (1, 2, 2, 65), (2, 4, 6, 5), (3, 6, 4, 11), (2, 16, 16, 33),
+                                   (5, 32, 32, 64)])
+def test_one_launch_maxpool(mpc, lane, shape, parties, chain):
+    """64 outputs per wave: ragged last tiles (also of the packed words), channel counts around a wave, several tiles per
+    workgroup; outputs and both levels' sign shares."""
+    print(f"one-launch maxpool {shape} {chain} parties={parties}", flush=True)
+    B, H, W, C = shape
+    n_out = B * (H // 2) * (W // 2) * C
+    rng = np.random.default_rng(n_out)
+    X = synth.normal_fixed(rng, shape, 4.0)
+    if parties == 2:
+        xs, m1, m2 = synth.share_additive(rng, X), synth.deal_relu_material(rng, 2 * n_out), synth.deal_relu_material(rng, n_out)
+        want, s1, s2 = oracle.maxpool2x2(xs, m1, m2, want_signs=True, adder="tree" if chain == "tree" else "kogge-stone")
+        lane.set_adder("tree" if chain == "tree" else "kogge-stone")
+        pool, pack = lane.maxpool2x2, lane.pack_material
+    else:
+        xs, m1, m2 = synth.share_additive3(rng, X), synth.deal_relu3_material(rng, 2 * n_out), synth.deal_relu3_material(rng, n_out)
+        want, s1, s2 = oracle.maxpool2x2_3(xs, m1, m2, want_signs=True)
+        pool, pack = lane.maxpool3, lane.pack_material3
+    d1, d2 = mpc.material_to_device(m1), mpc.material_to_device(m2)
+    if chain == "packed":
+        d1, d2 = pack(d1), pack(d2)
+    y, g1, g2 = pool(dev(mpc, xs), d1, d2, packed=chain == "packed", want_signs=True)
+    lane.sync()
+    equal(mpc, y, want, "output")
+    equal(mpc, g1, s1, "first level's sign shares")
+    equal(mpc, g2, s2, "second level's sign shares")
