@@ -153,13 +153,14 @@ int mpc_graph_destroy(mpc_graph* graph);
  *   party's send buffer into the other party's receive buffer after each round.
  * MPC_EXCHANGE_PUT: the kernel that forms the masked words also stores them
  *   into the peer's receive buffer (what a peer-to-peer store would be between
- *   two devices).  Beaver products: the next step starts when that kernel has
- *   ended.  Secure ReLU and max-pool: all rounds of a conversion run in one
- *   launch; a round ends when the waves of all parties that hold the same
- *   elements have stored their words, and n_chunks has nothing to cut.  Takes
+ *   two devices).  Linear layers: the next step starts when that kernel has
+ *   ended.  Secure ReLU, max-pool, element-wise products and the backward calls
+ *   built on them: all rounds run in one launch; a round ends when the waves of
+ *   all parties that hold the same elements have stored their words, and
+ *   n_chunks has nothing to cut.  Takes
  *   effect on lanes whose three streams are one queue; elsewhere the copy
- *   kernels are used.  Results are identical.  The three-party ReLU and
- *   max-pool calls honour it on every lane (they use one stream). */
+ *   kernels are used.  Results are identical.  The three-party calls
+ *   honour it on every lane (they use one stream). */
 enum { MPC_EXCHANGE_COPY = 0, MPC_EXCHANGE_PUT = 1 };
 int mpc_ctx_set_exchange(mpc_ctx* ctx, int mode);
 

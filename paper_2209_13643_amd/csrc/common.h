@@ -91,6 +91,9 @@ static inline int lane_join(mpc_ctx* c)
     return MPC_OK;
 }
 
+// the exchange by remote store takes effect on single-queue lanes
+static inline bool remote_store(const mpc_ctx* c) { return c->exchange_put && c->s[0] == c->s[1] && c->s[1] == c->s[2]; }
+
 // End of an entry point that issued everything on the lane's first stream: the
 // other two streams wait for it, so whichever stream the caller synchronises
 // sees the outputs.

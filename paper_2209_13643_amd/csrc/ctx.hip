@@ -1,5 +1,6 @@
 // Context (execution lane), opening and truncation entry points.
 #include "common.h"
+#include "mul_fused.h"
 
 #include <mutex>
 #include <new>
@@ -348,6 +349,13 @@ static int mul_entry(mpc_ctx* c, mpc_cshare x, mpc_cshare y, mpc_cshare a, mpc_c
     }
     q.n = n; q.trunc_bits = (flags & MPC_TRUNCATE) ? c->frac_bits : 0; q.mask_from_sign = mask_from_sign;
     MPC_TRY(lane_join(c));
+    if (remote_store(c)) {
+        FusedMul f{};
+        for (int i = 0; i < 2; ++i) { f.x[i] = x.p[i]; f.y[i] = y.p[i]; f.a[i] = a.p[i]; f.b[i] = b.p[i]; f.c[i] = cc.p[i]; f.z[i] = z.p[i]; }
+        f.box = reinterpret_cast<u64*>(c->ws + ws_off); f.n = n; f.trunc_bits = q.trunc_bits; f.mask_from_sign = mask_from_sign;
+        if (c->ws_bytes - ws_off < mul_fused_box_bytes(2, n)) return MPC_ENOMEM;
+        return launch_mul_fused(c, c->s[0], 2, f);
+    }
     MPC_TRY(launch_mul_mask(c, c->s[0], q));
     MPC_TRY(chain(c, c->s[0], c->s[2]));
     CopySeg cp[4];
@@ -400,6 +408,17 @@ int mpc_maxpool2x2_backward(mpc_ctx* c, mpc_cshare g, mpc_cshare s1, mpc_cshare 
     }
     if (!ws.ok) return MPC_ENOMEM;
     const size_t off = ws.off;
+    if (remote_store(c)) {
+        FusedPoolBwd f{};
+        for (int i = 0; i < 2; ++i) {
+            if (!a1.p[i] || !b1.p[i] || !c1.p[i] || !a2.p[i] || !b2.p[i] || !c2.p[i]) return MPC_EINVAL;
+            f.g[i] = g.p[i]; f.s1[i] = s1.p[i]; f.s2[i] = s2.p[i]; f.gx[i] = gx.p[i];
+            f.a1[i] = a1.p[i]; f.b1[i] = b1.p[i]; f.c1[i] = c1.p[i]; f.a2[i] = a2.p[i]; f.b2[i] = b2.p[i]; f.c2[i] = c2.p[i];
+        }
+        f.box = reinterpret_cast<u64*>(c->ws); f.n_out = n_out; f.H = H; f.W = W; f.C = C;
+        if (c->ws_bytes < mpc_maxpool_backward_workspace_bytes(B, H, W, C)) return MPC_ENOMEM;
+        return launch_poolbwd_fused(c, c->s[0], 2, f);
+    }
     const mpc_cshare pairs_c = { { pairs.p[0], pairs.p[1] } };
     // grad_u = g * (1 - s2)
     MPC_TRY(mul_entry(c, g, s2, a2, b2, c2, gu, n_out, 0, 1, off));

@@ -578,7 +578,7 @@ PackedTriples packed_triples(const MsbGeom& g)
 int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, const MsbGeom* geom = nullptr)
 {
     const bool one_queue = c->s[0] == c->s[1] && c->s[1] == c->s[2];   // in-order queue: no events needed
-    if (one_queue && c->exchange_put) {
+    if (remote_store(c)) {
         FusedRelu q{};
         for (int i = 0; i < 2; ++i)
             q.p[i] = FusedReluParty{ pp[i].x, pp[i].r, nullptr, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].rb, pp[i].ra,
@@ -838,7 +838,7 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
     const ReluWs w2 = packed ? carve_relu_msb(c->ws + wa.off, c->ws_bytes - wa.off, n_out, g2) : w1;
     if (!w1.ok || !w2.ok) return MPC_ENOMEM;
     MPC_TRY(lane_join(c));
-    if (c->exchange_put && c->s[0] == c->s[1] && c->s[1] == c->s[2]) {
+    if (remote_store(c)) {
         if (c->ws_bytes < maxpool_fused_box_bytes(2, packed, n_out)) return MPC_ENOMEM;
         FusedPool q{};
         for (int i = 0; i < 2; ++i) {

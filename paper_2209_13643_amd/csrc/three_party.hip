@@ -9,6 +9,7 @@
 // layers with three parties live in linear.hip.
 #include "common.h"
 #include "msb_pack.h"
+#include "mul_fused.h"
 #include "relu_fused.h"
 
 namespace {
@@ -711,7 +712,11 @@ __global__ __launch_bounds__(kT) void k3_mul_finish(Mul3Args q)
     }
 }
 
-size_t mul3_ws_bytes(size_t n) { return 18 * align_up(n * sizeof(u64)); }
+size_t mul3_ws_bytes(size_t n)
+{
+    const size_t arrays = 18 * align_up(n * sizeof(u64)), box = mul_fused_box_bytes(3, n);
+    return arrays > box ? arrays : box;
+}
 
 // z = x * y element by element (no rescale); ws_off: bytes of the workspace the caller keeps for itself
 int mul3_run(mpc_ctx* c, hipStream_t st, const u64* const x[3], const u64* const y[3], const u64* const a[3],
@@ -728,6 +733,13 @@ int mul3_run(mpc_ctx* c, hipStream_t st, const u64* const x[3], const u64* const
     if (!ws.ok) return MPC_ENOMEM;
     for (int i = 0; i < 3; ++i) { q.x[i] = x[i]; q.y[i] = y[i]; q.a[i] = a[i]; q.b[i] = b[i]; q.c[i] = cc[i]; q.z[i] = z[i]; }
     q.n = n; q.mask_from_sign = mask_from_sign;
+    if (c->exchange_put) {
+        FusedMul f{};
+        for (int i = 0; i < 3; ++i) { f.x[i] = x[i]; f.y[i] = y[i]; f.a[i] = a[i]; f.b[i] = b[i]; f.c[i] = cc[i]; f.z[i] = z[i]; }
+        f.box = reinterpret_cast<u64*>(c->ws + ws_off); f.n = n; f.mask_from_sign = mask_from_sign;
+        if (c->ws_bytes - ws_off < mul_fused_box_bytes(3, n)) return MPC_ENOMEM;
+        return launch_mul_fused(c, st, 3, f);
+    }
     hipLaunchKernelGGL(k3_mul_mask, dim3(grid3(n), 3), dim3(kT), 0, st, q);
     MPC_HIP(c, hipGetLastError());
     // both masked words of every party go to both peers: two launches of six copies
@@ -1043,7 +1055,9 @@ size_t mpc_maxpool3_backward_workspace_bytes(int B, int H, int W, int C)
     if (B <= 0 || H <= 0 || W <= 0 || C <= 0 || (H & 1) || (W & 1)) return 0;
     const size_t n_out = (size_t)B * (H / 2) * (W / 2) * C;
     // per party grad_u (n_out), pairs and their product (2 n_out each); then the larger product's scratch
-    return 3 * (align_up(n_out * 8) + 2 * align_up(2 * n_out * 8)) + mul3_ws_bytes(2 * n_out);
+    const size_t bytes = 3 * (align_up(n_out * 8) + 2 * align_up(2 * n_out * 8)) + mul3_ws_bytes(2 * n_out);
+    const size_t box = poolbwd_fused_box_bytes(3, n_out);
+    return bytes > box ? bytes : box;
 }
 
 int mpc_maxpool3_backward(mpc_ctx* c, mpc_cshare3 g, mpc_cshare3 s1, mpc_cshare3 s2,
@@ -1063,6 +1077,17 @@ int mpc_maxpool3_backward(mpc_ctx* c, mpc_cshare3 g, mpc_cshare3 s1, mpc_cshare3
     const size_t off = ws.off;
     hipStream_t st = c->s[0];
     MPC_TRY(lane_join(c));
+    if (c->exchange_put) {
+        FusedPoolBwd f{};
+        for (int i = 0; i < 3; ++i) {
+            f.g[i] = g.p[i]; f.s1[i] = s1.p[i]; f.s2[i] = s2.p[i]; f.gx[i] = gx.p[i];
+            f.a1[i] = a1.p[i]; f.b1[i] = b1.p[i]; f.c1[i] = c1.p[i]; f.a2[i] = a2.p[i]; f.b2[i] = b2.p[i]; f.c2[i] = c2.p[i];
+        }
+        f.box = reinterpret_cast<u64*>(c->ws); f.n_out = n_out; f.H = H; f.W = W; f.C = C;
+        if (c->ws_bytes < poolbwd_fused_box_bytes(3, n_out)) return MPC_ENOMEM;
+        MPC_TRY(launch_poolbwd_fused(c, st, 3, f));
+        return lane_fanout(c);
+    }
     // grad_u = g * (1 - s2)
     MPC_TRY(mul3_run(c, st, g.p, s2.p, a2.p, b2.p, c2.p, gu, n_out, 1, off));
     PoolBwd3Args q{};
