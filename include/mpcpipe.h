@@ -15,7 +15,10 @@
  *     library never allocates or frees device memory in these calls (the
  *     context owns only streams and events);
  *   - calls enqueue work and return; party i's outputs are ordered on party
- *     i's stream (mpc_ctx_sync waits for all three streams);
+ *     i's stream (mpc_ctx_sync waits for all three streams); a call without
+ *     tiles (n_chunks <= 1) and without MPC_TWO_PHASE issues everything, the
+ *     copies included, on party 0's stream, and the other two wait for it if
+ *     the caller has their handles;
  *   - return value 0 = success, negative = error (see mpc_strerror); on an
  *     argument error nothing has been enqueued and no output is written;
  *   - build party 0 is the paper's "Party #1": the one whose share receives

@@ -30,7 +30,10 @@ struct mpc_ctx {
     size_t ws_bytes;
     int last_hip;
     int adder;               // carry network of mpc_relu / mpc_maxpool2x2: MPC_ADDER_*
-    bool exchange_put;       // secure ReLU on a single queue: exchange by remote store instead of copy kernels
+    bool exchange_put;       // single-queue lanes: exchange by remote store instead of copy kernels
+    bool spread;             // distinct streams: the party 1 / wire streams may hold work that stream 0 has not waited for
+    bool exposed;            // distinct streams: the caller knows the party 1 / wire stream and may order its own work with it
+    bool narrowed;           // inside a call that issues everything on stream 0 (Narrow)
     size_t relu_chunk[2];    // elements per chunk when n_chunks = 0 (whole words, packed chain); 0: the library's default
     bool capturing;          // between mpc_ctx_capture_begin and mpc_ctx_capture_end
     bool profiling;
@@ -74,12 +77,15 @@ static inline int chain(mpc_ctx* c, hipStream_t from, hipStream_t to)
     return MPC_OK;
 }
 
-// Start of an entry point: every stream of the lane waits for the work already
+static inline bool one_queue(const mpc_ctx* c) { return c->s[0] == c->s[1] && c->s[1] == c->s[2]; }
+
+// Start of an entry point that uses all three streams: every stream of the lane waits for the work already
 // enqueued on the other two, so a call may reuse the workspace and may read the
 // previous call's outputs of either party.
 static inline int lane_join(mpc_ctx* c)
 {
-    if (c->s[0] == c->s[1] && c->s[1] == c->s[2]) return MPC_OK;   // one in-order queue: nothing to join
+    if (one_queue(c)) return MPC_OK;   // one in-order queue: nothing to join
+    c->spread = true;
     hipEvent_t e[3];
     for (int i = 0; i < 3; ++i) {
         e[i] = next_event(c);
@@ -92,17 +98,50 @@ static inline int lane_join(mpc_ctx* c)
 }
 
 // the exchange by remote store takes effect on single-queue lanes
-static inline bool remote_store(const mpc_ctx* c) { return c->exchange_put && c->s[0] == c->s[1] && c->s[1] == c->s[2]; }
+static inline bool remote_store(const mpc_ctx* c) { return c->exchange_put && one_queue(c) && !c->narrowed; }
 
-// End of an entry point that issued everything on the lane's first stream: the
-// other two streams wait for it, so whichever stream the caller synchronises
-// sees the outputs.
-static inline int lane_fanout(mpc_ctx* c)
+// Start and end of an entry point that issues everything on the lane's first stream.  Stream 0 waits for the other two
+// only if they hold work (a call on three streams since, or a caller that has their handles); at the end they wait for
+// it, so that whichever stream the caller synchronises sees the outputs, if the caller has their handles.
+static inline int lane_first(mpc_ctx* c)
 {
-    MPC_TRY(chain(c, c->s[0], c->s[1]));
-    if (c->s[2] != c->s[1]) MPC_TRY(chain(c, c->s[0], c->s[2]));
+    if (one_queue(c)) return MPC_OK;
+    if (c->spread || c->exposed) {
+        MPC_TRY(chain(c, c->s[1], c->s[0]));
+        if (c->s[2] != c->s[1]) MPC_TRY(chain(c, c->s[2], c->s[0]));
+    }
+    c->spread = false;
     return MPC_OK;
 }
+static inline int lane_fanout(mpc_ctx* c)
+{
+    if (one_queue(c) || !c->exposed) return MPC_OK;
+    hipEvent_t e = next_event(c);
+    MPC_HIP(c, hipEventRecord(e, c->s[0]));
+    for (int i = 1; i < 3; ++i)
+        if (c->s[i] != c->s[0]) MPC_HIP(c, hipStreamWaitEvent(c->s[i], e, 0));
+    return MPC_OK;
+}
+
+// A call without tiles on a lane with three streams runs as on a single queue, on stream 0: the parties' kernels and
+// both directions of a copy share launches, and no round waits for events.  Three streams pay only where the caller
+// asks for tiles (or Alg. 3's two phases) to travel under computation.  Both ways measured, copy exchange, host and
+// device: 64 x 256 x 128 Beaver product 150 us on three streams, 28 us here, ReLU on its output 373 / 75 us;
+// 2048 x 1024 x 1024: 360 / 301 us and 1579 / 1179 us.
+struct Narrow {
+    mpc_ctx* c; hipStream_t s1, s2; bool on;
+    explicit Narrow(mpc_ctx* ctx) : c(ctx), s1(ctx->s[1]), s2(ctx->s[2]), on(false) {}
+    int begin()
+    {
+        if (one_queue(c)) return MPC_OK;
+        MPC_TRY(lane_first(c));
+        c->s[1] = c->s[2] = c->s[0]; c->narrowed = on = true;
+        return MPC_OK;
+    }
+    void restore() { if (on) { c->s[1] = s1; c->s[2] = s2; c->narrowed = on = false; } }
+    int end() { restore(); return lane_fanout(c); }
+    ~Narrow() { restore(); }
+};
 
 // Timing regions (no-ops unless profiling is on): prof_begin records a start
 // event on `st` and returns its index, prof_end records the matching stop.

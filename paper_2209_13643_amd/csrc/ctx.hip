@@ -72,6 +72,7 @@ static int ctx_create(mpc_ctx** out, int device, int frac_bits, int n_streams)
     c->device = device; c->frac_bits = frac_bits; c->ev_next = 0;
     c->ws = nullptr; c->ws_bytes = 0; c->last_hip = 0; c->profiling = false;
     c->relu_chunk[0] = c->relu_chunk[1] = 0;
+    c->spread = c->exposed = c->narrowed = false;
     for (int i = 0; i < 3; ++i) { c->s[i] = nullptr; c->own_stream[i] = false; }
     for (int i = 0; i < kEventPool; ++i) c->ev[i] = nullptr;
     hipError_t e = hipSetDevice(device);
@@ -128,6 +129,7 @@ int mpc_ctx_set_streams(mpc_ctx* c, void* s0, void* s1, void* sw)
             c->own_stream[i] = false;
         }
         c->s[i] = (hipStream_t)in[i];
+        c->exposed = true;
     }
     return MPC_OK;
 }
@@ -135,6 +137,7 @@ int mpc_ctx_set_streams(mpc_ctx* c, void* s0, void* s1, void* sw)
 void* mpc_ctx_stream(mpc_ctx* c, int which)
 {
     if (!c || which < 0 || which > 2) return nullptr;
+    if (which > 0) c->exposed = true;
     return (void*)c->s[which];
 }
 
@@ -296,38 +299,35 @@ int mpc_open(mpc_ctx* c, mpc_cshare s, uint64_t* out, size_t n)
     u64* r0 = ws.take<u64>(n);
     u64* r1 = ws.take<u64>(n);
     if (!ws.ok) return MPC_ENOMEM;
-    MPC_TRY(lane_join(c));
-    MPC_TRY(launch_copy(c, c->s[2], s.p[0], r0, n * sizeof(u64)));
-    MPC_TRY(launch_copy(c, c->s[2], s.p[1], r1, n * sizeof(u64)));
-    MPC_TRY(chain(c, c->s[2], c->s[0]));
+    MPC_TRY(lane_first(c));
+    MPC_TRY(launch_copy(c, c->s[0], s.p[0], r0, n * sizeof(u64)));
+    MPC_TRY(launch_copy(c, c->s[0], s.p[1], r1, n * sizeof(u64)));
     MPC_TRY(launch_add(c, c->s[0], r0, r1, out, n));
-    // the workspace may be reused by party 1's next call only after the add
-    MPC_TRY(chain(c, c->s[0], c->s[1]));
-    return MPC_OK;
+    return lane_fanout(c);
 }
 
 int mpc_sub(mpc_ctx* c, mpc_cshare x, mpc_cshare a, mpc_share out, size_t n)
 {
     if (!c || n == 0) return MPC_EINVAL;
     for (int i = 0; i < 2; ++i) if (!x.p[i] || !a.p[i] || !out.p[i]) return MPC_EINVAL;
-    MPC_TRY(lane_join(c));
-    for (int i = 0; i < 2; ++i) MPC_TRY(launch_sub(c, c->s[i], x.p[i], a.p[i], out.p[i], n));
-    return MPC_OK;
+    MPC_TRY(lane_first(c));
+    for (int i = 0; i < 2; ++i) MPC_TRY(launch_sub(c, c->s[0], x.p[i], a.p[i], out.p[i], n));
+    return lane_fanout(c);
 }
 
 int mpc_add(mpc_ctx* c, mpc_cshare x, mpc_cshare y, mpc_share out, size_t n)
 {
     if (!c || n == 0) return MPC_EINVAL;
     for (int i = 0; i < 2; ++i) if (!x.p[i] || !y.p[i] || !out.p[i]) return MPC_EINVAL;
-    MPC_TRY(lane_join(c));
-    for (int i = 0; i < 2; ++i) MPC_TRY(launch_add(c, c->s[i], x.p[i], y.p[i], out.p[i], n));
-    return MPC_OK;
+    MPC_TRY(lane_first(c));
+    for (int i = 0; i < 2; ++i) MPC_TRY(launch_add(c, c->s[0], x.p[i], y.p[i], out.p[i], n));
+    return lane_fanout(c);
 }
 
 size_t mpc_mul_workspace_bytes(size_t n) { return n ? 8 * align_up(n * sizeof(u64)) : 0; }
 
-// Element-wise Alg. 1.  Both parties' mask and finish kernels share a launch on
-// party 0's stream; the exchange of the masked words runs on the wire stream.
+// Element-wise Alg. 1, on the lane's first stream: both parties' mask and finish kernels share a launch, and so do the
+// copies of the exchange between them.
 static int mul_entry(mpc_ctx* c, mpc_cshare x, mpc_cshare y, mpc_cshare a, mpc_cshare b, mpc_cshare cc,
                      mpc_share z, size_t n, int flags, int mask_from_sign, size_t ws_off = 0)
 {
@@ -348,7 +348,7 @@ static int mul_entry(mpc_ctx* c, mpc_cshare x, mpc_cshare y, mpc_cshare a, mpc_c
         q.re[i] = re[i]; q.rf[i] = rf[i];
     }
     q.n = n; q.trunc_bits = (flags & MPC_TRUNCATE) ? c->frac_bits : 0; q.mask_from_sign = mask_from_sign;
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     if (remote_store(c)) {
         FusedMul f{};
         for (int i = 0; i < 2; ++i) { f.x[i] = x.p[i]; f.y[i] = y.p[i]; f.a[i] = a.p[i]; f.b[i] = b.p[i]; f.c[i] = cc.p[i]; f.z[i] = z.p[i]; }
@@ -357,17 +357,14 @@ static int mul_entry(mpc_ctx* c, mpc_cshare x, mpc_cshare y, mpc_cshare a, mpc_c
         return launch_mul_fused(c, c->s[0], 2, f);
     }
     MPC_TRY(launch_mul_mask(c, c->s[0], q));
-    MPC_TRY(chain(c, c->s[0], c->s[2]));
     CopySeg cp[4];
     for (int i = 0; i < 2; ++i) {
         cp[2 * i] = CopySeg{ (const u8*)q.se[i], (u8*)re[1 - i], n * sizeof(u64), 0 };
         cp[2 * i + 1] = CopySeg{ (const u8*)q.sf[i], (u8*)rf[1 - i], n * sizeof(u64), 0 };
     }
-    MPC_TRY(launch_copy_multi(c, c->s[2], cp, 4));
-    MPC_TRY(chain(c, c->s[2], c->s[0]));
+    MPC_TRY(launch_copy_multi(c, c->s[0], cp, 4));
     MPC_TRY(launch_mul_finish(c, c->s[0], q));
-    MPC_TRY(chain(c, c->s[0], c->s[1]));
-    return MPC_OK;
+    return lane_fanout(c);
 }
 
 int mpc_mul(mpc_ctx* c, mpc_cshare x, mpc_cshare y, mpc_cshare a, mpc_cshare b, mpc_cshare cc, mpc_share z,
@@ -426,21 +423,18 @@ int mpc_maxpool2x2_backward(mpc_ctx* c, mpc_cshare g, mpc_cshare s1, mpc_cshare 
     for (int i = 0; i < 2; ++i) { q.g[i] = g.p[i]; q.gu[i] = gu.p[i]; q.pairs[i] = pairs.p[i]; q.prod[i] = prod.p[i]; q.gx[i] = gx.p[i]; }
     q.n_out = n_out; q.B = B; q.H = H; q.W = W; q.C = C;
     MPC_TRY(launch_poolbwd_pairs(c, c->s[0], q));
-    MPC_TRY(chain(c, c->s[0], c->s[1]));
     // (grad_p00, grad_p10) = (grad_u, grad_v) * (1 - s1)
     MPC_TRY(mul_entry(c, pairs_c, s1, a1, b1, c1, prod, 2 * n_out, 0, 1, off));
     MPC_TRY(launch_poolbwd_scatter(c, c->s[0], q));
-    MPC_TRY(chain(c, c->s[0], c->s[1]));
-    return MPC_OK;
+    return lane_fanout(c);
 }
 
 int mpc_truncate(mpc_ctx* c, mpc_share z, size_t n, int bits)
 {
     if (!c || !z.p[0] || !z.p[1] || n == 0 || bits < 0 || bits > 63) return MPC_EINVAL;
-    MPC_TRY(lane_join(c));
-    MPC_TRY(launch_truncate(c, c->s[0], z.p[0], n, bits, 0));
-    MPC_TRY(launch_truncate(c, c->s[1], z.p[1], n, bits, 1));
-    return MPC_OK;
+    MPC_TRY(lane_first(c));
+    for (int i = 0; i < 2; ++i) MPC_TRY(launch_truncate(c, c->s[0], z.p[i], n, bits, i));
+    return lane_fanout(c);
 }
 
 }  // extern "C"

@@ -255,15 +255,18 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
     const bool two_phase = (flags & MPC_TWO_PHASE) != 0;
     const int trunc = (flags & MPC_TRUNCATE) ? c->frac_bits : 0;
 
-    MPC_TRY(lane_join(c));
+    Narrow nar(c);
+    if (n_chunks == 1 && !two_phase) MPC_TRY(nar.begin());      // nothing to overlap inside the call
+    else                             MPC_TRY(lane_join(c));
     const int pi = prof_begin(c, MPC_PROF_LINEAR, P0);
 
-    if (P0 == P1 && P1 == Wr) {
+    if (one_queue(c)) {
+        const bool put = remote_store(c);
         // One in-order queue: same steps, same order, but jobs of equal kind share a launch.
         GemmArgs g{};
         fill_geom(s, w, g);
         g.nparty = 2;
-        if (folded && c->exchange_put && !s.im2colT) {
+        if (folded && put && !s.im2colT) {
             // Folded call with the exchange by remote store: three passes over the activation, each word touched once.
             //   party 0 masks and sends:           e_0 = x_0 - a_0                  -> party 1's receive buffer
             //   party 1 masks, sends and recodes:  e_1 = x_1 - a_1 -> party 0's receive buffer; planes of e = e_1 + e_0
@@ -295,9 +298,9 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             g.trunc_bits = trunc;
             MPC_TRY(launch_limb_gemm(c, P0, g));
             prof_end(c, MPC_PROF_LINEAR, pi, P0);
-            return MPC_OK;
+            return nar.end();
         }
-        if (c->exchange_put && !folded && !skip_left && !x_public && !s.im2colT && !(two_phase && have_f)) {
+        if (put && !folded && !skip_left && !x_public && !s.im2colT && !(two_phase && have_f)) {
             // Plain call with the exchange by remote store: the pass that recodes the triple's [a_i] forms the masked
             // shares on the way (e_i = x_i - a_i, stored into the peer's receive buffer), and the opened e is recoded
             // from party 0's own shares and the word it received: every activation word is read once per use.
@@ -334,7 +337,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             g.trunc_bits = trunc;
             MPC_TRY(launch_limb_gemm(c, P0, g));
             prof_end(c, MPC_PROF_LINEAR, pi, P0);
-            return MPC_OK;
+            return nar.end();
         }
         if ((size_t)n_chunks > s.nx) n_chunks = (int)s.nx;
         bool f_pending = !have_f;                            // the weight mask rides with the first launch issued
@@ -345,14 +348,14 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             SubSeg sub[4]; CopySeg cp[4]; int ns = 0;
             for (int i = 0; i < 2 && !x_public && hi > lo; ++i) {
                 sub[ns] = SubSeg{ x.p[i] + lo, a.p[i] + lo, w.se[i] + lo, hi - lo, 0,
-                                  c->exchange_put ? w.re[1 - i] + lo : nullptr };
+                                  put ? w.re[1 - i] + lo : nullptr };
                 cp[ns] = CopySeg{ (const u8*)(w.se[i] + lo), (u8*)(w.re[1 - i] + lo), (hi - lo) * sizeof(u64), 0 };
                 ++ns;
             }
             // an empty chunk (fewer than two words per chunk) issues nothing; the weight mask must not depend on it
             if (f_pending && (ns > 0 || last)) {
                 for (int i = 0; i < 2; ++i) {
-                    sub[ns] = SubSeg{ y.p[i], b.p[i], w.sf[i], s.nw, 0, c->exchange_put ? w.rf[1 - i] : nullptr };
+                    sub[ns] = SubSeg{ y.p[i], b.p[i], w.sf[i], s.nw, 0, put ? w.rf[1 - i] : nullptr };
                     cp[ns] = CopySeg{ (const u8*)w.sf[i], (u8*)w.rf[1 - i], s.nw * sizeof(u64), 0 };
                     ++ns;
                 }
@@ -360,7 +363,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             }
             if (ns == 0) continue;                           // empty chunk, or both operands were opened ahead of time
             MPC_TRY(launch_sub_multi(c, P0, sub, ns));       // Alg. 1: mask (and, by remote store, send)
-            if (!c->exchange_put) MPC_TRY(launch_copy_multi(c, P0, cp, ns));       // Alg. 1: exchange
+            if (!put) MPC_TRY(launch_copy_multi(c, P0, cp, ns));       // Alg. 1: exchange
         }
         const u64* f0 = f_public ? f_public : w.sf[0];
         const u64* f1 = f_public ? nullptr : w.rf[0];
@@ -417,7 +420,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             MPC_TRY(launch_limb_gemm(c, P0, g));
         }
         prof_end(c, MPC_PROF_LINEAR, pi, P0);
-        return MPC_OK;
+        return nar.end();
     }
 
     // -- Alg. 1 / Alg. 3, masking step: mask and start the exchange, chunk by chunk
@@ -594,7 +597,7 @@ int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 
     }
     const bool have_f = f_public != nullptr || skip_right;
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     const int pi = prof_begin(c, MPC_PROF_LINEAR, st);
 
     // Alg. 1: every party masks its shares ...

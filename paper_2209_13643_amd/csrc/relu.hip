@@ -577,7 +577,7 @@ PackedTriples packed_triples(const MsbGeom& g)
 // whole words.
 int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, const MsbGeom* geom = nullptr)
 {
-    const bool one_queue = c->s[0] == c->s[1] && c->s[1] == c->s[2];   // in-order queue: no events needed
+    const bool in_order = one_queue(c);   // in-order queue: no events needed
     if (remote_store(c)) {
         FusedRelu q{};
         for (int i = 0; i < 2; ++i)
@@ -595,7 +595,7 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
     if (n_chunks == 0)
         // automatic: about a million elements per chunk on a single queue (the chunk's
         // state then survives in the last-level cache from round to round), one chunk otherwise
-        n_chunks = one_queue ? (int)((n + auto_elems / 2) / auto_elems) : 1;
+        n_chunks = in_order ? (int)((n + auto_elems / 2) / auto_elems) : 1;
     if (n_chunks > kMaxChunks) n_chunks = kMaxChunks;
     if ((size_t)n_chunks > (n + align - 1) / align) n_chunks = (int)((n + align - 1) / align);
     if (n_chunks < 1) n_chunks = 1;
@@ -661,7 +661,7 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
     };
     bool sent;
 
-    if (one_queue) {
+    if (in_order) {
         // One in-order queue: chunk-major order.  A chunk runs through all ten
         // rounds before the next one starts, so its carried state and exchange
         // buffers are still in the last-level cache when the next round reads them.
@@ -786,7 +786,9 @@ int relu_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat, mpc_share
         w = carve_relu(ws, ws_bytes, n);
     }
     if (!w.ok) return MPC_ENOMEM;
-    MPC_TRY(lane_join(c));
+    Narrow nar(c);
+    if (n_chunks <= 1) MPC_TRY(nar.begin());      // no tiles to overlap
+    else               MPC_TRY(lane_join(c));
     const int pi = timed ? prof_begin(c, MPC_PROF_RELU, c->s[0]) : -1;
     ReluParty pp[2];
     for (int i = 0; i < 2; ++i)
@@ -796,7 +798,7 @@ int relu_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat, mpc_share
         MPC_TRY(chain(c, c->s[1], c->s[0]));
         prof_end(c, MPC_PROF_RELU, pi, c->s[0]);
     }
-    return MPC_OK;
+    return n_chunks <= 1 ? nar.end() : MPC_OK;
 }
 
 size_t maxpool_ws(int B, int H, int W, int C, bool packed)
@@ -837,7 +839,9 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
                              : carve_relu(c->ws + wa.off, c->ws_bytes - wa.off, 2 * n_out);
     const ReluWs w2 = packed ? carve_relu_msb(c->ws + wa.off, c->ws_bytes - wa.off, n_out, g2) : w1;
     if (!w1.ok || !w2.ok) return MPC_ENOMEM;
-    MPC_TRY(lane_join(c));
+    Narrow nar(c);
+    if (n_chunks <= 1) MPC_TRY(nar.begin());
+    else               MPC_TRY(lane_join(c));
     if (remote_store(c)) {
         if (c->ws_bytes < maxpool_fused_box_bytes(2, packed, n_out)) return MPC_ENOMEM;
         FusedPool q{};
@@ -869,7 +873,7 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
     MPC_TRY(relu_run(c, pp, w2.box, n_out, n_chunks, packed ? &g2 : nullptr));
     for (int i = 0; i < 2; ++i)
         MPC_TRY(launch_add(c, c->s[i], y.p[i], v[i], y.p[i], n_out));
-    return MPC_OK;
+    return n_chunks <= 1 ? nar.end() : MPC_OK;
 }
 
 // ---- the entry point that allocates nothing ------------------------------------

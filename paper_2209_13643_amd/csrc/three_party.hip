@@ -808,7 +808,7 @@ int mpc_open3(mpc_ctx* c, mpc_cshare3 s, uint64_t* out, size_t n)
     for (int i = 0; i < 3; ++i) r[i] = ws.take<u64>(n);
     if (!ws.ok) return MPC_ENOMEM;
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     CopySeg cp[3];
     for (int i = 0; i < 3; ++i) cp[i] = CopySeg{ (const u8*)s.p[i], (u8*)r[i], n * sizeof(u64), 0 };
     MPC_TRY(launch_copy_multi(c, st, cp, 3));
@@ -833,7 +833,7 @@ int mpc_truncate3(mpc_ctx* c, mpc_share3 z, mpc_cshare3 r, mpc_cshare3 rt, size_
     for (int i = 0; i < 3; ++i) { q.z[i] = z.p[i]; q.r[i] = r.p[i]; q.rt[i] = rt.p[i]; }
     q.n = n; q.bits = bits;
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     hipLaunchKernelGGL(k3_trunc_mask, dim3(grid3(n), 2), dim3(kT), 0, st, q);
     MPC_HIP(c, hipGetLastError());
     CopySeg cp[2];
@@ -864,7 +864,7 @@ int mpc_relu3(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m, mpc_share3
     if (!ok) return MPC_ENOMEM;
     fill3(q, x.p, m, y.p, s_bit, s_arith, n);
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     const int pi = prof_begin(c, MPC_PROF_RELU, st);
     MPC_TRY(relu3_run(c, st, q));
     prof_end(c, MPC_PROF_RELU, pi, st);
@@ -887,7 +887,7 @@ int mpc_relu3_pack_triples(mpc_ctx* c, mpc_cshare3 words, mpc_share3 packed, siz
     for (int i = 0; i < 3; ++i) if (!words.p[i] || !packed.p[i]) return MPC_EINVAL;
     const Msb3Geom g = msb3_geom(n);
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     for (int i = 0; i < 3; ++i) {
         hipLaunchKernelGGL(k3_pack_triples, dim3(grid3(n), 13), dim3(kT), 0, st, words.p[i], packed.p[i], g);
         MPC_HIP(c, hipGetLastError());
@@ -911,7 +911,7 @@ int mpc_relu3_msb(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m, mpc_sh
     fill3(q, x.p, m, y.p, s_bit, s_arith, n);
     q.tn = g.toff[1];
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     const int pi = prof_begin(c, MPC_PROF_RELU, st);
     MPC_TRY(relu3_msb_run(c, st, q, g));
     prof_end(c, MPC_PROF_RELU, pi, st);
@@ -969,7 +969,7 @@ static int maxpool3_entry(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m
     fill3(q2, pq.d2, mat2, y.p, nullptr, s2, n_out);
     if (packed) { q1.tn = g1.toff[1]; q2.tn = g2.toff[1]; }
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     if (c->exchange_put) {
         if (c->ws_bytes < maxpool_fused_box_bytes(3, packed, n_out)) return MPC_ENOMEM;
         FusedPool q{};
@@ -1018,7 +1018,7 @@ static int linear3(mpc_ctx* c, mpc_cshare3 x, mpc_cshare3 y, mpc_share3 out, siz
     if (!c || n == 0) return MPC_EINVAL;
     for (int i = 0; i < 3; ++i) if (!x.p[i] || !y.p[i] || !out.p[i]) return MPC_EINVAL;
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     for (int i = 0; i < 3; ++i)
         MPC_TRY(subtract ? launch_sub(c, st, x.p[i], y.p[i], out.p[i], n) : launch_add(c, st, x.p[i], y.p[i], out.p[i], n));
     return lane_fanout(c);
@@ -1034,7 +1034,7 @@ int mpc_mul3(mpc_ctx* c, mpc_cshare3 x, mpc_cshare3 y, mpc_cshare3 a, mpc_cshare
     if (!c || n == 0) return MPC_EINVAL;
     for (int i = 0; i < 3; ++i) if (!x.p[i] || !y.p[i] || !a.p[i] || !b.p[i] || !cc.p[i] || !z.p[i]) return MPC_EINVAL;
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     MPC_TRY(mul3_run(c, st, x.p, y.p, a.p, b.p, cc.p, z.p, n, 0, 0));
     return lane_fanout(c);
 }
@@ -1045,7 +1045,7 @@ int mpc_relu3_backward(mpc_ctx* c, mpc_cshare3 g, mpc_cshare3 s_arith, mpc_cshar
     if (!c || n == 0) return MPC_EINVAL;
     for (int i = 0; i < 3; ++i) if (!g.p[i] || !s_arith.p[i] || !a.p[i] || !b.p[i] || !cc.p[i] || !gx.p[i]) return MPC_EINVAL;
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     MPC_TRY(mul3_run(c, st, g.p, s_arith.p, a.p, b.p, cc.p, gx.p, n, 1, 0));
     return lane_fanout(c);
 }
@@ -1076,7 +1076,7 @@ int mpc_maxpool3_backward(mpc_ctx* c, mpc_cshare3 g, mpc_cshare3 s1, mpc_cshare3
     if (!ws.ok) return MPC_ENOMEM;
     const size_t off = ws.off;
     hipStream_t st = c->s[0];
-    MPC_TRY(lane_join(c));
+    MPC_TRY(lane_first(c));
     if (c->exchange_put) {
         FusedPoolBwd f{};
         for (int i = 0; i < 3; ++i) {

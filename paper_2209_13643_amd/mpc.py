@@ -424,9 +424,8 @@ class Lane:
     def wait_torch(self):
         """Order the lane after the work torch has enqueued on its current stream
         (inputs produced by torch ops are otherwise not ordered with the lane's queues)."""
-        cur = torch.cuda.current_stream(self.device)
-        for s in {self.stream(0), self.stream(1), self.stream(2)}:
-            torch.cuda.ExternalStream(s, device=self.device).wait_stream(cur)
+        # every call starts from stream 0 or joins the other streams with it
+        torch.cuda.ExternalStream(self.stream(0), device=self.device).wait_stream(torch.cuda.current_stream(self.device))
 
     def capture(self):
         """Context manager: record the lane calls made inside it into a Graph (`.graph` afterwards).
