@@ -302,18 +302,40 @@ void k_limb_gemm(GemmArgs g)
                        : g.out[party] + (size_t)bidx * g.out_bstride;
     const int rbase = m0 + wm * 32 + g2 * 4;
     const int shift = partial ? 0 : g.trunc_bits;
-    const bool interior = m0 + C::TM <= g.M && n0 + C::TN <= g.N;   // uniform: no per-word bounds checks
+    // Word v of a lane's column half lies row_of(v) rows below the lane's first row: a uniform distance.  In tiles that
+    // lie inside the output (uniform) a word is addressed as scalar base + one 32-bit lane offset, without vector
+    // arithmetic and without bounds checks.  (With an address product, a branch on the addend and three on the
+    // truncation per word, and branches between the MFMAs of the last two steps, per-head Q K^T took 358 us and the
+    // 1x1 convolution on 56 x 56 x 64 to 256 channels 381 us; so 334 and 361 us.)
+    auto row_of = [](int v) { return (v >> 2) * 8 + (v & 3); };
+    const bool interior = m0 + C::TM <= g.M && n0 + C::TN <= g.N && g.N < (1 << 27);
+    const unsigned lane_off = ((unsigned)(g2 * 4) * (unsigned)g.N + (unsigned)i32) * 8u;
+    const size_t wave_at = (size_t)(m0 + wm * 32) * g.N + (n0 + wn * C::WN);
     u64 addw[NH][16];
     auto load_addend = [&]() {
+        if (!addend) {
 #pragma unroll
-        for (int c = 0; c < NH; ++c) {
-            const int col = n0 + wn * C::WN + c * 32 + i32;
-            const int colc = col < g.N ? col : g.N - 1;
+            for (int c = 0; c < NH; ++c)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = rbase + (v >> 2) * 8 + (v & 3);
-                const int rowc = row < g.M ? row : g.M - 1;
-                addw[c][v] = addend ? addend[(size_t)rowc * g.N + colc] : 0;
+                for (int v = 0; v < 16; ++v) addw[c][v] = 0;
+        } else if (interior) {
+            const u64* base = addend + wave_at;
+#pragma unroll
+            for (int c = 0; c < NH; ++c)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    addw[c][v] = *reinterpret_cast<const u64*>(reinterpret_cast<const u8*>(base + (size_t)row_of(v) * g.N + c * 32) + lane_off);
+        } else {
+#pragma unroll
+            for (int c = 0; c < NH; ++c) {
+                const int col = n0 + wn * C::WN + c * 32 + i32;
+                const int colc = col < g.N ? col : g.N - 1;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = rbase + row_of(v);
+                    const int rowc = row < g.M ? row : g.M - 1;
+                    addw[c][v] = addend[(size_t)rowc * g.N + colc];
+                }
             }
         }
     };
@@ -343,16 +365,18 @@ void k_limb_gemm(GemmArgs g)
     for (int d = 0; d < 8; ++d) { read_A(0, d); read_B(0, d); }
 
     int slot = 0;                        // t % NS
-    // FULL: steps with both a successor to prefetch operands from and a stage to issue
-    auto step = [&](auto full_tag, int t) {
-        constexpr bool FULL = decltype(full_tag)::value;
-        const bool have_next = FULL || t + 1 < T, fill = FULL || t + NS < T;
+    // The last NS steps have forms of their own, so that no step branches between its MFMAs: kFull prefetches operands
+    // and issues a stage; kNext only prefetches while a later stage is in flight; kNext1 when none is; kLast neither.
+    enum { kFull, kNext, kNext1, kLast };
+    auto step = [&](auto form_tag) {
+        constexpr int form = decltype(form_tag)::value;
+        constexpr bool have_next = form != kLast, fill = form == kFull;
         // slot t+1 must have landed; with three slots the loads of step t+2 may still be in flight
-        if (NS > 2 && (FULL || t + 2 < T)) __builtin_amdgcn_s_waitcnt(vmcnt_imm(PER_STAGE));
-        else if (have_next)               __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        __syncthreads();
+        if constexpr (NS > 2 && (form == kFull || form == kNext)) __builtin_amdgcn_s_waitcnt(vmcnt_imm(PER_STAGE));
+        else if constexpr (have_next)                             __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        if constexpr (have_next) __syncthreads();
         const int nslot = slot + 1 == NS ? 0 : slot + 1;
-        if (fill) stage_begin(slot);
+        if constexpr (fill) stage_begin(slot);
         // MFMA number n (0..71) <-> block j, left digit i, column half c
         static_for<8>([&](auto jt) {
             constexpr int j = decltype(jt)::value;
@@ -363,22 +387,22 @@ void k_limb_gemm(GemmArgs g)
                     // MFMAs before this block: sum_{j'<j} NH*(8-j') = NH*j*(17-j)/2
                     constexpr int n = NH * (j * (17 - j) / 2 + (7 - j - i)) + c;
                     acc[c][i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[i], B[c][j], acc[c][i + j], 0, 0, 0);
-                    if constexpr (n % 4 == 1 && n / 4 < PER_STAGE) {
-                        if (fill) issue_one(std::integral_constant<int, n / 4>{});
-                    }
+                    if constexpr (fill && n % 4 == 1 && n / 4 < PER_STAGE) issue_one(std::integral_constant<int, n / 4>{});
                 });
-                if (i == 7 - j && have_next) read_A(nslot, i);       // last use of A[7-j] in this step
+                if constexpr (i == 7 - j && have_next) read_A(nslot, i);       // last use of A[7-j] in this step
                 // keep this interleaving: without the fence the scheduler packs the
                 // MFMAs back to back and everything else into one exposed cluster
                 __builtin_amdgcn_sched_barrier(0);
             });
-            if (have_next) read_B(nslot, j);                          // last use of B[.][j]
+            if constexpr (have_next) read_B(nslot, j);                          // last use of B[.][j]
         });
         slot = nslot;
     };
     int t = 0;
-    for (; t + NS < T; ++t) step(std::true_type{}, t);
-    for (; t < T; ++t) step(std::false_type{}, t);
+    for (; t + NS < T; ++t) step(std::integral_constant<int, kFull>{});
+    if (NS > 2 && t + 2 < T) { step(std::integral_constant<int, kNext>{}); ++t; }
+    if (t + 1 < T) step(std::integral_constant<int, kNext1>{});
+    step(std::integral_constant<int, kLast>{});
 
     load_addend();
     // The explicit accumulator reads below are opaque to the compiler's hazard
@@ -395,7 +419,7 @@ void k_limb_gemm(GemmArgs g)
             u64 more[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = rbase + (v >> 2) * 8 + (v & 3);
+                const int row = rbase + row_of(v);
                 const int rowc = row < g.M ? row : g.M - 1;
                 more[v] = addend2[(size_t)rowc * g.N + colc];
             }
@@ -413,31 +437,36 @@ void k_limb_gemm(GemmArgs g)
         static_for<16>([&](auto vt) {
             constexpr int v = decltype(vt)::value;
             int d[8];
-            static_for<8>([&](auto st) {
-                constexpr int sg = decltype(st)::value;
-                int t;
-                asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(t) : "a"(acc[c][sg][v]));
-                d[sg] = t;
-            });
+            asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
+                         "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
+                         : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]), "=&v"(d[7])
+                         : "a"(acc[c][0][v]), "a"(acc[c][1][v]), "a"(acc[c][2][v]), "a"(acc[c][3][v]),
+                           "a"(acc[c][4][v]), "a"(acc[c][5][v]), "a"(acc[c][6][v]), "a"(acc[c][7][v]));
             u64 acc64 = (u64)(long long)d[0];
 #pragma unroll
             for (int sg = 1; sg < 4; ++sg)
                 acc64 += (u64)((unsigned)d[sg] << (8 * sg)) | ((u64)(unsigned)(d[sg] >> (32 - 8 * sg)) << 32);
             const unsigned high = (unsigned)d[4] + ((unsigned)d[5] << 8) + ((unsigned)d[6] << 16) + ((unsigned)d[7] << 24);
             acc64 += (u64)high << 32;
-            acc64 += add[v];
-            // local truncation (party is uniform over the workgroup): party 0 shifts, party 1 negates around the shift
-            if (shift == 0)      z[v] = acc64;
-            else if (party == 0) z[v] = acc64 >> shift;
-            else                 z[v] = (u64)0 - (((u64)0 - acc64) >> shift);
+            z[v] = acc64 + add[v];
         });
-        if (interior) {
+        // local truncation (shift and party are uniform over the workgroup): party 0 shifts, party 1 negates around the shift
+        if (shift && party == 0) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) out[(size_t)(rbase + (v >> 2) * 8 + (v & 3)) * g.N + col] = z[v];
+            for (int v = 0; v < 16; ++v) z[v] >>= shift;
+        } else if (shift) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) z[v] = (u64)0 - (((u64)0 - z[v]) >> shift);
+        }
+        if (interior) {
+            u64* base = out + wave_at + c * 32;
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                *reinterpret_cast<u64*>(reinterpret_cast<u8*>(base + (size_t)row_of(v) * g.N) + lane_off) = z[v];
         } else {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = rbase + (v >> 2) * 8 + (v & 3);
+                const int row = rbase + row_of(v);
                 if (row < g.M && col < g.N) out[(size_t)row * g.N + col] = z[v];
             }
         }
