@@ -48,17 +48,18 @@ template <int WGM, int WGN, int NS, int NH>
 struct Cfg {
     static constexpr int WN = 32 * NH;
     static constexpr int TM = 32 * WGM, TN = WN * WGN, NW = WGM * WGN, NT = 64 * NW;
-    static constexpr int L_UNITS = 8 * KS * TM, R_UNITS = 8 * KS * TN;   // 16-byte units per stage
+    static constexpr int LM = TM < 64 ? 64 : TM;      // left rows held: whole 64-row loads (a 32-row tile reads its rows clamped)
+    static constexpr int L_UNITS = 8 * KS * LM, R_UNITS = 8 * KS * TN;   // 16-byte units per stage
     static constexpr int STAGE_UNITS = L_UNITS + R_UNITS;
     static constexpr size_t LDS_BYTES = (size_t)NS * STAGE_UNITS * 16;
     // Tiles are loaded in chunks of 64 rows x 16 bytes (one wave-wide load).
     // Wave w loads digits w, w+NW, ... (DPW of them) of every k block and row
     // chunk: load j <-> digit w + NW*(j % DPW), k block (j / DPW) % KS,
     // row chunk j / (DPW * KS).
-    static constexpr int RCM = TM / 64, RCN = TN / 64;
+    static constexpr int RCM = LM / 64, RCN = TN / 64;
     static constexpr int DPW = 8 / NW;
     static constexpr int LPW = DPW * KS * RCM, RPW = DPW * KS * RCN;     // loads per wave per stage
-    static_assert(TM % 64 == 0 && TN % 64 == 0, "tiles are whole numbers of 64-row chunks");
+    static_assert(LM % 64 == 0 && TN % 64 == 0, "operand tiles are whole numbers of 64-row chunks");
     static_assert(8 % NW == 0, "digits divide evenly over waves");
 };
 
@@ -87,8 +88,7 @@ __device__ __forceinline__ void load_lds16(const u8* base, unsigned voff, unsign
 }
 
 template <int WGM, int WGN, bool CONV, int NS, int NH>
-__global__ __launch_bounds__(64 * WGM * WGN, NH == 1 ? 2 : 1)
-void k_limb_gemm(GemmArgs g)
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g)
 {
     using C = Cfg<WGM, WGN, NS, NH>;
     extern __shared__ uint4 lds[];
@@ -127,7 +127,7 @@ void k_limb_gemm(GemmArgs g)
         tile = q < per_xcd ? r8 * per_xcd + q : 0xffffffffu;
     }
     if (tile >= (unsigned)g.tiles_party[party]) return;      // padding of the last group of eight
-    constexpr unsigned GN = NH == 1 ? 8 : 4;
+    constexpr unsigned GN = NH == 1 && C::TN == 64 ? 8 : 4;
     const unsigned per_item = (unsigned)g.tiles_m * (unsigned)g.tiles_n;
     const unsigned t2 = tile / per_item, tq = tile - t2 * per_item;
     const unsigned panel = tq / (GN * (unsigned)g.tiles_m), rem = tq - panel * GN * (unsigned)g.tiles_m;
@@ -227,7 +227,7 @@ void k_limb_gemm(GemmArgs g)
         // KS divides every segment, so a stage never straddles two segments
         // (the cursor may move on to the next segment at the end of this stage)
         s_dsL = dsL; s_dsR = dsR;
-        s_slotL = lds_base + (unsigned)(slot * C::STAGE_UNITS * 16) + (unsigned)(wave * KS * C::TM * 16);
+        s_slotL = lds_base + (unsigned)(slot * C::STAGE_UNITS * 16) + (unsigned)(wave * KS * C::LM * 16);
         s_slotR = lds_base + (unsigned)((slot * C::STAGE_UNITS + C::L_UNITS) * 16) + (unsigned)(wave * KS * C::TN * 16);
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
@@ -253,8 +253,8 @@ void k_limb_gemm(GemmArgs g)
                 const bool ok = s_tap[kk] < ntaps && ((lvalid[rc] >> (s_tap[kk] & 63)) & 1);
                 voff = ok ? voff : s_zoff[kk];
             }
-            // destination unit: ((d*KS + kk)*TM + rc*64) with d = wave + NW*dj
-            load_lds16<((C::NW * dj * KS + kk) * C::TM + rc * 64) * 16>(s_L[kk] + dj * s_dsL, voff, s_slotL);
+            // destination unit: ((d*KS + kk)*LM + rc*64) with d = wave + NW*dj
+            load_lds16<((C::NW * dj * KS + kk) * C::LM + rc * 64) * 16>(s_L[kk] + dj * s_dsL, voff, s_slotL);
         } else {
             constexpr int r = q - C::LPW;
             constexpr int dj = r % C::DPW, kk = (r / C::DPW) % KS, rc = r / (C::DPW * KS);
@@ -262,6 +262,8 @@ void k_limb_gemm(GemmArgs g)
         }
     };
     constexpr int PER_STAGE = C::LPW + C::RPW;
+    constexpr int EVERY = 36 * NH / PER_STAGE < 4 ? 36 * NH / PER_STAGE : 4;       // MFMAs per load
+    static_assert(EVERY >= 2, "every load of a stage has a place between the MFMAs");
     auto issue_all = [&](int slot) {
         stage_begin(slot);
         static_for<PER_STAGE>([&](auto q) { issue_one(q); });
@@ -277,7 +279,7 @@ void k_limb_gemm(GemmArgs g)
 
     v4i A[8], B[NH][8];
     auto read_A = [&](int slot, int d) {
-        const uint4 a = lds[(size_t)slot * C::STAGE_UNITS + (d * KS + g2) * C::TM + wm * 32 + i32];
+        const uint4 a = lds[(size_t)slot * C::STAGE_UNITS + (d * KS + g2) * C::LM + wm * 32 + i32];
         A[d] = v4i{ (int)a.x, (int)a.y, (int)a.z, (int)a.w };
     };
     auto read_B = [&](int slot, int d) {
@@ -348,7 +350,8 @@ void k_limb_gemm(GemmArgs g)
     // block by block over the right-operand digit j (left digits 7-j .. 0);
     // an operand register is refilled from the next slot right after its last
     // use, in an order that gives every refill at least ~14 MFMAs of cover,
-    // and one global->LDS load is issued after every fourth MFMA: a wave can
+    // and one global->LDS load is issued after every fourth MFMA (every third
+    // where twelve loads share 36 MFMAs): a wave can
     // issue one instruction per four cycles, so everything that is not an MFMA
     // has to sit in the seven free issue slots an 8-pass MFMA leaves behind.
     issue_all(0);
@@ -387,7 +390,7 @@ void k_limb_gemm(GemmArgs g)
                     // MFMAs before this block: sum_{j'<j} NH*(8-j') = NH*j*(17-j)/2
                     constexpr int n = NH * (j * (17 - j) / 2 + (7 - j - i)) + c;
                     acc[c][i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[i], B[c][j], acc[c][i + j], 0, 0, 0);
-                    if constexpr (fill && n % 4 == 1 && n / 4 < PER_STAGE) issue_one(std::integral_constant<int, n / 4>{});
+                    if constexpr (fill && n % EVERY == 1 && n / EVERY < PER_STAGE) issue_one(std::integral_constant<int, n / EVERY>{});
                 });
                 if constexpr (i == 7 - j && have_next) read_A(nslot, i);       // last use of A[7-j] in this step
                 // keep this interleaving: without the fence the scheduler packs the
@@ -474,6 +477,12 @@ void k_limb_gemm(GemmArgs g)
     });
 }
 
+template <int WGM, int WGN, bool CONV, int NS, int NH>
+__global__ __launch_bounds__(64 * WGM * WGN, NH == 1 ? 2 : 1) void k_limb_gemm(GemmArgs g) { gemm_tile<WGM, WGN, CONV, NS, NH>(g); }
+// the tile of products with at most 32 rows
+template <bool CONV>
+__global__ __launch_bounds__(256, 2) void k_few_rows_gemm(GemmArgs g) { gemm_tile<1, 4, CONV, 3, 1>(g); }
+
 // Second pass of a split contraction: out = sum over splits of the partial
 // products + addends, then truncation.  One thread per output word.
 __global__ __launch_bounds__(256) void k_splitk_finish(GemmArgs g)
@@ -499,7 +508,9 @@ int launch_cfg(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
     using C = Cfg<WGM, WGN, NS, NH>;
     // once per device and kernel: allow the large dynamic LDS allocation (lanes may live on several host threads)
     static std::atomic<bool> attr_set[16];
-    auto kern = k_limb_gemm<WGM, WGN, CONV, NS, NH>;
+    void (*kern)(GemmArgs);
+    if constexpr (C::TM == 32) kern = k_few_rows_gemm<CONV>;
+    else                       kern = k_limb_gemm<WGM, WGN, CONV, NS, NH>;
     if (c->device < 0 || c->device >= 16) return MPC_EINVAL;
     if (!attr_set[c->device].load(std::memory_order_acquire)) {
         MPC_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -543,6 +554,9 @@ constexpr int kMaxStepsExact = 1023;
 // would be empty, 2 = 64 x 64 (2 x 2 waves of 32 x 32 with half the accumulator registers, two-slot ring: two
 // workgroups per compute unit, two waves per SIMD) for short contractions, where a workgroup's life is mostly
 // pipeline fill and epilogue and a second resident wave hides them.
+// 3 = 32 x 128 (1 x 4 waves of 32 x 32) for at most 32 rows, where a 64-row tile multiplies padding: with two rows and
+// weights of 25088 x 4096 the matrix pipeline was as busy as the memory (616 us a call, 413 us on this tile: 6.0 TB/s of weight planes; 32 rows 641 and 476 us; level
+// where a call is all launches).
 // Tile 2 is chosen when the longest contraction of the launch has at most g_small_max_steps K steps (32 terms each)
 // and the output has at least g_small_min_tiles tiles of 64 x 64 (mpc_set_gemm_small_tile changes both).
 // A launch whose parties contract different lengths (the folded calls: party 0 one segment, party 1 two) also takes
@@ -553,6 +567,7 @@ static std::atomic<int> g_small_max_steps{ 16 }, g_small_min_tiles{ 512 };
 constexpr long long kAsymMinTiles = 768;
 static int tile_kind(int M, int N, int batch, int longest_steps, bool asymmetric)
 {
+    if (M <= 32) return 3;
     const long long tiles64 = (long long)((M + 63) / 64) * ((N + 63) / 64) * batch;
     const int max_steps = g_small_max_steps.load(std::memory_order_relaxed);
     if (longest_steps <= max_steps && tiles64 >= g_small_min_tiles.load(std::memory_order_relaxed)) return 2;
@@ -568,7 +583,7 @@ static int ksplit_for(int M, int N, int batch, const int steps[2])
     const int nparty = steps[1] > 0 ? 2 : 1;
     const int longest = steps[0] > steps[1] ? steps[0] : steps[1];
     const int kind = tile_kind(M, N, batch, longest, nparty == 2 && steps[0] != steps[1]);
-    const int tm = kind == 1 ? 128 : 64, tn = kind == 0 ? 128 : 64;
+    const int tm = kind == 1 ? 128 : kind == 3 ? 32 : 64, tn = kind == 0 || kind == 3 ? 128 : 64;
     const long long tiles_pp = (long long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * batch;      // per party
     // the int32 digit sums of one workgroup stay exact for at most kMaxStepsExact steps
     const int s_exact = (longest + kMaxStepsExact - 1) / kMaxStepsExact;
@@ -645,6 +660,8 @@ int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
     // 64x128 workgroup tiles, or 128x64 when a second 64-column half would be empty
     const int kind = g.ksplit > 1 ? tile_kind(g.M, g.N, g.batch, 1 << 30, false) : tile_kind(g.M, g.N, g.batch, longest_steps, g.heavy_first != 0);
     if (g.conv.enabled)
-        return kind == 2 ? launch_cfg<2, 2, true, 2, 1>(c, st, g) : kind == 1 ? launch_cfg<4, 1, true>(c, st, g) : launch_cfg<2, 2, true>(c, st, g);
-    return kind == 2 ? launch_cfg<2, 2, false, 2, 1>(c, st, g) : kind == 1 ? launch_cfg<4, 1, false>(c, st, g) : launch_cfg<2, 2, false>(c, st, g);
+        return kind == 3 ? launch_cfg<1, 4, true, 3, 1>(c, st, g) : kind == 2 ? launch_cfg<2, 2, true, 2, 1>(c, st, g)
+             : kind == 1 ? launch_cfg<4, 1, true>(c, st, g) : launch_cfg<2, 2, true>(c, st, g);
+    return kind == 3 ? launch_cfg<1, 4, false, 3, 1>(c, st, g) : kind == 2 ? launch_cfg<2, 2, false, 2, 1>(c, st, g)
+         : kind == 1 ? launch_cfg<4, 1, false>(c, st, g) : launch_cfg<2, 2, false>(c, st, g);
 }
