@@ -39,6 +39,39 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int KS = 2;   // 16-wide k blocks per pipeline stage = one MFMA K step
+
+// Division by a number the host knows: n / d for n < 2^31, exact with mul = ceil(2^(31 + s) / d), s = ceil(log2 d)
+// (Granlund and Montgomery, "Division by invariant integers using multiplication").
+struct Divider {
+    unsigned mul; int shift;
+    __host__ static Divider by(unsigned d)
+    {
+        int s = 0;
+        while ((1ull << s) < d) ++s;
+        return Divider{ (unsigned)(((1ull << (31 + s)) + d - 1) / d), 31 + s };
+    }
+    __device__ __forceinline__ unsigned operator()(unsigned n) const { return (unsigned)(((u64)n * mul) >> shift); }
+};
+
+// What a launch passes to the kernel: everything of a party in one place, and the divisors of the tile order.  A
+// workgroup runs through its set-up alone, mostly as one chain of scalar instructions and loads, before it can ask for
+// its first tile; with divisions in the kernel and a party's operands picked field by field that was 625-860
+// instructions, as long as the matrix work of a 64-deep contraction; now 390-650 (per-head Q K^T 334 -> 330 us).
+struct GemmParty {
+    GemmSeg seg[2];
+    const u64 *addend, *addend2; u64* out;
+    int tiles, per_xcd;                     // tiles of the party, and how many of them an XCD owns
+};
+struct GemmDev {
+    GemmParty p[2];
+    int M, N, rows_L, nseg, nparty, trunc_bits, ksplit, steps_per_split;
+    long long out_bstride;
+    u64* partial;
+    unsigned heavy_blocks;                  // > 0: so many workgroups of party 1 come first, then party 0's
+    unsigned per_item, batch, panel_tiles, tiles_n, last_width;
+    Divider by_item, by_batch, by_panel, by_last_width, by_Wo, by_Ho;
+    ConvGeom conv;
+};
 // LDS ring depth: three slots for the one-workgroup-per-unit tiles; two for the small tile of short
 // contractions, which then fits twice on a compute unit
 
@@ -88,7 +121,7 @@ __device__ __forceinline__ void load_lds16(const u8* base, unsigned voff, unsign
 }
 
 template <int WGM, int WGN, bool CONV, int NS, int NH>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g)
+__device__ __forceinline__ void gemm_tile(const GemmDev& g)
 {
     using C = Cfg<WGM, WGN, NS, NH>;
     extern __shared__ uint4 lds[];
@@ -111,36 +144,31 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g)
     //  - parties that contract different lengths: party 1's workgroups (the long ones) fill the chip first,
     //    party 0's follow as units free up.
     const unsigned id = blockIdx.x;
-    int party; unsigned tile;
-    if (g.heavy_first) {
-        const unsigned blk1 = (unsigned)((g.tiles_party[1] + 7) / 8 * 8);
-        party = id < blk1 ? 1 : 0;
-        const unsigned local = party ? id : id - blk1;
-        const unsigned per_xcd = (unsigned)((g.tiles_party[party] + 7) / 8);
-        const unsigned q = local >> 3;
-        tile = q < per_xcd ? (local & 7) * per_xcd + q : 0xffffffffu;
+    int party; unsigned q, tile;
+    if (g.heavy_blocks) {
+        party = id < g.heavy_blocks ? 1 : 0;
+        q = (party ? id : id - g.heavy_blocks) >> 3;
     } else {
-        const unsigned r8 = id & 7, sl = id >> 3;
-        const unsigned per_xcd = (unsigned)((g.tiles_party[0] + 7) / 8);
-        const unsigned q = sl / (unsigned)g.nparty;
-        party = (int)(sl % (unsigned)g.nparty);
-        tile = q < per_xcd ? r8 * per_xcd + q : 0xffffffffu;
+        const unsigned sl = id >> 3;
+        party = g.nparty == 2 ? (int)(sl & 1) : 0;
+        q = g.nparty == 2 ? sl >> 1 : sl;
     }
-    if (tile >= (unsigned)g.tiles_party[party]) return;      // padding of the last group of eight
+    const GemmParty P = g.p[party];
+    tile = (id & 7) * (unsigned)P.per_xcd + q;
+    if (q >= (unsigned)P.per_xcd || tile >= (unsigned)P.tiles) return;      // padding of the last group of eight
     constexpr unsigned GN = NH == 1 && C::TN == 64 ? 8 : 4;
-    const unsigned per_item = (unsigned)g.tiles_m * (unsigned)g.tiles_n;
-    const unsigned t2 = tile / per_item, tq = tile - t2 * per_item;
-    const unsigned panel = tq / (GN * (unsigned)g.tiles_m), rem = tq - panel * GN * (unsigned)g.tiles_m;
-    const unsigned width = (unsigned)g.tiles_n - panel * GN < GN ? (unsigned)g.tiles_n - panel * GN : GN;
-    const int mt = (int)(rem / width);
-    const int nt = (int)(panel * GN + rem % width);
-    const int bidx = (int)(t2 % (unsigned)g.batch);
-    const int split = (int)(t2 / (unsigned)g.batch);
+    const unsigned t2 = g.by_item(tile), tq = tile - t2 * g.per_item;
+    const unsigned panel = g.by_panel(tq), rem = tq - panel * g.panel_tiles;
+    const bool whole_panel = g.tiles_n - panel * GN >= GN;
+    const unsigned row_tile = whole_panel ? rem / GN : g.by_last_width(rem);
+    const int mt = (int)row_tile;
+    const int nt = (int)(panel * GN + rem - row_tile * (whole_panel ? GN : g.last_width));
+    const int split = (int)g.by_batch(t2);
+    const int bidx = (int)(t2 - (unsigned)split * g.batch);
     const int m0 = mt * C::TM, n0 = nt * C::TN;
 
     // ---- per-party operands as scalars
-    const GemmSeg& sg0 = party ? g.seg[1][0] : g.seg[0][0];
-    const GemmSeg& sg1 = party ? g.seg[1][1] : g.seg[0][1];
+    const GemmSeg &sg0 = P.seg[0], &sg1 = P.seg[1];
     const int KB0 = sg0.KB, KB1 = g.nseg > 1 ? sg1.KB : 0;        // a party's second segment may be empty
     // K steps of this workgroup: all of them, or one slice when the contraction is split
     const int T_all = (KB0 + KB1) / KS;
@@ -159,8 +187,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g)
     for (int rc = 0; rc < C::RCM; ++rc) {
         int m = m0 + rc * 64 + lane; if (m > g.M - 1) m = g.M - 1;
         if (CONV) {
-            const int wo = m % g.conv.Wo; const int t = m / g.conv.Wo;
-            const int ho = t % g.conv.Ho; const int b = t / g.conv.Ho;
+            const int t = (int)g.by_Wo((unsigned)m), wo = m - t * g.conv.Wo;
+            const int b = (int)g.by_Ho((unsigned)t), ho = t - b * g.conv.Ho;
             const int hi0 = ho * g.conv.stride - g.conv.pad, wi0 = wo * g.conv.stride - g.conv.pad;
             const long long pix00 = ((long long)b * g.conv.H + hi0) * g.conv.W + wi0;
             voffL[rc] = (unsigned)((pix00 + bias) * 16);
@@ -298,10 +326,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g)
     // kernel from another lane (secure ReLU: at most 128) fits beside it on the same SIMD
     // and fills the issue slots the MFMAs leave free: 7-13 % on the inter-batch pipeline.
     const bool partial = g.ksplit > 1;      // raw partial products go to the workspace; a second kernel finishes
-    const u64* addend = (g.addend[party] && !partial) ? g.addend[party] + (size_t)bidx * g.out_bstride : nullptr;
-    const u64* addend2 = (g.addend2[party] && !partial) ? g.addend2[party] + (size_t)bidx * g.out_bstride : nullptr;
+    const u64* addend = (P.addend && !partial) ? P.addend + (size_t)bidx * g.out_bstride : nullptr;
+    const u64* addend2 = (P.addend2 && !partial) ? P.addend2 + (size_t)bidx * g.out_bstride : nullptr;
     u64* out = partial ? g.partial + (((size_t)split * g.nparty + party) * g.batch + bidx) * g.out_bstride
-                       : g.out[party] + (size_t)bidx * g.out_bstride;
+                       : P.out + (size_t)bidx * g.out_bstride;
     const int rbase = m0 + wm * 32 + g2 * 4;
     const int shift = partial ? 0 : g.trunc_bits;
     // Word v of a lane's column half lies row_of(v) rows below the lane's first row: a uniform distance.  In tiles that
@@ -478,10 +506,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g)
 }
 
 template <int WGM, int WGN, bool CONV, int NS, int NH>
-__global__ __launch_bounds__(64 * WGM * WGN, NH == 1 ? 2 : 1) void k_limb_gemm(GemmArgs g) { gemm_tile<WGM, WGN, CONV, NS, NH>(g); }
+__global__ __launch_bounds__(64 * WGM * WGN, NH == 1 ? 2 : 1) void k_limb_gemm(GemmDev g) { gemm_tile<WGM, WGN, CONV, NS, NH>(g); }
 // the tile of products with at most 32 rows
 template <bool CONV>
-__global__ __launch_bounds__(256, 2) void k_few_rows_gemm(GemmArgs g) { gemm_tile<1, 4, CONV, 3, 1>(g); }
+__global__ __launch_bounds__(256, 2) void k_few_rows_gemm(GemmDev g) { gemm_tile<1, 4, CONV, 3, 1>(g); }
 
 // Second pass of a split contraction: out = sum over splits of the partial
 // products + addends, then truncation.  One thread per output word.
@@ -508,7 +536,7 @@ int launch_cfg(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
     using C = Cfg<WGM, WGN, NS, NH>;
     // once per device and kernel: allow the large dynamic LDS allocation (lanes may live on several host threads)
     static std::atomic<bool> attr_set[16];
-    void (*kern)(GemmArgs);
+    void (*kern)(GemmDev);
     if constexpr (C::TM == 32) kern = k_few_rows_gemm<CONV>;
     else                       kern = k_limb_gemm<WGM, WGN, CONV, NS, NH>;
     if (c->device < 0 || c->device >= 16) return MPC_EINVAL;
@@ -526,12 +554,30 @@ int launch_cfg(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
         ga.tiles_party[p] = (int)tiles;
         wgs += (tiles + 7) / 8 * 8;
     }
-    // equal slice counts: the interleaved / party-major orders of the kernel assume equal blocks
+    // equal slice counts: the interleaved order of the kernel assumes equal blocks
     if (!ga.heavy_first && g.nparty == 2 && ga.tiles_party[0] != ga.tiles_party[1]) return MPC_EINVAL;
     if (wgs >= (1ll << 31)) return MPC_EINVAL;
+    GemmDev d{};
+    for (int p = 0; p < 2; ++p) {
+        GemmParty& q = d.p[p];
+        q.seg[0] = g.seg[p][0]; q.seg[1] = g.seg[p][1];
+        q.addend = g.addend[p]; q.addend2 = g.addend2[p]; q.out = g.out[p];
+        q.tiles = ga.tiles_party[p]; q.per_xcd = (ga.tiles_party[p] + 7) / 8;
+    }
+    d.M = g.M; d.N = g.N; d.rows_L = g.rows_L; d.nseg = g.nseg; d.nparty = g.nparty; d.trunc_bits = g.trunc_bits;
+    d.ksplit = g.ksplit; d.steps_per_split = g.steps_per_split; d.out_bstride = g.out_bstride; d.partial = g.partial;
+    d.heavy_blocks = ga.heavy_first ? (unsigned)(d.p[1].per_xcd * 8) : 0;
+    constexpr unsigned GN = NH == 1 && C::TN == 64 ? 8 : 4;        // column tiles of a panel
+    d.per_item = (unsigned)ga.tiles_m * (unsigned)ga.tiles_n; d.batch = (unsigned)g.batch;
+    d.panel_tiles = GN * (unsigned)ga.tiles_m; d.tiles_n = (unsigned)ga.tiles_n;
+    d.last_width = d.tiles_n % GN ? d.tiles_n % GN : GN;
+    d.by_item = Divider::by(d.per_item); d.by_batch = Divider::by(d.batch); d.by_panel = Divider::by(d.panel_tiles);
+    d.by_last_width = Divider::by(d.last_width);
+    d.conv = g.conv;
+    d.by_Wo = Divider::by(CONV ? (unsigned)g.conv.Wo : 1); d.by_Ho = Divider::by(CONV ? (unsigned)g.conv.Ho : 1);
     dim3 grid((unsigned)wgs, 1, 1);
     const int pi = prof_begin(c, MPC_PROF_GEMM_KERNEL, st);
-    hipLaunchKernelGGL(kern, grid, dim3(C::NT), C::LDS_BYTES, st, ga);
+    hipLaunchKernelGGL(kern, grid, dim3(C::NT), C::LDS_BYTES, st, d);
     if (g.ksplit > 1) {
         const size_t total = (size_t)g.batch * g.out_bstride * g.nparty;
         size_t blocks = (total + 255) / 256; if (blocks > 4096) blocks = 4096;
@@ -657,6 +703,12 @@ int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
             if (g.seg[p][s].KB < (s == 0 ? 1 : 0) || g.seg[p][s].KB % KS) return MPC_EINVAL;     // a second segment may be empty
     // per-lane byte offsets inside one k block of a plane are 32-bit
     if ((long long)g.rows_L * 16 >= (1ll << 32) || (long long)g.N * 16 >= (1ll << 32)) return MPC_EINVAL;
+    // A 1x1 convolution of stride 1 without padding reads pixel m for output row m: its planes are those of a matrix with
+    // one row more (the zero row), and the plain kernel contracts them without gather, bounds of taps and divisions.
+    // (An odd number of channel blocks is filled up from the zero row, which only the gather does.)  56 x 56 x 64
+    // to 256 channels, 32 images: 361 -> 350 us a call with the shorter set-up.
+    if (g.conv.enabled && g.conv.KH == 1 && g.conv.KW == 1 && g.conv.stride == 1 && g.conv.pad == 0 && g.conv.CB % KS == 0)
+        g.conv = ConvGeom{};
     // 64x128 workgroup tiles, or 128x64 when a second 64-column half would be empty
     const int kind = g.ksplit > 1 ? tile_kind(g.M, g.N, g.batch, 1 << 30, false) : tile_kind(g.M, g.N, g.batch, longest_steps, g.heavy_first != 0);
     if (g.conv.enabled)
