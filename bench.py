@@ -51,18 +51,14 @@ INT8_PEAK_TOPS = 5000.0      # MI355X dense int8 MFMA, published
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, published
 INT8_OPS_PER_SECURE_MAC = 288          # 2 parties x 2 ring GEMMs x 36 digit products x 2 ops
 RELU_BYTES_PER_ELEMENT = 86 * 8 + 2 + 216 * 8 + 137 * 8   # compulsory + openings + carried state, both parties
-# the same chain with the exchange by remote store (no copy kernels; a level stage recomputes its own masked words from
-# the carried state and stores them to the peer only; so do the first and the B2A stage, whose own words the next stage
-# re-forms from x, r, P and from x, ra and the opened bit), per party in words: A2B copy 2, first 8, level-0 stage 18,
-# levels 1..4 22 each, level 5 18, sign 7, B2A 6, select 8 = 155 W, plus 9 bytes (sign bit, random bit, masked bits)
-RELU_PUT_BYTES_PER_ELEMENT = 2 * (155 * 8 + 9)
 RELU_COMPULSORY_BYTES = 86 * 8 + 2                        # x, y, r, 12 AND triples, B2A pair, select triple: DRAM-compulsory
+# the same chain with the exchange by remote store is one launch: the state stays in registers and the exchanged words in
+# receive buffers that fit the L2, so what has to stream from memory is the compulsory part alone
+RELU_PUT_BYTES_PER_ELEMENT = RELU_COMPULSORY_BYTES
 # the sign-only packed chain (mpc_relu_msb), same three classes: 31.72 W + 2 B, 71.25 W + 8 B, 41.56 W + 6 B
 RELU_MSB_BYTES_PER_ELEMENT = (31.71875 + 71.25 + 41.5625) * 8 + 16
-# remote store: one of the four traversals of every opened word less, and the first and the B2A stage store their
-# masked words (2 W each per party) to the peer only (the select stage reads two bytes more instead)
-RELU_MSB_PUT_BYTES_PER_ELEMENT = RELU_MSB_BYTES_PER_ELEMENT - 71.25 * 8 / 4 - 2 * 4 * 8 + 2 * 2
 RELU_MSB_COMPULSORY_BYTES = 31.71875 * 8 + 2
+RELU_MSB_PUT_BYTES_PER_ELEMENT = RELU_MSB_COMPULSORY_BYTES          # remote store: one launch, as above
 RELU3_BYTES_PER_ELEMENT = 966 * 8 + 33      # three parties: 141 W + 3 B, 606 W + 21 B, 219 W + 9 B (same three classes)
 RELU3_MSB_BYTES_PER_ELEMENT = 2961          # three parties, sign-only chain: 59.6 W + 3 B, 226.0 W + 21 B, 80.3 W + 9 B
 
@@ -514,8 +510,7 @@ def config1_leg(steps, warmup, pmc_summary):
             "traffic": traffic,
             "measured_ceiling": ceiling},
         "roofline_relu": {
-            "kernel": "secure ReLU chain on whole words, exchange by remote store: k_relu_stage<0..9, put> (both parties per launch) "
-                      "+ k_wire_words<1> for the A2B masks",
+            "kernel": "secure ReLU on whole words, exchange by remote store: k_relu_fused (all rounds, both parties, one launch)",
             "workload": f"configs[1], {n} elements", "bound": "hbm", "achieved": gbs(RELU_PUT_BYTES_PER_ELEMENT, relu_ms),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs(RELU_PUT_BYTES_PER_ELEMENT, relu_ms) / HBM_PEAK_GBS,
             "bytes_per_element": RELU_PUT_BYTES_PER_ELEMENT, "ms_call": relu_ms, "elems_per_s": n / (relu_ms * 1e-3),
@@ -525,11 +520,11 @@ def config1_leg(steps, warmup, pmc_summary):
                               "frac": gbs(RELU_BYTES_PER_ELEMENT, relu_copy_ms) / HBM_PEAK_GBS, "traffic": rt.get("relu_bytes_per_element")},
             "dram_compulsory": {"bytes_per_element": RELU_COMPULSORY_BYTES,
                                 "frac": gbs(RELU_COMPULSORY_BYTES, relu_ms) / HBM_PEAK_GBS,
-                                "note": "inputs, outputs and offline material only: the exchanged words and the state carried from "
-                                        "round to round are served by the 256 MB last-level cache when a chunk fits it"},
+                                "note": "inputs, outputs and offline material only: the exchanged words pass through receive buffers "
+                                        "in the L2, the state carried from round to round stays in registers"},
             "traffic": rt.get("relu_put_bytes_per_element")},
         "roofline_relu_msb": {
-            "kernel": "sign-only packed ReLU chain, exchange by remote store: k_relu_msb_stage<0..9, put>",
+            "kernel": "sign-only packed ReLU chain, exchange by remote store: k_relu_fused_msb (one launch)",
             "workload": f"configs[1], {n} elements", "bound": "hbm", "achieved": gbs(RELU_MSB_PUT_BYTES_PER_ELEMENT, msb_ms),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs(RELU_MSB_PUT_BYTES_PER_ELEMENT, msb_ms) / HBM_PEAK_GBS,
             "bytes_per_element": RELU_MSB_PUT_BYTES_PER_ELEMENT, "ms_call": msb_ms, "elems_per_s": n / (msb_ms * 1e-3),

@@ -20,8 +20,8 @@ INT8_PEAK = 5.0e15
 HBM_PEAK = 8.0e12
 RELU_BYTES = 3514
 RELU_MSB_BYTES = 1172.25      # the sign-only packed chain
-RELU_PUT_BYTES = 2 * (155 * 8 + 9)            # whole words, exchange by remote store (bench.py derives it)
-RELU_MSB_PUT_BYTES = RELU_MSB_BYTES - 71.25 * 8 / 4 - 2 * 4 * 8 + 2 * 2
+RELU_PUT_BYTES = 86 * 8 + 2                   # whole words, exchange by remote store: one launch, compulsory bytes only
+RELU_MSB_PUT_BYTES = 31.71875 * 8 + 2         # the same for the packed chain
 
 
 def layer_macs(L):

@@ -57,13 +57,13 @@ def per_kernel(rows):
 
 
 def is_relu(name):
-    return name.startswith(("k_relu_stage", "k_relu_msb_stage", "k_wire_words", "k_wire_bytes"))
+    return name.startswith(("k_relu_stage", "k_relu_msb_stage", "k_relu_fused", "k_wire_words", "k_wire_bytes"))
 
 
 def relu_calls(rows):
     """KiB per secure-ReLU call by chain and exchange: a call is a maximal run of stage and wire dispatches (the
     conv call's kernels separate the runs; the chunks of a call follow each other), the chain shows in the stage
-    kernels' name, the exchange in their last template argument."""
+    kernels' name, the exchange in their last template argument.  The one-launch kernels exchange by remote store."""
     out = collections.defaultdict(list)
     run = []
     for r in list(rows) + [(0, "end", 0, 0.0)]:
@@ -71,10 +71,10 @@ def relu_calls(rows):
             run.append(r)
             continue
         if run:
-            stages = [q[1] for q in run if "stage<" in q[1]]
+            stages = [q[1] for q in run if "stage<" in q[1] or "fused" in q[1]]
             if stages:
                 chain = "sign-only" if any("msb" in q for q in stages) else "whole words"
-                put = any(q.rstrip(">").endswith("true") for q in stages)
+                put = any("fused" in q or q.rstrip(">").endswith("true") for q in stages)
                 out[(chain, "remote store" if put else "copy")].append(sum(q[3] for q in run))
             run = []
     return {k: sum(v) / len(v) for k, v in out.items()}
