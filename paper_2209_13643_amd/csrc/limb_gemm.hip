@@ -511,28 +511,20 @@ __global__ __launch_bounds__(64 * WGM * WGN, NH == 1 ? 2 : 1) void k_limb_gemm(G
 template <bool CONV>
 __global__ __launch_bounds__(256, 2) void k_few_rows_gemm(GemmDev g) { gemm_tile<1, 4, CONV, 3, 1>(g); }
 
-// Second pass of a split contraction: out = sum over splits of the partial products + addends, then truncation.  One
-// thread per output word, blockIdx.y the party.  The partial products are read from the last-level cache and an output
-// is small, so the pass is bound by latency: eight slices are loaded together (the passes of the VGG16 training
-// step of 32 images 269 -> 219 us, of 2 x 25088 x 4096 12 -> 6 us against one load at a time).
+// Second pass of a split contraction: out = sum over splits of the partial
+// products + addends, then truncation.  One thread per output word.
 __global__ __launch_bounds__(256) void k_splitk_finish(GemmArgs g)
 {
-    constexpr int kTogether = 8;
     const size_t per = (size_t)g.batch * g.out_bstride;            // words per party
-    const size_t stride = (size_t)gridDim.x * blockDim.x, slice = per * g.nparty;
-    const int party = (int)blockIdx.y, slices = g.ksplit_p[party];
-    const u64 *addend = g.addend[party], *addend2 = g.addend2[party];
-    for (size_t w = (size_t)blockIdx.x * blockDim.x + threadIdx.x; w < per; w += stride) {
-        const u64* src = g.partial + (size_t)party * per + w;
-        u64 z = addend ? addend[w] : 0;
-        if (addend2) z += addend2[w];
-        for (int sp = 0; sp < slices; sp += kTogether) {
-            u64 t[kTogether];
-#pragma unroll
-            for (int k = 0; k < kTogether; ++k) t[k] = sp + k < slices ? src[(size_t)(sp + k) * slice] : 0;
-#pragma unroll
-            for (int k = 0; k < kTogether; ++k) z += t[k];
-        }
+    const size_t total = per * g.nparty;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
+        const int party = (int)(i / per);
+        const size_t w = i - (size_t)party * per;
+        u64 z = 0;
+        for (int sp = 0; sp < g.ksplit_p[party]; ++sp) z += g.partial[((size_t)sp * g.nparty + party) * per + w];
+        if (g.addend[party]) z += g.addend[party][w];
+        if (g.addend2[party]) z += g.addend2[party][w];
         if (g.trunc_bits) z = party == 0 ? (z >> g.trunc_bits) : (u64)0 - (((u64)0 - z) >> g.trunc_bits);
         g.out[party][w] = z;
     }
@@ -587,9 +579,9 @@ int launch_cfg(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
     const int pi = prof_begin(c, MPC_PROF_GEMM_KERNEL, st);
     hipLaunchKernelGGL(kern, grid, dim3(C::NT), C::LDS_BYTES, st, d);
     if (g.ksplit > 1) {
-        const size_t per = (size_t)g.batch * g.out_bstride;
-        size_t blocks = (per + 255) / 256; if (blocks > 2048) blocks = 2048;
-        hipLaunchKernelGGL(k_splitk_finish, dim3((unsigned)blocks, (unsigned)g.nparty), dim3(256), 0, st, ga);
+        const size_t total = (size_t)g.batch * g.out_bstride * g.nparty;
+        size_t blocks = (total + 255) / 256; if (blocks > 4096) blocks = 4096;
+        hipLaunchKernelGGL(k_splitk_finish, dim3((unsigned)blocks), dim3(256), 0, st, ga);
     }
     prof_end(c, MPC_PROF_GEMM_KERNEL, pi, st);
     MPC_HIP(c, hipGetLastError());
