@@ -379,12 +379,19 @@ int mpc_relu_backward(mpc_ctx* c, mpc_cshare g, mpc_cshare s_arith, mpc_cshare a
     return mul_entry(c, g, s_arith, a, b, cc, gx, n, 0, 1);
 }
 
+// per party grad_u (n_out), pairs and their product (2 n_out each); then the larger product's scratch
+static size_t poolbwd_arrays_bytes(size_t n_out)
+{
+    return 2 * (align_up(n_out * 8) + 2 * align_up(2 * n_out * 8)) + mpc_mul_workspace_bytes(2 * n_out);
+}
+
 size_t mpc_maxpool_backward_workspace_bytes(int B, int H, int W, int C)
 {
     if (B <= 0 || H <= 0 || W <= 0 || C <= 0 || (H & 1) || (W & 1)) return 0;
     const size_t n_out = (size_t)B * (H / 2) * (W / 2) * C;
-    // per party grad_u (n_out), pairs and their product (2 n_out each); then the larger product's scratch
-    return 2 * (align_up(n_out * 8) + 2 * align_up(2 * n_out * 8)) + mpc_mul_workspace_bytes(2 * n_out);
+    // up to 16 outputs the receive buffers of one workgroup are larger than the arrays
+    const size_t arrays = poolbwd_arrays_bytes(n_out), box = poolbwd_fused_box_bytes(2, n_out);
+    return arrays > box ? arrays : box;
 }
 
 // Backward of mpc_maxpool2x2: two element-wise products with the masks of the
@@ -403,9 +410,10 @@ int mpc_maxpool2x2_backward(mpc_ctx* c, mpc_cshare g, mpc_cshare s1, mpc_cshare 
     for (int i = 0; i < 2; ++i) {
         gu.p[i] = ws.take<u64>(n_out); pairs.p[i] = ws.take<u64>(2 * n_out); prod.p[i] = ws.take<u64>(2 * n_out);
     }
-    if (!ws.ok) return MPC_ENOMEM;
+    if (!ws.ok || c->ws_bytes < poolbwd_arrays_bytes(n_out)) return MPC_ENOMEM;
     const size_t off = ws.off;
-    if (remote_store(c)) {
+    // one launch where its receive buffers fit; a workspace that holds the arrays only runs launch by launch
+    if (remote_store(c) && c->ws_bytes >= poolbwd_fused_box_bytes(2, n_out)) {
         FusedPoolBwd f{};
         for (int i = 0; i < 2; ++i) {
             if (!a1.p[i] || !b1.p[i] || !c1.p[i] || !a2.p[i] || !b2.p[i] || !c2.p[i]) return MPC_EINVAL;
@@ -413,7 +421,6 @@ int mpc_maxpool2x2_backward(mpc_ctx* c, mpc_cshare g, mpc_cshare s1, mpc_cshare 
             f.a1[i] = a1.p[i]; f.b1[i] = b1.p[i]; f.c1[i] = c1.p[i]; f.a2[i] = a2.p[i]; f.b2[i] = b2.p[i]; f.c2[i] = c2.p[i];
         }
         f.box = reinterpret_cast<u64*>(c->ws); f.n_out = n_out; f.H = H; f.W = W; f.C = C;
-        if (c->ws_bytes < mpc_maxpool_backward_workspace_bytes(B, H, W, C)) return MPC_ENOMEM;
         return launch_poolbwd_fused(c, c->s[0], 2, f);
     }
     const mpc_cshare pairs_c = { { pairs.p[0], pairs.p[1] } };

@@ -1,0 +1,79 @@
+"""Calls on a workspace that is a part of a larger buffer, of exactly the size the query names: nothing is written outside
+it and the results are the oracle's.  Single-queue lanes, exchange by remote store, sizes around one wave."""
+from ctypes import c_void_p
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2209_13643_amd import synth
+
+pytestmark = pytest.mark.gpu
+GUARD, FILL = 8192, 0xA5
+
+
+@pytest.fixture(scope="module")
+def mpc():
+    from paper_2209_13643_amd import mpc as m
+    return m
+
+
+class Guarded:
+    """A single-queue lane whose workspace of `nbytes` lies between two guard areas."""
+
+    def __init__(self, mpc, nbytes, exchange="put"):
+        self.lane = mpc.Lane(0, single_queue=True)
+        self.lane.set_exchange(exchange)
+        self.buf = torch.full((nbytes + 2 * GUARD + 256,), FILL, dtype=torch.uint8, device="cuda:0")
+        self.at = GUARD + (-(self.buf.data_ptr() + GUARD)) % 256
+        torch.cuda.synchronize()
+        self.lane._check(mpc.lib().mpc_ctx_set_workspace(self.lane._h, c_void_p(self.buf.data_ptr() + self.at), nbytes))
+        self.nbytes = nbytes
+
+    def check(self):
+        self.lane.sync()
+        b = self.buf.cpu().numpy()
+        assert (b[:self.at] == FILL).all(), "written before the workspace"
+        behind = b[self.at + self.nbytes:]
+        assert (behind == FILL).all(), f"written behind the workspace, up to byte {int(np.flatnonzero(behind != FILL)[-1])}"
+        self.lane.close()
+
+
+def dev(mpc, shares):
+    return tuple(mpc.to_device(s) for s in shares)
+
+
+def empty(shape, parties):
+    return tuple(torch.empty(shape, dtype=torch.int64, device="cuda:0") for _ in range(parties))
+
+
+def equal(mpc, got, want):
+    for i, w in enumerate(want):
+        assert np.array_equal(mpc.to_host(got[i]).reshape(w.shape), w), f"party {i}"
+
+
+def triple(rng, n, share):
+    A, B = synth.rand_words(rng, n), synth.rand_words(rng, n)
+    return share(rng, A), share(rng, B), share(rng, A * B)
+
+
+@pytest.mark.parametrize("parties", [2, 3])
+@pytest.mark.parametrize("n", [1, 16, 17, 64, 65])
+def test_maxpool_backward_stays_inside_its_workspace(mpc, n, parties):
+    print(f"maxpool backward, {n} outputs, {parties} parties", flush=True)
+    shape, L = (1, 2, 2, n), mpc.lib()
+    rng = np.random.default_rng(n)
+    share = synth.share_additive if parties == 2 else synth.share_additive3
+    signs = lambda k: share(rng, rng.integers(0, 2, size=k).astype(np.uint64))
+    g, s1, s2 = share(rng, synth.normal_fixed(rng, (1, 1, 1, n), 0.5)), signs(2 * n), signs(n)
+    t1, t2 = triple(rng, 2 * n, share), triple(rng, n, share)
+    want = (oracle.maxpool2x2_backward if parties == 2 else oracle.maxpool2x2_backward3)(g, s1, s2, t1, t2, shape)
+    query, call, c = ((L.mpc_maxpool_backward_workspace_bytes, L.mpc_maxpool2x2_backward, mpc._share) if parties == 2 else
+                      (L.mpc_maxpool3_backward_workspace_bytes, L.mpc_maxpool3_backward, mpc._share3))
+    args = [dev(mpc, v) for v in (g, s1, s2, *t1, *t2)]
+    gx = empty(shape, parties)
+    w = Guarded(mpc, query(*shape))
+    w.lane._check(call(w.lane._h, *(c(v) for v in args), c(gx), *shape))
+    w.check()
+    equal(mpc, gx, want)
