@@ -93,9 +93,10 @@ int mpc_ctx_create_single_queue(mpc_ctx** out, int device, int frac_bits);
 int mpc_ctx_destroy(mpc_ctx* ctx);
 
 /* Replace the lane's streams by caller-owned hipStream_t handles (e.g. from
- * torch.cuda.Stream); NULL keeps the current one. */
+ * torch.cuda.Stream); NULL keeps the current one.  The lane's own streams are
+ * waited for, with everything the lane has issued, before they are replaced. */
 int mpc_ctx_set_streams(mpc_ctx* ctx, void* s_party0, void* s_party1, void* s_wire);
-/* stream handle: which = 0, 1 (party) or 2 (wire) */
+/* stream handle: which = 0, 1 (party) or 2 (wire); outputs of the calls made so far are ordered on it */
 void* mpc_ctx_stream(mpc_ctx* ctx, int which);
 
 /* Caller-allocated device scratch, 256-byte aligned.  Contents are undefined

@@ -117,10 +117,23 @@ int mpc_ctx_destroy(mpc_ctx* c)
     return MPC_OK;
 }
 
+// The caller gets to know a stream other than the first: what calls before this one issued on stream 0 alone is ordered
+// on the others from here on, as every later call orders it at its end (lane_fanout).
+static int expose(mpc_ctx* c)
+{
+    if (c->exposed) return MPC_OK;
+    c->exposed = true;
+    return lane_fanout(c);
+}
+
 int mpc_ctx_set_streams(mpc_ctx* c, void* s0, void* s1, void* sw)
 {
     if (!c || c->capturing) return MPC_EINVAL;
     void* in[3] = { s0, s1, sw };
+    // A new stream starts behind what the old ones hold: the lane's own streams are waited for here, and they wait for
+    // stream 0 first.
+    for (int i = 0; i < 3; ++i)
+        if (in[i] && in[i] != (void*)c->s[i]) { MPC_TRY(expose(c)); break; }
     for (int i = 0; i < 3; ++i) {
         if (!in[i] || in[i] == (void*)c->s[i]) continue;
         if (c->own_stream[i]) {
@@ -129,7 +142,6 @@ int mpc_ctx_set_streams(mpc_ctx* c, void* s0, void* s1, void* sw)
             c->own_stream[i] = false;
         }
         c->s[i] = (hipStream_t)in[i];
-        c->exposed = true;
     }
     return MPC_OK;
 }
@@ -137,7 +149,7 @@ int mpc_ctx_set_streams(mpc_ctx* c, void* s0, void* s1, void* sw)
 void* mpc_ctx_stream(mpc_ctx* c, int which)
 {
     if (!c || which < 0 || which > 2) return nullptr;
-    if (which > 0) c->exposed = true;
+    if (which > 0 && expose(c) != MPC_OK) return nullptr;
     return (void*)c->s[which];
 }
 

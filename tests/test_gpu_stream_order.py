@@ -48,3 +48,53 @@ def test_tiled_and_untiled_calls_in_turn(mpc, chunks, handles):
     for i in range(2):
         assert np.array_equal(mpc.to_host(z[i]), want_z[i]) and np.array_equal(mpc.to_host(y[i]).reshape(-1), want[i].reshape(-1)), i
     lane.close()
+
+
+def long_relu(mpc, lane, n=1 << 20):
+    """An untiled call of about a millisecond: (material kept alive, output, expected shares)."""
+    rng = np.random.default_rng(11)
+    xs = synth.share_additive(rng, synth.normal_fixed(rng, n, 4.0))
+    mat = synth.deal_relu_material(rng, n)
+    x, md = dev(mpc, xs), mpc.material_to_device(mat)
+    y = tuple(torch.zeros(n, dtype=torch.int64, device="cuda:0") for _ in range(2))
+    lane.relu(x, md, out=y); lane.sync()                 # kernels loaded, workspace in place
+    for t in y:
+        t.zero_()
+    torch.cuda.synchronize()
+    lane.relu(x, md, out=y)
+    return (x, md), y, oracle.relu(xs, mat).y
+
+
+@pytest.mark.parametrize("which", [1, 2])
+def test_stream_handle_taken_after_the_call(mpc, which):
+    """The handle of another stream, asked for after an untiled call, is ordered behind that call's outputs."""
+    print(f"stream {which} taken after the call", flush=True)
+    lane = mpc.Lane(0)
+    keep, y, want = long_relu(mpc, lane)
+    s = torch.cuda.ExternalStream(lane.stream(which))
+    with torch.cuda.stream(s):
+        got = [t.clone() for t in y]
+    s.synchronize()
+    for i in range(2):
+        assert np.array_equal(mpc.to_host(got[i]), want[i]), i
+    lane.sync()
+    lane.close()
+
+
+@pytest.mark.parametrize("which", [1, 2])
+def test_stream_replaced_after_the_call(mpc, which):
+    """A caller's stream put in the place of the lane's own one starts behind what the lane has issued."""
+    print(f"stream {which} replaced after the call", flush=True)
+    lane = mpc.Lane(0)
+    keep, y, want = long_relu(mpc, lane)
+    s = torch.cuda.Stream()
+    handles = [None, None, None]
+    handles[which] = s.cuda_stream
+    lane._check(mpc.lib().mpc_ctx_set_streams(lane._h, *handles))
+    with torch.cuda.stream(s):
+        got = [t.clone() for t in y]
+    s.synchronize()
+    for i in range(2):
+        assert np.array_equal(mpc.to_host(got[i]), want[i]), i
+    lane.sync()
+    lane.close()
