@@ -161,7 +161,10 @@ int mpc_graph_destroy(mpc_graph* graph);
  *   ended.  Secure ReLU, max-pool, element-wise products and the backward calls
  *   built on them: all rounds run in one launch; a round ends when the waves of
  *   all parties that hold the same elements have stored their words, and
- *   n_chunks has nothing to cut.  Takes
+ *   n_chunks has nothing to cut.  A call whose output overlaps one of its inputs
+ *   (other than element for element) runs launch by launch with the copy
+ *   kernels instead, since the one launch stores results while other words are
+ *   still to be read.  Takes
  *   effect on lanes whose three streams are one queue; elsewhere the copy
  *   kernels are used.  Results are identical.  The three-party calls
  *   honour it on every lane (they use one stream). */

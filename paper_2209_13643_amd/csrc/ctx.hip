@@ -366,7 +366,7 @@ static int mul_entry(mpc_ctx* c, mpc_cshare x, mpc_cshare y, mpc_cshare a, mpc_c
         for (int i = 0; i < 2; ++i) { f.x[i] = x.p[i]; f.y[i] = y.p[i]; f.a[i] = a.p[i]; f.b[i] = b.p[i]; f.c[i] = cc.p[i]; f.z[i] = z.p[i]; }
         f.box = reinterpret_cast<u64*>(c->ws + ws_off); f.n = n; f.trunc_bits = q.trunc_bits; f.mask_from_sign = mask_from_sign;
         if (c->ws_bytes - ws_off < mul_fused_box_bytes(2, n)) return MPC_ENOMEM;
-        return launch_mul_fused(c, c->s[0], 2, f);
+        if (mul_outputs_apart(2, f)) return launch_mul_fused(c, c->s[0], 2, f);
     }
     MPC_TRY(launch_mul_mask(c, c->s[0], q));
     CopySeg cp[4];
@@ -433,7 +433,7 @@ int mpc_maxpool2x2_backward(mpc_ctx* c, mpc_cshare g, mpc_cshare s1, mpc_cshare 
             f.a1[i] = a1.p[i]; f.b1[i] = b1.p[i]; f.c1[i] = c1.p[i]; f.a2[i] = a2.p[i]; f.b2[i] = b2.p[i]; f.c2[i] = c2.p[i];
         }
         f.box = reinterpret_cast<u64*>(c->ws); f.n_out = n_out; f.H = H; f.W = W; f.C = C;
-        return launch_poolbwd_fused(c, c->s[0], 2, f);
+        if (poolbwd_outputs_apart(2, f)) return launch_poolbwd_fused(c, c->s[0], 2, f);
     }
     const mpc_cshare pairs_c = { { pairs.p[0], pairs.p[1] } };
     // grad_u = g * (1 - s2)

@@ -1,6 +1,7 @@
 // Interface of the one-launch element-wise products (mul_fused.hip).
 #pragma once
 #include "common.h"
+#include "overlap.h"
 
 struct FusedMul {
     const u64 *x[3], *y[3], *a[3], *b[3], *c[3];
@@ -10,6 +11,16 @@ struct FusedMul {
     int trunc_bits, mask_from_sign;      // truncation: two parties only; mask_from_sign: y holds sign shares s, the factor is 1 - s
     unsigned tiles;                      // filled by the launcher
 };
+// whether the call may run as one launch (overlap.h)
+inline bool mul_outputs_apart(int parties, const FusedMul& q)
+{
+    Spans<15> in; Spans<3> out;
+    for (int i = 0; i < parties; ++i) {
+        for (const u64* p : { q.x[i], q.y[i], q.a[i], q.b[i], q.c[i] }) in.words(p, q.n);
+        out.words(q.z[i], q.n);
+    }
+    return outputs_apart(out, in, true);
+}
 size_t mul_fused_box_bytes(int parties, size_t n);
 int launch_mul_fused(mpc_ctx* c, hipStream_t st, int parties, FusedMul q);
 
@@ -21,5 +32,15 @@ struct FusedPoolBwd {
     size_t n_out; int H, W, C;
     unsigned tiles;
 };
+inline bool poolbwd_outputs_apart(int parties, const FusedPoolBwd& q)
+{
+    Spans<27> in; Spans<3> out;
+    for (int i = 0; i < parties; ++i) {
+        for (const u64* p : { q.g[i], q.s2[i], q.a2[i], q.b2[i], q.c2[i] }) in.words(p, q.n_out);
+        for (const u64* p : { q.s1[i], q.a1[i], q.b1[i], q.c1[i] }) in.words(p, 2 * q.n_out);
+        out.words(q.gx[i], 4 * q.n_out);
+    }
+    return outputs_apart(out, in, false);
+}
 size_t poolbwd_fused_box_bytes(int parties, size_t n_out);
 int launch_poolbwd_fused(mpc_ctx* c, hipStream_t st, int parties, FusedPoolBwd q);

@@ -584,8 +584,10 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
             q.p[i] = FusedReluParty{ pp[i].x, pp[i].r, nullptr, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].rb, pp[i].ra,
                                      pp[i].ma, pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_bit, pp[i].s_arith };
         q.box = box; q.n = n;
-        if (!geom) return launch_relu_fused(c, c->s[0], 2, q, c->adder);
-        return launch_relu_fused_msb(c, c->s[0], 2, q, packed_triples(*geom));
+        if (relu_outputs_apart(2, q, geom ? geom->words_triples : MPC_N_AND_TRIPLES * n)) {
+            if (!geom) return launch_relu_fused(c, c->s[0], 2, q, c->adder);
+            return launch_relu_fused_msb(c, c->s[0], 2, q, packed_triples(*geom));
+        }
     }
     // chunk boundaries: multiples of four elements, and of 256 on the packed path
     // (four whole words of the deepest level)
@@ -851,7 +853,8 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
         }
         q.box = reinterpret_cast<u64*>(c->ws); q.n_out = n_out; q.H = H; q.W = W; q.C = C;
         const PackedTriples t1 = packed_triples(g1), t2 = packed_triples(g2);
-        return launch_maxpool_fused(c, c->s[0], 2, q, c->adder, packed ? &t1 : nullptr, packed ? &t2 : nullptr);
+        if (pool_outputs_apart(2, q, packed ? g1.words_triples : MPC_N_AND_TRIPLES * 2 * n_out, packed ? g2.words_triples : MPC_N_AND_TRIPLES * n_out))
+            return launch_maxpool_fused(c, c->s[0], 2, q, c->adder, packed ? &t1 : nullptr, packed ? &t2 : nullptr);
     }
     const dim3 grid(grid_for(n_out)), block(kThreads);
     ReluParty pp[2];

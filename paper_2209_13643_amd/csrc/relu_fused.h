@@ -1,6 +1,7 @@
 // Interface of the one-launch secure ReLU (relu_fused.hip) to the entry points (relu.hip, three_party.hip).
 #pragma once
 #include "common.h"
+#include "overlap.h"
 
 struct FusedReluParty {
     const u64 *x, *r, *r1;               // input share, A2B mask (three parties: r to party + 1, r1 to party + 2)
@@ -15,6 +16,22 @@ struct FusedRelu {
     size_t n;
     unsigned tiles;                      // filled by the launcher
 };
+template <int NI>
+inline void add_material(Spans<NI>& in, const FusedReluParty& p, size_t n, size_t triple_words)
+{
+    in.words(p.r, n); in.words(p.r1, n); in.words(p.ta, triple_words); in.words(p.tb, triple_words); in.words(p.tc, triple_words);
+    in.bytes(p.rb, n); in.words(p.ra, n); in.words(p.ma, n); in.words(p.mb, n); in.words(p.mc, n);
+}
+// whether the call may run as one launch (overlap.h); triple_words: words of one of a party's AND triple arrays
+inline bool relu_outputs_apart(int parties, const FusedRelu& q, size_t triple_words)
+{
+    Spans<33> in; Spans<9> out;
+    for (int i = 0; i < parties; ++i) {
+        in.words(q.p[i].x, q.n); add_material(in, q.p[i], q.n, triple_words);
+        out.words(q.p[i].y, q.n); out.bytes(q.p[i].s_bit, q.n); out.words(q.p[i].s_arith, q.n);
+    }
+    return outputs_apart(out, in, true);
+}
 size_t relu_fused_box_bytes(int parties, size_t n);
 int launch_relu_fused(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, int topo);
 // the sign-only chain; offsets of the triples in the packed buffers
@@ -30,6 +47,16 @@ struct FusedPool {
     size_t n_out; int H, W, C;
     unsigned tiles;                      // filled by the launcher
 };
+inline bool pool_outputs_apart(int parties, const FusedPool& q, size_t triple_words1, size_t triple_words2)
+{
+    Spans<63> in; Spans<9> out;
+    for (int i = 0; i < parties; ++i) {
+        in.words(q.x[i], 4 * q.n_out);
+        add_material(in, q.m1[i], 2 * q.n_out, triple_words1); add_material(in, q.m2[i], q.n_out, triple_words2);
+        out.words(q.y[i], q.n_out); out.words(q.s1[i], 2 * q.n_out); out.words(q.s2[i], q.n_out);
+    }
+    return outputs_apart(out, in, false);
+}
 size_t maxpool_fused_box_bytes(int parties, bool packed, size_t n_out);
 // g1, g2: packed layouts of the two conversions (sign-only chain), or null (whole words)
 int launch_maxpool_fused(mpc_ctx* c, hipStream_t st, int parties, FusedPool q, int topo, const PackedTriples* g1, const PackedTriples* g2);

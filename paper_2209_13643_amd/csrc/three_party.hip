@@ -552,7 +552,10 @@ inline size_t relu3_chunk_cap(size_t n, size_t chunk = kChunk3)          // larg
 int relu3_run(mpc_ctx* c, hipStream_t st, const Relu3Args& q)
 {
     const size_t n = q.n;
-    if (c->exchange_put) return launch_relu_fused(c, st, 3, fused3(q), 0);
+    if (c->exchange_put) {
+        const FusedRelu f = fused3(q);
+        if (relu_outputs_apart(3, f, 13 * n)) return launch_relu_fused(c, st, 3, f, 0);
+    }
     const int k = relu3_chunks(n, relu3_chunk_of(c));
     if (k == 1) return relu3_chunk(c, st, q);
     const size_t cap = relu3_chunk_cap(n, relu3_chunk_of(c));
@@ -611,7 +614,10 @@ int launch_plevel(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom
 int relu3_msb_run(mpc_ctx* c, hipStream_t st, const Relu3Args& q, const Msb3Geom& g)
 {
     const size_t n = q.n;
-    if (c->exchange_put) return launch_relu_fused_msb(c, st, 3, fused3(q), packed_triples3(g));
+    if (c->exchange_put) {
+        const FusedRelu f = fused3(q);
+        if (relu_outputs_apart(3, f, g.words_triples)) return launch_relu_fused_msb(c, st, 3, f, packed_triples3(g));
+    }
     const int vec = relu3_vectorisable(q);
     const bool vec0 = vec >= 2 && n % 4 == 0;
     {
@@ -738,7 +744,7 @@ int mul3_run(mpc_ctx* c, hipStream_t st, const u64* const x[3], const u64* const
         for (int i = 0; i < 3; ++i) { f.x[i] = x[i]; f.y[i] = y[i]; f.a[i] = a[i]; f.b[i] = b[i]; f.c[i] = cc[i]; f.z[i] = z[i]; }
         f.box = reinterpret_cast<u64*>(c->ws + ws_off); f.n = n; f.mask_from_sign = mask_from_sign;
         if (c->ws_bytes - ws_off < mul_fused_box_bytes(3, n)) return MPC_ENOMEM;
-        return launch_mul_fused(c, st, 3, f);
+        if (mul_outputs_apart(3, f)) return launch_mul_fused(c, st, 3, f);
     }
     hipLaunchKernelGGL(k3_mul_mask, dim3(grid3(n), 3), dim3(kT), 0, st, q);
     MPC_HIP(c, hipGetLastError());
@@ -980,8 +986,10 @@ static int maxpool3_entry(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m
         }
         q.box = reinterpret_cast<u64*>(c->ws); q.n_out = n_out; q.H = H; q.W = W; q.C = C;
         const PackedTriples t1 = packed_triples3(g1), t2 = packed_triples3(g2);
-        MPC_TRY(launch_maxpool_fused(c, st, 3, q, 0, packed ? &t1 : nullptr, packed ? &t2 : nullptr));
-        return lane_fanout(c);
+        if (pool_outputs_apart(3, q, packed ? g1.words_triples : 13 * 2 * n_out, packed ? g2.words_triples : 13 * n_out)) {
+            MPC_TRY(launch_maxpool_fused(c, st, 3, q, 0, packed ? &t1 : nullptr, packed ? &t2 : nullptr));
+            return lane_fanout(c);
+        }
     }
     MPC_TRY(launch_pool<0>(c, st, pq, n_out));       // first tournament level: max(p00, p01), max(p10, p11)
     MPC_TRY(packed ? relu3_msb_run(c, st, q1, g1) : relu3_run(c, st, q1));
@@ -1085,8 +1093,7 @@ int mpc_maxpool3_backward(mpc_ctx* c, mpc_cshare3 g, mpc_cshare3 s1, mpc_cshare3
         }
         f.box = reinterpret_cast<u64*>(c->ws); f.n_out = n_out; f.H = H; f.W = W; f.C = C;
         if (c->ws_bytes < poolbwd_fused_box_bytes(3, n_out)) return MPC_ENOMEM;
-        MPC_TRY(launch_poolbwd_fused(c, st, 3, f));
-        return lane_fanout(c);
+        if (poolbwd_outputs_apart(3, f)) { MPC_TRY(launch_poolbwd_fused(c, st, 3, f)); return lane_fanout(c); }
     }
     // grad_u = g * (1 - s2)
     MPC_TRY(mul3_run(c, st, g.p, s2.p, a2.p, b2.p, c2.p, gu, n_out, 1, off));
