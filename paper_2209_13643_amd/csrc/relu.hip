@@ -844,8 +844,8 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
     Narrow nar(c);
     if (n_chunks <= 1) MPC_TRY(nar.begin());
     else               MPC_TRY(lane_join(c));
-    if (remote_store(c)) {
-        if (c->ws_bytes < maxpool_fused_box_bytes(2, packed, n_out)) return MPC_ENOMEM;
+    // one launch where its receive buffers fit (up to 8 outputs they are larger than everything else)
+    if (remote_store(c) && c->ws_bytes >= maxpool_fused_box_bytes(2, packed, n_out)) {
         FusedPool q{};
         for (int i = 0; i < 2; ++i) {
             q.m1[i] = fused_party(mat1, i); q.m2[i] = fused_party(mat2, i);

@@ -449,10 +449,11 @@ size_t relu3_ws(u8* base, size_t cap, size_t n, size_t calln, Relu3Args* q, bool
     }
     // 24 n more words belong to the documented size of this workspace (a second set of receive buffers, once)
     for (int i = 0; i < 6; ++i) w.take<u64>(4 * n);
-    q->box = reinterpret_cast<u64*>(base);
-    const size_t box = relu_fused_box_bytes(3, calln), bytes = w.off > box ? w.off : box;
-    if (ok) *ok = w.ok && cap >= bytes;
-    return bytes;
+    // up to 8 elements the receive buffers are larger: a workspace without them runs launch by launch
+    const size_t box = relu_fused_box_bytes(3, calln);
+    q->box = cap >= box ? reinterpret_cast<u64*>(base) : nullptr;
+    if (ok) *ok = w.ok;
+    return w.off > box ? w.off : box;
 }
 
 int check_material3(const mpc_relu3_material* m)
@@ -552,7 +553,7 @@ inline size_t relu3_chunk_cap(size_t n, size_t chunk = kChunk3)          // larg
 int relu3_run(mpc_ctx* c, hipStream_t st, const Relu3Args& q)
 {
     const size_t n = q.n;
-    if (c->exchange_put) {
+    if (c->exchange_put && q.box) {
         const FusedRelu f = fused3(q);
         if (relu_outputs_apart(3, f, 13 * n)) return launch_relu_fused(c, st, 3, f, 0);
     }
@@ -739,11 +740,11 @@ int mul3_run(mpc_ctx* c, hipStream_t st, const u64* const x[3], const u64* const
     if (!ws.ok) return MPC_ENOMEM;
     for (int i = 0; i < 3; ++i) { q.x[i] = x[i]; q.y[i] = y[i]; q.a[i] = a[i]; q.b[i] = b[i]; q.c[i] = cc[i]; q.z[i] = z[i]; }
     q.n = n; q.mask_from_sign = mask_from_sign;
-    if (c->exchange_put) {
+    // one launch where its receive buffers fit (up to 32 words they are larger than the arrays)
+    if (c->exchange_put && c->ws_bytes - ws_off >= mul_fused_box_bytes(3, n)) {
         FusedMul f{};
         for (int i = 0; i < 3; ++i) { f.x[i] = x[i]; f.y[i] = y[i]; f.a[i] = a[i]; f.b[i] = b[i]; f.c[i] = cc[i]; f.z[i] = z[i]; }
         f.box = reinterpret_cast<u64*>(c->ws + ws_off); f.n = n; f.mask_from_sign = mask_from_sign;
-        if (c->ws_bytes - ws_off < mul_fused_box_bytes(3, n)) return MPC_ENOMEM;
         if (mul_outputs_apart(3, f)) return launch_mul_fused(c, st, 3, f);
     }
     hipLaunchKernelGGL(k3_mul_mask, dim3(grid3(n), 3), dim3(kT), 0, st, q);
@@ -976,8 +977,7 @@ static int maxpool3_entry(mpc_ctx* c, mpc_cshare3 x, const mpc_relu3_material* m
     if (packed) { q1.tn = g1.toff[1]; q2.tn = g2.toff[1]; }
     hipStream_t st = c->s[0];
     MPC_TRY(lane_first(c));
-    if (c->exchange_put) {
-        if (c->ws_bytes < maxpool_fused_box_bytes(3, packed, n_out)) return MPC_ENOMEM;
+    if (c->exchange_put && c->ws_bytes >= maxpool_fused_box_bytes(3, packed, n_out)) {      // as for two parties
         FusedPool q{};
         const FusedRelu f1 = fused3(q1), f2 = fused3(q2);
         for (int i = 0; i < 3; ++i) {
@@ -1085,14 +1085,13 @@ int mpc_maxpool3_backward(mpc_ctx* c, mpc_cshare3 g, mpc_cshare3 s1, mpc_cshare3
     const size_t off = ws.off;
     hipStream_t st = c->s[0];
     MPC_TRY(lane_first(c));
-    if (c->exchange_put) {
+    if (c->exchange_put && c->ws_bytes >= poolbwd_fused_box_bytes(3, n_out)) {
         FusedPoolBwd f{};
         for (int i = 0; i < 3; ++i) {
             f.g[i] = g.p[i]; f.s1[i] = s1.p[i]; f.s2[i] = s2.p[i]; f.gx[i] = gx.p[i];
             f.a1[i] = a1.p[i]; f.b1[i] = b1.p[i]; f.c1[i] = c1.p[i]; f.a2[i] = a2.p[i]; f.b2[i] = b2.p[i]; f.c2[i] = c2.p[i];
         }
         f.box = reinterpret_cast<u64*>(c->ws); f.n_out = n_out; f.H = H; f.W = W; f.C = C;
-        if (c->ws_bytes < poolbwd_fused_box_bytes(3, n_out)) return MPC_ENOMEM;
         if (poolbwd_outputs_apart(3, f)) { MPC_TRY(launch_poolbwd_fused(c, st, 3, f)); return lane_fanout(c); }
     }
     // grad_u = g * (1 - s2)
