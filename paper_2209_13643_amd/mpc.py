@@ -366,6 +366,7 @@ class Lane:
             raise RuntimeError("mpcpipe needs a GPU: no HIP device is visible")
         self.device = torch.device("cuda", device)
         self._h = c_void_p()
+        self._handed = set()         # streams whose handles the caller has
         self._pending = []           # tensors the enqueued calls still use (see _note); released by sync()
         create = lib().mpc_ctx_create_single_queue if single_queue else lib().mpc_ctx_create
         self._check(create(byref(self._h), device, frac_bits))
@@ -424,8 +425,11 @@ class Lane:
     def wait_torch(self):
         """Order the lane after the work torch has enqueued on its current stream
         (inputs produced by torch ops are otherwise not ordered with the lane's queues)."""
-        # every call starts from stream 0 or joins the other streams with it
-        torch.cuda.ExternalStream(self.stream(0), device=self.device).wait_stream(torch.cuda.current_stream(self.device))
+        # every call starts from stream 0 or joins the other streams with it; a caller that holds another stream's handle
+        # may use that one directly
+        cur = torch.cuda.current_stream(self.device)
+        for s in {self.stream(i) for i in self._handed | {0}}:
+            torch.cuda.ExternalStream(s, device=self.device).wait_stream(cur)
 
     def capture(self):
         """Context manager: record the lane calls made inside it into a Graph (`.graph` afterwards).
@@ -452,6 +456,7 @@ class Lane:
         self._check(lib().mpc_ctx_set_streams(self._h, c_void_p(s0), c_void_p(s0), c_void_p(s0)))
 
     def stream(self, which: int) -> int:
+        self._handed.add(which)
         return lib().mpc_ctx_stream(self._h, which) or 0
 
     def reserve(self, nbytes: int):

@@ -98,3 +98,21 @@ def test_stream_replaced_after_the_call(mpc, which):
         assert np.array_equal(mpc.to_host(got[i]), want[i]), i
     lane.sync()
     lane.close()
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+def test_wait_torch_covers_streams_the_caller_holds(mpc, which):
+    print(f"wait_torch, stream {which}", flush=True)
+    lane = mpc.Lane(0)
+    s = torch.cuda.ExternalStream(lane.stream(which))
+    x = torch.zeros(1 << 26, dtype=torch.int64, device="cuda:0")
+    torch.cuda.synchronize()
+    for _ in range(20):
+        x += 1                                           # some milliseconds on torch's stream
+    lane.wait_torch()
+    with torch.cuda.stream(s):
+        got = x[-1000:].clone()
+    s.synchronize()
+    assert (got == 20).all()
+    torch.cuda.synchronize()
+    lane.close()
