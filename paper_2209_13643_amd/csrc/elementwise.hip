@@ -2,6 +2,7 @@
 // and the recoding of ring words into balanced base-256 digit planes.
 // All of them are HBM-bound; they use 16-byte accesses and grid-stride loops.
 #include "common.h"
+#include "recode_tiles.h"
 
 #include <algorithm>
 
@@ -188,14 +189,11 @@ __global__ __launch_bounds__(kThreads) void k_recode(RecodeArgs a)
 // filter tap, reads it with lanes along k (coalesced 16-byte loads), scatters the digits into LDS in
 // plane order, and writes each plane's 16-byte units with lanes along rows
 // (coalesced again).  bx = row tile, by = (tap, group of 4 k blocks); the loads of an operand are issued together.
-__device__ __forceinline__ int row_groups(const RecodeArgs& a) { return ((a.ntaps == 1 ? a.KB_total : a.KB_tap) + 3) / 4; }
 __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, unsigned bx, unsigned by, uint32_t (*tile)[4][64][4])
 {
-    const int groups = row_groups(a), tap = (int)by / groups;
-    const int row0 = bx * 64, kb0 = ((int)by - tap * groups) * 4;
-    const bool padtap = tap >= a.ntaps;                          // the k blocks behind the last tap: zero
-    const int kb_lim = padtap ? a.KB_total - a.ntaps * a.KB_tap : a.ntaps == 1 ? a.KB_total : a.KB_tap;
-    const int kb_first = tap * a.KB_tap;
+    const RecodeTile rt = recode_tile(a.ntaps, a.KB_tap, a.KB_total, by);
+    const int row0 = bx * 64, tap = rt.tap, kb0 = rt.kb0, kb_lim = rt.kb_lim, kb_first = tap * a.KB_tap;
+    const bool padtap = rt.zero;                                 // the k blocks behind the last tap: zero
     if (row0 >= a.plane_rows || kb0 >= kb_lim) return;           // uniform per workgroup
     const long long at = (long long)b * a.src_batch_stride + (padtap ? 0 : (long long)tap * a.tap_stride);
     const u64* src = a.src + at;
@@ -565,12 +563,7 @@ int launch_truncate(mpc_ctx* c, hipStream_t st, u64* z, size_t n, int bits, int 
 
 // contiguous k, and taps (if any) of at least two whole k blocks: the tile recoder; else one thread per (row, k block)
 static bool rows_form(const RecodeArgs& a) { return a.k_stride == 1 && (a.ntaps == 1 || a.KB_tap >= 2); }
-// (tap, group of four k blocks) pairs of the tile recoder, the padding behind the last tap included
-static unsigned rows_gy(const RecodeArgs& a)
-{
-    const unsigned groups = (unsigned)(((a.ntaps == 1 ? a.KB_total : a.KB_tap) + 3) / 4);
-    return groups * (unsigned)(a.ntaps + (a.ntaps > 1 && a.KB_total > a.ntaps * a.KB_tap ? 1 : 0));
-}
+static unsigned rows_gy(const RecodeArgs& a) { return recode_tile_count(a.ntaps, a.KB_tap, a.KB_total); }
 
 int launch_recode_multi(mpc_ctx* c, hipStream_t st, const RecodeArgs* sets, int count)
 {
