@@ -72,6 +72,12 @@ struct GemmDev {
     Divider by_item, by_batch, by_panel, by_last_width, by_Wo, by_Ho;
     ConvGeom conv;
 };
+// Widest output whose words the epilogue addresses by a 32-bit lane offset: the last lane's is (4 N + 31) words.
+constexpr int kLaneOffsetMaxN = (1 << 27) - 8;
+constexpr u64 last_lane_offset(u64 N) { return (4 * N + 31) * 8; }
+static_assert(last_lane_offset(kLaneOffsetMaxN) < (1ull << 32), "the widest output's lane offsets fit 32 bits");
+static_assert(last_lane_offset(kLaneOffsetMaxN + 1) >= (1ull << 32), "and no wider one's do");
+
 // LDS ring depth: three slots for the one-workgroup-per-unit tiles; two for the small tile of short
 // contractions, which then fits twice on a compute unit
 
@@ -338,7 +344,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g)
     // truncation per word, and branches between the MFMAs of the last two steps, per-head Q K^T took 358 us and the
     // 1x1 convolution on 56 x 56 x 64 to 256 channels 381 us; so 334 and 361 us.)
     auto row_of = [](int v) { return (v >> 2) * 8 + (v & 3); };
-    const bool interior = m0 + C::TM <= g.M && n0 + C::TN <= g.N && g.N < (1 << 27);
+    const bool interior = m0 + C::TM <= g.M && n0 + C::TN <= g.N && g.N <= kLaneOffsetMaxN;
     const unsigned lane_off = ((unsigned)(g2 * 4) * (unsigned)g.N + (unsigned)i32) * 8u;
     const size_t wave_at = (size_t)(m0 + wm * 32) * g.N + (n0 + wn * C::WN);
     u64 addw[NH][16];
