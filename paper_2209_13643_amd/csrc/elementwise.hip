@@ -5,6 +5,7 @@
 #include "recode_tiles.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(kThreads) void k_recode(RecodeArgs a)
 // NHWC activations, filters read with their channel roles swapped): a workgroup takes a 64-row x 64-k tile of one
 // filter tap, reads it with lanes along k (coalesced 16-byte loads), scatters the digits into LDS in
 // plane order, and writes each plane's 16-byte units with lanes along rows
-// (coalesced again).  bx = row tile, by = (tap, group of 4 k blocks); the loads of an operand are issued together.
+// (coalesced again).  bx = row tile, by = (tap, group of 4 k blocks).
 __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, unsigned bx, unsigned by, uint32_t (*tile)[4][64][4])
 {
     const RecodeTile rt = recode_tile(a.ntaps, a.KB_tap, a.KB_total, by);
@@ -208,69 +209,96 @@ __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, uns
                                                   (uintptr_t)side | (uintptr_t)minuend) & 15) == 0;
     // thread's segments: 4 words each, segment p at row (threadIdx.x + 256 p) / 16 of the tile
     const int s4 = threadIdx.x & 15, k = kb0 * 16 + s4 * 4;
-    const bool whole = vec && k + 3 < k_lim;                     // 16-byte accesses allowed
-    auto row_of = [&](int p) { return row0 + (int)(threadIdx.x >> 4) + 16 * p; };
-    auto load = [&](const u64* q, u64 (&w)[4][4]) {
-        if (whole) {
+    // 16-byte accesses allowed; threads past the last k read column 0 with the others instead of a way of their own
+    const bool beyond = k >= k_lim, whole = vec && (beyond ? k_lim > 3 : k + 3 < k_lim);
+    const int kc = beyond ? 0 : k;
+    // The loads of two segments in one straight line per way of access and kind of sum.  With the way chosen anew for
+    // every operand the ways joined in between, and the next operand's loads waited for the joined registers; with the
+    // threads past the last k on the word-wise way, every wave of a tile that K leaves ragged ran both.  Masked sum of
+    // 4096 x 768 words 28.3 -> 24.5 us, of 32 x 56 x 56 x 64 52.0 -> 45.6, of 1000 x 2000 15.4 -> 13.7; plain sums level
+    // (ragged K: 300 x 4000 8.3 -> 7.1).  All four segments at once or one at a time: 24.8, 25.4 us.
+    enum { kAny, kSum, kMaskedSum };
+    const bool masked_sum = sub && side && src2 && !src3, sum = !sub && !minuend && src2 && !src3;      // uniform
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int r = row_of(p);
-                const u64x2* t = reinterpret_cast<const u64x2*>(q + (size_t)(r < a.rows ? r : 0) * a.row_stride + k);
-                const u64x2 lo = t[0], hi = t[1];
-                w[p][0] = lo.a; w[p][1] = lo.b; w[p][2] = hi.a; w[p][3] = hi.b;
-            }
-        } else {
+    for (int p0 = 0; p0 < 4; p0 += 2) {
+        auto row_of = [&](int p) { return row0 + (int)(threadIdx.x >> 4) + 16 * (p0 + p); };
+        u64 v[2][4];
+        auto gather = [&](auto whole_tag, auto kind_tag) {
+            constexpr bool W = decltype(whole_tag)::value;
+            constexpr int kind = decltype(kind_tag)::value;
+            auto load = [&](const u64* q, u64 (&w)[2][4]) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int r = row_of(p);
+                for (int p = 0; p < 2; ++p) {
+                    const int r = row_of(p);
+                    const u64* t = q + (size_t)(r < a.rows ? r : 0) * a.row_stride;
+                    if constexpr (W) {
+                        const u64x2 lo = reinterpret_cast<const u64x2*>(t + kc)[0], hi = reinterpret_cast<const u64x2*>(t + kc)[1];
+                        w[p][0] = lo.a; w[p][1] = lo.b; w[p][2] = hi.a; w[p][3] = hi.b;
+                    } else {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) w[p][t] = q[(size_t)(r < a.rows ? r : 0) * a.row_stride + (k + t < k_lim ? k + t : 0)];
-            }
-        }
-    };
-    auto store = [&](u64* q, const u64 (&w)[4][4]) {
+                        for (int u = 0; u < 4; ++u) w[p][u] = t[k + u < k_lim ? k + u : 0];
+                    }
+                }
+            };
+            auto store = [&](u64* q, const u64 (&w)[2][4]) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int r = row_of(p);
-            if (r >= a.rows) continue;
-            u64* o = q + (size_t)r * a.row_stride + k;
-            if (whole) {
-                u64x2 lo, hi; lo.a = w[p][0]; lo.b = w[p][1]; hi.a = w[p][2]; hi.b = w[p][3];
-                reinterpret_cast<u64x2*>(o)[0] = lo; reinterpret_cast<u64x2*>(o)[1] = hi;
+                for (int p = 0; p < 2; ++p) {
+                    const int r = row_of(p);
+                    if (beyond || r >= a.rows) continue;
+                    u64* o = q + (size_t)r * a.row_stride + k;
+                    if constexpr (W) {
+                        u64x2 lo, hi; lo.a = w[p][0]; lo.b = w[p][1]; hi.a = w[p][2]; hi.b = w[p][3];
+                        reinterpret_cast<u64x2*>(o)[0] = lo; reinterpret_cast<u64x2*>(o)[1] = hi;
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) if (k + u < k_lim) o[u] = w[p][u];
+                    }
+                }
+            };
+            auto fold = [&](u64 (&x)[2][4], const u64 (&w)[2][4], bool minus) {
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[p][u] = minus ? x[p][u] - w[p][u] : x[p][u] + w[p][u];
+            };
+            u64 w[2][4], w2[2][4];
+            load(src, v);
+            if constexpr (kind == kMaskedSum) {
+                load(sub, w); load(src2, w2);
+                fold(v, w, true);
+                store(side, v);
+                fold(v, w2, false);
+            } else if constexpr (kind == kSum) {
+                load(src2, w);
+                fold(v, w, false);
             } else {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) if (k + t < k_lim) o[t] = w[p][t];
+                if (sub) {
+                    load(sub, w);
+                    fold(v, w, true);
+                    if (side) store(side, v);
+                } else if (minuend) {
+                    load(minuend, w);
+                    fold(w, v, true);
+                    store(side, w);
+                }
+                if (src2) { load(src2, w); fold(v, w, false); }
+                if (src3) { load(src3, w); fold(v, w, false); }
             }
+        };
+        if (!whole)          gather(std::false_type{}, std::integral_constant<int, kAny>{});
+        else if (masked_sum) gather(std::true_type{}, std::integral_constant<int, kMaskedSum>{});
+        else if (sum)        gather(std::true_type{}, std::integral_constant<int, kSum>{});
+        else                 gather(std::true_type{}, std::integral_constant<int, kAny>{});
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const bool row_ok = row_of(p) < a.rows;
+            u64 four[4]; uint32_t d[8];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) four[u] = row_ok && k + u < k_lim ? v[p][u] : 0;
+            digits_of_4(four, d);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) tile[q][s4 >> 2][(threadIdx.x >> 4) + 16 * (p0 + p)][s4 & 3] = d[q];
         }
-    };
-    auto fold = [&](u64 (&v)[4][4], const u64 (&w)[4][4], bool minus) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) v[p][t] = minus ? v[p][t] - w[p][t] : v[p][t] + w[p][t];
-    };
-    u64 v[4][4], w[4][4];
-    load(src, v);
-    if (sub) {
-        load(sub, w);
-        fold(v, w, true);
-        if (side) store(side, v);
-    } else if (minuend) {
-        load(minuend, w);
-        fold(w, v, true);
-        store(side, w);
-    }
-    if (src2) { load(src2, w); fold(v, w, false); }
-    if (src3) { load(src3, w); fold(v, w, false); }
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const bool row_ok = row_of(p) < a.rows;
-        u64 four[4]; uint32_t d[8];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) four[t] = row_ok && k + t < k_lim ? v[p][t] : 0;
-        digits_of_4(four, d);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) tile[q][s4 >> 2][(threadIdx.x >> 4) + 16 * p][s4 & 3] = d[q];
     }
     __syncthreads();
 #pragma unroll

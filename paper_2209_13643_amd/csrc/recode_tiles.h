@@ -19,11 +19,15 @@ MPC_HD inline unsigned recode_tile_count(int ntaps, int KB_tap, int KB_total)
 
 MPC_HD inline RecodeTile recode_tile(int ntaps, int KB_tap, int KB_total, unsigned by)
 {
-    const int groups = recode_groups(ntaps, KB_tap, KB_total);
     RecodeTile t;
+    if (ntaps == 1) {                  // without the division, which every workgroup would wait for
+        t.tap = 0; t.kb0 = (int)by * 4; t.kb_lim = KB_total; t.zero = false;
+        return t;
+    }
+    const int groups = recode_groups(ntaps, KB_tap, KB_total);
     t.tap = (int)by / groups;
     t.kb0 = ((int)by - t.tap * groups) * 4;
     t.zero = t.tap >= ntaps;
-    t.kb_lim = !t.zero ? (ntaps == 1 ? KB_total : KB_tap) : ntaps > 1 && t.tap == ntaps ? KB_total - ntaps * KB_tap : 0;
+    t.kb_lim = !t.zero ? KB_tap : t.tap == ntaps ? KB_total - ntaps * KB_tap : 0;
     return t;
 }

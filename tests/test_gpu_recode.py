@@ -58,3 +58,31 @@ def test_transposed_im2col(mpc, lane, hw, stride, pad):
     got = lane.ring_conv2d_grad_w(mpc.to_device(x), mpc.to_device(g), 3, 3, pad, stride)
     lane.sync()
     assert np.array_equal(mpc.to_host(got), oracle.ring_conv2d_grad_w(x, g, 3, 3, pad, stride))
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 1, 5), (2, 3, 4), (65, 4, 7), (63, 62, 33), (64, 64, 16), (66, 68, 20), (130, 129, 9), (300, 200, 31)])
+@pytest.mark.parametrize("call", ["folded", "plain", "activations"])
+def test_masked_recodings_of_ragged_tiles(mpc, call, M, K, N):
+    """Exchange by remote store: the recodings that mask, send and open on the way, with threads past the last k, word-wise
+    and 16-byte accesses and rows past the last one."""
+    from helpers import deal_matmul, oracle_matmul
+    print(f"masked recoding {call} {M}x{K}x{N}", flush=True)
+    lane = mpc.Lane(0, single_queue=True)
+    lane.set_exchange("put")
+    d = deal_matmul(np.random.default_rng(M + K + N), M, K, N)
+    want = oracle_matmul(d)
+    x, y, a, b, c = (tuple(mpc.to_device(p) for p in d[k]) for k in ("x", "y", "a", "b", "c"))
+    if call == "plain":
+        z = lane.beaver_matmul(x, y, a, b, c)
+    else:
+        f = lane.open(lane.sub(y, b)) if call == "folded" else None
+        right, left = lane.prepare_matmul(a, b, f)
+        cf = (lane.fold_matmul(a, b, c), c[1])
+        if call == "folded":
+            z = lane.beaver_matmul_prepared(x, a, cf, right, left, flags=mpc.MPC_TRUNCATE | mpc.MPC_FOLDED)
+        else:
+            z = lane.beaver_matmul_folded(x, y, a, b, cf, right, left)
+    lane.sync()
+    for i in range(2):
+        assert np.array_equal(mpc.to_host(z[i]), want[i]), f"party {i}"
+    lane.close()
