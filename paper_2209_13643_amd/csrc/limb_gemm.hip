@@ -609,6 +609,11 @@ constexpr int kMaxStepsExact = 1023;
 // 3 = 32 x 128 (1 x 4 waves of 32 x 32) for at most 32 rows, where a 64-row tile multiplies padding: with two rows and
 // weights of 25088 x 4096 the matrix pipeline was as busy as the memory (616 us a call, 413 us on this tile: 6.0 TB/s of weight planes; 32 rows 641 and 476 us; level
 // where a call is all launches).
+// Batched products of few rows that meet tile 2's rule stay on tile 2 where half of tile 3's columns would be padding:
+// GEMM launch of 768 products with 4 / 32 rows, tile 2 against 3, K = 64: N = 32 29 / 35 and 41 / 47 us, N = 64 33 / 46 and
+// 43 / 56; N = 96 (8 / 32 rows) 60 / 76 and 50 / 68, N = 128 66 / 82 and 61 / 73; K = 256, N = 64 98 / 113 and 104 / 119.  Below 512
+// products and on longer contractions tile 3 takes the place of the 128 x 64 tile: 96 products, K = 64 and N = 64, 16 / 18
+// and 11 / 13 us; K = 512, 768 products, 275 / 290 and 173 / 186.
 // Tile 2 is chosen when the longest contraction of the launch has at most g_small_max_steps K steps (32 terms each)
 // and the output has at least g_small_min_tiles tiles of 64 x 64 (mpc_set_gemm_small_tile changes both).
 // A launch whose parties contract different lengths (the folded calls: party 0 one segment, party 1 two) also takes
@@ -619,10 +624,11 @@ static std::atomic<int> g_small_max_steps{ 16 }, g_small_min_tiles{ 512 };
 constexpr long long kAsymMinTiles = 768;
 static int tile_kind(int M, int N, int batch, int longest_steps, bool asymmetric)
 {
-    if (M <= 32) return 3;
     const long long tiles64 = (long long)((M + 63) / 64) * ((N + 63) / 64) * batch;
     const int max_steps = g_small_max_steps.load(std::memory_order_relaxed);
-    if (longest_steps <= max_steps && tiles64 >= g_small_min_tiles.load(std::memory_order_relaxed)) return 2;
+    const bool few_rows = M <= 32;
+    if (longest_steps <= max_steps && tiles64 >= g_small_min_tiles.load(std::memory_order_relaxed) && !(few_rows && N > 64)) return 2;
+    if (few_rows) return 3;
     // (not the batched products one 64-column tile wide, per-head A*V: those are 5 % faster on the 128 x 64 tile)
     if (asymmetric && max_steps > 0 && tiles64 >= kAsymMinTiles && !(batch > 1 && N <= 64)) return 2;
     return (((N - 1) % 128) < 64 && (N <= 64 || M >= 4096)) ? 1 : 0;

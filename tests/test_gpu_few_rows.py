@@ -47,6 +47,20 @@ def test_matmul(mpc, lane, M, K, N, batch):
         same(mpc, lane, z, oracle_matmul(d, bits), f"{M}x{K}x{N} batch {batch} flags {flags}")
 
 
+@pytest.mark.parametrize("M,K,N,batch", [
+    (8, 64, 64, 512), (8, 64, 64, 511), (32, 40, 33, 600), (33, 40, 33, 600), (3, 128, 65, 300), (4, 129, 64, 513), (1, 1, 1, 512),
+])
+def test_batched_products_of_few_rows(mpc, lane, M, K, N, batch):
+    """Around the rule that gives batched products of at most 64 columns and short contractions the 64 x 64 tile."""
+    rng = np.random.default_rng(M + K + N + batch)
+    d = deal_matmul(rng, M, K, N, batch=batch)
+    x, y, a, b, c = (dev(mpc, d[k]) for k in ("x", "y", "a", "b", "c"))
+    same(mpc, lane, lane.beaver_matmul(x, y, a, b, c), oracle_matmul(d), f"{batch} x {M}x{K}x{N}")
+    right, left = lane.prepare_matmul(a, b, None)
+    z = lane.beaver_matmul_folded(x, y, a, b, (lane.fold_matmul(a, b, c), c[1]), right, left)
+    same(mpc, lane, z, oracle_matmul(d), f"folded, {batch} x {M}x{K}x{N}")
+
+
 @pytest.mark.parametrize("B,H,W,Cin,Cout,k,pad,stride", [
     (1, 2, 2, 40, 130, 3, 1, 1), (8, 2, 2, 17, 128, 3, 1, 1), (1, 8, 8, 5, 64, 3, 1, 2), (2, 7, 7, 64, 70, 1, 0, 2), (1, 5, 6, 3, 200, 3, 1, 1),
 ])
