@@ -96,7 +96,7 @@ int mpc_ctx_destroy(mpc_ctx* ctx);
  * torch.cuda.Stream); NULL keeps the current one.  The lane's own streams are
  * waited for, with everything the lane has issued, before they are replaced. */
 int mpc_ctx_set_streams(mpc_ctx* ctx, void* s_party0, void* s_party1, void* s_wire);
-/* stream handle: which = 0, 1 (party) or 2 (wire); outputs of the calls made so far are ordered on it */
+/* stream handle: which = 0, 1 (party) or 2 (wire); party i's outputs of the calls made so far are ordered on party i's */
 void* mpc_ctx_stream(mpc_ctx* ctx, int which);
 
 /* Caller-allocated device scratch, 256-byte aligned.  Contents are undefined
@@ -423,7 +423,7 @@ int mpc_ctx_set_relu_chunk(mpc_ctx* ctx, size_t whole_word_elems, size_t packed_
  * instead of the context's workspace.  The call performs no device or pinned
  * allocation and opens no timing region (mpc_ctx_profile never counts it).
  *   n <= mpc_relu_static_max_n() (65536), else MPC_ERANGE; the array takes
- *   about 14.4 MiB on every device the library runs on, until the process ends.
+ *   about 10.4 MiB on every device the library runs on, until the process ends.
  *   The context must come from mpc_ctx_create or mpc_ctx_create_single_queue
  *   (which resolve the array's device address for the context's device), else
  *   MPC_EINVAL.

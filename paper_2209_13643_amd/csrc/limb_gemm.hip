@@ -55,8 +55,8 @@ struct Divider {
 
 // What a launch passes to the kernel: everything of a party in one place, and the divisors of the tile order.  A
 // workgroup runs through its set-up alone, mostly as one chain of scalar instructions and loads, before it can ask for
-// its first tile; with divisions in the kernel and a party's operands picked field by field that was 625-860
-// instructions, as long as the matrix work of a 64-deep contraction; now 390-650 (per-head Q K^T 334 -> 330 us).
+// its first tile; with divisions in the kernel and a party's operands picked field by field that was 490 instructions
+// (convolutions 710-800), as long as the matrix work of a 64-deep contraction; now 370 (540-610) (per-head Q K^T 334 -> 330 us).
 struct GemmParty {
     GemmSeg seg[2];
     const u64 *addend, *addend2; u64* out;

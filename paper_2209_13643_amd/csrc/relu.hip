@@ -605,7 +605,7 @@ int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, c
     // four elements per thread additionally need n % 4 == 0 and 4-byte aligned byte arrays
     bool vec = (n % 2 == 0);
     for (int i = 0; i < 2 && vec; ++i) {
-        const void* ptrs[] = { pp[i].x, pp[i].r, nullptr, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].ra, pp[i].ma,
+        const void* ptrs[] = { pp[i].x, pp[i].r, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].ra, pp[i].ma,
                                pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_arith };
         for (const void* q : ptrs) if (q && ((uintptr_t)q & 15)) vec = false;
     }

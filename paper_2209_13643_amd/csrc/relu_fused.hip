@@ -8,8 +8,11 @@
 // material and the output, each once: 690 bytes per element of both parties instead of the 2498 that one launch per
 // round moves.  2 097 152 elements: 0.95 ms as ten launches, 0.323 ms here (4.5 TB/s of compulsory bytes).
 //
-// What bounds it is the vector memory path: a build that exchanges through LDS takes 0.25 ms (5.8 TB/s, what a large
-// copy reaches), the stores of the masked words cost 0.05 and their loads 0.035 ms of the difference.  The receive
+// What bounds it is the exchange through vector memory: a build that exchanges through LDS takes 0.25 ms (5.8 TB/s, more
+// than a large copy reaches).  Of the difference, 0.05 ms went with the stores of the masked words and 0.035 with their
+// loads; how much of that is their traffic and how much the order of the loads is not separated: vector loads return in
+// order, and a round asks for the next level's triples before it loads the received words, so it cannot end before those
+// triples have come from memory.  That is all of a small call: 16 411 elements, eleven rounds, take 27 us.  The receive
 // buffers have to stay in the L2: with a grid of 2048 workgroups and two buffers per party (33 MB) they were written
 // back to memory (0.64 GB per call) and the call took 0.345 ms; with one buffer and a second barrier per round, and 1024
 // workgroups, they are 8 MB, and four lanes converting at once still fit (batch-128 VGG16 on four lanes: 11.7 ms with
@@ -219,7 +222,7 @@ __global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused(FusedRelu q)
 // triple words and store the same masked words, so no lane ever moves data and element k of the lane finds its carry
 // in the lane's own word at the end.
 // 2 097 152 elements: 0.378 ms as ten launches, 0.141 ms here (256 compulsory bytes per element: 3.8 TB/s; what is
-// left is the vector memory path of the exchange, as for whole words).  Four elements per lane, whose loads touch every
+// left is the exchange through vector memory, as for whole words).  Four elements per lane, whose loads touch every
 // line twice: 0.144 ms; 1024 workgroups: 0.145 ms.
 __device__ __forceinline__ u64 from_lane_xor(u64 v, int mask)
 {
