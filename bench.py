@@ -717,6 +717,44 @@ def cpu_baseline_all_configs():
     return out
 
 
+def brief(out):
+    """The line that is printed without --full: the whole step's figures as measured, and of every other leg its main
+    numbers to five digits, so that the line stays a few thousand characters long."""
+    def short(v):
+        if isinstance(v, float):
+            return float(f"{v:.5g}")
+        if isinstance(v, dict):
+            return {k: short(w) for k, w in v.items()}
+        return [short(w) for w in v] if isinstance(v, list) else v
+
+    def pick(d, *keys):
+        return {k: d[k] for k in keys if k in d}
+
+    line = {k: v for k, v in out.items() if not isinstance(v, (dict, list))}
+    line["config"] = out["config"]
+    rest = {"pipeline": {m: pick(d, "serial_ms", "four_lanes_ms", "four_lanes_recorded_graphs_ms", "max_abs_err_logits")
+                         for m, d in out.get("pipeline", {}).items()}}
+    if "configs" in out:
+        rest["configs"] = [{"name": c["name"], **pick(c["folded_prepared_calls"], "ms_beaver_calls", "call_frac_of_int8_peak",
+                                                      "kernel_frac_of_int8_peak")} for c in out["configs"]]
+    if "config1_step" in out:
+        rest["config1_step"] = {k: v for k, v in out["config1_step"].items() if not isinstance(v, (dict, str))}
+    for name in ("roofline", "roofline_relu", "roofline_relu_msb"):
+        if name in out:
+            r = out[name]
+            rest[name] = {**pick(r, "bound", "achieved", "peak", "unit", "frac", "frac_executed_ops", "bytes_per_element", "ms_call"),
+                          "kernel": r["kernel"].split(" (")[0], "traffic": r["traffic"]}
+            if "kernel_only" in r:
+                rest[name]["kernel_only"] = pick(r["kernel_only"], "achieved", "frac", "ms")
+            if "copy_exchange" in r:
+                rest[name]["copy_exchange"] = pick(r["copy_exchange"], "ms_call", "frac", "traffic")
+    if "three_party" in out:
+        rest["three_party"] = pick(out["three_party"], "ms_beaver_conv_call", "ms_relu_call", "ms_relu_msb_call", "value", "relu_value", "max_abs_err_vs_float64")
+    if "cpu_baseline" in out:
+        rest["cpu_baseline"] = pick(out["cpu_baseline"], "value", "unit", "cores", "cpu", "kind", "relu_value", "images_per_s")
+    return {**line, **short(rest)}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -726,11 +764,12 @@ def main():
     ap.add_argument("--no-three-party", action="store_true", help="skip the three-party leg (configs[1], N = 3)")
     ap.add_argument("--no-per-config", action="store_true", help="skip the table of all five workloads (and the rooflines taken from it)")
     ap.add_argument("--no-other-modes", action="store_true", help="skip the pipeline legs beside the step's own mode")
-    ap.add_argument("--layers", action="store_true", help="per-layer rows inside `configs`")
+    ap.add_argument("--full", action="store_true", help="print every leg's whole record (the line is then some 25 000 characters long)")
+    ap.add_argument("--layers", action="store_true", help="per-layer rows inside `configs` (with --full)")
     ap.add_argument("--only-config1", action="store_true",
                     help="run only the configs[1] leg (conv block + ReLU) and print its rooflines: the command the rocprofv3 summaries are taken with")
     ap.add_argument("--cpu-all-configs", action="store_true",
-                    help="also time the oracle on a sample of every layer of all five workloads")
+                    help="also time the oracle on a sample of every layer of all five workloads (with --full)")
     ap.add_argument("--pmc-summary", default=os.path.join(ROOT, "profiles", "gemm_vgg_block_hbm_traffic.md"),
                     help="counter summary to quote as roofline.traffic (ignored unless taken from the current sources)")
     args = ap.parse_args()
@@ -765,7 +804,7 @@ def main():
         "config": {"workload": "configs[4] vgg16-cifar inter-batch pipeline: 32x32x3 input, 13 conv3x3 layers 64..512 channels with "
                                "2x2 max-pooling, FC 512-512-10, batch 128 = 4 micro-batches of 32 on four lanes; per layer Beaver "
                                "conv / matmul + truncation, whole-word secure ReLU, max-pool by two conversions",
-                   "parties": 2, "frac_bits": 16, "lanes": N_MB, "lane": "single in-order queue each", "relu_chunks": "auto: 2^20 elements on one lane, 2^20 / lanes = 2^18 on the four concurrent lanes (their share of the last-level cache)",
+                   "parties": 2, "frac_bits": 16, "lanes": N_MB, "lane": "single in-order queue each", "relu_chunks": "none: one launch per conversion",
                    "mode": legs["pipeline"]["step_mode"]["relu"] + "; exchange: " + legs["pipeline"]["step_mode"]["exchange"] + "; planes: " + legs["pipeline"]["step_mode"]["planes"],
                    "secure_macs_per_step": legs["macs"], "relu_elements_per_step": legs["relu_elements"],
                    "maxpool_comparisons_per_step": legs["pool_comparisons"], "images_per_s": N_MB * MICRO_BATCH / ms_step * 1e3,
@@ -789,7 +828,7 @@ def main():
         out["cpu_baseline"] = cpu_baseline()
         if args.cpu_all_configs:
             out["cpu_baseline"]["per_layer"] = cpu_baseline_all_configs()
-    print(json.dumps(out))
+    print(json.dumps(out if args.full else brief(out)))
 
 
 if __name__ == "__main__":
