@@ -21,9 +21,10 @@ __device__ __forceinline__ Pack<V> product(const Wire<NP>& wire, u64 m0, unsigne
 #pragma unroll
     for (int k = 0; k < V; ++k) { e.v[k] = x.v[k] - a.v[k]; f.v[k] = y.v[k] - b.v[k]; }
     wire.drained();
-    wire.put(slot, e); wire.put(slot + row, f);
+    wire.put(slot, e); wire.put(slot, f, row);
     wire.opened();
-    const Pack<V> re = wire.template summed<V>(slot), rf = wire.template summed<V>(slot + row);
+    const auto ge = wire.template received<V>(slot), gf = wire.template received<V>(slot, row);
+    const Pack<V> re = ge.summed(), rf = gf.summed();
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const u64 eo = e.v[k] + re.v[k], fo = f.v[k] + rf.v[k];

@@ -40,6 +40,30 @@ template <> struct ByteWord<4> { typedef uint32_t type __attribute__((aligned(1)
 template <int V> __device__ __forceinline__ unsigned ld_flags(const u8* p) { return *reinterpret_cast<const typename ByteWord<V>::type*>(p); }
 template <int V> __device__ __forceinline__ void st_flags(u8* p, unsigned w) { *reinterpret_cast<typename ByteWord<V>::type*>(p) = (typename ByteWord<V>::type)w; }
 
+// What a wave received from its peers, loaded but not yet combined (XOR shares / additive shares): a round's words are
+// asked for together before the first of them is used.
+template <int NP, int W> struct Received {
+    Pack<W> q[NP - 1];
+    __device__ __forceinline__ Pack<W> xored() const
+    {
+        Pack<W> r = q[0];
+        if constexpr (NP == 3) {
+#pragma unroll
+            for (int k = 0; k < W; ++k) r.v[k] ^= q[1].v[k];
+        }
+        return r;
+    }
+    __device__ __forceinline__ Pack<W> summed() const
+    {
+        Pack<W> r = q[0];
+        if constexpr (NP == 3) {
+#pragma unroll
+            for (int k = 0; k < W; ++k) r.v[k] += q[1].v[k];
+        }
+        return r;
+    }
+};
+
 // The receive buffers of a workgroup, one per ordered pair of parties: party i's buffer s holds what party
 // (i + 1 + s) mod NP sent last.  `box_words` words each.
 template <int NP>
@@ -56,32 +80,19 @@ struct Wire {
             out[s] = wg + ((size_t)to * (NP - 1) + s) * step;
         }
     }
-    template <int W> __device__ __forceinline__ void put_to(int s, unsigned off, const Pack<W>& w) const { w.st(reinterpret_cast<u64*>(out[s] + off), 0); }
-    template <int W> __device__ __forceinline__ void put(unsigned off, const Pack<W>& w) const
+    // off: the lane's place; row: a uniform distance, kept apart so that it goes to the scalar base
+    template <int W> __device__ __forceinline__ void put_to(int s, unsigned off, const Pack<W>& w, unsigned row = 0) const { w.st(reinterpret_cast<u64*>(out[s] + row + off), 0); }
+    template <int W> __device__ __forceinline__ void put(unsigned off, const Pack<W>& w, unsigned row = 0) const
     {
 #pragma unroll
-        for (int s = 0; s < NP - 1; ++s) put_to(s, off, w);
+        for (int s = 0; s < NP - 1; ++s) put_to(s, off, w, row);
     }
-    template <int W> __device__ __forceinline__ Pack<W> from(int s, unsigned off) const { return Pack<W>::ld(reinterpret_cast<const u64*>(in + s * step + off), 0); }
-    // what the peers sent, added up (XOR shares / additive shares)
-    template <int W> __device__ __forceinline__ Pack<W> xored(unsigned off) const
+    template <int W> __device__ __forceinline__ Pack<W> from(int s, unsigned off, unsigned row = 0) const { return Pack<W>::ld(reinterpret_cast<const u64*>(in + s * step + row + off), 0); }
+    template <int W> __device__ __forceinline__ Received<NP, W> received(unsigned off, unsigned row = 0) const
     {
-        Pack<W> r = from<W>(0, off);
-        if constexpr (NP == 3) {
-            const Pack<W> t = from<W>(1, off);
+        Received<NP, W> r;
 #pragma unroll
-            for (int k = 0; k < W; ++k) r.v[k] ^= t.v[k];
-        }
-        return r;
-    }
-    template <int W> __device__ __forceinline__ Pack<W> summed(unsigned off) const
-    {
-        Pack<W> r = from<W>(0, off);
-        if constexpr (NP == 3) {
-            const Pack<W> t = from<W>(1, off);
-#pragma unroll
-            for (int k = 0; k < W; ++k) r.v[k] += t.v[k];
-        }
+        for (int i = 0; i < NP - 1; ++i) r.q[i] = from<W>(i, off, row);
         return r;
     }
     template <int V> __device__ __forceinline__ void put_flags(unsigned off, unsigned w) const
