@@ -155,6 +155,10 @@ int mpc_graph_destroy(mpc_graph* graph);
  * operands of the Beaver products).
  * MPC_EXCHANGE_COPY (default): a copy kernel on the wire stream moves every
  *   party's send buffer into the other party's receive buffer after each round.
+ *   A two-party secure ReLU without tiles (n_chunks <= 1) of up to 2^18 elements
+ *   runs its rounds in one launch, the copies between them inside it, if the
+ *   workspace has room for the buffers and the outputs do not overlap inputs
+ *   (other than element for element).
  * MPC_EXCHANGE_PUT: the kernel that forms the masked words also stores them
  *   into the peer's receive buffer (what a peer-to-peer store would be between
  *   two devices).  Linear layers: the next step starts when that kernel has

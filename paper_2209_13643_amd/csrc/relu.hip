@@ -393,7 +393,7 @@ struct ReluWs {
     u8 *sendb[2], *recvb[2];
     u64 *G[2], *P[2]; u8* p63[2];
     u64 *sendL[2], *recvL[2], *gsel[2];     // packed levels only
-    u64* box;                               // all of it: the receive buffers of the one-launch chain
+    u64* box; size_t box_bytes;             // all of it: the buffers of the one-launch chain
     size_t bytes; bool ok;
 };
 
@@ -406,7 +406,7 @@ ReluWs carve_relu(u8* base, size_t cap, size_t n)
         r.sendb[i] = w.take<u8>(n); r.recvb[i] = w.take<u8>(n);
         r.G[i] = w.take<u64>(n); r.P[i] = w.take<u64>(n); r.p63[i] = w.take<u8>(n);
     }
-    r.box = reinterpret_cast<u64*>(base);
+    r.box = reinterpret_cast<u64*>(base); r.box_bytes = cap;
     const size_t box = relu_fused_box_bytes(2, n);
     r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
     return r;
@@ -423,7 +423,7 @@ ReluWs carve_relu_msb(u8* base, size_t cap, size_t n, const MsbGeom& g)
         r.sendL[i] = w.take<u64>(g.words_level_blocks); r.recvL[i] = w.take<u64>(g.words_level_blocks);
         r.gsel[i] = w.take<u64>(g.words_gsel);
     }
-    r.box = reinterpret_cast<u64*>(base);
+    r.box = reinterpret_cast<u64*>(base); r.box_bytes = cap;
     const size_t box = relu_fused_msb_box_bytes(2, n);
     r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
     return r;
@@ -575,24 +575,33 @@ PackedTriples packed_triples(const MsbGeom& g)
 // The protocol on n elements whose buffers are described by parties[2].  With
 // `geom` the carry chain runs on packed words (mpc_relu_msb), without it on
 // whole words.
-int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t n, int n_chunks, const MsbGeom* geom = nullptr)
+// box, box_bytes: scratch of the one-launch form.  It runs where the exchange is by remote store, and, its exchange made of
+// copies inside the launch (wire.h), where a call without tiles has up to 2^18 elements.  Twenty launches take 87 us whatever
+// they do: 8 192 elements 89 us a call, 65 536 90, 131 072 110, 262 144 165 (half of it still launches), and as one launch
+// 28, 27, 28 (all of it the host) and 50 us; sign-only 89-93 us, 28.  Beyond, the copies are most of the call, and
+// stay launches of their own, which the caller of MPC_EXCHANGE_COPY can tile and place on the wire stream.
+constexpr size_t kCopyInLaunchMaxN = (size_t)1 << 18;
+int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t box_bytes, size_t n, int n_chunks, const MsbGeom* geom = nullptr)
 {
     const bool in_order = one_queue(c);   // in-order queue: no events needed
-    if (remote_store(c)) {
+    const bool put = remote_store(c);
+    const size_t lane_elems = c->relu_chunk[geom ? 1 : 0];
+    const bool copies = !put && in_order && n_chunks <= 1 && n <= kCopyInLaunchMaxN && (n_chunks == 1 || !lane_elems || n <= lane_elems) &&
+                        (geom ? relu_fused_msb_box_bytes(2, n, true) : relu_fused_box_bytes(2, n, true)) <= box_bytes;
+    if (put || copies) {
         FusedRelu q{};
         for (int i = 0; i < 2; ++i)
             q.p[i] = FusedReluParty{ pp[i].x, pp[i].r, nullptr, pp[i].ta, pp[i].tb, pp[i].tc, pp[i].rb, pp[i].ra,
                                      pp[i].ma, pp[i].mb, pp[i].mc, pp[i].y, pp[i].s_bit, pp[i].s_arith };
         q.box = box; q.n = n;
         if (relu_outputs_apart(2, q, geom ? geom->words_triples : MPC_N_AND_TRIPLES * n)) {
-            if (!geom) return launch_relu_fused(c, c->s[0], 2, q, c->adder);
-            return launch_relu_fused_msb(c, c->s[0], 2, q, packed_triples(*geom));
+            if (!geom) return launch_relu_fused(c, c->s[0], 2, q, c->adder, copies);
+            return launch_relu_fused_msb(c, c->s[0], 2, q, packed_triples(*geom), copies);
         }
     }
     // chunk boundaries: multiples of four elements, and of 256 on the packed path
     // (four whole words of the deepest level)
     const size_t align = geom ? 256 : 4;
-    const size_t lane_elems = c->relu_chunk[geom ? 1 : 0];
     const size_t auto_elems = lane_elems ? lane_elems : geom ? kAutoChunkElemsPacked : kAutoChunkElems;
     if (n_chunks == 0)
         // automatic: about a million elements per chunk on a single queue (the chunk's
@@ -795,7 +804,7 @@ int relu_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat, mpc_share
     ReluParty pp[2];
     for (int i = 0; i < 2; ++i)
         fill_party(pp[i], i, x.p[i], mat, w, y.p[i], s_bit ? s_bit[i] : nullptr, s_arith ? s_arith[i] : nullptr, n);
-    MPC_TRY(relu_run(c, pp, w.box, n, n_chunks, packed ? &g : nullptr));
+    MPC_TRY(relu_run(c, pp, w.box, w.box_bytes, n, n_chunks, packed ? &g : nullptr));
     if (pi >= 0) {      // the region ends when both parties' last kernels are done
         MPC_TRY(chain(c, c->s[1], c->s[0]));
         prof_end(c, MPC_PROF_RELU, pi, c->s[0]);
@@ -865,7 +874,7 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
         fill_party(pp[i], i, d1[i], mat1, w1, r1[i], nullptr, s1 ? s1[i] : nullptr, 2 * n_out);
     }
     MPC_TRY(lane_join(c));
-    MPC_TRY(relu_run(c, pp, w1.box, 2 * n_out, n_chunks, packed ? &g1 : nullptr));
+    MPC_TRY(relu_run(c, pp, w1.box, w1.box_bytes, 2 * n_out, n_chunks, packed ? &g1 : nullptr));
     // second level: max of the two winners; out = v + ReLU(u - v)
     for (int i = 0; i < 2; ++i) {
         hipLaunchKernelGGL(k_pool_l2, grid, block, 0, c->s[i], x.p[i], r1[i], v[i], d2[i], B, H, W, C);
@@ -873,7 +882,7 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
         fill_party(pp[i], i, d2[i], mat2, w2, y.p[i], nullptr, s2 ? s2[i] : nullptr, n_out);
     }
     MPC_TRY(lane_join(c));
-    MPC_TRY(relu_run(c, pp, w2.box, n_out, n_chunks, packed ? &g2 : nullptr));
+    MPC_TRY(relu_run(c, pp, w2.box, w2.box_bytes, n_out, n_chunks, packed ? &g2 : nullptr));
     for (int i = 0; i < 2; ++i)
         MPC_TRY(launch_add(c, c->s[i], y.p[i], v[i], y.p[i], n_out));
     return n_chunks <= 1 ? nar.end() : MPC_OK;

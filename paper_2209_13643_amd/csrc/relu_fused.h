@@ -32,12 +32,13 @@ inline bool relu_outputs_apart(int parties, const FusedRelu& q, size_t triple_wo
     }
     return outputs_apart(out, in, true);
 }
-size_t relu_fused_box_bytes(int parties, size_t n);
-int launch_relu_fused(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, int topo);
+// copies (two parties): the exchange by copies inside the launch (wire.h) instead of by remote store
+size_t relu_fused_box_bytes(int parties, size_t n, bool copies = false);
+int launch_relu_fused(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, int topo, bool copies = false);
 // the sign-only chain; offsets of the triples in the packed buffers
 struct PackedTriples { size_t off[13]; size_t words[6]; };      // words[l]: packed words of level l
-size_t relu_fused_msb_box_bytes(int parties, size_t n);
-int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, const PackedTriples& g);
+size_t relu_fused_msb_box_bytes(int parties, size_t n, bool copies = false);
+int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, const PackedTriples& g, bool copies = false);
 // 2x2 max-pool of [B][H][W][C] (n_out = B * H/2 * W/2 * C outputs); material of the two conversions in m1 (2 n_out
 // elements) and m2 (n_out); x, y and the sign shares of FusedReluParty are not used; s1, s2 optional
 struct FusedPool {

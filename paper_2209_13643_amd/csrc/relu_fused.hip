@@ -53,8 +53,8 @@ template <int NP, int V, typename Row> __device__ __forceinline__ void load_firs
 // the words x_0, x_1; three: the carry-save sum of x_0, x_1, x_2 and its majority shifted up.  row: loads the
 // wave's words of an array; t1: offset of triple 1; whole: bytes between two rows of the receive buffers; masks0: loads
 // level 0's masks; masks1: level 1's masks and level 0's c.
-template <int NP, int V, typename Row, typename Masks0, typename Masks1>
-__device__ __forceinline__ Operands<V> a2b(const FusedReluParty& p, const Wire<NP>& wire, int party, u64 m0, const Pack<V>& x,
+template <int NP, int V, bool COPY, typename Row, typename Masks0, typename Masks1>
+__device__ __forceinline__ Operands<V> a2b(const FusedReluParty& p, const Wire<NP, COPY>& wire, int party, u64 m0, const Pack<V>& x,
                                            const Head<NP, V>& h, unsigned slot, unsigned whole, Row&& row, size_t t1,
                                            Masks0&& masks0, Masks1&& masks1)
 {
@@ -125,8 +125,8 @@ __device__ __forceinline__ Operands<V> a2b(const FusedReluParty& p, const Wire<N
 
 // B2A of the sign share and the select product.  masked: the share xor rb, one byte per element; y and the additive share
 // out.  after_flags, after_words: loads for the wave's next elements.
-template <int NP, int V, typename Row, typename AfterFlags, typename AfterWords>
-__device__ __forceinline__ void select(const FusedReluParty& p, const Wire<NP>& wire, u64 m0, unsigned lane, unsigned slot, unsigned whole,
+template <int NP, int V, bool COPY, typename Row, typename AfterFlags, typename AfterWords>
+__device__ __forceinline__ void select(const FusedReluParty& p, const Wire<NP, COPY>& wire, u64 m0, unsigned lane, unsigned slot, unsigned whole,
                                        unsigned masked, const Pack<V>& x, const Pack<V>& ra, const Pack<V>& ma, const Pack<V>& mb,
                                        Row&& row, AfterFlags&& after_flags, AfterWords&& after_words, Pack<V>& y, Pack<V>& sa)
 {
@@ -169,8 +169,8 @@ template <int W> struct LevelC { Pack<W> c1, c2; };
 // y = ReLU(x) on a wave's elements, whole-word adder.  row: loads the wave's words of an array of n; rb: its random
 // bits.  s: the sign bit shares (one byte per element), sa: the additive ones.
 template <int V> struct Converted { Pack<V> y, sa; unsigned s; };
-template <int NP, int V, int TOPO, typename Row, typename AfterFlags, typename AfterWords>
-__device__ __forceinline__ Converted<V> convert_words(const FusedReluParty& p, const Wire<NP>& wire, int party, unsigned lane, unsigned slot,
+template <int NP, int V, int TOPO, bool COPY, typename Row, typename AfterFlags, typename AfterWords>
+__device__ __forceinline__ Converted<V> convert_words(const FusedReluParty& p, const Wire<NP, COPY>& wire, int party, unsigned lane, unsigned slot,
                                                       size_t n, const Pack<V>& x, const Head<NP, V>& h, unsigned rb_at, const u8* rb_base,
                                                       Row&& row, AfterFlags&& after_flags, AfterWords&& after_words)
 {
@@ -256,15 +256,15 @@ __device__ __forceinline__ Converted<V> convert_words(const FusedReluParty& p, c
 }
 
 // Registers: 128, so that a wave fits beside the GEMM's on a SIMD; the operands of three rounds of three parties need 156
-// (held at 128 they are spilled; 512 workgroups are less than two waves per SIMD either way).
-template <int NP, int V, int TOPO>
-__global__ __launch_bounds__(NP * kWave, NP == 3 && V == 2 ? 3 : 4) void k_relu_fused(FusedRelu q)
+// (held at 128 they are spilled; 512 workgroups are less than two waves per SIMD either way), those of the copying exchange 135.
+template <int NP, int V, int TOPO, bool COPY>
+__global__ __launch_bounds__(NP * kWave, (NP == 3 || COPY) && V == 2 ? 3 : 4) void k_relu_fused(FusedRelu q)
 {
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int lane = threadIdx.x % kWave;
     const FusedReluParty& p = q.p[party];
     const size_t n = q.n;
-    const Wire<NP> wire(q.box, party, (size_t)kRows * kWave * V);
+    const Wire<NP, COPY> wire(q.box, party, (size_t)kRows * kWave * V);
     unsigned slot = lane * V * 8u;
 
     // a tile's elements for the wave: base + off .. ; a ragged last tile takes the last 64 V elements and stores its own only
@@ -325,8 +325,8 @@ constexpr int level_words(int V, int L) { return (2 << L) <= V ? V >> (L + 1) : 
 
 // y = ReLU(x) on a wave's elements from `base` (a multiple of 64 V) on; lane's elements at lane V.  RAGGED: the tile may
 // reach past the packed words of the call's elements (word indices are clamped then).
-template <int NP, int V, bool RAGGED, typename Row, typename AfterFlags, typename AfterWords>
-__device__ __forceinline__ Converted<V> convert_packed(const FusedReluParty& p, const PackedTriples& g, const Wire<NP>& wire, int party,
+template <int NP, int V, bool RAGGED, bool COPY, typename Row, typename AfterFlags, typename AfterWords>
+__device__ __forceinline__ Converted<V> convert_packed(const FusedReluParty& p, const PackedTriples& g, const Wire<NP, COPY>& wire, int party,
                                                        unsigned lane, size_t base, const Pack<V>& x, const Head<NP, V>& h,
                                                        unsigned rb_at, const u8* rb_base, Row&& row,
                                                        AfterFlags&& after_flags, AfterWords&& after_words)
@@ -423,8 +423,8 @@ __device__ __forceinline__ Converted<V> convert_packed(const FusedReluParty& p, 
 
 // The workgroup's tiles of 64 V elements: tile blockIdx.x and every gridDim.x-th after it from `tile` to below `end`;
 // tile t starts at element at0 + (t - tile0) 64 V.  Returns the workgroup's first tile from `end` on.
-template <int NP, int V>
-__device__ __forceinline__ unsigned msb_tiles(const FusedReluParty& p, const PackedTriples& g, const Wire<NP>& wire, int party,
+template <int NP, int V, bool COPY>
+__device__ __forceinline__ unsigned msb_tiles(const FusedReluParty& p, const PackedTriples& g, const Wire<NP, COPY>& wire, int party,
                                               unsigned tile, unsigned tile0, unsigned end, size_t at0, size_t n)
 {
     if (tile >= end) return tile;
@@ -465,11 +465,11 @@ __device__ __forceinline__ unsigned msb_tiles(const FusedReluParty& p, const Pac
 // tiles 0 .. wide-1: 128 elements each, two per lane; the others 64 elements, one per lane (the last one ragged)
 constexpr int kMsbV = 2;
 constexpr size_t kMsbBox = 2 * kWave * kMsbV;      // words: two rows of whole words, or four of level 0
-template <int NP>
+template <int NP, bool COPY>
 __global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused_msb(FusedRelu q, PackedTriples g, unsigned wide)
 {
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const Wire<NP> wire(q.box, party, kMsbBox);
+    const Wire<NP, COPY> wire(q.box, party, kMsbBox);
     const unsigned tile = msb_tiles<NP, kMsbV>(q.p[party], g, wire, party, blockIdx.x, 0, wide, 0, q.n);
     msb_tiles<NP, 1>(q.p[party], g, wire, party, tile, wide, q.tiles, (size_t)wide * kMsbV * kWave, q.n);
 }
@@ -568,49 +568,51 @@ unsigned msb_tiles(size_t n, unsigned blocks)
 }
 unsigned least(unsigned a, unsigned b) { return a < b ? a : b; }
 
-template <int NP, int V>
+template <int NP, int V, bool COPY>
 void launch(hipStream_t st, const FusedRelu& q, int topo)
 {
     const dim3 grid(least(q.tiles, kBlocks[NP - 2])), block(NP * kWave);
     if constexpr (NP == 2)
-        if (topo) { hipLaunchKernelGGL((k_relu_fused<NP, V, 1>), grid, block, 0, st, q); return; }
-    hipLaunchKernelGGL((k_relu_fused<NP, V, 0>), grid, block, 0, st, q);
+        if (topo) { hipLaunchKernelGGL((k_relu_fused<NP, V, 1, COPY>), grid, block, 0, st, q); return; }
+    hipLaunchKernelGGL((k_relu_fused<NP, V, 0, COPY>), grid, block, 0, st, q);
 }
 
 }  // namespace
 
-size_t relu_fused_box_bytes(int parties, size_t n)
+size_t relu_fused_box_bytes(int parties, size_t n, bool copies)
 {
     const unsigned blocks = kBlocks[parties - 2];
     const int v = width(n, blocks);
-    return (size_t)least(tiles_of(n, v), blocks) * kMaxBlockPairs[parties - 2] * (kRows * kWave * v) * sizeof(u64);
+    return (size_t)least(tiles_of(n, v), blocks) * kMaxBlockPairs[parties - 2] * (copies ? 2 : 1) * (kRows * kWave * v) * sizeof(u64);
 }
 
-int launch_relu_fused(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, int topo)
+int launch_relu_fused(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, int topo, bool copies)
 {
-    if (q.n == 0 || q.n >= ((size_t)1 << 37)) return MPC_EINVAL;
+    if (q.n == 0 || q.n >= ((size_t)1 << 37) || (copies && parties != 2)) return MPC_EINVAL;
     const int v = width(q.n, kBlocks[parties - 2]);
     q.tiles = tiles_of(q.n, v);
-    if (parties == 2) { if (v == 2) launch<2, 2>(st, q, topo); else launch<2, 1>(st, q, topo); }
-    else              { if (v == 2) launch<3, 2>(st, q, 0);    else launch<3, 1>(st, q, 0); }
+    if (copies)            { if (v == 2) launch<2, 2, true>(st, q, topo);  else launch<2, 1, true>(st, q, topo); }
+    else if (parties == 2) { if (v == 2) launch<2, 2, false>(st, q, topo); else launch<2, 1, false>(st, q, topo); }
+    else                   { if (v == 2) launch<3, 2, false>(st, q, 0);    else launch<3, 1, false>(st, q, 0); }
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }
 
-size_t relu_fused_msb_box_bytes(int parties, size_t n)
+size_t relu_fused_msb_box_bytes(int parties, size_t n, bool copies)
 {
     const unsigned blocks = kMsbBlocks[parties - 2];
-    return (size_t)least(msb_tiles(n, blocks), blocks) * kMaxBlockPairs[parties - 2] * kMsbBox * sizeof(u64);
+    return (size_t)least(msb_tiles(n, blocks), blocks) * kMaxBlockPairs[parties - 2] * (copies ? 2 : 1) * kMsbBox * sizeof(u64);
 }
 
-int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, const PackedTriples& g)
+int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, const PackedTriples& g, bool copies)
 {
-    if (q.n == 0 || q.n >= ((size_t)1 << 37)) return MPC_EINVAL;
+    if (q.n == 0 || q.n >= ((size_t)1 << 37) || (copies && parties != 2)) return MPC_EINVAL;
     const unsigned blocks = kMsbBlocks[parties - 2], wide = wide_tiles(q.n, blocks);
     q.tiles = msb_tiles(q.n, blocks);
     const dim3 grid(least(q.tiles, blocks));
-    if (parties == 2) hipLaunchKernelGGL(k_relu_fused_msb<2>, grid, dim3(2 * kWave), 0, st, q, g, wide);
-    else              hipLaunchKernelGGL(k_relu_fused_msb<3>, grid, dim3(3 * kWave), 0, st, q, g, wide);
+    if (copies)            hipLaunchKernelGGL((k_relu_fused_msb<2, true>), grid, dim3(2 * kWave), 0, st, q, g, wide);
+    else if (parties == 2) hipLaunchKernelGGL((k_relu_fused_msb<2, false>), grid, dim3(2 * kWave), 0, st, q, g, wide);
+    else                   hipLaunchKernelGGL((k_relu_fused_msb<3, false>), grid, dim3(3 * kWave), 0, st, q, g, wide);
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }

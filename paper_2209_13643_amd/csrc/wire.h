@@ -66,14 +66,19 @@ template <int NP, int W> struct Received {
 
 // The receive buffers of a workgroup, one per ordered pair of parties: party i's buffer s holds what party
 // (i + 1 + s) mod NP sent last.  `box_words` words each.
-template <int NP>
+// COPY (two parties): a party stores its words into a send buffer of its own, and after the barrier the peer's wave moves
+// them into its receive buffer, using each word as it passes; two buffers per party.
+template <int NP, bool COPY = false>
 struct Wire {
+    static_assert(!COPY || NP == 2, "the copying exchange is written for two parties");
     u8* in; u8* out[NP - 1]; size_t step;
+    u8* peer;                                 // COPY: the peer's send buffer
     __device__ __forceinline__ Wire(u64* box, int party, size_t box_words)
     {
         step = box_words * 8;
-        u8* const wg = reinterpret_cast<u8*>(box) + (size_t)blockIdx.x * (NP * (NP - 1)) * step;
+        u8* const wg = reinterpret_cast<u8*>(box) + (size_t)blockIdx.x * (NP * (NP - 1) * (COPY ? 2 : 1)) * step;
         in = wg + (size_t)party * (NP - 1) * step;
+        if constexpr (COPY) { out[0] = wg + (size_t)(2 + party) * step; peer = wg + (size_t)(3 - party) * step; return; }
 #pragma unroll
         for (int s = 0; s < NP - 1; ++s) {
             int to = party + NP - 1 - s; if (to >= NP) to -= NP;             // the party whose buffer s is filled from here
@@ -87,7 +92,14 @@ struct Wire {
 #pragma unroll
         for (int s = 0; s < NP - 1; ++s) put_to(s, off, w, row);
     }
-    template <int W> __device__ __forceinline__ Pack<W> from(int s, unsigned off, unsigned row = 0) const { return Pack<W>::ld(reinterpret_cast<const u64*>(in + s * step + row + off), 0); }
+    template <int W> __device__ __forceinline__ Pack<W> from(int s, unsigned off, unsigned row = 0) const
+    {
+        if constexpr (COPY) {
+            const Pack<W> w = Pack<W>::ld(reinterpret_cast<const u64*>(peer + row + off), 0);
+            w.st(reinterpret_cast<u64*>(in + row + off), 0);
+            return w;
+        } else return Pack<W>::ld(reinterpret_cast<const u64*>(in + s * step + row + off), 0);
+    }
     template <int W> __device__ __forceinline__ Received<NP, W> received(unsigned off, unsigned row = 0) const
     {
         Received<NP, W> r;
@@ -102,7 +114,8 @@ struct Wire {
     }
     template <int V> __device__ __forceinline__ unsigned flags(unsigned off) const
     {
-        unsigned w = ld_flags<V>(in + off);
+        unsigned w = ld_flags<V>((COPY ? peer : in) + off);
+        if constexpr (COPY) st_flags<V>(in + off, w);
         if constexpr (NP == 3) w ^= ld_flags<V>(in + step + off);
         return w;
     }

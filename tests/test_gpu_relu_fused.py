@@ -118,3 +118,43 @@ def test_one_launch_maxpool(mpc, lane, shape, parties, chain):
     equal(mpc, y, want, "output")
     equal(mpc, g1, s1, "first level's sign shares")
     equal(mpc, g2, s2, "second level's sign shares")
+
+
+@pytest.mark.parametrize("chain", ["kogge-stone", "tree", "packed"])
+@pytest.mark.parametrize("queues", ["one", "three"])
+@pytest.mark.parametrize("n", [1, 33, 63, 64, 65, 65536, 65537, 131072 + 129, 262144, 262145])
+def test_copies_inside_the_launch(mpc, n, queues, chain):
+    """Exchange by copies, the default: up to 2^18 elements the rounds and their copies are one launch, beyond it (and where
+    the queried workspace has no room for the buffers, n = 1) launches of their own.  On a workspace of exactly the queried
+    size between guard areas."""
+    from ctypes import c_void_p
+    import torch
+    print(f"copying relu n={n} {queues} {chain}", flush=True)
+    rng = np.random.default_rng(n)
+    xs = synth.share_additive(rng, synth.normal_fixed(rng, n, 4.0))
+    mat = synth.deal_relu_material(rng, n)
+    want = oracle.relu(xs, mat, adder="tree" if chain == "tree" else "kogge-stone")
+    packed = chain == "packed"
+    ln = mpc.Lane(0, single_queue=queues == "one")
+    ln.set_adder("tree" if chain == "tree" else "kogge-stone")
+    md = mpc.material_to_device(mat)
+    if packed:
+        md = ln.pack_material(md)
+    nbytes = (mpc.lib().mpc_relu_msb_workspace_bytes if packed else mpc.lib().mpc_relu_workspace_bytes)(n)
+    guard = 4096
+    buf = torch.full((nbytes + 2 * guard + 256,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    at = guard + (-(buf.data_ptr() + guard)) % 256
+    ln.sync()
+    torch.cuda.synchronize()
+    ln._check(mpc.lib().mpc_ctx_set_workspace(ln._h, c_void_p(buf.data_ptr() + at), nbytes))
+    ln._ws, ln._ws_bytes = buf, nbytes
+    x = dev(mpc, xs)
+    torch.cuda.synchronize()
+    y, sb, sa = ln.relu(x, md, want_sign=True, packed=packed, out=x if n % 2 else None)
+    ln.sync()
+    equal(mpc, y, want.y, "output")
+    equal(mpc, sb, want.s_bit, "sign bit share")
+    equal(mpc, sa, want.s_arith, "sign arithmetic share")
+    b = buf.cpu().numpy()
+    assert (b[:at] == 0xA5).all() and (b[at + nbytes:] == 0xA5).all(), "written outside the workspace"
+    ln.close()
