@@ -2,6 +2,7 @@
 // and the recoding of ring words into balanced base-256 digit planes.
 // All of them are HBM-bound; they use 16-byte accesses and grid-stride loops.
 #include "common.h"
+#include "digits.h"
 #include "recode_tiles.h"
 
 #include <algorithm>
@@ -75,31 +76,6 @@ __global__ __launch_bounds__(kThreads) void k_truncate(u64* __restrict__ z, size
     }
 }
 
-// Balanced base-256 digits of x: x = sum_j d_j 2^(8j) (mod 2^64), d_j in
-// [-128, 127].  Adding 0x80 to every byte position (with carries) and flipping
-// the top bit of every byte yields the eight digits as two's-complement bytes.
-__device__ __forceinline__ u64 balanced_digits(u64 x)
-{
-    const u64 h = 0x8080808080808080ull;
-    return (x + h) ^ h;
-}
-
-// The digits of four words, digit by digit: out[d] holds digit d of w[0..3] in bytes 0..3.
-__device__ __forceinline__ void digits_of_4(const u64 (&w)[4], uint32_t (&out)[8])
-{
-    uint32_t h[2][4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) { const u64 d = balanced_digits(w[t]); h[0][t] = (uint32_t)d; h[1][t] = (uint32_t)(d >> 32); }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        // a 4 x 4 byte transpose in eight byte permutes
-        const uint32_t x0 = __builtin_amdgcn_perm(h[q][1], h[q][0], 0x05010400), y0 = __builtin_amdgcn_perm(h[q][3], h[q][2], 0x05010400);
-        const uint32_t x1 = __builtin_amdgcn_perm(h[q][1], h[q][0], 0x07030602), y1 = __builtin_amdgcn_perm(h[q][3], h[q][2], 0x07030602);
-        out[4 * q + 0] = __builtin_amdgcn_perm(y0, x0, 0x05040100); out[4 * q + 1] = __builtin_amdgcn_perm(y0, x0, 0x07060302);
-        out[4 * q + 2] = __builtin_amdgcn_perm(y1, x1, 0x05040100); out[4 * q + 3] = __builtin_amdgcn_perm(y1, x1, 0x07060302);
-    }
-}
-
 // 16 consecutive k of one row to the eight planes of one k block
 __device__ __forceinline__ void store_unit(const u64 (&v)[16], u8* out, long long digit_stride)
 {
@@ -155,10 +131,6 @@ __device__ __forceinline__ void recode_body(const RecodeArgs& a, int tap /* == n
             load(sub, w);
 #pragma unroll
             for (int t = 0; t < 16; ++t) v[t] -= w[t];
-            if (side) {
-#pragma unroll
-                for (int t = 0; t < 16; ++t) if (t < have) side[base + (long long)t * a.k_stride] = v[t];
-            }
         } else if (minuend) {
             load(minuend, w);
 #pragma unroll
@@ -214,11 +186,10 @@ __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, uns
     const int kc = beyond ? 0 : k;
     // The loads of two segments in one straight line per way of access and kind of sum.  With the way chosen anew for
     // every operand the ways joined in between, and the next operand's loads waited for the joined registers; with the
-    // threads past the last k on the word-wise way, every wave of a tile that K leaves ragged ran both.  Masked sum of
-    // 4096 x 768 words 28.3 -> 24.5 us, of 32 x 56 x 56 x 64 52.0 -> 45.6, of 1000 x 2000 15.4 -> 13.7; plain sums level
-    // (ragged K: 300 x 4000 8.3 -> 7.1).  All four segments at once or one at a time: 24.8, 25.4 us.
-    enum { kAny, kSum, kMaskedSum };
-    const bool masked_sum = sub && side && src2 && !src3, sum = !sub && !minuend && src2 && !src3;      // uniform
+    // threads past the last k on the word-wise way, every wave of a tile that K leaves ragged ran both: 300 x 4000 words
+    // 8.3 -> 7.1 us.
+    enum { kAny, kSum };
+    const bool sum = !sub && !minuend && src2 && !src3;      // uniform
 #pragma unroll
     for (int p0 = 0; p0 < 4; p0 += 2) {
         auto row_of = [&](int p) { return row0 + (int)(threadIdx.x >> 4) + 16 * (p0 + p); };
@@ -261,21 +232,15 @@ __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, uns
 #pragma unroll
                     for (int u = 0; u < 4; ++u) x[p][u] = minus ? x[p][u] - w[p][u] : x[p][u] + w[p][u];
             };
-            u64 w[2][4], w2[2][4];
+            u64 w[2][4];
             load(src, v);
-            if constexpr (kind == kMaskedSum) {
-                load(sub, w); load(src2, w2);
-                fold(v, w, true);
-                store(side, v);
-                fold(v, w2, false);
-            } else if constexpr (kind == kSum) {
+            if constexpr (kind == kSum) {
                 load(src2, w);
                 fold(v, w, false);
             } else {
                 if (sub) {
                     load(sub, w);
                     fold(v, w, true);
-                    if (side) store(side, v);
                 } else if (minuend) {
                     load(minuend, w);
                     fold(w, v, true);
@@ -286,7 +251,6 @@ __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, uns
             }
         };
         if (!whole)          gather(std::false_type{}, std::integral_constant<int, kAny>{});
-        else if (masked_sum) gather(std::true_type{}, std::integral_constant<int, kMaskedSum>{});
         else if (sum)        gather(std::true_type{}, std::integral_constant<int, kSum>{});
         else                 gather(std::true_type{}, std::integral_constant<int, kAny>{});
 #pragma unroll

@@ -2,6 +2,7 @@
 // of Alg. 3: host-side orchestration of mask kernels, wire copies, digit
 // recoding and the limb GEMM on the lane's three streams.
 #include "common.h"
+#include "open_recode.h"
 
 namespace {
 
@@ -169,6 +170,18 @@ RecodeArgs recode_right(const LinearShape& s, const u64* src, const u64* src2, c
     return a;
 }
 
+// An operand laid out as `a` describes, as shares v and masks m, to the planes dst0 (v_0 + the word received) and dst1 (opened).
+OpenSet open_set(const RecodeArgs& a, mpc_cshare v, mpc_cshare m, u8* dst0, u8* dst1)
+{
+    OpenSet o{};
+    for (int i = 0; i < 2; ++i) { o.x[i] = v.p[i]; o.a[i] = m.p[i]; }
+    o.dst[0] = dst0; o.dst[1] = dst1;
+    o.row_stride = a.row_stride; o.k_stride = a.k_stride; o.src_batch_stride = a.src_batch_stride;
+    o.digit_stride = a.digit_stride; o.dst_batch_stride = a.dst_batch_stride;
+    o.rows = a.rows; o.plane_rows = a.plane_rows; o.K = a.K; o.KB_total = a.KB_total; o.batch = a.batch;
+    return o;
+}
+
 void fill_geom(const LinearShape& s, const LinearWs& w, GemmArgs& g)
 {
     g.M = s.M; g.N = s.N; g.batch = s.batch;
@@ -266,31 +279,15 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
         GemmArgs g{};
         fill_geom(s, w, g);
         g.nparty = 2;
-        if (folded && put && !s.im2colT) {
-            // Folded call with the exchange by remote store: three passes over the activation, each word touched once.
-            //   party 0 masks and sends:           e_0 = x_0 - a_0                  -> party 1's receive buffer
-            //   party 1 masks, sends and recodes:  e_1 = x_1 - a_1 -> party 0's receive buffer; planes of e = e_1 + e_0
-            //   party 0 recodes:                   planes of a_0 + e = x_0 + e_1
-            // (party 1's word leaves after party 0's has arrived: on a network the two directions of this exchange
-            // would follow each other; with the copy exchange they stay simultaneous.)
-            // A product of two activations opens f the same way, in the same three launches:
-            //   f_0 = y_0 - b_0 -> party 1;  f_1 = y_1 - b_1 -> party 0 and planes of f;  planes of b_0 + f = y_0 + f_1.
-            SubSeg sub0[2] = { SubSeg{ x.p[0], a.p[0], w.re[1], s.nx, 0, nullptr },
-                               SubSeg{ y.p[0], b.p[0], w.rf[1], s.nw, 0, nullptr } };
-            MPC_TRY(launch_sub_multi(c, P0, sub0, right_online ? 2 : 1));
-            RecodeArgs r1[2] = { recode_left(s, x.p[1], w.re[1], w.pl_e), RecodeArgs{} };
-            r1[0].sub = a.p[1]; r1[0].side = w.re[0];
-            RecodeArgs r0[2] = { recode_left(s, x.p[0], w.re[0], w.pl_a[0]), RecodeArgs{} };
-            if (right_online) {
-                r1[1] = recode_right(s, y.p[1], w.rf[1], nullptr, w.pr_f);
-                r1[1].sub = b.p[1]; r1[1].side = w.rf[0];
-                r0[1] = recode_right(s, y.p[0], w.rf[0], nullptr, w.pr_b[0]);
-                MPC_TRY(launch_recode_any(c, P0, r1, 2));
-                MPC_TRY(launch_recode_any(c, P0, r0, 2));
-            } else {
-                MPC_TRY(launch_recode(c, P0, r1[0]));
-                MPC_TRY(launch_recode(c, P0, r0[0]));
-            }
+        // receive buffers of the one-launch opening: the parts of the workspace ahead of the planes
+        const size_t box_bytes = (size_t)(w.pl_e - reinterpret_cast<u8*>(w.se[0]));
+        if (folded && put && !s.im2colT && box_bytes >= kOpenBoxBytes) {
+            // Folded call with the exchange by remote store, in one launch (open_recode.hip): both parties mask and send
+            // e_i = x_i - a_i, then party 0 recodes a_0 + e = x_0 + e_1 and party 1 the opened e.  A product of two
+            // activations opens f in the same launch: f_i = y_i - b_i, b_0 + f = y_0 + f_1, f.
+            OpenSet open[2] = { open_set(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_a[0], w.pl_e), OpenSet{} };
+            if (right_online) open[1] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_b[0], w.pr_f);
+            MPC_TRY(launch_open_recode(c, P0, open, right_online ? 2 : 1, reinterpret_cast<u8*>(w.se[0]), box_bytes));
             g.nseg = 2;
             g.seg[0][0] = make_seg(s, w.pl_a[0], w.pr_b[0]); g.seg[0][1] = GemmSeg{};
             g.seg[1][0] = make_seg(s, w.pl_e, w.pr_b[1]);    g.seg[1][1] = make_seg(s, w.pl_a[1], w.pr_f);
