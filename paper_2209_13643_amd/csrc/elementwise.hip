@@ -106,9 +106,6 @@ __device__ __forceinline__ void recode_body(const RecodeArgs& a, int tap /* == n
     const u64* src = a.src + at;
     const u64* src2 = a.src2 ? a.src2 + at : nullptr;
     const u64* src3 = a.src3 ? a.src3 + at : nullptr;
-    const u64* sub = a.sub ? a.sub + at : nullptr;
-    u64* side = a.side ? a.side + at : nullptr;
-    const u64* minuend = (a.minuend && a.side && !a.sub) ? a.minuend + at : nullptr;
     u8* dst = a.dst + (size_t)b * a.dst_batch_stride;
     const int kb_count = padtap ? a.KB_total - a.ntaps * a.KB_tap : a.KB_tap;
     const size_t items = (size_t)kb_count * a.plane_rows;
@@ -127,15 +124,6 @@ __device__ __forceinline__ void recode_body(const RecodeArgs& a, int tap /* == n
         };
         u64 v[16], w[16];
         load(src, v);
-        if (sub) {
-            load(sub, w);
-#pragma unroll
-            for (int t = 0; t < 16; ++t) v[t] -= w[t];
-        } else if (minuend) {
-            load(minuend, w);
-#pragma unroll
-            for (int t = 0; t < 16; ++t) if (t < have) side[base + (long long)t * a.k_stride] = w[t] - v[t];
-        }
         if (src2) {
             load(src2, w);
 #pragma unroll
@@ -172,13 +160,9 @@ __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, uns
     const u64* src = a.src + at;
     const u64* src2 = a.src2 ? a.src2 + at : nullptr;
     const u64* src3 = a.src3 ? a.src3 + at : nullptr;
-    const u64* sub = a.sub ? a.sub + at : nullptr;
-    u64* side = a.side ? a.side + at : nullptr;
-    const u64* minuend = (a.minuend && a.side && !a.sub) ? a.minuend + at : nullptr;
     u8* dst = a.dst + (size_t)b * a.dst_batch_stride;
     const int k_lim = padtap ? 0 : a.K;
-    const bool vec = (a.row_stride % 2 == 0) && (((uintptr_t)src | (uintptr_t)src2 | (uintptr_t)src3 | (uintptr_t)sub |
-                                                  (uintptr_t)side | (uintptr_t)minuend) & 15) == 0;
+    const bool vec = (a.row_stride % 2 == 0) && (((uintptr_t)src | (uintptr_t)src2 | (uintptr_t)src3) & 15) == 0;
     // thread's segments: 4 words each, segment p at row (threadIdx.x + 256 p) / 16 of the tile
     const int s4 = threadIdx.x & 15, k = kb0 * 16 + s4 * 4;
     // 16-byte accesses allowed; threads past the last k read column 0 with the others instead of a way of their own
@@ -188,15 +172,12 @@ __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, uns
     // every operand the ways joined in between, and the next operand's loads waited for the joined registers; with the
     // threads past the last k on the word-wise way, every wave of a tile that K leaves ragged ran both: 300 x 4000 words
     // 8.3 -> 7.1 us.
-    enum { kAny, kSum };
-    const bool sum = !sub && !minuend && src2 && !src3;      // uniform
 #pragma unroll
     for (int p0 = 0; p0 < 4; p0 += 2) {
         auto row_of = [&](int p) { return row0 + (int)(threadIdx.x >> 4) + 16 * (p0 + p); };
         u64 v[2][4];
-        auto gather = [&](auto whole_tag, auto kind_tag) {
-            constexpr bool W = decltype(whole_tag)::value;
-            constexpr int kind = decltype(kind_tag)::value;
+        auto gather = [&](auto whole_tag, auto sum_tag) {
+            constexpr bool W = decltype(whole_tag)::value, sum = decltype(sum_tag)::value;       // sum: src and src2 alone
             auto load = [&](const u64* q, u64 (&w)[2][4]) {
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
@@ -211,48 +192,24 @@ __device__ __forceinline__ void recode_rows_body(const RecodeArgs& a, int b, uns
                     }
                 }
             };
-            auto store = [&](u64* q, const u64 (&w)[2][4]) {
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const int r = row_of(p);
-                    if (beyond || r >= a.rows) continue;
-                    u64* o = q + (size_t)r * a.row_stride + k;
-                    if constexpr (W) {
-                        u64x2 lo, hi; lo.a = w[p][0]; lo.b = w[p][1]; hi.a = w[p][2]; hi.b = w[p][3];
-                        reinterpret_cast<u64x2*>(o)[0] = lo; reinterpret_cast<u64x2*>(o)[1] = hi;
-                    } else {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) if (k + u < k_lim) o[u] = w[p][u];
-                    }
-                }
-            };
-            auto fold = [&](u64 (&x)[2][4], const u64 (&w)[2][4], bool minus) {
+            auto add = [&](const u64* q) {
+                u64 w[2][4];
+                load(q, w);
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) x[p][u] = minus ? x[p][u] - w[p][u] : x[p][u] + w[p][u];
+                    for (int u = 0; u < 4; ++u) v[p][u] += w[p][u];
             };
-            u64 w[2][4];
             load(src, v);
-            if constexpr (kind == kSum) {
-                load(src2, w);
-                fold(v, w, false);
-            } else {
-                if (sub) {
-                    load(sub, w);
-                    fold(v, w, true);
-                } else if (minuend) {
-                    load(minuend, w);
-                    fold(w, v, true);
-                    store(side, w);
-                }
-                if (src2) { load(src2, w); fold(v, w, false); }
-                if (src3) { load(src3, w); fold(v, w, false); }
+            if constexpr (sum) add(src2);
+            else {
+                if (src2) add(src2);
+                if (src3) add(src3);
             }
         };
-        if (!whole)          gather(std::false_type{}, std::integral_constant<int, kAny>{});
-        else if (sum)        gather(std::true_type{}, std::integral_constant<int, kSum>{});
-        else                 gather(std::true_type{}, std::integral_constant<int, kAny>{});
+        if (!whole)             gather(std::false_type{}, std::false_type{});
+        else if (src2 && !src3) gather(std::true_type{}, std::true_type{});
+        else                    gather(std::true_type{}, std::false_type{});
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             const bool row_ok = row_of(p) < a.rows;

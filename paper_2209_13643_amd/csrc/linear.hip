@@ -170,15 +170,16 @@ RecodeArgs recode_right(const LinearShape& s, const u64* src, const u64* src2, c
     return a;
 }
 
-// An operand laid out as `a` describes, as shares v and masks m, to the planes dst0 (v_0 + the word received) and dst1 (opened).
-OpenSet open_set(const RecodeArgs& a, mpc_cshare v, mpc_cshare m, u8* dst0, u8* dst1)
+// An operand laid out as `r` describes, as shares v and masks m, to be opened in one launch: planes dst0 (folded: v_0 + the
+// word received; plain: the opened words) and dst1 (folded: the opened words), plain calls also those of the masks.
+OpenSet open_set(const RecodeArgs& r, mpc_cshare v, mpc_cshare m, u8* dst0, u8* dst1, u8* mask0 = nullptr, u8* mask1 = nullptr, bool add_open = false)
 {
     OpenSet o{};
     for (int i = 0; i < 2; ++i) { o.x[i] = v.p[i]; o.a[i] = m.p[i]; }
-    o.dst[0] = dst0; o.dst[1] = dst1;
-    o.row_stride = a.row_stride; o.k_stride = a.k_stride; o.src_batch_stride = a.src_batch_stride;
-    o.digit_stride = a.digit_stride; o.dst_batch_stride = a.dst_batch_stride;
-    o.rows = a.rows; o.plane_rows = a.plane_rows; o.K = a.K; o.KB_total = a.KB_total; o.batch = a.batch;
+    o.dst[0] = dst0; o.dst[1] = dst1; o.mask_dst[0] = mask0; o.mask_dst[1] = mask1; o.add_open = add_open;
+    o.row_stride = r.row_stride; o.k_stride = r.k_stride; o.src_batch_stride = r.src_batch_stride; o.tap_stride = r.tap_stride;
+    o.digit_stride = r.digit_stride; o.dst_batch_stride = r.dst_batch_stride;
+    o.rows = r.rows; o.plane_rows = r.plane_rows; o.K = r.K; o.KB_tap = r.KB_tap; o.ntaps = r.ntaps; o.KB_total = r.KB_total; o.batch = r.batch;
     return o;
 }
 
@@ -287,7 +288,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             // activations opens f in the same launch: f_i = y_i - b_i, b_0 + f = y_0 + f_1, f.
             OpenSet open[2] = { open_set(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_a[0], w.pl_e), OpenSet{} };
             if (right_online) open[1] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_b[0], w.pr_f);
-            MPC_TRY(launch_open_recode(c, P0, open, right_online ? 2 : 1, reinterpret_cast<u8*>(w.se[0]), box_bytes));
+            MPC_TRY(launch_open_recode(c, P0, open, right_online ? 2 : 1, false, reinterpret_cast<u8*>(w.se[0]), box_bytes));
             g.nseg = 2;
             g.seg[0][0] = make_seg(s, w.pl_a[0], w.pr_b[0]); g.seg[0][1] = GemmSeg{};
             g.seg[1][0] = make_seg(s, w.pl_e, w.pr_b[1]);    g.seg[1][1] = make_seg(s, w.pl_a[1], w.pr_f);
@@ -297,53 +298,28 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             prof_end(c, MPC_PROF_LINEAR, pi, P0);
             return nar.end();
         }
-        if (put && !folded && !skip_left && !x_public && !s.im2colT && !(two_phase && have_f)) {
-            // Plain call with the exchange by remote store: the pass that recodes the triple's [a_i] forms the masked
-            // shares on the way (e_i = x_i - a_i, stored into the peer's receive buffer), and the opened e is recoded
-            // from party 0's own shares and the word it received: every activation word is read once per use.
-            if (!have_f) {
-                SubSeg sub[2];
-                for (int i = 0; i < 2; ++i) sub[i] = SubSeg{ y.p[i], b.p[i], w.sf[i], s.nw, 0, w.rf[1 - i] };
-                MPC_TRY(launch_sub_multi(c, P0, sub, 2));
-            }
-            RecodeArgs k1[3]; int n1 = 0;
-            for (int i = 0; i < 2; ++i) {
-                k1[n1] = recode_left(s, a.p[i], nullptr, w.pl_a[i]);
-                k1[n1].minuend = x.p[i]; k1[n1].side = w.re[1 - i];
-                ++n1;
-            }
-            if (!skip_right) k1[n1++] = recode_right(s, b.p[1], nullptr, nullptr, w.pr_b[1]);
-            MPC_TRY(launch_recode_any(c, P0, k1, n1));
-            RecodeArgs k2[3]; int n2 = 0;
-            k2[n2] = recode_left(s, x.p[0], w.re[0], w.pl_e);
-            k2[n2].sub = a.p[0];
-            ++n2;
-            if (!skip_right) {
-                const u64* f0 = f_public ? f_public : w.sf[0];
-                const u64* f1 = f_public ? nullptr : w.rf[0];
-                k2[n2++] = recode_right(s, f0, f1, nullptr, w.pr_f);
-                k2[n2++] = recode_right(s, b.p[0], f0, f1, w.pr_b[0]);
-            }
-            MPC_TRY(launch_recode_any(c, P0, k2, n2));
-            g.nseg = 2;
-            for (int i = 0; i < 2; ++i) {
-                g.seg[i][0] = make_seg(s, w.pl_e, w.pr_b[i]);
-                g.seg[i][1] = make_seg(s, w.pl_a[i], w.pr_f);
-                g.addend[i] = cc.p[i]; g.addend2[i] = nullptr; g.out[i] = z.p[i];
-            }
-            g.trunc_bits = trunc;
-            MPC_TRY(launch_limb_gemm(c, P0, g));
-            prof_end(c, MPC_PROF_LINEAR, pi, P0);
-            return nar.end();
+        // Plain calls with the exchange by remote store open what they open in one launch, planes of the masks with it.
+        // (A filter read in reverse tap order, or operands of less than half a tile, take the steps below.)
+        const bool one_launch = put && !folded && box_bytes >= kOpenBoxBytes && !(two_phase && have_f);
+        OpenSet opens[2]; int n_open = 0;
+        bool left_done = false, right_done = false;
+        if (one_launch && !skip_left && !x_public && !s.im2colT) {
+            opens[n_open++] = open_set(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_e, nullptr, w.pl_a[0], w.pl_a[1]);
+            left_done = true;
         }
+        if (one_launch && !have_f && !s.wflip) {
+            opens[n_open++] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_f, nullptr, w.pr_b[0], w.pr_b[1], true);
+            right_done = true;
+        }
+        if (n_open) MPC_TRY(launch_open_recode(c, P0, opens, n_open, true, reinterpret_cast<u8*>(w.se[0]), box_bytes));
         if ((size_t)n_chunks > s.nx) n_chunks = (int)s.nx;
-        bool f_pending = !have_f;                            // the weight mask rides with the first launch issued
+        bool f_pending = !have_f && !right_done;             // the weight mask rides with the first launch issued
         for (int ch = 0; ch < n_chunks; ++ch) {
             size_t lo = (s.nx * ch / n_chunks) & ~(size_t)1, hi = (s.nx * (ch + 1) / n_chunks) & ~(size_t)1;
             if (ch == n_chunks - 1) hi = s.nx;
             const bool last = ch == n_chunks - 1;
             SubSeg sub[4]; CopySeg cp[4]; int ns = 0;
-            for (int i = 0; i < 2 && !x_public && hi > lo; ++i) {
+            for (int i = 0; i < 2 && !x_public && !left_done && hi > lo; ++i) {
                 sub[ns] = SubSeg{ x.p[i] + lo, a.p[i] + lo, w.se[i] + lo, hi - lo, 0,
                                   put ? w.re[1 - i] + lo : nullptr };
                 cp[ns] = CopySeg{ (const u8*)(w.se[i] + lo), (u8*)(w.re[1 - i] + lo), (hi - lo) * sizeof(u64), 0 };
@@ -375,13 +351,13 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
         }
         // all digit planes of the call in one launch (the transposed-im2col recoder is a kernel of its own)
         int nr = 0;
-        const int l0 = folded ? 1 : skip_left ? 2 : 0;
+        const int l0 = left_done ? 3 : folded ? 1 : skip_left ? 2 : 0;
         if (s.im2colT) {
             MPC_TRY(launch_left(c, P0, s, 3 - l0, lsrc + l0, lsrc2 + l0, ldst + l0));
         } else {
             for (int i = l0; i < 3; ++i) rr[nr++] = recode_left(s, lsrc[i], lsrc2[i], ldst[i]);
         }
-        if (!skip_right) {
+        if (!skip_right && !right_done) {
             if (!right_online) rr[nr++] = recode_right(s, b.p[1], nullptr, nullptr, w.pr_b[1]);
             rr[nr++] = recode_right(s, f0, f1, nullptr, w.pr_f);
             rr[nr++] = recode_right(s, b.p[0], f0, f1, w.pr_b[0]);

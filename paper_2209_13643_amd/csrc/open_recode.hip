@@ -1,11 +1,13 @@
-// Masking, exchange by remote store and recoding of a linear layer's opened operands in one launch (folded calls on a
-// single queue).  A workgroup is two waves per party on the same words: every wave masks its share (e_i = x_i - a_i),
+// Masking, exchange by remote store and recoding of a linear layer's opened operands in one launch (single-queue lanes).
+// A workgroup is two waves per party on the same words: every wave masks its share (e_i = x_i - a_i),
 // stores it into the peer's receive buffer in device memory, and after the workgroup barrier recodes what its party
 // contracts: party 0 its own share plus the received word (a_0 + e = x_0 + e_1), party 1 the opened e.  Bound by memory:
 // every share and mask is read once and every plane written once, six traversals of the operand, and the receive buffers
 // stay in the L2.  As three launches (mask and send, open and recode, recode) there were eleven; 32 x 56 x 56 x 64
 // words took 104 us in all, here 77 (4.0 TB/s).  Calls, same box, three launches / one: per-head Q K^T 342 / 305 us, A V 636 / 465,
 // 1x1 convolution of 64 to 256 channels 362 / 334, 3x3 of 128 channels 233 / 222, 8 products of 64 x 64 x 64 27.4 / 19.0.
+// Plain calls write the planes of the masks from the same pass, seven traversals instead of twelve (left) and seventeen
+// (right operand): VGG16 training step of 32 images 7.61 / 7.51 ms.
 // Non-temporal loads lose (3x3: 235 us): the operand was often written just before and is in the last-level cache.
 #include "open_recode.h"
 #include "digits.h"
@@ -26,8 +28,8 @@ constexpr int block_pitch(int KBT) { return tile_rows(KBT) * 4 + 64 / KBT; }
 constexpr int kTileWords = 8 * (512 + 64);
 int tile_blocks(int KB_total) { return KB_total > 2 ? 4 : KB_total; }
 // Workgroups resident at once: three to a compute unit (167 registers; held at 128 for a fourth they are spilled, and the
-// 3x3 convolution takes 228 us).  Each has 8 KB of receive buffer per party.  512 / 768 / 1024 workgroups: level within 1-2 %.
-constexpr unsigned kMaxBlocks = 768;
+// 3x3 convolution takes 228 us), two in plain calls (228).  Each has 8 KB of receive buffer per party.  512 / 768 / 1024 workgroups: level within 1-2 %.
+constexpr unsigned kMaxBlocks = 768, kMaxPlainBlocks = 512;
 static_assert(kOpenBoxBytes == 2 * kPartyThreads * 8 * sizeof(u64), "a party exchanges eight words per thread at a time");
 
 struct OpenBatch { OpenSet s[kMaxOpenSets]; int count; unsigned tiles; u8* box; };
@@ -58,12 +60,11 @@ struct Exchange {
 
 // Contiguous k: lanes along k read the tile, digits go to LDS in plane order, planes are written with lanes along rows.
 // H = 1: tiles of which at most half the rows are there (few-row products), half the loads and one exchange.
-template <int KBT, int H>
+template <bool PLAIN, int KBT, int H>
 __device__ __forceinline__ void open_rows(const OpenSet& s, const Exchange& ex, int party, int t, int b, int row0, int kb0, uint32_t* tile)
 {
     const u64* x = s.x[party] + (long long)b * s.src_batch_stride;
     const u64* a = s.a[party] + (long long)b * s.src_batch_stride;
-    u8* dst = s.dst[party] + (size_t)b * s.dst_batch_stride;
     // thread's segments: 4 words each, segment p at row t / lanes + step p of the tile
     constexpr int lanes = 4 * KBT, step = kPartyThreads / lanes, pitch = block_pitch(KBT);
     const int s4 = t % lanes, k = kb0 * 16 + s4 * 4;
@@ -88,6 +89,24 @@ __device__ __forceinline__ void open_rows(const OpenSet& s, const Exchange& ex, 
     };
     if (whole) { load(std::true_type{}, x, v); load(std::true_type{}, a, m); }
     else       { load(std::false_type{}, x, v); load(std::false_type{}, a, m); }
+    auto scatter = [&](int p, const u64 (&w)[4]) {
+        const int r = t / lanes + step * p;
+        const bool row_ok = row0 + r < s.rows;
+        u64 four[4]; uint32_t d[8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) four[u] = row_ok && k + u < s.K ? w[u] : 0;
+        digits_of_4(four, d);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) tile[(q * KBT + (s4 >> 2)) * pitch + r * 4 + (s4 & 3)] = d[q];
+    };
+    auto store = [&](u8* dst) {
+        const int kbl = t / tile_rows(KBT), row = t % tile_rows(KBT);
+        if (!dst || row0 + row >= s.plane_rows || kb0 + kbl >= s.KB_total) return;
+        u8* const o = dst + (size_t)b * s.dst_batch_stride + ((size_t)(kb0 + kbl) * s.plane_rows + row0 + row) * 16;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            *reinterpret_cast<uint4*>(o + (size_t)q * s.digit_stride) = *reinterpret_cast<const uint4*>(&tile[(q * KBT + kbl) * pitch + row * 4]);
+    };
 #pragma unroll
     for (int h = 0; h < H; ++h) {
         u64 e[8], got[8];
@@ -96,41 +115,57 @@ __device__ __forceinline__ void open_rows(const OpenSet& s, const Exchange& ex, 
         ex.swap(e, got);
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            const int r = t / lanes + step * (2 * h + p);
-            const bool row_ok = row0 + r < s.rows;
-            u64 four[4]; uint32_t d[8];
+            u64 four[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                four[u] = row_ok && k + u < s.K ? (party == 0 ? v[2 * h + p][u] : e[4 * p + u]) + got[4 * p + u] : 0;
-            digits_of_4(four, d);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) tile[(q * KBT + (s4 >> 2)) * pitch + r * 4 + (s4 & 3)] = d[q];
+            for (int u = 0; u < 4; ++u) {
+                four[u] = (!PLAIN && party == 0 ? v[2 * h + p][u] : e[4 * p + u]) + got[4 * p + u];
+                if (PLAIN && party == 0 && s.add_open) m[2 * h + p][u] += four[u];
+            }
+            scatter(2 * h + p, four);
         }
     }
     __syncthreads();
-    const int kbl = t / tile_rows(KBT), row = t % tile_rows(KBT);
-    if (row0 + row < s.plane_rows && kb0 + kbl < s.KB_total) {
-        u8* const o = dst + ((size_t)(kb0 + kbl) * s.plane_rows + row0 + row) * 16;
+    store(s.dst[party]);
+    if constexpr (PLAIN) {
+        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            *reinterpret_cast<uint4*>(o + (size_t)q * s.digit_stride) = *reinterpret_cast<const uint4*>(&tile[(q * KBT + kbl) * pitch + row * 4]);
+        for (int p = 0; p < 2 * H; ++p) scatter(p, m[p]);
+        __syncthreads();
+        store(s.mask_dst[party]);
     }
 }
 
-// Contiguous rows (an operand stored [K][N]): a thread takes one (row, k block), lanes along rows.
+// Contiguous rows (an operand stored [K][N], a filter): a thread takes one (row, k block of a tap), lanes along rows.
+template <bool PLAIN>
 __device__ __forceinline__ void open_columns(const OpenSet& s, const Exchange& ex, int party, int t, int b, unsigned bx, unsigned kb)
 {
-    const int row = (int)bx * kPartyThreads + t, k0 = (int)kb * 16;
-    const int have = row < s.rows ? (s.K - k0 < 16 ? (s.K - k0 > 0 ? s.K - k0 : 0) : 16) : 0;      // valid words of the unit
-    const long long at = (long long)b * s.src_batch_stride + (long long)(row < s.rows ? row : 0) * s.row_stride +
-                         (long long)(k0 < s.K ? k0 : 0) * s.k_stride;
+    const int tap = s.ntaps == 1 ? 0 : (int)kb / s.KB_tap;             // == ntaps: padding behind the last tap
+    const int row = (int)bx * kPartyThreads + t, k0 = ((int)kb - tap * s.KB_tap) * 16;
+    const bool there = row < s.rows && tap < s.ntaps && k0 < s.K;
+    const int have = there ? (s.K - k0 < 16 ? s.K - k0 : 16) : 0;      // valid words of the unit
+    const long long at = (long long)b * s.src_batch_stride + (there ? tap * s.tap_stride + row * s.row_stride + k0 * s.k_stride : 0);
     const u64 *x = s.x[party] + at, *a = s.a[party] + at;
     u64 v[16], m[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) v[u] = x[(long long)(u < have ? u : 0) * s.k_stride];
 #pragma unroll
     for (int u = 0; u < 16; ++u) m[u] = a[(long long)(u < have ? u : 0) * s.k_stride];
-    uint32_t w[8][4];
+    auto store = [&](u8* dst, const u64 (&w)[16]) {
+        if (!dst || row >= s.plane_rows) return;
+        uint32_t unit[8][4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            u64 four[4]; uint32_t d[8];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) four[u] = 4 * p + u < have ? w[4 * p + u] : 0;
+            digits_of_4(four, d);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) unit[q][p] = d[q];
+        }
+        u8* const o = dst + (size_t)b * s.dst_batch_stride + ((size_t)kb * s.plane_rows + row) * 16;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) *reinterpret_cast<uint4*>(o + (size_t)q * s.digit_stride) = make_uint4(unit[q][0], unit[q][1], unit[q][2], unit[q][3]);
+    };
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         u64 e[8], got[8];
@@ -138,26 +173,17 @@ __device__ __forceinline__ void open_columns(const OpenSet& s, const Exchange& e
         for (int q = 0; q < 8; ++q) e[q] = v[8 * h + q] - m[8 * h + q];
         ex.swap(e, got);
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            u64 four[4]; uint32_t d[8];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = 4 * p + u;
-                four[u] = 8 * h + q < have ? (party == 0 ? v[8 * h + q] : e[q]) + got[q] : 0;
-            }
-            digits_of_4(four, d);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) w[q][2 * h + p] = d[q];
+        for (int q = 0; q < 8; ++q) {
+            v[8 * h + q] = (!PLAIN && party == 0 ? v[8 * h + q] : e[q]) + got[q];
+            if (PLAIN && party == 0 && s.add_open) m[8 * h + q] += v[8 * h + q];
         }
     }
-    if (row < s.plane_rows) {
-        u8* const o = s.dst[party] + (size_t)b * s.dst_batch_stride + ((size_t)kb * s.plane_rows + row) * 16;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) *reinterpret_cast<uint4*>(o + (size_t)q * s.digit_stride) = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
-    }
+    store(s.dst[party], v);
+    if constexpr (PLAIN) store(s.mask_dst[party], m);
 }
 
-__global__ __launch_bounds__(kThreads, 3) void k_open_recode(OpenBatch g)
+template <bool PLAIN>
+__global__ __launch_bounds__(kThreads, PLAIN ? 2 : 3) void k_open_recode(OpenBatch g)
 {
     __shared__ __align__(16) uint32_t lds[2][kTileWords];
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kPartyThreads));
@@ -168,18 +194,18 @@ __global__ __launch_bounds__(kThreads, 3) void k_open_recode(OpenBatch g)
         unsigned q = id - s.first;
         const unsigned bx = q % s.gx; q /= s.gx;
         const unsigned by = q % s.gy; const int b = (int)(q / s.gy);
-        if (!s.kbt) { open_columns(s, ex, party, t, b, bx, by); continue; }
+        if (!s.kbt) { open_columns<PLAIN>(s, ex, party, t, b, bx, by); continue; }
         const int row0 = (int)bx * tile_rows(s.kbt), kb0 = (int)by * s.kbt;
-        if (s.kbt == 1)                    open_rows<1, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
-        else if (s.kbt == 2)               open_rows<2, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
-        else if (s.plane_rows - row0 > 16) open_rows<4, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
-        else                               open_rows<4, 1>(s, ex, party, t, b, row0, kb0, lds[party]);
+        if (s.kbt == 1)                    open_rows<PLAIN, 1, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
+        else if (s.kbt == 2)               open_rows<PLAIN, 2, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
+        else if (s.plane_rows - row0 > 16) open_rows<PLAIN, 4, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
+        else                               open_rows<PLAIN, 4, 1>(s, ex, party, t, b, row0, kb0, lds[party]);
     }
 }
 
 }  // namespace
 
-int launch_open_recode(mpc_ctx* c, hipStream_t st, const OpenSet* sets, int count, u8* box, size_t box_bytes)
+int launch_open_recode(mpc_ctx* c, hipStream_t st, const OpenSet* sets, int count, bool plain, u8* box, size_t box_bytes)
 {
     if (count < 1 || count > kMaxOpenSets || !box || box_bytes < kOpenBoxBytes) return MPC_EINVAL;
     OpenBatch g{};
@@ -188,8 +214,8 @@ int launch_open_recode(mpc_ctx* c, hipStream_t st, const OpenSet* sets, int coun
         OpenSet& s = g.s[i];
         s = sets[i];
         if (s.rows < 1 || s.K < 1 || s.batch < 1 || s.plane_rows < s.rows || (long long)s.KB_total * 16 < s.K) return MPC_EINVAL;
-        if (s.k_stride != 1 && s.row_stride != 1) return MPC_EINVAL;
-        s.kbt = s.k_stride == 1 ? tile_blocks(s.KB_total) : 0;
+        if (!can_open(s) || s.ntaps < 1 || s.KB_tap < 1) return MPC_EINVAL;
+        s.kbt = s.k_stride == 1 && s.ntaps == 1 ? tile_blocks(s.KB_total) : 0;
         const int high = s.kbt ? tile_rows(s.kbt) : kPartyThreads, wide = s.kbt ? s.kbt : 1;
         s.gx = (unsigned)((s.plane_rows + high - 1) / high);
         s.gy = (unsigned)((s.KB_total + wide - 1) / wide);
@@ -200,10 +226,11 @@ int launch_open_recode(mpc_ctx* c, hipStream_t st, const OpenSet* sets, int coun
     g.count = count; g.tiles = (unsigned)tiles; g.box = box;
     // as many workgroups as have buffers, all of them with the same number of tiles (but for the last few)
     unsigned long long blocks = box_bytes / kOpenBoxBytes;
-    if (blocks > kMaxBlocks) blocks = kMaxBlocks;
+    if (blocks > (plain ? kMaxPlainBlocks : kMaxBlocks)) blocks = plain ? kMaxPlainBlocks : kMaxBlocks;
     const unsigned long long rounds = (tiles + blocks - 1) / blocks;
     blocks = (tiles + rounds - 1) / rounds;
-    hipLaunchKernelGGL(k_open_recode, dim3((unsigned)blocks), dim3(kThreads), 0, st, g);
+    if (plain) hipLaunchKernelGGL(k_open_recode<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, g);
+    else       hipLaunchKernelGGL(k_open_recode<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, g);
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }

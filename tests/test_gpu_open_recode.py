@@ -1,5 +1,5 @@
-"""The one launch that masks, exchanges and recodes the opened operands of a folded call (single-queue lanes, exchange by
-remote store) against the oracle bit for bit: its tiles are 128 rows x 16 k, 64 x 32 and 32 x 64 by the width of the operand,
+"""The one launch that masks, exchanges and recodes the opened operands of a call (single-queue lanes, exchange by remote
+store), folded or plain, against the oracle bit for bit: its tiles are 128 rows x 16 k, 64 x 32 and 32 x 64 by the width of the operand,
 128 rows x 16 k for operands stored [K][N]; few rows, ragged edges, the zero row of a convolution's planes at the start of a
 tile of its own, several tiles per workgroup, words at odd addresses."""
 import numpy as np
@@ -55,7 +55,7 @@ def same(mpc, lane, got, want, what):
     (2, 2000, 30, None), (20, 70, 24, 5), (3, 200, 129, 4), (24640, 64, 1, None), (5, 7, 1500, 3),
 ])
 def test_products(mpc, lane, M, K, N, batch):
-    """Both operands opened by the call, and the left one alone."""
+    """Both operands opened by the call, and the left one alone; folded, and plain with the masks' planes."""
     print(f"one-launch opening {M}x{K}x{N} batch {batch}", flush=True)
     d = deal_matmul(np.random.default_rng(M * 1000003 + K * 1009 + N), M, K, N, batch=batch)
     want = oracle_matmul(d)
@@ -68,6 +68,9 @@ def test_products(mpc, lane, M, K, N, batch):
     right, left = lane.prepare_matmul(a, b, lane.open(lane.sub(y, b)))
     z = lane.beaver_matmul_prepared(x, a, cf, right, left, flags=mpc.MPC_TRUNCATE | mpc.MPC_FOLDED)
     same(mpc, lane, z, want, "left operand")
+    same(mpc, lane, lane.beaver_matmul(x, y, a, b, c), want, "plain")
+    z = lane.beaver_matmul(x, None, a, b, c, f_public=lane.open(lane.sub(y, b)))
+    same(mpc, lane, z, want, "plain, weight mask opened ahead")
 
 
 @pytest.mark.parametrize("trans", ["x", "y", "both"])
@@ -85,6 +88,8 @@ def test_transposed_operands(mpc, lane, trans):
     cf = (lane.fold_matmul(a, b, c, flags=flags), c[1])
     z = lane.beaver_matmul_folded(x, y, a, b, cf, right, left, flags=flags | mpc.MPC_TRUNCATE)
     same(mpc, lane, z, oracle_matmul(d), f"transposed {trans}")
+    z = lane.beaver_matmul(x, y, a, b, c, flags=flags | mpc.MPC_TRUNCATE)
+    same(mpc, lane, z, oracle_matmul(d), f"transposed {trans}, plain")
 
 
 @pytest.mark.parametrize("B,H,W,Cin,Cout,k", [
@@ -98,3 +103,4 @@ def test_convolutions(mpc, lane, B, H, W, Cin, Cout, k):
     cf = (lane.fold_conv2d(a, b, c, k // 2, 1), c[1])
     z = lane.conv2d_prepared(x, a, cf, right, left, k, k, k // 2, 1, flags=mpc.MPC_TRUNCATE | mpc.MPC_FOLDED)
     same(mpc, lane, z, oracle_conv(d, 16), "conv")
+    same(mpc, lane, lane.conv2d(x, w, a, b, c, k // 2, 1), oracle_conv(d, 16), "conv, plain")      # opens the filter too
