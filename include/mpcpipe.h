@@ -249,8 +249,9 @@ int mpc_conv2d(mpc_ctx* ctx, mpc_cshare x, mpc_cshare w,
  * compute unit: short contractions spend most of a workgroup's life in pipeline fill and epilogue, which a second
  * resident wave per SIMD hides.  Launches whose parties contract different lengths (the folded calls) also take
  * that tile at any contraction length once the output has 768 such tiles.  Outputs of at most 32 rows take it only where
- * they have at most 64 columns, else a tile of 32 x 128.  max_steps = 0 switches the small tile off.  MPC_EINVAL for max_steps < 0 or
- * min_tiles < 1. */
+ * they have at most 64 columns, else a tile of 32 x 128.  Contractions of at most 64 K steps with at most 1024 tiles of
+ * 32 x 32 (both parties) run with the waves of a workgroup sharing one such tile's contraction.  max_steps = 0 switches
+ * that and the small tile off.  MPC_EINVAL for max_steps < 0 or min_tiles < 1. */
 int mpc_set_gemm_small_tile(int max_steps, int min_tiles);
 
 /* Measurement aid for the roofline of the ring GEMM (no step of the protocol): the int8 matrix-core rate the

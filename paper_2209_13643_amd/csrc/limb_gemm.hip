@@ -517,6 +517,160 @@ __global__ __launch_bounds__(64 * WGM * WGN, NH == 1 ? 2 : 1) void k_limb_gemm(G
 template <bool CONV>
 __global__ __launch_bounds__(256, 2) void k_few_rows_gemm(GemmDev g) { gemm_tile<1, 4, CONV, 3, 1>(g); }
 
+// ---- products with few output tiles --------------------------------------------------
+// Recombination sum_s acc_s 2^(8s) mod 2^64 of one word's eight digit sums, read out of the accumulator registers.
+template <int V>
+__device__ __forceinline__ u64 recombine(const v16i (&acc)[8])
+{
+    int d[8];
+    asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
+                 "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
+                 : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]), "=&v"(d[7])
+                 : "a"(acc[0][V]), "a"(acc[1][V]), "a"(acc[2][V]), "a"(acc[3][V]),
+                   "a"(acc[4][V]), "a"(acc[5][V]), "a"(acc[6][V]), "a"(acc[7][V]));
+    u64 acc64 = (u64)(long long)d[0];
+#pragma unroll
+    for (int sg = 1; sg < 4; ++sg)
+        acc64 += (u64)((unsigned)d[sg] << (8 * sg)) | ((u64)(unsigned)(d[sg] >> (32 - 8 * sg)) << 32);
+    const unsigned high = (unsigned)d[4] + ((unsigned)d[5] << 8) + ((unsigned)d[6] << 16) + ((unsigned)d[7] << 24);
+    return acc64 + ((u64)high << 32);
+}
+
+// (Chosen by sliced_waves below, with what it measured.)
+// A workgroup has one 32 x 32 output tile, and its KW waves share the contraction: each contracts a slice of the K steps
+// with operands loaded straight into registers (the planes' layout is that of the matrix operands; nothing is shared
+// between the waves, so nothing goes through LDS), then the 64-bit partial words are added up in LDS and finished there:
+// one launch, no partial products in memory.
+//
+// The MFMAs run in nested angles: level l holds the digit pairs (l, j) and (i, l) with i, j >= l.  With level l the
+// operand digits l and 7 - l have had their last use, and are refilled for the next step at once; the next step asks for
+// them in the same order, 11 to 21 MFMAs later (twice that with the SIMD's second wave), which covers an L2 access.
+template <bool CONV, int KW>
+__global__ __launch_bounds__(64 * KW, 2) void k_sliced_gemm(GemmDev g)
+{
+    __shared__ u64 part[KW][16][64];
+    const int lane = threadIdx.x & 63, i32 = lane & 31, g2 = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned id = blockIdx.x;
+    const int party = g.nparty == 2 && id < g.heavy_blocks ? 1 : 0;        // party 1's workgroups, the longer ones, come first
+    const unsigned q = (party ? id : id - g.heavy_blocks) >> 3;
+    const GemmParty& P = g.p[party];
+    const unsigned tile = (id & 7) * (unsigned)P.per_xcd + q;
+    if (q >= (unsigned)P.per_xcd || tile >= (unsigned)P.tiles) return;
+    const unsigned item = g.by_item(tile), rem = tile - item * g.per_item;
+    const unsigned mt = g.by_panel(rem), nt = rem - mt * g.panel_tiles;
+    const int m0 = (int)mt * 32, n0 = (int)nt * 32;
+    const int T0 = P.seg[0].KB / KS, T = T0 + (g.nseg > 1 ? P.seg[1].KB / KS : 0);
+    const int per = (T + KW - 1) / KW, first = wave * per, last = first + per < T ? first + per : T;      // this wave's steps
+
+    // the workgroup's words: thread t has words t and t + 64 KW (of 1024), in the accumulators' order
+    constexpr int WPT = 16 / KW;
+    size_t at[WPT]; bool ok[WPT]; u64 add[WPT];
+#pragma unroll
+    for (int k = 0; k < WPT; ++k) {
+        const int v = wave + KW * k, row = m0 + (v >> 2) * 8 + g2 * 4 + (v & 3), col = n0 + i32;
+        ok[k] = row < g.M && col < g.N;
+        at[k] = (size_t)item * g.out_bstride + (size_t)(row < g.M ? row : g.M - 1) * g.N + (col < g.N ? col : g.N - 1);
+        add[k] = (P.addend ? P.addend[at[k]] : 0) + (P.addend2 ? P.addend2[at[k]] : 0);
+    }
+
+    v16i acc[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[s][v] = 0;
+    if (first < last) {
+        const int rowL = m0 + i32 < g.M ? m0 + i32 : g.M - 1, rowR = n0 + i32 < g.N ? n0 + i32 : g.N - 1;
+        const unsigned krowL = (unsigned)g.rows_L * 16u, krowR = (unsigned)g.N * 16u;
+        // convolution: image position of filter tap (0, 0)
+        int hi0 = 0, wi0 = 0, pix0 = 0;
+        if (CONV) {
+            const int t = (int)g.by_Wo((unsigned)rowL), wo = rowL - t * g.conv.Wo;
+            const int b = (int)g.by_Ho((unsigned)t), ho = t - b * g.conv.Ho;
+            hi0 = ho * g.conv.stride - g.conv.pad; wi0 = wo * g.conv.stride - g.conv.pad;
+            pix0 = (b * g.conv.H + hi0) * g.conv.W + wi0;
+        }
+        // cursor: the next step to load.  Lanes 0..31 read its first k block, lanes 32..63 its second.
+        int seg = first >= T0 ? 1 : 0;
+        int left = seg ? T - first : T0 - first;              // steps of the segment from the cursor on
+        const u8 *baseL, *baseR; long long dsL, dsR;
+        unsigned voffL, voffR;
+        int cb = 0, kh = 0, kw = 0;
+        auto enter = [&](int kb) {          // k block kb of the segment (uniform) under the cursor
+            const GemmSeg& sg = P.seg[seg];
+            baseL = sg.L + (size_t)item * sg.L_bstride; baseR = sg.R + (size_t)item * sg.R_bstride;
+            dsL = sg.L_dstride; dsR = sg.R_dstride;
+            const int k = kb + g2;
+            voffR = (unsigned)k * krowR + (unsigned)rowR * 16u;
+            if (CONV) { const int tap = k / g.conv.CB; cb = k - tap * g.conv.CB; kh = tap / g.conv.KW; kw = tap - kh * g.conv.KW; }
+            else voffL = (unsigned)k * krowL + (unsigned)rowL * 16u;
+        };
+        auto gather = [&]() {               // convolution: the lane's unit of the left planes; taps outside the image read the zero row
+            if (!CONV) return;
+            const int hi = hi0 + kh, wi = wi0 + kw;
+            const bool in = kh < g.conv.KH && hi >= 0 && hi < g.conv.H && wi >= 0 && wi < g.conv.W;
+            const int pix = in ? pix0 + kh * g.conv.W + kw : (int)g.conv.npix;
+            voffL = ((unsigned)cb * (unsigned)(g.conv.npix + 1) + (unsigned)pix) * 16u;
+        };
+        auto next = [&](bool more) {        // on to the next step (more: there is one)
+            if (--left == 0) {
+                if (seg == 0 && more) { seg = 1; left = T - T0; enter(0); }
+            } else {
+                voffR += 2 * krowR;
+                if (CONV) {
+                    cb += 2;
+                    while (cb >= g.conv.CB) { cb -= g.conv.CB; if (++kw == g.conv.KW) { kw = 0; ++kh; } }
+                } else voffL += 2 * krowL;
+            }
+            gather();
+        };
+        enter((first - (seg ? T0 : 0)) * KS);
+        gather();
+        v4i A[8], B[8];
+        auto load_A = [&](int d) { const uint4 x = *reinterpret_cast<const uint4*>(baseL + d * dsL + voffL); A[d] = v4i{ (int)x.x, (int)x.y, (int)x.z, (int)x.w }; };
+        auto load_B = [&](int d) { const uint4 x = *reinterpret_cast<const uint4*>(baseR + d * dsR + voffR); B[d] = v4i{ (int)x.x, (int)x.y, (int)x.z, (int)x.w }; };
+        static_for<4>([&](auto l) { load_A(l); load_B(l); load_A(7 - l); load_B(7 - l); });
+        auto step = [&](auto refill) {
+            constexpr bool more = decltype(refill)::value;
+            if (more) next(true);
+            static_for<4>([&](auto lt) {
+                constexpr int l = decltype(lt)::value;
+                auto mm = [&](auto it, auto jt) {
+                    constexpr int i = decltype(it)::value, j = decltype(jt)::value;
+                    acc[i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[i], B[j], acc[i + j], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                auto pair = [&](auto kt) {          // (l, k) and (k, l)
+                    constexpr int k = decltype(kt)::value;
+                    mm(std::integral_constant<int, l>{}, std::integral_constant<int, k>{});
+                    if constexpr (k != l) mm(std::integral_constant<int, k>{}, std::integral_constant<int, l>{});
+                };
+                // partners l .. 7 - l of digit l in the order of their refills: l, 7 - l, l + 1, 6 - l, ...
+                static_for<4 - l>([&](auto dt) {
+                    constexpr int d = decltype(dt)::value;
+                    pair(std::integral_constant<int, l + d>{});
+                    pair(std::integral_constant<int, 7 - l - d>{});
+                });
+                if constexpr (more) { load_A(l); load_B(l); load_A(7 - l); load_B(7 - l); __builtin_amdgcn_sched_barrier(0); }
+            });
+        };
+        for (int t = first; t + 1 < last; ++t) step(std::true_type{});
+        step(std::false_type{});
+    }
+    // the explicit accumulator reads are opaque to the compiler's hazard handling (see the epilogue above)
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    static_for<16>([&](auto vt) { part[wave][decltype(vt)::value][lane] = recombine<decltype(vt)::value>(acc); });
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < WPT; ++k) {
+        u64 z = add[k];
+#pragma unroll
+        for (int w = 0; w < KW; ++w) z += part[w][wave + KW * k][lane];
+        if (g.trunc_bits) z = party == 0 ? z >> g.trunc_bits : (u64)0 - (((u64)0 - z) >> g.trunc_bits);
+        if (ok[k]) P.out[at[k]] = z;
+    }
+}
+
 // Second pass of a split contraction: out = sum over splits of the partial
 // products + addends, then truncation.  One thread per output word.
 __global__ __launch_bounds__(256) void k_splitk_finish(GemmArgs g)
@@ -594,6 +748,34 @@ int launch_cfg(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
     return MPC_OK;
 }
 
+template <bool CONV, int KW>
+int launch_sliced(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
+{
+    GemmDev d{};
+    const int tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32;
+    const long long tiles = (long long)tiles_m * tiles_n * g.batch;
+    if (tiles >= (1ll << 27)) return MPC_EINVAL;
+    for (int p = 0; p < g.nparty; ++p) {
+        GemmParty& q = d.p[p];
+        q.seg[0] = g.seg[p][0]; q.seg[1] = g.seg[p][1];
+        q.addend = g.addend[p]; q.addend2 = g.addend2[p]; q.out = g.out[p];
+        q.tiles = (int)tiles; q.per_xcd = (int)((tiles + 7) / 8);
+    }
+    d.M = g.M; d.N = g.N; d.rows_L = g.rows_L; d.nseg = g.nseg; d.nparty = g.nparty; d.trunc_bits = g.trunc_bits;
+    d.out_bstride = g.out_bstride;
+    d.heavy_blocks = g.nparty == 2 ? (unsigned)(d.p[1].per_xcd * 8) : 0;
+    d.per_item = (unsigned)tiles_m * (unsigned)tiles_n; d.batch = (unsigned)g.batch;
+    d.panel_tiles = (unsigned)tiles_n;
+    d.by_item = Divider::by(d.per_item); d.by_panel = Divider::by(d.panel_tiles);
+    d.conv = g.conv;
+    d.by_Wo = Divider::by(CONV ? (unsigned)g.conv.Wo : 1); d.by_Ho = Divider::by(CONV ? (unsigned)g.conv.Ho : 1);
+    const int pi = prof_begin(c, MPC_PROF_GEMM_KERNEL, st);
+    hipLaunchKernelGGL((k_sliced_gemm<CONV, KW>), dim3((unsigned)(d.p[0].per_xcd * 8 * g.nparty)), dim3(64 * KW), 0, st, d);
+    prof_end(c, MPC_PROF_GEMM_KERNEL, pi, st);
+    MPC_HIP(c, hipGetLastError());
+    return MPC_OK;
+}
+
 }  // namespace
 
 // How many ways to split the contraction so that a small output still fills
@@ -632,6 +814,31 @@ static int tile_kind(int M, int N, int batch, int longest_steps, bool asymmetric
     // (not the batched products one 64-column tile wide, per-head A*V: those are 5 % faster on the 128 x 64 tile)
     if (asymmetric && max_steps > 0 && tiles64 >= kAsymMinTiles && !(batch > 1 && N <= 64)) return 2;
     return (((N - 1) % 128) < 64 && (N <= 64 || M >= 4096)) ? 1 : 0;
+}
+
+// Waves of a workgroup that share a 32 x 32 tile's contraction (k_sliced_gemm), or 0 for the tiles above.  Few tiles and a
+// contraction of at most 64 steps: a workgroup's life is latency, and the finishing pass of a contraction split over
+// workgroups one more launch.  Eight waves as long as every compute unit has one workgroup at most, then four.  Folded
+// prepared calls, tiles above / 4 waves / 8 waves, us (13.9 is the host's time of a call):
+//   64 x 256 x 128 (16 workgroups)       20.4 / 14.1 / 14.0     256 x 1024 x 512 (256)    32.3 / 28.1 / 27.5
+//   64 x 1024 x 128                      24.2 / 22.4 / 20.7     512 x 512 x 384 (384)     29.8 / 22.9 / 25.7
+//   64 x 2048 x 128, 128 steps           28.7 / 35.7 / 31.5     512 x 1024 x 512 (512)    43.4 / 37.7 / 42.4
+//   256 x 512 x 512 (256)                28.5 / 20.0 / 19.7     1024 x 128 x 512 (1024)   29.5 / 22.0 / 25.3
+//   1024 x 1024 x 512                    70.2 / 66.4 / 77.0     1024 x 512 x 768 (1536)   54.6 / 58.6 / 69.2
+// Beyond 1024 workgroups the larger tiles' reuse of operands wins, beyond 64 steps the split over more workgroups (512 steps:
+// 48 / 108 / 98).  Convolutions: 8 x 14 x 14 x 128, 3x3, 42.2 / 32.7 / 37.0; 4 x 14 x 14 x 64 27.5 / 18.6 / 17.9.
+// mpc_set_gemm_small_tile(0, ...) switches this form off as well.
+constexpr int kSlicedMaxSteps = 64;
+constexpr long long kSlicedMaxBlocks = 1024, kSlicedWideBlocks = 256;
+static int sliced_waves(const GemmArgs& g, int longest_steps)
+{
+    const int max_steps = g_small_max_steps.load(std::memory_order_relaxed);
+    if (longest_steps > kSlicedMaxSteps || max_steps == 0) return 0;
+    const long long blocks = (long long)((g.M + 31) / 32) * ((g.N + 31) / 32) * g.batch * g.nparty;
+    if (blocks > kSlicedMaxBlocks || tile_kind(g.M, g.N, g.batch, longest_steps, false) == 2) return 0;
+    // a lane's offset inside a left plane is 32 bits wide
+    if (g.conv.enabled && (g.conv.npix + 1) * g.conv.CB * 16 >= (1ll << 31)) return 0;
+    return blocks <= kSlicedWideBlocks ? 8 : 4;
 }
 
 // steps[p]: K steps party p contracts (steps[1] = 0 for a one-party launch).  Returns the number of slices
@@ -721,6 +928,10 @@ int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
     // to 256 channels, 32 images: 361 -> 350 us a call with the shorter set-up.
     if (g.conv.enabled && g.conv.KH == 1 && g.conv.KW == 1 && g.conv.stride == 1 && g.conv.pad == 0 && g.conv.CB % KS == 0)
         g.conv = ConvGeom{};
+    if (const int kw = sliced_waves(g, longest_steps)) {
+        if (g.conv.enabled) return kw == 8 ? launch_sliced<true, 8>(c, st, g) : launch_sliced<true, 4>(c, st, g);
+        return kw == 8 ? launch_sliced<false, 8>(c, st, g) : launch_sliced<false, 4>(c, st, g);
+    }
     // 64x128 workgroup tiles, or 128x64 when a second 64-column half would be empty
     const int kind = g.ksplit > 1 ? tile_kind(g.M, g.N, g.batch, 1 << 30, false) : tile_kind(g.M, g.N, g.batch, longest_steps, g.heavy_first != 0);
     if (g.conv.enabled)
