@@ -126,6 +126,19 @@ __device__ __forceinline__ void load_lds16(const u8* base, unsigned voff, unsign
                  :: "s"(lds_slot), "n"(LDS_OFF), "v"(voff), "s"(base) : "memory", "scc");
 }
 
+// Recombination sum_s d_s 2^(8s) mod 2^64 of a word's eight digit sums in 32-bit pieces: those of weights 0..3 add up exactly
+// as 64-bit terms built from two shifts each; of weights 4..7 only the low 32 bits reach the result, and those land in the
+// high word.
+__device__ __forceinline__ u64 recombine(const int (&d)[8])
+{
+    u64 acc64 = (u64)(long long)d[0];
+#pragma unroll
+    for (int sg = 1; sg < 4; ++sg)
+        acc64 += (u64)((unsigned)d[sg] << (8 * sg)) | ((u64)(unsigned)(d[sg] >> (32 - 8 * sg)) << 32);
+    const unsigned high = (unsigned)d[4] + ((unsigned)d[5] << 8) + ((unsigned)d[6] << 16) + ((unsigned)d[7] << 24);
+    return acc64 + ((u64)high << 32);
+}
+
 template <int WGM, int WGN, bool CONV, int NS, int NH>
 __device__ __forceinline__ void gemm_tile(const GemmDev& g)
 {
@@ -444,7 +457,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g)
     load_addend();
     // The explicit accumulator reads below are opaque to the compiler's hazard
     // handling: give the last MFMA (8 passes) time to retire before the first read.
-    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    if constexpr (NH == 2) asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 
     // ---- epilogue: recombine, add, truncate, store.
     static_for<NH>([&](auto ct) {
@@ -467,25 +480,24 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g)
         // 256 accumulator registers into vector registers at the loop exit, which leaves no
         // room for anything else to stay live across the main loop); the two column halves
         // are fenced from each other, inside a half the 16 words are independent chains.
-        // Recombination sum_s acc_s 2^(8s) mod 2^64 in 32-bit pieces: the digit sums of weights 0..3 add up exactly
-        // as 64-bit terms built from two shifts each; of weights 4..7 only the low 32 bits reach the result, and
-        // those land in the high word.
+        // With half the accumulators all of a wave's registers fit the vector file, and the words are read as they are (1x1
+        // convolution of 64 to 256 channels 330 -> 322 us, per-head Q K^T 304 -> 296).  Fewer vector instructions on top of
+        // that (a shorter recombination of short contractions, the truncation as two funnel shifts) gained nothing.
         u64 z[16];
         static_for<16>([&](auto vt) {
             constexpr int v = decltype(vt)::value;
             int d[8];
-            asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
-                         "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
-                         : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]), "=&v"(d[7])
-                         : "a"(acc[c][0][v]), "a"(acc[c][1][v]), "a"(acc[c][2][v]), "a"(acc[c][3][v]),
-                           "a"(acc[c][4][v]), "a"(acc[c][5][v]), "a"(acc[c][6][v]), "a"(acc[c][7][v]));
-            u64 acc64 = (u64)(long long)d[0];
+            if constexpr (NH == 2)
+                asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
+                             "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
+                             : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]), "=&v"(d[7])
+                             : "a"(acc[c][0][v]), "a"(acc[c][1][v]), "a"(acc[c][2][v]), "a"(acc[c][3][v]),
+                               "a"(acc[c][4][v]), "a"(acc[c][5][v]), "a"(acc[c][6][v]), "a"(acc[c][7][v]));
+            else {
 #pragma unroll
-            for (int sg = 1; sg < 4; ++sg)
-                acc64 += (u64)((unsigned)d[sg] << (8 * sg)) | ((u64)(unsigned)(d[sg] >> (32 - 8 * sg)) << 32);
-            const unsigned high = (unsigned)d[4] + ((unsigned)d[5] << 8) + ((unsigned)d[6] << 16) + ((unsigned)d[7] << 24);
-            acc64 += (u64)high << 32;
-            z[v] = acc64 + add[v];
+                for (int sg = 0; sg < 8; ++sg) d[sg] = acc[c][sg][v];
+            }
+            z[v] = recombine(d) + add[v];
         });
         // local truncation (shift and party are uniform over the workgroup): party 0 shifts, party 1 negates around the shift
         if (shift && party == 0) {
@@ -518,24 +530,6 @@ template <bool CONV>
 __global__ __launch_bounds__(256, 2) void k_few_rows_gemm(GemmDev g) { gemm_tile<1, 4, CONV, 3, 1>(g); }
 
 // ---- products with few output tiles --------------------------------------------------
-// Recombination sum_s acc_s 2^(8s) mod 2^64 of one word's eight digit sums, read out of the accumulator registers.
-template <int V>
-__device__ __forceinline__ u64 recombine(const v16i (&acc)[8])
-{
-    int d[8];
-    asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
-                 "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
-                 : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]), "=&v"(d[7])
-                 : "a"(acc[0][V]), "a"(acc[1][V]), "a"(acc[2][V]), "a"(acc[3][V]),
-                   "a"(acc[4][V]), "a"(acc[5][V]), "a"(acc[6][V]), "a"(acc[7][V]));
-    u64 acc64 = (u64)(long long)d[0];
-#pragma unroll
-    for (int sg = 1; sg < 4; ++sg)
-        acc64 += (u64)((unsigned)d[sg] << (8 * sg)) | ((u64)(unsigned)(d[sg] >> (32 - 8 * sg)) << 32);
-    const unsigned high = (unsigned)d[4] + ((unsigned)d[5] << 8) + ((unsigned)d[6] << 16) + ((unsigned)d[7] << 24);
-    return acc64 + ((u64)high << 32);
-}
-
 // (Chosen by sliced_waves below, with what it measured.)
 // A workgroup has one 32 x 32 output tile, and its KW waves share the contraction: each contracts a slice of the K steps
 // with operands loaded straight into registers (the planes' layout is that of the matrix operands; nothing is shared
@@ -657,9 +651,13 @@ __global__ __launch_bounds__(64 * KW, 2) void k_sliced_gemm(GemmDev g)
         for (int t = first; t + 1 < last; ++t) step(std::true_type{});
         step(std::false_type{});
     }
-    // the explicit accumulator reads are opaque to the compiler's hazard handling (see the epilogue above)
-    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    static_for<16>([&](auto vt) { part[wave][decltype(vt)::value][lane] = recombine<decltype(vt)::value>(acc); });
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        int d[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) d[s] = acc[s][v];
+        part[wave][v][lane] = recombine(d);
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < WPT; ++k) {
