@@ -161,8 +161,10 @@ int mpc_graph_destroy(mpc_graph* graph);
  *   (other than element for element).
  * MPC_EXCHANGE_PUT: the kernel that forms the masked words also stores them
  *   into the peer's receive buffer (what a peer-to-peer store would be between
- *   two devices).  Linear layers: the next step starts when that kernel has
- *   ended.  Secure ReLU, max-pool, element-wise products and the backward calls
+ *   two devices).  Linear layers: masking, exchange and opening of a call's
+ *   operands are one launch where they are stored as they are read (not the
+ *   activations of a filter gradient), else the next step starts when the
+ *   masking kernel has ended.  Secure ReLU, three-party rescale, max-pool, element-wise products and the backward calls
  *   built on them: all rounds run in one launch; a round ends when the waves of
  *   all parties that hold the same elements have stored their words, and
  *   n_chunks has nothing to cut.  A call whose output overlaps one of its inputs
@@ -517,7 +519,7 @@ int mpc_maxpool2x2_backward(mpc_ctx* ctx, mpc_cshare g, mpc_cshare s1, mpc_cshar
  * party 0 (the paper's "Party #1") adds the Delta*epsilon term.  All work is
  * issued on the lane's first stream (the other two streams of the lane wait
  * for it on return), one launch per step for all parties, every exchange a
- * copy kernel; outputs are valid after any stream of the lane, or
+ * copy kernel (or a remote store, mpc_ctx_set_exchange); outputs are valid after any stream of the lane, or
  * mpc_ctx_sync.  Pointers are device memory, one per party; nothing is
  * allocated.  Errors as for the two-party calls. */
 typedef struct { const uint64_t* p[3]; } mpc_cshare3;
@@ -531,7 +533,8 @@ int mpc_open3(mpc_ctx* ctx, mpc_cshare3 s, uint64_t* out_public, size_t n);
  * layouts and f_public as for mpc_beaver_matmul / mpc_conv2d; flags:
  * MPC_TRANS_X, MPC_TRANS_Y only (the rescale needs an exchange with three
  * parties: follow with mpc_truncate3).  Six ring products on the matrix
- * cores: parties 0 and 1 in one launch, party 2 in a second one. */
+ * cores: parties 0 and 1 in one launch, party 2 in a second one (all three in
+ * one where there are few tiles). */
 size_t mpc_matmul3_workspace_bytes(int M, int K, int N, int batch);
 int mpc_beaver_matmul3(mpc_ctx* ctx, mpc_cshare3 x, mpc_cshare3 y,
                        mpc_cshare3 a, mpc_cshare3 b, mpc_cshare3 c, mpc_share3 z,

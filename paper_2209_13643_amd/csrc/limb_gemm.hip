@@ -63,7 +63,7 @@ struct GemmParty {
     int tiles, per_xcd;                     // tiles of the party, and how many of them an XCD owns
 };
 struct GemmDev {
-    GemmParty p[2];
+    GemmParty p[3];
     int M, N, rows_L, nseg, nparty, trunc_bits, ksplit, steps_per_split;
     long long out_bstride;
     u64* partial;
@@ -546,8 +546,10 @@ __global__ __launch_bounds__(64 * KW, 2) void k_sliced_gemm(GemmDev g)
     const int lane = threadIdx.x & 63, i32 = lane & 31, g2 = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const unsigned id = blockIdx.x;
-    const int party = g.nparty == 2 && id < g.heavy_blocks ? 1 : 0;        // party 1's workgroups, the longer ones, come first
-    const unsigned q = (party ? id : id - g.heavy_blocks) >> 3;
+    // a party's workgroups one after the other; of two, party 1's, the longer ones, come first
+    const int nth = id < g.heavy_blocks ? 0 : id < 2 * g.heavy_blocks ? 1 : 2;
+    const int party = g.nparty == 2 ? 1 - nth : nth;
+    const unsigned q = (id - (unsigned)nth * g.heavy_blocks) >> 3;
     const GemmParty& P = g.p[party];
     const unsigned tile = (id & 7) * (unsigned)P.per_xcd + q;
     if (q >= (unsigned)P.per_xcd || tile >= (unsigned)P.tiles) return;
@@ -761,7 +763,7 @@ int launch_sliced(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
     }
     d.M = g.M; d.N = g.N; d.rows_L = g.rows_L; d.nseg = g.nseg; d.nparty = g.nparty; d.trunc_bits = g.trunc_bits;
     d.out_bstride = g.out_bstride;
-    d.heavy_blocks = g.nparty == 2 ? (unsigned)(d.p[1].per_xcd * 8) : 0;
+    d.heavy_blocks = (unsigned)(d.p[0].per_xcd * 8);          // of each party
     d.per_item = (unsigned)tiles_m * (unsigned)tiles_n; d.batch = (unsigned)g.batch;
     d.panel_tiles = (unsigned)tiles_n;
     d.by_item = Divider::by(d.per_item); d.by_panel = Divider::by(d.panel_tiles);
@@ -891,15 +893,21 @@ extern "C" int mpc_set_gemm_small_tile(int max_steps, int min_tiles)
     return MPC_OK;
 }
 
+bool gemm_takes_three(const GemmArgs& g)
+{
+    return g.nparty == 3 && g.nseg == 2 && sliced_waves(g, (g.seg[0][0].KB + g.seg[0][1].KB) / KS) != 0;
+}
+
 int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
 {
     GemmArgs g = g_in;
-    if (g.nparty < 1 || g.nparty > 2 || g.nseg < 1 || g.nseg > 2) return MPC_EINVAL;
+    if (g.nparty < 1 || g.nparty > (gemm_takes_three(g) ? 3 : 2) || g.nseg < 1 || g.nseg > 2) return MPC_EINVAL;
     int longest_steps = 0;
     {
-        int steps[2] = { 0, 0 };
+        int steps[3] = { 0, 0, 0 };
         for (int p = 0; p < g.nparty; ++p)
             for (int s = 0; s < g.nseg; ++s) steps[p] += g.seg[p][s].KB / KS;
+        if (g.nparty == 3 && (steps[1] != steps[0] || steps[2] != steps[0])) return MPC_EINVAL;
         const int longest = steps[0] > steps[1] ? steps[0] : steps[1];
         longest_steps = longest;
         if (g.ksplit < 1 || !g.partial) g.ksplit = 1;

@@ -172,14 +172,28 @@ RecodeArgs recode_right(const LinearShape& s, const u64* src, const u64* src2, c
 
 // An operand laid out as `r` describes, as shares v and masks m, to be opened in one launch: planes dst0 (folded: v_0 + the
 // word received; plain: the opened words) and dst1 (folded: the opened words), plain calls also those of the masks.
-OpenSet open_set(const RecodeArgs& r, mpc_cshare v, mpc_cshare m, u8* dst0, u8* dst1, u8* mask0 = nullptr, u8* mask1 = nullptr, bool add_open = false)
+template <int NP, typename Share>
+OpenSet open_set(const RecodeArgs& r, const Share& v, const Share& m)
 {
     OpenSet o{};
-    for (int i = 0; i < 2; ++i) { o.x[i] = v.p[i]; o.a[i] = m.p[i]; }
-    o.dst[0] = dst0; o.dst[1] = dst1; o.mask_dst[0] = mask0; o.mask_dst[1] = mask1; o.add_open = add_open;
+    for (int i = 0; i < NP; ++i) { o.x[i] = v.p[i]; o.a[i] = m.p[i]; }
     o.row_stride = r.row_stride; o.k_stride = r.k_stride; o.src_batch_stride = r.src_batch_stride; o.tap_stride = r.tap_stride;
     o.digit_stride = r.digit_stride; o.dst_batch_stride = r.dst_batch_stride;
     o.rows = r.rows; o.plane_rows = r.plane_rows; o.K = r.K; o.KB_tap = r.KB_tap; o.ntaps = r.ntaps; o.KB_total = r.KB_total; o.batch = r.batch;
+    return o;
+}
+OpenSet open_set(const RecodeArgs& r, mpc_cshare v, mpc_cshare m, u8* dst0, u8* dst1, u8* mask0 = nullptr, u8* mask1 = nullptr, bool add_open = false)
+{
+    OpenSet o = open_set<2>(r, v, m);
+    o.dst[0] = dst0; o.dst[1] = dst1; o.mask_dst[0] = mask0; o.mask_dst[1] = mask1; o.add_open = add_open;
+    return o;
+}
+// three parties: planes dst of the opened words; masks: planes of the masks, if wanted
+OpenSet open_set3(const RecodeArgs& r, mpc_cshare3 v, mpc_cshare3 m, u8* dst, u8* const* masks, bool add_open = false)
+{
+    OpenSet o = open_set<3>(r, v, m);
+    o.dst[0] = dst; o.add_open = add_open;
+    for (int i = 0; i < 3 && masks; ++i) o.mask_dst[i] = masks[i];
     return o;
 }
 
@@ -282,13 +296,13 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
         g.nparty = 2;
         // receive buffers of the one-launch opening: the parts of the workspace ahead of the planes
         const size_t box_bytes = (size_t)(w.pl_e - reinterpret_cast<u8*>(w.se[0]));
-        if (folded && put && !s.im2colT && box_bytes >= kOpenBoxBytes) {
+        if (folded && put && !s.im2colT && box_bytes >= open_box_bytes(2)) {
             // Folded call with the exchange by remote store, in one launch (open_recode.hip): both parties mask and send
             // e_i = x_i - a_i, then party 0 recodes a_0 + e = x_0 + e_1 and party 1 the opened e.  A product of two
             // activations opens f in the same launch: f_i = y_i - b_i, b_0 + f = y_0 + f_1, f.
             OpenSet open[2] = { open_set(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_a[0], w.pl_e), OpenSet{} };
             if (right_online) open[1] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_b[0], w.pr_f);
-            MPC_TRY(launch_open_recode(c, P0, open, right_online ? 2 : 1, false, reinterpret_cast<u8*>(w.se[0]), box_bytes));
+            MPC_TRY(launch_open_recode(c, P0, 2, OpenPlanes::kFolded, open, right_online ? 2 : 1, reinterpret_cast<u8*>(w.se[0]), box_bytes));
             g.nseg = 2;
             g.seg[0][0] = make_seg(s, w.pl_a[0], w.pr_b[0]); g.seg[0][1] = GemmSeg{};
             g.seg[1][0] = make_seg(s, w.pl_e, w.pr_b[1]);    g.seg[1][1] = make_seg(s, w.pl_a[1], w.pr_f);
@@ -300,7 +314,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
         }
         // Plain calls with the exchange by remote store open what they open in one launch, planes of the masks with it.
         // (A filter read in reverse tap order, or operands of less than half a tile, take the steps below.)
-        const bool one_launch = put && !folded && box_bytes >= kOpenBoxBytes && !(two_phase && have_f);
+        const bool one_launch = put && !folded && box_bytes >= open_box_bytes(2) && !(two_phase && have_f);
         OpenSet opens[2]; int n_open = 0;
         bool left_done = false, right_done = false;
         if (one_launch && !skip_left && !x_public && !s.im2colT) {
@@ -311,7 +325,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             opens[n_open++] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_f, nullptr, w.pr_b[0], w.pr_b[1], true);
             right_done = true;
         }
-        if (n_open) MPC_TRY(launch_open_recode(c, P0, opens, n_open, true, reinterpret_cast<u8*>(w.se[0]), box_bytes));
+        if (n_open) MPC_TRY(launch_open_recode(c, P0, 2, OpenPlanes::kMasks, opens, n_open, reinterpret_cast<u8*>(w.se[0]), box_bytes));
         if ((size_t)n_chunks > s.nx) n_chunks = (int)s.nx;
         bool f_pending = !have_f && !right_done;             // the weight mask rides with the first launch issued
         for (int ch = 0; ch < n_chunks; ++ch) {
@@ -573,6 +587,23 @@ int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 
     MPC_TRY(lane_first(c));
     const int pi = prof_begin(c, MPC_PROF_LINEAR, st);
 
+    // Exchange by remote store: what opens, opens in one launch (open_recode.hip), with the planes of the masks that are not
+    // prepared.  (Not where the planes are a transposed im2col, a filter is read in reverse tap order, or there is less than
+    // half a tile.)
+    const size_t box_bytes = (size_t)(w.pl_e - reinterpret_cast<u8*>(w.se[0]));
+    const bool open_right = !have_f;
+    if (c->exchange_put && box_bytes >= open_box_bytes(3) && !s.im2colT && !(open_right && s.wflip)) {
+        const bool masks = !skip_left || open_right;
+        OpenSet open[2] = { open_set3(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_e, skip_left ? nullptr : w.pl_a), OpenSet{} };
+        if (open_right) open[1] = open_set3(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_f, w.pr_b, true);
+        MPC_TRY(launch_open_recode(c, st, 3, masks ? OpenPlanes::kMasks : OpenPlanes::kOpened, open, open_right ? 2 : 1,
+                                   reinterpret_cast<u8*>(w.se[0]), box_bytes));
+        if (!skip_right && f_public) {
+            RecodeArgs rr[4] = { recode_right(s, b.p[1], nullptr, nullptr, w.pr_b[1]), recode_right(s, b.p[2], nullptr, nullptr, w.pr_b[2]),
+                                 recode_right(s, f_public, nullptr, nullptr, w.pr_f), recode_right(s, b.p[0], f_public, nullptr, w.pr_b[0]) };
+            MPC_TRY(launch_recode_multi(c, st, rr, 4));
+        }
+    } else {
     // Alg. 1: every party masks its shares ...
     SubSeg sub[6]; int ns = 0;
     for (int i = 0; i < 3; ++i) sub[ns++] = SubSeg{ x.p[i], a.p[i], w.se[i], s.nx, 0, nullptr };
@@ -614,15 +645,23 @@ int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 
         }
     }
 
+    }
+
     GemmArgs g{};
     fill_geom(s, w.g, g);
     g.nseg = 2; g.trunc_bits = 0;
-    g.nparty = 2;
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < 3; ++i) {
         g.seg[i][0] = make_seg(s, w.pl_e, w.pr_b[i]);
         g.seg[i][1] = make_seg(s, w.pl_a[i], w.pr_f);
         g.addend[i] = cc.p[i]; g.addend2[i] = nullptr; g.out[i] = z.p[i];
     }
+    g.nparty = 3;
+    if (gemm_takes_three(g)) {              // few tiles: one launch for all parties
+        MPC_TRY(launch_limb_gemm(c, st, g));
+        prof_end(c, MPC_PROF_LINEAR, pi, st);
+        return lane_fanout(c);
+    }
+    g.nparty = 2;
     MPC_TRY(launch_limb_gemm(c, st, g));
     g.nparty = 1;
     g.seg[0][0] = make_seg(s, w.pl_e, w.pr_b[2]);

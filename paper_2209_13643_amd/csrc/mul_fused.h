@@ -44,3 +44,19 @@ inline bool poolbwd_outputs_apart(int parties, const FusedPoolBwd& q)
 }
 size_t poolbwd_fused_box_bytes(int parties, size_t n_out);
 int launch_poolbwd_fused(mpc_ctx* c, hipStream_t st, int parties, FusedPoolBwd q);
+
+// masked rescale of a three-party sharing (in place): party 0 opens z + r + 2^62 and shifts, the others negate their share of r >> bits
+struct FusedTrunc3 {
+    u64* z[3]; const u64 *r[3], *rt[3];
+    u64* box;                            // trunc3_fused_box_bytes(n) bytes
+    size_t n; int bits;
+    unsigned tiles;
+};
+inline bool trunc3_outputs_apart(const FusedTrunc3& q)
+{
+    Spans<9> in; Spans<3> out;
+    for (int i = 0; i < 3; ++i) { in.words(q.z[i], q.n); in.words(q.r[i], q.n); in.words(q.rt[i], q.n); out.words(q.z[i], q.n); }
+    return outputs_apart(out, in, true);
+}
+size_t trunc3_fused_box_bytes(size_t n);
+int launch_trunc3_fused(mpc_ctx* c, hipStream_t st, FusedTrunc3 q);

@@ -1,5 +1,5 @@
 // Masking, exchange by remote store and recoding of a linear layer's opened operands in one launch (single-queue lanes).
-// A workgroup is two waves per party on the same words: every wave masks its share (e_i = x_i - a_i),
+// A workgroup is two waves per party (two parties or three) on the same words: every wave masks its share (e_i = x_i - a_i),
 // stores it into the peer's receive buffer in device memory, and after the workgroup barrier recodes what its party
 // contracts: party 0 its own share plus the received word (a_0 + e = x_0 + e_1), party 1 the opened e.  Bound by memory:
 // every share and mask is read once and every plane written once, six traversals of the operand, and the receive buffers
@@ -8,6 +8,8 @@
 // 1x1 convolution of 64 to 256 channels 362 / 334, 3x3 of 128 channels 233 / 222, 8 products of 64 x 64 x 64 27.4 / 19.0.
 // Plain calls write the planes of the masks from the same pass, seven traversals instead of twelve (left) and seventeen
 // (right operand): VGG16 training step of 32 images 7.61 / 7.51 ms.
+// Three parties: an operand's masks, broadcast, sum and recoding were four launches and 84 us for 64 x 16 x 16 x 128 words,
+// 47 here.
 // Non-temporal loads lose (3x3: 235 us): the operand was often written just before and is in the last-level cache.
 #include "open_recode.h"
 #include "digits.h"
@@ -18,7 +20,7 @@ namespace {
 
 typedef u64 u64v2u __attribute__((ext_vector_type(2), aligned(8)));
 
-constexpr int kThreads = 256, kPartyThreads = 128;
+constexpr int kPartyThreads = 128;
 // Tile of a workgroup where k is contiguous: KBT k blocks wide and 128 / KBT rows high, so that a thread has 16 words of it
 // (narrow operands fill only the first k blocks of a wide tile: a 3x3 convolution of 3 channels, 32 x 56 x 56, takes 134 us a
 // call on tiles of 64 k, 111 on tiles of 16).
@@ -27,41 +29,64 @@ constexpr int tile_rows(int KBT) { return 128 / KBT; }
 constexpr int block_pitch(int KBT) { return tile_rows(KBT) * 4 + 64 / KBT; }
 constexpr int kTileWords = 8 * (512 + 64);
 int tile_blocks(int KB_total) { return KB_total > 2 ? 4 : KB_total; }
-// Workgroups resident at once: three to a compute unit (167 registers; held at 128 for a fourth they are spilled, and the
-// 3x3 convolution takes 228 us), two in plain calls (228).  Each has 8 KB of receive buffer per party.  512 / 768 / 1024 workgroups: level within 1-2 %.
-constexpr unsigned kMaxBlocks = 768, kMaxPlainBlocks = 512;
-static_assert(kOpenBoxBytes == 2 * kPartyThreads * 8 * sizeof(u64), "a party exchanges eight words per thread at a time");
+// Workgroups of a launch, as many as are resident at once: two parties three to a compute unit (167 registers; held at 128
+// for a fourth they are spilled, and the 3x3 convolution takes 228 us), two in plain calls (228); three parties two and one.
+// 512 / 768 / 1024 workgroups of folded calls: level within 1-2 %.
+constexpr unsigned max_blocks(int parties, OpenPlanes planes)
+{
+    return parties == 2 ? (planes == OpenPlanes::kFolded ? 768 : 512) : planes == OpenPlanes::kMasks ? 256 : 512;
+}
+constexpr int waves_per_simd(int parties, OpenPlanes planes) { return planes == OpenPlanes::kMasks ? 2 : 3; }
 
 struct OpenBatch { OpenSet s[kMaxOpenSets]; int count; unsigned tiles; u8* box; };
 
+// The receive buffers: per workgroup and ordered pair of parties, kWords words per thread.  Party i's buffer k holds what
+// party (i + 1 + k) mod NP sent last.
+template <int NP>
 struct Exchange {
-    u8 *in, *out; unsigned at;
+    static constexpr int kWords = NP == 2 ? 8 : 4;
+    static constexpr unsigned kBox = kPartyThreads * kWords * 8;
+    static_assert((size_t)NP * (NP - 1) * kBox == open_box_bytes(NP), "buffers of a workgroup");
+    u8 *in, *out[NP - 1]; unsigned at;
     __device__ __forceinline__ Exchange(u8* box, int party, int t)
     {
-        u8* const wg = box + (size_t)blockIdx.x * kOpenBoxBytes;
-        in = wg + party * (kOpenBoxBytes / 2); out = wg + (1 - party) * (kOpenBoxBytes / 2);
+        u8* const wg = box + (size_t)blockIdx.x * open_box_bytes(NP);
+        in = wg + party * (NP - 1) * kBox;
+#pragma unroll
+        for (int k = 0; k < NP - 1; ++k) {
+            int to = party + NP - 1 - k; if (to >= NP) to -= NP;
+            out[k] = wg + (to * (NP - 1) + k) * kBox;
+        }
         at = (unsigned)t * 16;
     }
-    // eight words to the peer and eight back; 16 bytes per lane and access, lanes side by side
-    __device__ __forceinline__ void swap(const u64 (&mine)[8], u64 (&theirs)[8]) const
+    // kWords words to every peer, and the sum of what the peers sent; 16 bytes per lane and access, lanes side by side
+    __device__ __forceinline__ void swap(const u64 (&mine)[kWords], u64 (&theirs)[kWords]) const
     {
-        __syncthreads();                   // the peer holds the last words it was sent
+        __syncthreads();                   // the peers hold the last words they were sent
 #pragma unroll
-        for (int q = 0; q < 4; ++q) *reinterpret_cast<u64v2u*>(out + q * (kPartyThreads * 16) + at) = u64v2u{ mine[2 * q], mine[2 * q + 1] };
+        for (int k = 0; k < NP - 1; ++k)
+#pragma unroll
+            for (int q = 0; q < kWords / 2; ++q)
+                *reinterpret_cast<u64v2u*>(out[k] + q * (kPartyThreads * 16) + at) = u64v2u{ mine[2 * q], mine[2 * q + 1] };
         __syncthreads();
+        u64v2u w[NP - 1][kWords / 2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const u64v2u w = *reinterpret_cast<const u64v2u*>(in + q * (kPartyThreads * 16) + at);
-            theirs[2 * q] = w.x; theirs[2 * q + 1] = w.y;
-        }
+        for (int k = 0; k < NP - 1; ++k)
+#pragma unroll
+            for (int q = 0; q < kWords / 2; ++q) w[k][q] = *reinterpret_cast<const u64v2u*>(in + k * kBox + q * (kPartyThreads * 16) + at);
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kWords / 2; ++q) {
+            theirs[2 * q] = w[0][q].x; theirs[2 * q + 1] = w[0][q].y;
+            if constexpr (NP == 3) { theirs[2 * q] += w[1][q].x; theirs[2 * q + 1] += w[1][q].y; }
+        }
     }
 };
 
 // Contiguous k: lanes along k read the tile, digits go to LDS in plane order, planes are written with lanes along rows.
 // H = 1: tiles of which at most half the rows are there (few-row products), half the loads and one exchange.
-template <bool PLAIN, int KBT, int H>
-__device__ __forceinline__ void open_rows(const OpenSet& s, const Exchange& ex, int party, int t, int b, int row0, int kb0, uint32_t* tile)
+template <int NP, OpenPlanes PLANES, int KBT, int H>
+__device__ __forceinline__ void open_rows(const OpenSet& s, const Exchange<NP>& ex, int party, int t, int b, int row0, int kb0, uint32_t* tile)
 {
     const u64* x = s.x[party] + (long long)b * s.src_batch_stride;
     const u64* a = s.a[party] + (long long)b * s.src_batch_stride;
@@ -107,26 +132,30 @@ __device__ __forceinline__ void open_rows(const OpenSet& s, const Exchange& ex, 
         for (int q = 0; q < 8; ++q)
             *reinterpret_cast<uint4*>(o + (size_t)q * s.digit_stride) = *reinterpret_cast<const uint4*>(&tile[(q * KBT + kbl) * pitch + row * 4]);
     };
+    constexpr int W = Exchange<NP>::kWords;
 #pragma unroll
-    for (int h = 0; h < H; ++h) {
-        u64 e[8], got[8];
+    for (int h = 0; h < 8 * H / W; ++h) {
+        u64 e[W], got[W];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) e[q] = v[2 * h + q / 4][q % 4] - m[2 * h + q / 4][q % 4];
+        for (int q = 0; q < W; ++q) e[q] = v[(h * W + q) / 4][q % 4] - m[(h * W + q) / 4][q % 4];
         ex.swap(e, got);
+        // party 0 recodes the opened words (the parties of kOpened in turn, and a third of the planes each: no faster)
+        if (PLANES != OpenPlanes::kFolded && party) continue;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
+        for (int p = h * W / 4; p < (h + 1) * W / 4; ++p) {
             u64 four[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                four[u] = (!PLAIN && party == 0 ? v[2 * h + p][u] : e[4 * p + u]) + got[4 * p + u];
-                if (PLAIN && party == 0 && s.add_open) m[2 * h + p][u] += four[u];
+                const int q = 4 * p + u - h * W;
+                four[u] = (PLANES == OpenPlanes::kFolded && party == 0 ? v[p][u] : e[q]) + got[q];
+                if (PLANES == OpenPlanes::kMasks && s.add_open) m[p][u] += four[u];
             }
-            scatter(2 * h + p, four);
+            scatter(p, four);
         }
     }
     __syncthreads();
     store(s.dst[party]);
-    if constexpr (PLAIN) {
+    if constexpr (PLANES == OpenPlanes::kMasks) {
         __syncthreads();
 #pragma unroll
         for (int p = 0; p < 2 * H; ++p) scatter(p, m[p]);
@@ -136,8 +165,8 @@ __device__ __forceinline__ void open_rows(const OpenSet& s, const Exchange& ex, 
 }
 
 // Contiguous rows (an operand stored [K][N], a filter): a thread takes one (row, k block of a tap), lanes along rows.
-template <bool PLAIN>
-__device__ __forceinline__ void open_columns(const OpenSet& s, const Exchange& ex, int party, int t, int b, unsigned bx, unsigned kb)
+template <int NP, OpenPlanes PLANES>
+__device__ __forceinline__ void open_columns(const OpenSet& s, const Exchange<NP>& ex, int party, int t, int b, unsigned bx, unsigned kb)
 {
     const int tap = s.ntaps == 1 ? 0 : (int)kb / s.KB_tap;             // == ntaps: padding behind the last tap
     const int row = (int)bx * kPartyThreads + t, k0 = ((int)kb - tap * s.KB_tap) * 16;
@@ -164,50 +193,65 @@ __device__ __forceinline__ void open_columns(const OpenSet& s, const Exchange& e
         }
         u8* const o = dst + (size_t)b * s.dst_batch_stride + ((size_t)kb * s.plane_rows + row) * 16;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) *reinterpret_cast<uint4*>(o + (size_t)q * s.digit_stride) = make_uint4(unit[q][0], unit[q][1], unit[q][2], unit[q][3]);
+        for (int q = 0; q < 8; ++q)
+            *reinterpret_cast<uint4*>(o + (size_t)q * s.digit_stride) = make_uint4(unit[q][0], unit[q][1], unit[q][2], unit[q][3]);
     };
+    constexpr int W = Exchange<NP>::kWords;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        u64 e[8], got[8];
+    for (int h = 0; h < 16 / W; ++h) {
+        u64 e[W], got[W];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) e[q] = v[8 * h + q] - m[8 * h + q];
+        for (int q = 0; q < W; ++q) e[q] = v[W * h + q] - m[W * h + q];
         ex.swap(e, got);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            v[8 * h + q] = (!PLAIN && party == 0 ? v[8 * h + q] : e[q]) + got[q];
-            if (PLAIN && party == 0 && s.add_open) m[8 * h + q] += v[8 * h + q];
+        for (int q = 0; q < W; ++q) {
+            v[W * h + q] = (PLANES == OpenPlanes::kFolded && party == 0 ? v[W * h + q] : e[q]) + got[q];
+            if (PLANES == OpenPlanes::kMasks && party == 0 && s.add_open) m[W * h + q] += v[W * h + q];
         }
     }
     store(s.dst[party], v);
-    if constexpr (PLAIN) store(s.mask_dst[party], m);
+    if constexpr (PLANES == OpenPlanes::kMasks) store(s.mask_dst[party], m);
 }
 
-template <bool PLAIN>
-__global__ __launch_bounds__(kThreads, PLAIN ? 2 : 3) void k_open_recode(OpenBatch g)
+template <int NP, OpenPlanes PLANES>
+__global__ __launch_bounds__(NP * kPartyThreads, waves_per_simd(NP, PLANES)) void k_open_recode(OpenBatch g)
 {
-    __shared__ __align__(16) uint32_t lds[2][kTileWords];
+    __shared__ __align__(16) uint32_t lds[NP == 2 || PLANES == OpenPlanes::kMasks ? NP : 1][kTileWords];
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kPartyThreads));
     const int t = threadIdx.x % kPartyThreads;
-    const Exchange ex(g.box, party, t);
+    uint32_t* const tile = lds[sizeof(lds) / sizeof(lds[0]) == 1 ? 0 : party];
+    const Exchange<NP> ex(g.box, party, t);
     for (unsigned id = blockIdx.x; id < g.tiles; id += gridDim.x) {
         const OpenSet& s = g.s[g.count > 1 && id >= g.s[1].first ? 1 : 0];
         unsigned q = id - s.first;
         const unsigned bx = q % s.gx; q /= s.gx;
         const unsigned by = q % s.gy; const int b = (int)(q / s.gy);
-        if (!s.kbt) { open_columns<PLAIN>(s, ex, party, t, b, bx, by); continue; }
+        if (!s.kbt) { open_columns<NP, PLANES>(s, ex, party, t, b, bx, by); continue; }
         const int row0 = (int)bx * tile_rows(s.kbt), kb0 = (int)by * s.kbt;
-        if (s.kbt == 1)                    open_rows<PLAIN, 1, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
-        else if (s.kbt == 2)               open_rows<PLAIN, 2, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
-        else if (s.plane_rows - row0 > 16) open_rows<PLAIN, 4, 2>(s, ex, party, t, b, row0, kb0, lds[party]);
-        else                               open_rows<PLAIN, 4, 1>(s, ex, party, t, b, row0, kb0, lds[party]);
+        if (s.kbt == 1)                    open_rows<NP, PLANES, 1, 2>(s, ex, party, t, b, row0, kb0, tile);
+        else if (s.kbt == 2)               open_rows<NP, PLANES, 2, 2>(s, ex, party, t, b, row0, kb0, tile);
+        else if (s.plane_rows - row0 > 16) open_rows<NP, PLANES, 4, 2>(s, ex, party, t, b, row0, kb0, tile);
+        else                               open_rows<NP, PLANES, 4, 1>(s, ex, party, t, b, row0, kb0, tile);
     }
+}
+
+template <int NP, OpenPlanes PLANES>
+void launch(hipStream_t st, const OpenBatch& g, size_t box_bytes)
+{
+    // as many workgroups as have buffers, all of them with the same number of tiles (but for the last few)
+    unsigned long long blocks = box_bytes / open_box_bytes(NP);
+    if (blocks > max_blocks(NP, PLANES)) blocks = max_blocks(NP, PLANES);
+    const unsigned long long rounds = (g.tiles + blocks - 1) / blocks;
+    blocks = (g.tiles + rounds - 1) / rounds;
+    hipLaunchKernelGGL((k_open_recode<NP, PLANES>), dim3((unsigned)blocks), dim3(NP * kPartyThreads), 0, st, g);
 }
 
 }  // namespace
 
-int launch_open_recode(mpc_ctx* c, hipStream_t st, const OpenSet* sets, int count, bool plain, u8* box, size_t box_bytes)
+int launch_open_recode(mpc_ctx* c, hipStream_t st, int parties, OpenPlanes planes, const OpenSet* sets, int count, u8* box, size_t box_bytes)
 {
-    if (count < 1 || count > kMaxOpenSets || !box || box_bytes < kOpenBoxBytes) return MPC_EINVAL;
+    if (parties < 2 || parties > 3 || count < 1 || count > kMaxOpenSets || !box || box_bytes < open_box_bytes(parties)) return MPC_EINVAL;
+    if (parties == (planes == OpenPlanes::kFolded ? 3 : planes == OpenPlanes::kOpened ? 2 : 0)) return MPC_EINVAL;
     OpenBatch g{};
     unsigned long long tiles = 0;
     for (int i = 0; i < count; ++i) {
@@ -224,13 +268,10 @@ int launch_open_recode(mpc_ctx* c, hipStream_t st, const OpenSet* sets, int coun
         if (tiles >= (1ull << 31)) return MPC_EINVAL;
     }
     g.count = count; g.tiles = (unsigned)tiles; g.box = box;
-    // as many workgroups as have buffers, all of them with the same number of tiles (but for the last few)
-    unsigned long long blocks = box_bytes / kOpenBoxBytes;
-    if (blocks > (plain ? kMaxPlainBlocks : kMaxBlocks)) blocks = plain ? kMaxPlainBlocks : kMaxBlocks;
-    const unsigned long long rounds = (tiles + blocks - 1) / blocks;
-    blocks = (tiles + rounds - 1) / rounds;
-    if (plain) hipLaunchKernelGGL(k_open_recode<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, g);
-    else       hipLaunchKernelGGL(k_open_recode<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, g);
+    if (planes == OpenPlanes::kFolded)      launch<2, OpenPlanes::kFolded>(st, g, box_bytes);
+    else if (planes == OpenPlanes::kOpened) launch<3, OpenPlanes::kOpened>(st, g, box_bytes);
+    else if (parties == 2)                  launch<2, OpenPlanes::kMasks>(st, g, box_bytes);
+    else                                    launch<3, OpenPlanes::kMasks>(st, g, box_bytes);
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }

@@ -841,6 +841,15 @@ int mpc_truncate3(mpc_ctx* c, mpc_share3 z, mpc_cshare3 r, mpc_cshare3 rt, size_
     q.n = n; q.bits = bits;
     hipStream_t st = c->s[0];
     MPC_TRY(lane_first(c));
+    if (c->exchange_put && c->ws_bytes >= trunc3_fused_box_bytes(n)) {
+        FusedTrunc3 f{};
+        for (int i = 0; i < 3; ++i) { f.z[i] = z.p[i]; f.r[i] = r.p[i]; f.rt[i] = rt.p[i]; }
+        f.box = reinterpret_cast<u64*>(c->ws); f.n = n; f.bits = bits;
+        if (trunc3_outputs_apart(f)) {
+            MPC_TRY(launch_trunc3_fused(c, st, f));
+            return lane_fanout(c);
+        }
+    }
     hipLaunchKernelGGL(k3_trunc_mask, dim3(grid3(n), 2), dim3(kT), 0, st, q);
     MPC_HIP(c, hipGetLastError());
     CopySeg cp[2];

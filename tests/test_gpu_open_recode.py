@@ -104,3 +104,46 @@ def test_convolutions(mpc, lane, B, H, W, Cin, Cout, k):
     z = lane.conv2d_prepared(x, a, cf, right, left, k, k, k // 2, 1, flags=mpc.MPC_TRUNCATE | mpc.MPC_FOLDED)
     same(mpc, lane, z, oracle_conv(d, 16), "conv")
     same(mpc, lane, lane.conv2d(x, w, a, b, c, k // 2, 1), oracle_conv(d, 16), "conv, plain")      # opens the filter too
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 700, 40), (17, 64, 33), (33, 130, 128), (65, 17, 63), (129, 33, 70), (300, 3, 200), (64, 1300, 40), (1000, 300, 5)])
+def test_three_parties(mpc, lane, M, K, N):
+    """Masks' planes of all parties (plain), the opened words alone (prepared), the weight mask opened ahead."""
+    import oracle
+    from paper_2209_13643_amd import synth
+    print(f"one-launch opening, three parties {M}x{K}x{N}", flush=True)
+    rng = np.random.default_rng(M * 31 + K)
+    A, Bm = synth.rand_words(rng, (M, K)), synth.rand_words(rng, (K, N))
+    words = dict(x=synth.rand_words(rng, (M, K)), y=synth.rand_words(rng, (K, N)), a=A, b=Bm, c=oracle.ring_matmul(A, Bm))
+    sh = {k: synth.share_additive3(rng, v) for k, v in words.items()}
+    want = oracle.beaver_matmul3(*(sh[k] for k in ("x", "y", "a", "b", "c")))
+    x, y, a, b, c = (tuple(mpc.to_device(p) for p in sh[k]) for k in ("x", "y", "a", "b", "c"))
+
+    def check(z, what):
+        lane.sync()
+        for i in range(3):
+            g = mpc.to_host(z[i])
+            assert np.array_equal(g, want[i]), f"{what}: party {i} differs in {(g != want[i]).sum()} of {g.size} words"
+
+    check(lane.beaver_matmul3(x, y, a, b, c), "plain")
+    f = lane.open3(lane.sub3(y, b))
+    check(lane.beaver_matmul3(x, y, a, b, c, f_public=f), "weight mask opened ahead")
+    right, left = lane.prepare_matmul3(a, b, f)
+    check(lane.beaver_matmul3_prepared(x, a, c, right, left), "prepared")
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130, 131072, 131073, 131072 + 129, 262144 + 77, 600001])
+def test_three_party_rescale(mpc, lane, n):
+    """One launch: fewer elements than a wave, ragged tiles, one or two elements per thread, several tiles per workgroup."""
+    import oracle
+    from paper_2209_13643_amd import synth
+    print(f"one-launch rescale n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    z = synth.share_additive3(rng, synth.normal_fixed(rng, n, 300.0) * np.uint64(1 << 16))
+    r, rt = synth.deal_trunc3_pair(rng, n)
+    want = oracle.truncate3(z, r, rt)
+    up = lambda t: tuple(mpc.to_device(p) for p in t)
+    got = lane.truncate3(up(z), up(r), up(rt))
+    lane.sync()
+    for i in range(3):
+        assert np.array_equal(mpc.to_host(got[i]), want[i]), f"party {i}"
