@@ -457,7 +457,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g)
     load_addend();
     // The explicit accumulator reads below are opaque to the compiler's hazard
     // handling: give the last MFMA (8 passes) time to retire before the first read.
-    if constexpr (NH == 2) asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 
     // ---- epilogue: recombine, add, truncate, store.
     static_for<NH>([&](auto ct) {
@@ -480,23 +480,15 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g)
         // 256 accumulator registers into vector registers at the loop exit, which leaves no
         // room for anything else to stay live across the main loop); the two column halves
         // are fenced from each other, inside a half the 16 words are independent chains.
-        // With half the accumulators all of a wave's registers fit the vector file, and the words are read as they are (1x1
-        // convolution of 64 to 256 channels 330 -> 322 us, per-head Q K^T 304 -> 296).  Fewer vector instructions on top of
-        // that (a shorter recombination of short contractions, the truncation as two funnel shifts) gained nothing.
         u64 z[16];
         static_for<16>([&](auto vt) {
             constexpr int v = decltype(vt)::value;
             int d[8];
-            if constexpr (NH == 2)
-                asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
-                             "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
-                             : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]), "=&v"(d[7])
-                             : "a"(acc[c][0][v]), "a"(acc[c][1][v]), "a"(acc[c][2][v]), "a"(acc[c][3][v]),
-                               "a"(acc[c][4][v]), "a"(acc[c][5][v]), "a"(acc[c][6][v]), "a"(acc[c][7][v]));
-            else {
-#pragma unroll
-                for (int sg = 0; sg < 8; ++sg) d[sg] = acc[c][sg][v];
-            }
+            asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\tv_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
+                         "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\tv_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15"
+                         : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]), "=&v"(d[7])
+                         : "a"(acc[c][0][v]), "a"(acc[c][1][v]), "a"(acc[c][2][v]), "a"(acc[c][3][v]),
+                           "a"(acc[c][4][v]), "a"(acc[c][5][v]), "a"(acc[c][6][v]), "a"(acc[c][7][v]));
             z[v] = recombine(d) + add[v];
         });
         // local truncation (shift and party are uniform over the workgroup): party 0 shifts, party 1 negates around the shift
