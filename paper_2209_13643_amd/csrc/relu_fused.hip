@@ -310,9 +310,9 @@ __global__ __launch_bounds__(NP * kWave, (NP == 3 || COPY) && V == 2 ? 3 : 4) vo
 // words of the same lane, every later one the words of lanes j and j ^ d: both lanes form the same word, load the same
 // triple words and store the same masked words, so no lane ever moves data and element k of the lane finds its carry
 // in the lane's own word at the end.
-// 2 097 152 elements: 0.378 ms as ten launches, 0.151 ms here (256 compulsory bytes per element: 3.6 TB/s; 0.131 ms through
-// LDS; the levels' vector work, the same for every level, is half of the rest).  With the received words behind the next
-// triples 0.155 ms.  1024 / 1536 / 3072 workgroups: 0.155 / 0.150 / 0.152 ms.
+// 2 097 152 elements: 0.378 ms as ten launches, 0.135 ms here (256 compulsory bytes per element: 4.0 TB/s).  With two elements
+// per lane 0.151 ms (0.131 through LDS; the levels' vector work, the same for every level, is half of the rest), with the
+// received words behind the next triples 0.155 ms.
 __device__ __forceinline__ u64 from_lane_xor(u64 v, int mask)
 {
     const unsigned lo = __shfl_xor((unsigned)v, mask), hi = __shfl_xor((unsigned)(v >> 32), mask);
@@ -462,16 +462,19 @@ __device__ __forceinline__ unsigned msb_tiles(const FusedReluParty& p, const Pac
     }
 }
 
-// tiles 0 .. wide-1: 128 elements each, two per lane; the others 64 elements, one per lane (the last one ragged)
-constexpr int kMsbV = 2;
-constexpr size_t kMsbBox = 2 * kWave * kMsbV;      // words: two rows of whole words, or four of level 0
+// tiles 0 .. wide-1: 64 V elements each, V per lane; the others 64 elements, one per lane (the last one ragged).  Two
+// parties: four per lane, the rounds and the vector work of the deeper levels shared by twice the elements of two per lane
+// (2 097 152 elements 150 -> 135 us; VGG16 of 32 images on one lane 2.31 -> 2.25 ms, on four lanes, where the 168 registers no
+// longer fit beside the GEMM's, 0.7 % more).  Three parties: two per lane (four 2 % slower).
+constexpr int msb_v(int parties) { return parties == 2 ? 4 : 2; }
+constexpr size_t msb_box(int v) { return 2 * kWave * (size_t)v; }      // words: two rows of whole words, or four of level 0
 template <int NP, bool COPY>
-__global__ __launch_bounds__(NP * kWave, 4) void k_relu_fused_msb(FusedRelu q, PackedTriples g, unsigned wide)
+__global__ __launch_bounds__(NP * kWave, NP == 2 ? 3 : 4) void k_relu_fused_msb(FusedRelu q, PackedTriples g, unsigned wide)
 {
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const Wire<NP, COPY> wire(q.box, party, kMsbBox);
-    const unsigned tile = msb_tiles<NP, kMsbV>(q.p[party], g, wire, party, blockIdx.x, 0, wide, 0, q.n);
-    msb_tiles<NP, 1>(q.p[party], g, wire, party, tile, wide, q.tiles, (size_t)wide * kMsbV * kWave, q.n);
+    const Wire<NP, COPY> wire(q.box, party, msb_box(wide ? msb_v(NP) : 1));
+    const unsigned tile = msb_tiles<NP, msb_v(NP)>(q.p[party], g, wire, party, blockIdx.x, 0, wide, 0, q.n);
+    msb_tiles<NP, 1>(q.p[party], g, wire, party, tile, wide, q.tiles, (size_t)wide * msb_v(NP) * kWave, q.n);
 }
 
 constexpr size_t kPoolBox = (size_t)kRows * kWave * 2;        // words: four rows of the first level's pairs
@@ -552,19 +555,23 @@ __global__ __launch_bounds__(NP * kWave, PACKED ? 4 : 3) void k_maxpool_fused(Fu
 // Workgroups of a launch, [parties - 2]: as many as their receive buffers fit the L2 of their XCD (a three-party
 // workgroup has six of them).  Whole words, 2 097 152 elements: two parties 512 / 1024 / 2048 workgroups 0.315 / 0.307 /
 // 0.315 ms; three parties 320 / 384 / 512 workgroups 0.81 / 0.70 / 0.58 ms (2.12 ms as eleven launches).
-// Sign-only: two parties 1024 / 2048 workgroups 0.155 / 0.151 ms; three parties 768 .. 2048 workgroups level
+// Sign-only: two parties 768 / 1024 / 1280 workgroups 0.144 / 0.141 / 0.145 ms; three parties 768 .. 2048 workgroups level
 // (0.99 ms as eleven launches).
-constexpr unsigned kBlocks[2] = { 1024, 512 }, kMsbBlocks[2] = { 2048, 1536 };
+constexpr unsigned kBlocks[2] = { 1024, 512 }, kMsbBlocks[2] = { 1024, 1536 }, kMsbPoolBlocks[2] = { 2048, 1536 };
 constexpr int kMaxBlockPairs[2] = { 2, 6 };        // ordered pairs of parties: receive buffers per workgroup
 
 // two elements per thread (16-byte accesses) once one element per thread would need a second round of workgroups
 int width(size_t n, unsigned blocks) { return n > (size_t)blocks * kWave ? 2 : 1; }
 unsigned tiles_of(size_t n, int v) { return (unsigned)((n + kWave * v - 1) / (kWave * v)); }
-unsigned wide_tiles(size_t n, unsigned blocks) { return width(n, blocks) == kMsbV ? (unsigned)(n / (kWave * kMsbV)) : 0; }
-unsigned msb_tiles(size_t n, unsigned blocks)
+// sign-only chain: wide tiles and all tiles of a call
+unsigned wide_tiles(int parties, size_t n)
 {
-    const unsigned wide = wide_tiles(n, blocks);
-    return wide + tiles_of(n - (size_t)wide * kWave * kMsbV, 1);
+    return width(n, kMsbBlocks[parties - 2]) == 2 ? (unsigned)(n / (kWave * msb_v(parties))) : 0;
+}
+unsigned msb_tile_count(int parties, size_t n)
+{
+    const unsigned wide = wide_tiles(parties, n);
+    return wide + tiles_of(n - (size_t)wide * kWave * msb_v(parties), 1);
 }
 unsigned least(unsigned a, unsigned b) { return a < b ? a : b; }
 
@@ -600,15 +607,15 @@ int launch_relu_fused(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, int 
 
 size_t relu_fused_msb_box_bytes(int parties, size_t n, bool copies)
 {
-    const unsigned blocks = kMsbBlocks[parties - 2];
-    return (size_t)least(msb_tiles(n, blocks), blocks) * kMaxBlockPairs[parties - 2] * (copies ? 2 : 1) * kMsbBox * sizeof(u64);
+    return (size_t)least(msb_tile_count(parties, n), kMsbBlocks[parties - 2]) * kMaxBlockPairs[parties - 2] * (copies ? 2 : 1) *
+           msb_box(wide_tiles(parties, n) ? msb_v(parties) : 1) * sizeof(u64);
 }
 
 int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, const PackedTriples& g, bool copies)
 {
     if (q.n == 0 || q.n >= ((size_t)1 << 37) || (copies && parties != 2)) return MPC_EINVAL;
-    const unsigned blocks = kMsbBlocks[parties - 2], wide = wide_tiles(q.n, blocks);
-    q.tiles = msb_tiles(q.n, blocks);
+    const unsigned blocks = kMsbBlocks[parties - 2], wide = wide_tiles(parties, q.n);
+    q.tiles = msb_tile_count(parties, q.n);
     const dim3 grid(least(q.tiles, blocks));
     if (copies)            hipLaunchKernelGGL((k_relu_fused_msb<2, true>), grid, dim3(2 * kWave), 0, st, q, g, wide);
     else if (parties == 2) hipLaunchKernelGGL((k_relu_fused_msb<2, false>), grid, dim3(2 * kWave), 0, st, q, g, wide);
@@ -619,7 +626,7 @@ int launch_relu_fused_msb(mpc_ctx* c, hipStream_t st, int parties, FusedRelu q, 
 
 size_t maxpool_fused_box_bytes(int parties, bool packed, size_t n_out)
 {
-    const unsigned blocks = (packed ? kMsbBlocks : kBlocks)[parties - 2];
+    const unsigned blocks = (packed ? kMsbPoolBlocks : kBlocks)[parties - 2];
     return (size_t)least(tiles_of(n_out, 1), blocks) * kMaxBlockPairs[parties - 2] * kPoolBox * sizeof(u64);
 }
 
@@ -628,7 +635,7 @@ int launch_maxpool_fused(mpc_ctx* c, hipStream_t st, int parties, FusedPool q, i
     if (q.n_out == 0 || q.n_out >= ((size_t)1 << 36)) return MPC_EINVAL;
     const bool packed = g1 != nullptr;
     q.tiles = tiles_of(q.n_out, 1);
-    const dim3 grid(least(q.tiles, (packed ? kMsbBlocks : kBlocks)[parties - 2])), block(parties * kWave);
+    const dim3 grid(least(q.tiles, (packed ? kMsbPoolBlocks : kBlocks)[parties - 2])), block(parties * kWave);
     const PackedTriples none{};
     if (parties == 2) {
         if (packed)    hipLaunchKernelGGL((k_maxpool_fused<2, true, 0>), grid, block, 0, st, q, *g1, *g2);

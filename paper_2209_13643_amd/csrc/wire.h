@@ -9,7 +9,9 @@ constexpr int kWave = 64;
 
 typedef u64 u64v2u __attribute__((ext_vector_type(2), aligned(8)));
 
-// V consecutive words at scalar base + 32-bit byte offset, any 8-byte aligned address, read once
+// V consecutive words at scalar base + 32-bit byte offset, any 8-byte aligned address, read once.  Four words per lane are two
+// accesses to the same lines, of which the second should find them: not non-temporal (sign-only ReLU of 2 097 152 elements
+// 141 -> 135 us).
 template <int V> __device__ __forceinline__ Pack<V> ld_once(const u64* p, unsigned off)
 {
     const u8* a = reinterpret_cast<const u8*>(p) + off;
@@ -17,7 +19,8 @@ template <int V> __device__ __forceinline__ Pack<V> ld_once(const u64* p, unsign
     if constexpr (V >= 2) {
 #pragma unroll
         for (int k = 0; k < V; k += 2) {
-            const u64v2u t = __builtin_nontemporal_load(reinterpret_cast<const u64v2u*>(a + 8 * k));
+            const u64v2u* const at = reinterpret_cast<const u64v2u*>(a + 8 * k);
+            const u64v2u t = V > 2 ? *at : __builtin_nontemporal_load(at);
             r.v[k] = t.x; r.v[k + 1] = t.y;
         }
     }

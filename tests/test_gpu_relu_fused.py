@@ -158,3 +158,24 @@ def test_copies_inside_the_launch(mpc, n, queues, chain):
     b = buf.cpu().numpy()
     assert (b[:at] == 0xA5).all() and (b[at + nbytes:] == 0xA5).all(), "written outside the workspace"
     ln.close()
+
+
+@pytest.mark.parametrize("exchange", ["put", "copy"])
+@pytest.mark.parametrize("n", [65536, 65537, 65536 + 255, 65536 + 256 + 65, 262144 - 1, 262144 + 191, 600000])
+def test_sign_only_relu_four_elements_per_lane(mpc, n, exchange):
+    """The packed chain takes four elements per lane from 65 537 elements on, its last n mod 256 one per lane; several tiles
+    per workgroup from 262 145 on."""
+    print(f"sign-only relu n={n} {exchange}", flush=True)
+    rng = np.random.default_rng(n)
+    xs = synth.share_additive(rng, synth.normal_fixed(rng, n, 4.0))
+    mat = synth.deal_relu_material(rng, n)
+    want = oracle.relu(xs, mat)
+    ln = mpc.Lane(0, single_queue=True)
+    ln.set_exchange(exchange)
+    x = dev(mpc, xs)
+    y, sb, sa = ln.relu(x, ln.pack_material(mpc.material_to_device(mat)), want_sign=True, packed=True, out=x if n % 2 else None)
+    ln.sync()
+    equal(mpc, y, want.y, "output")
+    equal(mpc, sb, want.s_bit, "sign bit share")
+    equal(mpc, sa, want.s_arith, "sign arithmetic share")
+    ln.close()
