@@ -545,11 +545,17 @@ __global__ __launch_bounds__(64 * KW, 2) void k_sliced_gemm(GemmDev g)
     const GemmParty& P = g.p[party];
     const unsigned tile = (id & 7) * (unsigned)P.per_xcd + q;
     if (q >= (unsigned)P.per_xcd || tile >= (unsigned)P.tiles) return;
-    const unsigned item = g.by_item(tile), rem = tile - item * g.per_item;
+    const unsigned t2 = g.by_item(tile), rem = tile - t2 * g.per_item;
+    const unsigned split = g.by_batch(t2), item = t2 - split * g.batch;
     const unsigned mt = g.by_panel(rem), nt = rem - mt * g.panel_tiles;
     const int m0 = (int)mt * 32, n0 = (int)nt * 32;
     const int T0 = P.seg[0].KB / KS, T = T0 + (g.nseg > 1 ? P.seg[1].KB / KS : 0);
-    const int per = (T + KW - 1) / KW, first = wave * per, last = first + per < T ? first + per : T;      // this wave's steps
+    // the workgroup's steps (all, or a slice of a contraction split over workgroups as well), and this wave's
+    const int begin = (int)split * g.steps_per_split, end = begin + g.steps_per_split < T ? begin + g.steps_per_split : T;
+    const int per = (end - begin + KW - 1) / KW, first = begin + wave * per, last = first + per < end ? first + per : end;
+    const bool partial = g.ksplit > 1;
+    const u64* const addend = partial ? nullptr : P.addend; const u64* const addend2 = partial ? nullptr : P.addend2;
+    u64* const out = partial ? g.partial + ((size_t)split * g.nparty + party) * g.batch * g.out_bstride : P.out;
 
     // the workgroup's words: thread t has words t and t + 64 KW (of 1024), in the accumulators' order
     constexpr int WPT = 16 / KW;
@@ -559,7 +565,7 @@ __global__ __launch_bounds__(64 * KW, 2) void k_sliced_gemm(GemmDev g)
         const int v = wave + KW * k, row = m0 + (v >> 2) * 8 + g2 * 4 + (v & 3), col = n0 + i32;
         ok[k] = row < g.M && col < g.N;
         at[k] = (size_t)item * g.out_bstride + (size_t)(row < g.M ? row : g.M - 1) * g.N + (col < g.N ? col : g.N - 1);
-        add[k] = (P.addend ? P.addend[at[k]] : 0) + (P.addend2 ? P.addend2[at[k]] : 0);
+        add[k] = (addend ? addend[at[k]] : 0) + (addend2 ? addend2[at[k]] : 0);
     }
 
     v16i acc[8];
@@ -658,8 +664,8 @@ __global__ __launch_bounds__(64 * KW, 2) void k_sliced_gemm(GemmDev g)
         u64 z = add[k];
 #pragma unroll
         for (int w = 0; w < KW; ++w) z += part[w][wave + KW * k][lane];
-        if (g.trunc_bits) z = party == 0 ? z >> g.trunc_bits : (u64)0 - (((u64)0 - z) >> g.trunc_bits);
-        if (ok[k]) P.out[at[k]] = z;
+        if (g.trunc_bits && !partial) z = party == 0 ? z >> g.trunc_bits : (u64)0 - (((u64)0 - z) >> g.trunc_bits);
+        if (ok[k]) out[at[k]] = z;
     }
 }
 
@@ -680,6 +686,14 @@ __global__ __launch_bounds__(256) void k_splitk_finish(GemmArgs g)
         if (g.trunc_bits) z = party == 0 ? (z >> g.trunc_bits) : (u64)0 - (((u64)0 - z) >> g.trunc_bits);
         g.out[party][w] = z;
     }
+}
+
+// finishing pass of a contraction split over workgroups
+void launch_finish(hipStream_t st, const GemmArgs& g)
+{
+    const size_t total = (size_t)g.batch * g.out_bstride * g.nparty;
+    size_t blocks = (total + 255) / 256; if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_splitk_finish, dim3((unsigned)blocks), dim3(256), 0, st, g);
 }
 
 template <int WGM, int WGN, bool CONV, int NS = 3, int NH = 2>
@@ -730,39 +744,41 @@ int launch_cfg(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
     dim3 grid((unsigned)wgs, 1, 1);
     const int pi = prof_begin(c, MPC_PROF_GEMM_KERNEL, st);
     hipLaunchKernelGGL(kern, grid, dim3(C::NT), C::LDS_BYTES, st, d);
-    if (g.ksplit > 1) {
-        const size_t total = (size_t)g.batch * g.out_bstride * g.nparty;
-        size_t blocks = (total + 255) / 256; if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(k_splitk_finish, dim3((unsigned)blocks), dim3(256), 0, st, ga);
-    }
+    if (g.ksplit > 1) launch_finish(st, ga);
     prof_end(c, MPC_PROF_GEMM_KERNEL, pi, st);
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }
 
+// g.ksplit_p[p] slices of g.steps_per_split steps per party
 template <bool CONV, int KW>
 int launch_sliced(mpc_ctx* c, hipStream_t st, const GemmArgs& g)
 {
     GemmDev d{};
     const int tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32;
     const long long tiles = (long long)tiles_m * tiles_n * g.batch;
-    if (tiles >= (1ll << 27)) return MPC_EINVAL;
+    unsigned blocks = 0;
     for (int p = 0; p < g.nparty; ++p) {
         GemmParty& q = d.p[p];
         q.seg[0] = g.seg[p][0]; q.seg[1] = g.seg[p][1];
         q.addend = g.addend[p]; q.addend2 = g.addend2[p]; q.out = g.out[p];
-        q.tiles = (int)tiles; q.per_xcd = (int)((tiles + 7) / 8);
+        const long long t = tiles * (g.ksplit > 1 ? g.ksplit_p[p] : 1);
+        if (t >= (1ll << 27)) return MPC_EINVAL;
+        q.tiles = (int)t; q.per_xcd = (int)((t + 7) / 8);
+        blocks += (unsigned)q.per_xcd * 8;
     }
     d.M = g.M; d.N = g.N; d.rows_L = g.rows_L; d.nseg = g.nseg; d.nparty = g.nparty; d.trunc_bits = g.trunc_bits;
+    d.ksplit = g.ksplit; d.steps_per_split = g.steps_per_split; d.partial = g.partial;
     d.out_bstride = g.out_bstride;
-    d.heavy_blocks = (unsigned)(d.p[0].per_xcd * 8);          // of each party
+    d.heavy_blocks = (unsigned)(d.p[g.nparty == 2 ? 1 : 0].per_xcd * 8);          // of the party that comes first (three: of each)
     d.per_item = (unsigned)tiles_m * (unsigned)tiles_n; d.batch = (unsigned)g.batch;
     d.panel_tiles = (unsigned)tiles_n;
-    d.by_item = Divider::by(d.per_item); d.by_panel = Divider::by(d.panel_tiles);
+    d.by_item = Divider::by(d.per_item); d.by_batch = Divider::by(d.batch); d.by_panel = Divider::by(d.panel_tiles);
     d.conv = g.conv;
     d.by_Wo = Divider::by(CONV ? (unsigned)g.conv.Wo : 1); d.by_Ho = Divider::by(CONV ? (unsigned)g.conv.Ho : 1);
     const int pi = prof_begin(c, MPC_PROF_GEMM_KERNEL, st);
-    hipLaunchKernelGGL((k_sliced_gemm<CONV, KW>), dim3((unsigned)(d.p[0].per_xcd * 8 * g.nparty)), dim3(64 * KW), 0, st, d);
+    hipLaunchKernelGGL((k_sliced_gemm<CONV, KW>), dim3(blocks), dim3(64 * KW), 0, st, d);
+    if (g.ksplit > 1) launch_finish(st, g);
     prof_end(c, MPC_PROF_GEMM_KERNEL, pi, st);
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
@@ -820,17 +836,43 @@ static int tile_kind(int M, int N, int batch, int longest_steps, bool asymmetric
 // Beyond 1024 workgroups the larger tiles' reuse of operands wins, beyond 64 steps the split over more workgroups (512 steps:
 // 48 / 108 / 98).  Convolutions: 8 x 14 x 14 x 128, 3x3, 42.2 / 32.7 / 37.0; 4 x 14 x 14 x 64 27.5 / 18.6 / 17.9.
 // mpc_set_gemm_small_tile(0, ...) switches this form off as well.
-constexpr int kSlicedMaxSteps = 64;
+//
+// Longer contractions with at most 256 workgroups: by cost, in steps of eight waves on a compute unit (about 1.05 us).  The
+// contraction is then split over workgroups too, over as many as the chip holds at once and the caller's partial products
+// have room for (*slices, of which the finishing pass costs 5).  Tiles above: rounds of workgroups x (steps per slice + 6), a
+// step of the 32-row tile counting half; sliced: steps per wave + 4.  Us, tiles above / sliced:
+//   2 x 25088 x 10      50.3 / 27.8     60 x 8000 x 400      49.3 / 40.8     128 x 4608 x 512 (left above)     50.7 / 52.7
+//   64 x 2048 x 128     29.5 / 19.5     100 x 20000 x 100    90.2 / 64.7     4 x 25088 x 1000 (left above)    130.4 / 130.1
+//   32 x 4096 x 1000    35.4 / 30.0     300 x 4000 x 200     53.8 / 49.8     64 x 8000 x 2000 (left above)    118.1 / 160.2
+//   30 x 1100 x 4000    37.2 / 28.4     200 x 3001 x 333     49.0 / 43.6     3x3 convolution of 4 x 7 x 7 x 256  35.5 / 30.3
+constexpr int kSlicedMaxSteps = 64, kFinishCost = 5;
 constexpr long long kSlicedMaxBlocks = 1024, kSlicedWideBlocks = 256;
-static int sliced_waves(const GemmArgs& g, int longest_steps)
+static int sliced_waves(const GemmArgs& g, int longest, const int steps[3], int* slices)
 {
-    const int max_steps = g_small_max_steps.load(std::memory_order_relaxed);
-    if (longest_steps > kSlicedMaxSteps || max_steps == 0) return 0;
-    const long long blocks = (long long)((g.M + 31) / 32) * ((g.N + 31) / 32) * g.batch * g.nparty;
-    if (blocks > kSlicedMaxBlocks || tile_kind(g.M, g.N, g.batch, longest_steps, false) == 2) return 0;
-    // a lane's offset inside a left plane is 32 bits wide
-    if (g.conv.enabled && (g.conv.npix + 1) * g.conv.CB * 16 >= (1ll << 31)) return 0;
-    return blocks <= kSlicedWideBlocks ? 8 : 4;
+    *slices = 1;
+    if (g_small_max_steps.load(std::memory_order_relaxed) == 0) return 0;
+    const long long tiles = (long long)((g.M + 31) / 32) * ((g.N + 31) / 32) * g.batch, blocks = tiles * g.nparty;
+    if (blocks > kSlicedMaxBlocks || tile_kind(g.M, g.N, g.batch, longest, false) == 2) return 0;
+    // a lane's offset inside a plane is 32 bits wide
+    if ((g.conv.enabled ? (g.conv.npix + 1) * g.conv.CB : (long long)longest * KS * g.rows_L) * 16 >= (1ll << 31)) return 0;
+    if ((long long)longest * KS * g.N * 16 >= (1ll << 31)) return 0;
+    if (longest <= kSlicedMaxSteps) return blocks <= kSlicedWideBlocks ? 8 : 4;
+    if (blocks > kSlicedWideBlocks || g.nparty > 2) return 0;
+    auto blocks_of = [&](int per, long long t) {
+        long long n = 0;
+        for (int p = 0; p < g.nparty; ++p) n += t * ((steps[p] + per - 1) / per);
+        return n;
+    };
+    int s = 1;
+    while (s < g.ksplit && (longest + s) / (s + 1) >= 8 && blocks_of((longest + s) / (s + 1), tiles) <= kSlicedWideBlocks) ++s;
+    const int per = (longest + s - 1) / s;
+    const double cost = (per + 7) / 8 + 4 + (s > 1 ? kFinishCost : 0);
+    const int kind = tile_kind(g.M, g.N, g.batch, 1 << 30, false), tm = kind == 1 ? 128 : kind == 3 ? 32 : 64, tn = kind == 1 ? 64 : 128;
+    const long long large = blocks_of(g.steps_per_split, (long long)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * g.batch);
+    const double cost_large = ((large + 255) / 256) * (g.steps_per_split * (kind == 3 ? 0.5 : 1.0) + 6) + (g.ksplit > 1 ? kFinishCost : 0);
+    if (cost >= cost_large || (per + 7) / 8 > kMaxStepsExact) return 0;
+    *slices = s;
+    return 8;
 }
 
 // steps[p]: K steps party p contracts (steps[1] = 0 for a one-party launch).  Returns the number of slices
@@ -887,29 +929,37 @@ extern "C" int mpc_set_gemm_small_tile(int max_steps, int min_tiles)
 
 bool gemm_takes_three(const GemmArgs& g)
 {
-    return g.nparty == 3 && g.nseg == 2 && sliced_waves(g, (g.seg[0][0].KB + g.seg[0][1].KB) / KS) != 0;
+    const int n = (g.seg[0][0].KB + g.seg[0][1].KB) / KS, steps[3] = { n, n, n };
+    int slices;
+    return g.nparty == 3 && g.nseg == 2 && sliced_waves(g, n, steps, &slices) != 0;
+}
+
+// slices of `per` steps for every party, none empty
+static void split_over(GemmArgs& g, const int steps[3], int per)
+{
+    g.steps_per_split = per; g.ksplit = 1;
+    for (int p = 0; p < 2; ++p) {
+        g.ksplit_p[p] = p < g.nparty ? (steps[p] + per - 1) / per : 0;
+        if (g.ksplit_p[p] > g.ksplit) g.ksplit = g.ksplit_p[p];
+    }
 }
 
 int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
 {
     GemmArgs g = g_in;
     if (g.nparty < 1 || g.nparty > (gemm_takes_three(g) ? 3 : 2) || g.nseg < 1 || g.nseg > 2) return MPC_EINVAL;
-    int longest_steps = 0;
+    int longest_steps = 0, party_steps[3] = { 0, 0, 0 };
     {
-        int steps[3] = { 0, 0, 0 };
+        int (&steps)[3] = party_steps;
         for (int p = 0; p < g.nparty; ++p)
             for (int s = 0; s < g.nseg; ++s) steps[p] += g.seg[p][s].KB / KS;
         if (g.nparty == 3 && (steps[1] != steps[0] || steps[2] != steps[0])) return MPC_EINVAL;
         const int longest = steps[0] > steps[1] ? steps[0] : steps[1];
         longest_steps = longest;
         if (g.ksplit < 1 || !g.partial) g.ksplit = 1;
-        g.steps_per_split = (longest + g.ksplit - 1) / g.ksplit;
-        if (g.steps_per_split < 1 || g.steps_per_split > kMaxStepsExact) return MPC_ERANGE;
-        g.ksplit = 1;
-        for (int p = 0; p < 2; ++p) {
-            g.ksplit_p[p] = p < g.nparty ? (steps[p] + g.steps_per_split - 1) / g.steps_per_split : 0;      // no empty slice
-            if (g.ksplit_p[p] > g.ksplit) g.ksplit = g.ksplit_p[p];
-        }
+        const int per = (longest + g.ksplit - 1) / g.ksplit;
+        if (per < 1 || per > kMaxStepsExact) return MPC_ERANGE;
+        split_over(g, steps, per);
         // the longer contraction first (party 1's by construction of the callers)
         g.heavy_first = g.nparty == 2 && steps[1] > steps[0];
         if (g.nparty == 2 && steps[1] < steps[0]) return MPC_EINVAL;
@@ -926,7 +976,9 @@ int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
     // to 256 channels, 32 images: 361 -> 350 us a call with the shorter set-up.
     if (g.conv.enabled && g.conv.KH == 1 && g.conv.KW == 1 && g.conv.stride == 1 && g.conv.pad == 0 && g.conv.CB % KS == 0)
         g.conv = ConvGeom{};
-    if (const int kw = sliced_waves(g, longest_steps)) {
+    int slices = 1;
+    if (const int kw = sliced_waves(g, longest_steps, party_steps, &slices)) {
+        split_over(g, party_steps, (longest_steps + slices - 1) / slices);
         if (g.conv.enabled) return kw == 8 ? launch_sliced<true, 8>(c, st, g) : launch_sliced<true, 4>(c, st, g);
         return kw == 8 ? launch_sliced<false, 8>(c, st, g) : launch_sliced<false, 4>(c, st, g);
     }

@@ -1,6 +1,6 @@
 """GEMM launches with few output tiles: the waves of a workgroup share one 32 x 32 tile's contraction.  Edges of the tile,
 fewer steps than waves, the two numbers of waves (256 | 257 tiles of both parties), the longest contraction it takes (64 K
-steps) and one more, taps that cross k blocks, one, two and three parties, partial sums of a two-phase call; each
+steps) without a choice by cost, contractions split over workgroups as well, taps that cross k blocks, one, two and three parties, partial sums of a two-phase call; each
 shape also on the tiles of larger products, which the tuning call leaves as the only ones.  Against the oracle bit for bit."""
 import numpy as np
 import pytest
@@ -44,7 +44,7 @@ def same(mpc, lane, got, want, what):
 @pytest.mark.parametrize("M,K,N,batch", [
     (1, 1, 1, None), (31, 17, 33, None), (32, 64, 32, None), (33, 128, 31, None), (64, 250, 70, None), (65, 512, 129, None),
     (40, 1008, 20, None), (40, 1024, 33, None), (40, 1025, 20, None), (500, 40, 256, None), (513, 40, 256, None), (40, 48, 36, 32),
-    (2, 300, 100, 3),
+    (2, 300, 100, 3), (5, 4100, 33, None), (65, 2500, 40, None), (20, 1300, 24, 3), (2, 12000, 130, None), (100, 1100, 1000, None),
 ])
 def test_products(mpc, lane, M, K, N, batch):
     print(f"sliced {M}x{K}x{N} batch {batch}", flush=True)
@@ -62,7 +62,7 @@ def test_products(mpc, lane, M, K, N, batch):
 
 @pytest.mark.parametrize("B,H,W,Cin,Cout,k,pad,stride", [
     (1, 4, 4, 3, 20, 3, 1, 1), (2, 5, 7, 17, 33, 3, 1, 1), (1, 9, 9, 40, 64, 3, 0, 2), (2, 6, 6, 33, 40, 1, 0, 2), (3, 4, 4, 48, 96, 3, 1, 1),
-    (1, 6, 5, 16, 32, 5, 2, 1), (8, 12, 12, 20, 130, 3, 1, 1),
+    (1, 6, 5, 16, 32, 5, 2, 1), (8, 12, 12, 20, 130, 3, 1, 1), (2, 4, 4, 200, 40, 3, 1, 1), (1, 5, 5, 500, 33, 3, 1, 2),
 ])
 def test_convolutions(mpc, lane, B, H, W, Cin, Cout, k, pad, stride):
     print(f"sliced conv {B}x{H}x{W}x{Cin}->{Cout} k{k} s{stride}", flush=True)
@@ -75,7 +75,7 @@ def test_convolutions(mpc, lane, B, H, W, Cin, Cout, k, pad, stride):
     same(mpc, lane, z, oracle_conv(d, 16), "folded")
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 5, 3), (70, 200, 40), (33, 1024, 65)])
+@pytest.mark.parametrize("M,K,N", [(1, 5, 3), (70, 200, 40), (33, 1024, 65), (20, 5000, 50)])
 def test_one_and_three_parties(mpc, lane, M, K, N):
     rng = np.random.default_rng(M + K)
     L, R = synth.rand_words(rng, (M, K)), synth.rand_words(rng, (K, N))
