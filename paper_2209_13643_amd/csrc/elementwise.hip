@@ -304,6 +304,60 @@ __global__ __launch_bounds__(kThreads) void k_recode_im2col_t(Im2colTBatch bt)
     }
 }
 
+// The same planes for a 3x3 filter of stride 1 and padding 1, whose output pixels are the input's: one thread fills the
+// three units of a filter row (dx = 0, 1, 2) of one (dy, ci), which read the same 16 pixels moved by one: 18 loads instead
+// of 48, at indices Cin words apart (pixel p of the flattened batch reads p + (dy - 1) W + dx - 1; a neighbour inside the
+// image row is the neighbour in the run).  Fourteen launches of a VGG16 training step 418 -> 331 us, the step of 32 images
+// 7.35 -> 7.25 ms.
+__global__ __launch_bounds__(kThreads) void k_recode_im2col3_t(Im2colTBatch bt)
+{
+    const Im2colTArgs& a = bt.a[blockIdx.z];
+    const int rows = 9 * a.Cin, per_kb = 3 * a.Cin;
+    const int npix = a.B * a.H * a.W;
+    const size_t items = (size_t)a.KB_total * per_kb;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t it = (size_t)blockIdx.x * blockDim.x + threadIdx.x; it < items; it += stride) {
+        const int kb = (int)(it / per_kb), q = (int)(it - (size_t)kb * per_kb);
+        const int dy = q / a.Cin, ci = q - dy * a.Cin;
+        const int m = kb * 16;
+        int wo = m % a.W, ho = m / a.W % a.H;
+        unsigned ok = 0, left = 0, right = 0;           // bit t: pixel m + t has an input row, and a left / right neighbour in it
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            const int hi = ho + dy - 1;
+            const bool in = m + t < npix && hi >= 0 && hi < a.H;
+            ok |= (unsigned)in << t; left |= (unsigned)(in && wo > 0) << t; right |= (unsigned)(in && wo + 1 < a.W) << t;
+            if (++wo == a.W) { wo = 0; if (++ho == a.H) ho = 0; }
+        }
+        // loads at clamped pixels with no branch between them, masked afterwards
+        const int p0 = m + (dy - 1) * a.W - 1;
+        size_t idx[18];
+#pragma unroll
+        for (int t = 0; t < 18; ++t) {
+            const int p = p0 + t;
+            idx[t] = (size_t)(p < 0 ? 0 : p < npix ? p : npix - 1) * a.Cin + ci;
+        }
+        u64 v[18];
+#pragma unroll
+        for (int t = 0; t < 18; ++t) v[t] = a.src[idx[t]];
+        if (a.src2) {
+            u64 w[18];
+#pragma unroll
+            for (int t = 0; t < 18; ++t) w[t] = a.src2[idx[t]];
+#pragma unroll
+            for (int t = 0; t < 18; ++t) v[t] += w[t];
+        }
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+            const unsigned there = dx == 0 ? left : dx == 1 ? ok : right;
+            u64 unit[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) unit[t] = (there >> t) & 1 ? v[t + dx] : 0;
+            store_unit(unit, a.dst + ((size_t)kb * rows + (dy * 3 + dx) * a.Cin + ci) * 16, a.digit_stride);
+        }
+    }
+}
+
 // Element-wise Alg. 1 after the exchange (blockIdx.y = party): e, f from the
 // own and the received masked words, z_i = c_i + e*b_i + a_i*f (+ e*f), then the
 // optional local truncation.  With `mask_from_sign` the second operand is the
@@ -617,8 +671,11 @@ int launch_recode_im2col_t(mpc_ctx* c, hipStream_t st, const Im2colTArgs* sets, 
     if (count < 1 || count > 3) return MPC_EINVAL;
     Im2colTBatch bt{};
     for (int i = 0; i < count; ++i) bt.a[i] = sets[i];
-    const size_t items = (size_t)sets[0].KB_total * sets[0].KH * sets[0].KW * sets[0].Cin;
-    hipLaunchKernelGGL(k_recode_im2col_t, dim3(grid_for(items), 1, count), dim3(kThreads), 0, st, bt);
+    const Im2colTArgs& s = sets[0];          // the sets of a launch have one geometry
+    const bool rows_of_three = s.KH == 3 && s.KW == 3 && s.stride == 1 && s.pad == 1 && (long long)s.B * s.H * s.W + 2ll * s.W + 32 < (1ll << 31);
+    const size_t items = (size_t)s.KB_total * s.KH * s.Cin * (rows_of_three ? 1 : s.KW);
+    if (rows_of_three) hipLaunchKernelGGL(k_recode_im2col3_t, dim3(grid_for(items), 1, count), dim3(kThreads), 0, st, bt);
+    else               hipLaunchKernelGGL(k_recode_im2col_t, dim3(grid_for(items), 1, count), dim3(kThreads), 0, st, bt);
     MPC_HIP(c, hipGetLastError());
     return MPC_OK;
 }

@@ -86,3 +86,15 @@ def test_masked_recodings_of_ragged_tiles(mpc, call, M, K, N):
     for i in range(2):
         assert np.array_equal(mpc.to_host(z[i]), want[i]), f"party {i}"
     lane.close()
+
+
+@pytest.mark.parametrize("B,H,W,Cin", [(1, 1, 1, 3), (2, 2, 2, 5), (1, 3, 5, 64), (3, 4, 4, 65), (2, 16, 16, 7), (1, 5, 17, 33), (2, 31, 3, 20), (1, 32, 32, 3)])
+def test_transposed_im2col_of_three_by_three_filters(mpc, lane, B, H, W, Cin):
+    """Filter gradient of a 3x3 filter with stride 1 and padding 1: units of 16 pixels that cross image rows and images,
+    neighbours outside the row, the end of the batch, images narrower and wider than a unit."""
+    print(f"im2col3_t {B}x{H}x{W}x{Cin}", flush=True)
+    rng = np.random.default_rng(B * H * W + Cin)
+    x = synth.rand_words(rng, (B, H, W, Cin)); g = synth.rand_words(rng, (B, H, W, 6))
+    got = lane.ring_conv2d_grad_w(mpc.to_device(x), mpc.to_device(g), 3, 3, 1, 1)
+    lane.sync()
+    assert np.array_equal(mpc.to_host(got), oracle.ring_conv2d_grad_w(x, g, 3, 3, 1, 1))
