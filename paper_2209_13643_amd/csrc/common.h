@@ -125,8 +125,8 @@ static inline int lane_fanout(mpc_ctx* c)
 
 // A call without tiles on a lane with three streams runs as on a single queue, on stream 0: the parties' kernels and
 // both directions of a copy share launches, and no round waits for events.  Three streams pay only where the caller
-// asks for tiles (or Alg. 3's two phases) to travel under computation.  Both ways measured, copy exchange, host and
-// device: 64 x 256 x 128 Beaver product 150 us on three streams, 28 us here, ReLU on its output 373 / 75 us;
+// asks for tiles (or Alg. 3's two phases) to travel under computation.  Both ways measured, copy exchange launch by launch,
+// host and device: 64 x 256 x 128 Beaver product 150 us on three streams, 28 us here, ReLU on its output 373 / 75 us;
 // 2048 x 1024 x 1024: 360 / 301 us and 1579 / 1179 us.
 struct Narrow {
     mpc_ctx* c; hipStream_t s1, s2; bool on;

@@ -27,6 +27,10 @@
 // gathers filter taps from NHWC activation planes (implicit im2col); taps
 // that fall into the zero padding read the all-zero row that ends every
 // activation plane.
+//
+// Products with few output tiles take another form (k_sliced_gemm): a workgroup
+// has one 32 x 32 tile, its waves slices of the contraction, and operands go
+// straight into registers.
 #include <atomic>
 #include "common.h"
 
