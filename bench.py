@@ -317,11 +317,11 @@ def per_config_table(args):
                          "whole_words_remote_store": {"ms": t["relu_put_ms"], "elems_per_s": n / (t["relu_put_ms"] * 1e-3),
                                                       "frac_of_hbm_peak": h(RELU_PUT_BYTES_PER_ELEMENT, t["relu_put_ms"])},
                          "whole_words_copy": {"ms": t["relu_ms"], "elems_per_s": n / (t["relu_ms"] * 1e-3),
-                                              "frac_of_hbm_peak": h(RELU_BYTES_PER_ELEMENT, t["relu_ms"])},
+                                              "frac_of_hbm_peak": h(sum(r["relu_copy_bytes"] for r in rl) / n, t["relu_ms"])},
                          "sign_only_remote_store": {"ms": t["msb_put_ms"], "elems_per_s": n / (t["msb_put_ms"] * 1e-3),
                                                     "frac_of_hbm_peak": h(RELU_MSB_PUT_BYTES_PER_ELEMENT, t["msb_put_ms"])},
                          "sign_only_copy": {"ms": t["msb_ms"], "elems_per_s": n / (t["msb_ms"] * 1e-3),
-                                            "frac_of_hbm_peak": h(RELU_MSB_BYTES_PER_ELEMENT, t["msb_ms"])}}
+                                            "frac_of_hbm_peak": h(sum(r["msb_copy_bytes"] for r in rl) / n, t["msb_ms"])}}
         if args.layers:
             e["layers"] = [{k: (round(v, 6) if isinstance(v, float) else v) for k, v in r.items()} for r in rows]
         table.append(e)

@@ -42,18 +42,27 @@ def gemm_algorithmic_bytes(L) -> int:
     return 2 * 8 * (2 * act + 2 * wts + 2 * out)
 
 
+def relu_copy_bytes(n: int, packed: bool) -> float:
+    """Bytes per element that a two-party ReLU call with the copy exchange is priced at: the round-by-round chain's, or the
+    compulsory ones where the rounds and their copies run as one launch (up to 2^18 elements), whose exchanged words and
+    carried state stay in the caches and registers."""
+    if n <= 1 << 18:
+        return RELU_MSB_PUT_BYTES if packed else RELU_PUT_BYTES
+    return RELU_MSB_BYTES if packed else RELU_BYTES
+
+
 def folded_call_algorithmic_bytes(L) -> int:
     """The folded call with the remote-store exchange, every word counted once per pass that has to touch it.  Activation
-    (8-byte words): mask and send e_0 (read x_0, a_0; write e_0), party 1's recode (read x_1, a_1, e_0; write e_1 and the
-    planes of e), party 0's recode (read x_0, e_1; write the planes of x_0 + e_1) = 11 passes, and the same 11 over the
-    right operand when it is a share too (per-head attention).  GEMM launch: the planes of x_0 + e_1, e, a_1 (3 x
-    activation) and of b_0 + f, b_1, f (3 x right operand), the addends c_i and the outputs z_i."""
+    (8-byte words): the opening launch reads x_0, a_0, x_1, a_1 and writes the planes of x_0 + e_1 and e (the masked words
+    go through receive buffers that stay in the L2) = 6 passes, and the same 6 over the right operand when it is a share
+    too (per-head attention).  GEMM launch: the planes of x_0 + e_1, e, a_1 (3 x activation) and of b_0 + f, b_1, f (3 x
+    right operand), the addends c_i and the outputs z_i."""
     if isinstance(L, synth.Conv):
         act, wts, out, shared_right = L.B * L.H * L.W * L.Cin, L.KH * L.KW * L.Cin * L.Cout, L.B * L.Ho * L.Wo * L.Cout, False
     else:
         b = max(L.batch, 1)
         act, wts, out, shared_right = b * L.M * L.K, b * L.K * L.N, b * L.M * L.N, L.batch > 1
-    return 8 * (14 * act + (14 if shared_right else 3) * wts + 4 * out)
+    return 8 * (9 * act + (9 if shared_right else 3) * wts + 4 * out)
 
 
 def bench_layers(idx: int, reps: int = 20, workload=None):
@@ -148,7 +157,8 @@ def bench_layers(idx: int, reps: int = 20, workload=None):
         if mat:
             rl, rn = lane.profile(mpc.PROF_RELU)
             row.update(relu_n=n_out, relu_ms=rl / rn, relu_elems_per_s=n_out / (rl / rn * 1e-3),
-                       hbm_frac=RELU_BYTES * n_out / (rl / rn * 1e-3) / HBM_PEAK,
+                       relu_copy_bytes=relu_copy_bytes(n_out, False) * n_out, msb_copy_bytes=relu_copy_bytes(n_out, True) * n_out,
+                       hbm_frac=relu_copy_bytes(n_out, False) * n_out / (rl / rn * 1e-3) / HBM_PEAK,
                        relu_put_ms=put_ms, relu_put_elems_per_s=n_out / (put_ms * 1e-3),
                        put_hbm_frac=RELU_PUT_BYTES * n_out / (put_ms * 1e-3) / HBM_PEAK)
             # the same ReLU on the sign's carry chain only, packed material
@@ -163,7 +173,7 @@ def bench_layers(idx: int, reps: int = 20, workload=None):
                     lane.relu(z, mat, out=y, packed=True)
                 lane.sync(); lane.set_profiling(False)
                 rl, rn = lane.profile(mpc.PROF_RELU)
-                bpe = RELU_MSB_BYTES if ex == "copy" else RELU_MSB_PUT_BYTES
+                bpe = relu_copy_bytes(n_out, True) if ex == "copy" else RELU_MSB_PUT_BYTES
                 row.update({f"{key}_ms": rl / rn, f"{key}_elems_per_s": n_out / (rl / rn * 1e-3),
                             f"{key}_hbm_frac": bpe * n_out / (rl / rn * 1e-3) / HBM_PEAK})
             lane.set_exchange("copy")

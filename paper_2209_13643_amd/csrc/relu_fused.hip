@@ -554,7 +554,8 @@ __global__ __launch_bounds__(NP * kWave, PACKED ? 4 : 3) void k_maxpool_fused(Fu
 
 // Workgroups of a launch, [parties - 2]: as many as their receive buffers fit the L2 of their XCD (a three-party
 // workgroup has six of them).  Whole words, 2 097 152 elements: two parties 512 / 1024 / 2048 workgroups 0.315 / 0.307 /
-// 0.315 ms; three parties 320 / 384 / 512 workgroups 0.83 / 0.71 / 0.60 ms (2.12 ms as eleven launches).
+// 0.315 ms; three parties 320 / 384 workgroups 0.23 / 0.11 ms slower than 512, which take 0.59 ms (2.12 ms as eleven
+// launches).
 // Sign-only: two parties 768 / 1024 / 1280 workgroups 0.144 / 0.141 / 0.145 ms; three parties 768 .. 2048 workgroups level
 // (0.99 ms as eleven launches).
 constexpr unsigned kBlocks[2] = { 1024, 512 }, kMsbBlocks[2] = { 1024, 1536 }, kMsbPoolBlocks[2] = { 2048, 1536 };

@@ -30,7 +30,8 @@ def sources_digest() -> str:
 
 
 def clean(name):
-    return name.replace("(anonymous namespace)::", "").replace("void ", "").split("(")[0]
+    name = name.replace("(anonymous namespace)::", "").replace("void ", "").replace("(OpenPlanes)", "")
+    return name.split("(")[0]
 
 
 def dispatches(path, counter):
@@ -82,8 +83,8 @@ def relu_calls(rows):
 
 def gemm_launches(rows):
     """{form of the Beaver call: [value per two-party GEMM launch]} for rows of (id, kernel, grid, value) in dispatch
-    order.  The form is read off the call's own kernels before the launch: the remote-store folded call recodes with
-    k_recode_rows alone; the other forms use one k_recode_mixed launch whose grid grows with the number of plane
+    order.  The form is read off the call's own kernels before the launch: the remote-store folded call opens and
+    recodes in k_open_recode (a small one in k_recode_rows) alone; the other forms use one k_recode_mixed launch whose grid grows with the number of plane
     sets (prepared call: e; folded call with the copy exchange: x_0 + e_1 and e; plain call: six sets)."""
     biggest = max((r[2] for r in rows if r[1].startswith("k_limb_gemm")), default=0)
     groups = collections.OrderedDict()
@@ -94,7 +95,7 @@ def gemm_launches(rows):
         elif r[1].startswith("k_limb_gemm"):
             if r[2] == biggest and prologue:
                 mixed = [g for n, g in prologue if n.startswith("k_recode_mixed")]
-                rows_only = not mixed and any(n.startswith("k_recode_rows") for n, _ in prologue)
+                rows_only = not mixed and any(n.startswith(("k_open_recode", "k_recode_rows")) for n, _ in prologue)
                 if mixed or rows_only:
                     groups.setdefault(("rows", 0) if rows_only else ("mixed", mixed[-1]), []).append(r[3])
             prologue = []
