@@ -273,7 +273,7 @@ struct ConvGeom {
     long long npix;                   // B*H*W: rows of the activation planes
 };
 struct GemmArgs {
-    GemmSeg seg[3][2];                // [party][segment]; three parties only where gemm_takes_three
+    GemmSeg seg[3][2];                // [party][segment]; three parties: launch_limb_gemm3
     int nseg, nparty;
     const u64* addend[3];             // c_i, may be nullptr
     const u64* addend2[3];            // partial sums of an earlier phase, may be nullptr
@@ -297,4 +297,4 @@ int gemm_ksplit(int M, int N, int batch, int nparty, int total_steps);
 // the same choice when party 0 contracts steps0 and party 1 steps1 K steps (slices of the longer one)
 int gemm_ksplit2(int M, int N, int batch, int steps0, int steps1);
 int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g);
-bool gemm_takes_three(const GemmArgs& g);      // whether one launch may hold three parties (g.nparty = 3, equal lengths)
+int launch_limb_gemm3(mpc_ctx* c, hipStream_t st, const GemmArgs& g);      // three parties of equal lengths, in one launch or two

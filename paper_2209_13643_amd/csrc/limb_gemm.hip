@@ -815,16 +815,18 @@ constexpr int kMaxStepsExact = 1023;
 // mix two to a compute unit, and the launch loses less to the imbalance (BERT-base layers 2-9 % faster; at 512 tiles,
 // configs[1]'s convolution, the two tilings are even, and the wide tile keeps room for another lane's streaming waves).
 static std::atomic<int> g_small_max_steps{ 16 }, g_small_min_tiles{ 512 };
+// The setting is the process's: a launch reads it once, and everything chosen for the launch follows from that reading.
+struct Tuning { int max_steps, min_tiles; };
+static Tuning tuning() { return { g_small_max_steps.load(std::memory_order_relaxed), g_small_min_tiles.load(std::memory_order_relaxed) }; }
 constexpr long long kAsymMinTiles = 768;
-static int tile_kind(int M, int N, int batch, int longest_steps, bool asymmetric)
+static int tile_kind(const Tuning& tune, int M, int N, int batch, int longest_steps, bool asymmetric)
 {
     const long long tiles64 = (long long)((M + 63) / 64) * ((N + 63) / 64) * batch;
-    const int max_steps = g_small_max_steps.load(std::memory_order_relaxed);
     const bool few_rows = M <= 32;
-    if (longest_steps <= max_steps && tiles64 >= g_small_min_tiles.load(std::memory_order_relaxed) && !(few_rows && N > 64)) return 2;
+    if (longest_steps <= tune.max_steps && tiles64 >= tune.min_tiles && !(few_rows && N > 64)) return 2;
     if (few_rows) return 3;
     // (not the batched products one 64-column tile wide, per-head A*V: those are 5 % faster on the 128 x 64 tile)
-    if (asymmetric && max_steps > 0 && tiles64 >= kAsymMinTiles && !(batch > 1 && N <= 64)) return 2;
+    if (asymmetric && tune.max_steps > 0 && tiles64 >= kAsymMinTiles && !(batch > 1 && N <= 64)) return 2;
     return (((N - 1) % 128) < 64 && (N <= 64 || M >= 4096)) ? 1 : 0;
 }
 
@@ -851,12 +853,12 @@ static int tile_kind(int M, int N, int batch, int longest_steps, bool asymmetric
 //   30 x 1100 x 4000    37.2 / 28.4     200 x 3001 x 333     49.0 / 43.6     3x3 convolution of 4 x 7 x 7 x 256  35.5 / 30.3
 constexpr int kSlicedMaxSteps = 64, kFinishCost = 5;
 constexpr long long kSlicedMaxBlocks = 1024, kSlicedWideBlocks = 256;
-static int sliced_waves(const GemmArgs& g, int longest, const int steps[3], int* slices)
+static int sliced_waves(const Tuning& tune, const GemmArgs& g, int longest, const int steps[3], int* slices)
 {
     *slices = 1;
-    if (g_small_max_steps.load(std::memory_order_relaxed) == 0) return 0;
+    if (tune.max_steps == 0) return 0;
     const long long tiles = (long long)((g.M + 31) / 32) * ((g.N + 31) / 32) * g.batch, blocks = tiles * g.nparty;
-    if (blocks > kSlicedMaxBlocks || tile_kind(g.M, g.N, g.batch, longest, false) == 2) return 0;
+    if (blocks > kSlicedMaxBlocks || tile_kind(tune, g.M, g.N, g.batch, longest, false) == 2) return 0;
     // a lane's offset inside a plane is 32 bits wide
     if ((g.conv.enabled ? (g.conv.npix + 1) * g.conv.CB : (long long)longest * KS * g.rows_L) * 16 >= (1ll << 31)) return 0;
     if ((long long)longest * KS * g.N * 16 >= (1ll << 31)) return 0;
@@ -871,7 +873,7 @@ static int sliced_waves(const GemmArgs& g, int longest, const int steps[3], int*
     while (s < g.ksplit && (longest + s) / (s + 1) >= 8 && blocks_of((longest + s) / (s + 1), tiles) <= kSlicedWideBlocks) ++s;
     const int per = (longest + s - 1) / s;
     const double cost = (per + 7) / 8 + 4 + (s > 1 ? kFinishCost : 0);
-    const int kind = tile_kind(g.M, g.N, g.batch, 1 << 30, false), tm = kind == 1 ? 128 : kind == 3 ? 32 : 64, tn = kind == 1 ? 64 : 128;
+    const int kind = tile_kind(tune, g.M, g.N, g.batch, 1 << 30, false), tm = kind == 1 ? 128 : kind == 3 ? 32 : 64, tn = kind == 1 ? 64 : 128;
     const long long large = blocks_of(g.steps_per_split, (long long)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * g.batch);
     const double cost_large = ((large + 255) / 256) * (g.steps_per_split * (kind == 3 ? 0.5 : 1.0) + 6) + (g.ksplit > 1 ? kFinishCost : 0);
     if (cost >= cost_large || (per + 7) / 8 > kMaxStepsExact) return 0;
@@ -885,7 +887,7 @@ static int ksplit_for(int M, int N, int batch, const int steps[2])
 {
     const int nparty = steps[1] > 0 ? 2 : 1;
     const int longest = steps[0] > steps[1] ? steps[0] : steps[1];
-    const int kind = tile_kind(M, N, batch, longest, nparty == 2 && steps[0] != steps[1]);
+    const int kind = tile_kind(tuning(), M, N, batch, longest, nparty == 2 && steps[0] != steps[1]);
     const int tm = kind == 1 ? 128 : kind == 3 ? 32 : 64, tn = kind == 0 || kind == 3 ? 128 : 64;
     const long long tiles_pp = (long long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * batch;      // per party
     // the int32 digit sums of one workgroup stay exact for at most kMaxStepsExact steps
@@ -931,13 +933,6 @@ extern "C" int mpc_set_gemm_small_tile(int max_steps, int min_tiles)
     return MPC_OK;
 }
 
-bool gemm_takes_three(const GemmArgs& g)
-{
-    const int n = (g.seg[0][0].KB + g.seg[0][1].KB) / KS, steps[3] = { n, n, n };
-    int slices;
-    return g.nparty == 3 && g.nseg == 2 && sliced_waves(g, n, steps, &slices) != 0;
-}
-
 // slices of `per` steps for every party, none empty
 static void split_over(GemmArgs& g, const int steps[3], int per)
 {
@@ -948,27 +943,24 @@ static void split_over(GemmArgs& g, const int steps[3], int per)
     }
 }
 
-int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
+// The checks of a launch and the choice of its kernel; completes g.  MPC_OK: f may be launched.
+struct Form { int waves, slices, kind; };          // waves: of k_sliced_gemm, or 0: a tile of `kind`
+static int choose_form(GemmArgs& g, Form* f)
 {
-    GemmArgs g = g_in;
-    if (g.nparty < 1 || g.nparty > (gemm_takes_three(g) ? 3 : 2) || g.nseg < 1 || g.nseg > 2) return MPC_EINVAL;
-    int longest_steps = 0, party_steps[3] = { 0, 0, 0 };
-    {
-        int (&steps)[3] = party_steps;
-        for (int p = 0; p < g.nparty; ++p)
-            for (int s = 0; s < g.nseg; ++s) steps[p] += g.seg[p][s].KB / KS;
-        if (g.nparty == 3 && (steps[1] != steps[0] || steps[2] != steps[0])) return MPC_EINVAL;
-        const int longest = steps[0] > steps[1] ? steps[0] : steps[1];
-        longest_steps = longest;
-        if (g.ksplit < 1 || !g.partial) g.ksplit = 1;
-        const int per = (longest + g.ksplit - 1) / g.ksplit;
-        if (per < 1 || per > kMaxStepsExact) return MPC_ERANGE;
-        split_over(g, steps, per);
-        // the longer contraction first (party 1's by construction of the callers)
-        g.heavy_first = g.nparty == 2 && steps[1] > steps[0];
-        if (g.nparty == 2 && steps[1] < steps[0]) return MPC_EINVAL;
-    }
-    if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.nseg < 1 || g.nseg > 2) return MPC_EINVAL;
+    if (g.nparty < 1 || g.nparty > 3 || g.nseg < 1 || g.nseg > 2) return MPC_EINVAL;
+    int longest = 0, steps[3] = { 0, 0, 0 };
+    for (int p = 0; p < g.nparty; ++p)
+        for (int s = 0; s < g.nseg; ++s) steps[p] += g.seg[p][s].KB / KS;
+    if (g.nparty == 3 && (steps[1] != steps[0] || steps[2] != steps[0])) return MPC_EINVAL;
+    longest = steps[0] > steps[1] ? steps[0] : steps[1];
+    if (g.ksplit < 1 || !g.partial) g.ksplit = 1;
+    const int per = (longest + g.ksplit - 1) / g.ksplit;
+    if (per < 1 || per > kMaxStepsExact) return MPC_ERANGE;
+    split_over(g, steps, per);
+    // the longer contraction first (party 1's by construction of the callers)
+    g.heavy_first = g.nparty == 2 && steps[1] > steps[0];
+    if (g.nparty == 2 && steps[1] < steps[0]) return MPC_EINVAL;
+    if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return MPC_EINVAL;
     for (int p = 0; p < g.nparty; ++p)
         for (int s = 0; s < g.nseg; ++s)
             if (g.seg[p][s].KB < (s == 0 ? 1 : 0) || g.seg[p][s].KB % KS) return MPC_EINVAL;     // a second segment may be empty
@@ -980,17 +972,50 @@ int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
     // to 256 channels, 32 images: 361 -> 350 us a call with the shorter set-up.
     if (g.conv.enabled && g.conv.KH == 1 && g.conv.KW == 1 && g.conv.stride == 1 && g.conv.pad == 0 && g.conv.CB % KS == 0)
         g.conv = ConvGeom{};
-    int slices = 1;
-    if (const int kw = sliced_waves(g, longest_steps, party_steps, &slices)) {
-        split_over(g, party_steps, (longest_steps + slices - 1) / slices);
-        if (g.conv.enabled) return kw == 8 ? launch_sliced<true, 8>(c, st, g) : launch_sliced<true, 4>(c, st, g);
-        return kw == 8 ? launch_sliced<false, 8>(c, st, g) : launch_sliced<false, 4>(c, st, g);
-    }
+    const Tuning tune = tuning();
+    f->waves = sliced_waves(tune, g, longest, steps, &f->slices);
+    if (f->waves) split_over(g, steps, (longest + f->slices - 1) / f->slices);
+    else if (g.nparty == 3) return MPC_EINVAL;               // the tiles below know two parties
     // 64x128 workgroup tiles, or 128x64 when a second 64-column half would be empty
-    const int kind = g.ksplit > 1 ? tile_kind(g.M, g.N, g.batch, 1 << 30, false) : tile_kind(g.M, g.N, g.batch, longest_steps, g.heavy_first != 0);
+    f->kind = g.ksplit > 1 ? tile_kind(tune, g.M, g.N, g.batch, 1 << 30, false) : tile_kind(tune, g.M, g.N, g.batch, longest, g.heavy_first != 0);
+    return MPC_OK;
+}
+
+static int launch_form(mpc_ctx* c, hipStream_t st, const GemmArgs& g, const Form& f)
+{
+    const int kind = f.kind;
+    if (f.waves) {
+        if (g.conv.enabled) return f.waves == 8 ? launch_sliced<true, 8>(c, st, g) : launch_sliced<true, 4>(c, st, g);
+        return f.waves == 8 ? launch_sliced<false, 8>(c, st, g) : launch_sliced<false, 4>(c, st, g);
+    }
     if (g.conv.enabled)
         return kind == 3 ? launch_cfg<1, 4, true, 3, 1>(c, st, g) : kind == 2 ? launch_cfg<2, 2, true, 2, 1>(c, st, g)
              : kind == 1 ? launch_cfg<4, 1, true>(c, st, g) : launch_cfg<2, 2, true>(c, st, g);
     return kind == 3 ? launch_cfg<1, 4, false, 3, 1>(c, st, g) : kind == 2 ? launch_cfg<2, 2, false, 2, 1>(c, st, g)
          : kind == 1 ? launch_cfg<4, 1, false>(c, st, g) : launch_cfg<2, 2, false>(c, st, g);
+}
+
+int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
+{
+    GemmArgs g = g_in;
+    Form f{};
+    if (g.nparty > 2) return MPC_EINVAL;
+    MPC_TRY(choose_form(g, &f));
+    return launch_form(c, st, g, f);
+}
+
+// Three parties of equal lengths (g.nparty is not read): few tiles in one launch, others in two.
+int launch_limb_gemm3(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
+{
+    GemmArgs g = g_in;
+    Form f{};
+    g.nparty = 3;
+    if (choose_form(g, &f) == MPC_OK) return launch_form(c, st, g, f);
+    g = g_in;
+    g.nparty = 2;
+    MPC_TRY(launch_limb_gemm(c, st, g));
+    g.nparty = 1;
+    for (int s = 0; s < 2; ++s) g.seg[0][s] = g_in.seg[2][s];
+    g.addend[0] = g_in.addend[2]; g.addend2[0] = g_in.addend2[2]; g.out[0] = g_in.out[2];
+    return launch_limb_gemm(c, st, g);
 }

@@ -655,20 +655,7 @@ int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 
         g.seg[i][1] = make_seg(s, w.pl_a[i], w.pr_f);
         g.addend[i] = cc.p[i]; g.addend2[i] = nullptr; g.out[i] = z.p[i];
     }
-    g.nparty = 3;
-    if (gemm_takes_three(g)) {              // few tiles: one launch for all parties
-        MPC_TRY(launch_limb_gemm(c, st, g));
-        prof_end(c, MPC_PROF_LINEAR, pi, st);
-        return lane_fanout(c);
-    }
-    g.nparty = 2;
-    MPC_TRY(launch_limb_gemm(c, st, g));
-    g.nparty = 1;
-    g.seg[0][0] = make_seg(s, w.pl_e, w.pr_b[2]);
-    g.seg[0][1] = make_seg(s, w.pl_a[2], w.pr_f);
-    g.addend[0] = cc.p[2]; g.out[0] = z.p[2];
-    g.seg[1][0] = GemmSeg{}; g.seg[1][1] = GemmSeg{}; g.addend[1] = nullptr; g.out[1] = nullptr;
-    MPC_TRY(launch_limb_gemm(c, st, g));
+    MPC_TRY(launch_limb_gemm3(c, st, g));
     prof_end(c, MPC_PROF_LINEAR, pi, st);
     return lane_fanout(c);
 }
