@@ -33,6 +33,7 @@
 // straight into registers.
 #include <atomic>
 #include "common.h"
+#include "overlap.h"
 
 #include <type_traits>
 #include <utility>
@@ -1004,13 +1005,27 @@ int launch_limb_gemm(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
     return launch_form(c, st, g, f);
 }
 
-// Three parties of equal lengths (g.nparty is not read): few tiles in one launch, others in two.
+// whether no party's output shares memory with another party's addend
+static bool parties_apart(const GemmArgs& g)
+{
+    const size_t n = (size_t)g.batch * g.out_bstride;
+    for (int i = 0; i < 3; ++i) {
+        Spans<1> out; Spans<4> in;
+        out.words(g.out[i], n);
+        for (int j = 0; j < 3; ++j) if (j != i) { in.words(g.addend[j], n); in.words(g.addend2[j], n); }
+        if (!outputs_apart(out, in, false)) return false;
+    }
+    return true;
+}
+
+// Three parties of equal lengths (g.nparty is not read): few tiles in one launch, others, and calls whose party 2 stores over
+// what parties 0 and 1 add, in two.
 int launch_limb_gemm3(mpc_ctx* c, hipStream_t st, const GemmArgs& g_in)
 {
     GemmArgs g = g_in;
     Form f{};
     g.nparty = 3;
-    if (choose_form(g, &f) == MPC_OK) return launch_form(c, st, g, f);
+    if (choose_form(g, &f) == MPC_OK && parties_apart(g)) return launch_form(c, st, g, f);
     g = g_in;
     g.nparty = 2;
     MPC_TRY(launch_limb_gemm(c, st, g));

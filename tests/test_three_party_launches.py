@@ -91,6 +91,22 @@ result["off"] = call(product(40, 1024, 33), 40, 1024, 33)
         assert sum("k_splitk" not in n for n in r[key][1]) == 2, r[key]
 
 
+def test_outputs_over_addends(run):
+    """Party 2 may store its output over c_0 or c_1 (parties 0 and 1 have read them by then): two launches.  Every party's
+    output over its own c: a word is read by the thread that stores it, one launch."""
+    r = run('''
+shape = (40, 1024, 33)
+for name, i, j, off in (("over c_0", 2, 0, 0), ("in c_1", 2, 1, 40), ("the end of c_0", 2, 0, 40 * 33 * 8 - 8), ("own c", 2, 2, 0), ("ahead of c_0", 2, 0, -40 * 33 * 8)):
+    s = product(*shape)
+    s[5].p[i] = s[4].p[j] + off
+    result[name] = call(s, *shape)
+''')
+    assert all(rc == 0 for rc, _ in r.values()), r
+    for name in ("over c_0", "in c_1", "the end of c_0"):
+        assert len([n for n in r[name][1] if "k_splitk" not in n]) == 2, (name, r[name])
+    assert one_launch(r["own c"][1]) and one_launch(r["ahead of c_0"][1])
+
+
 def test_tuning_changed_by_another_thread_meanwhile(run):
     """40 x 1024 x 33 takes three slices and more on the larger tiles: the partial products of a third party have no room."""
     r = run('''
