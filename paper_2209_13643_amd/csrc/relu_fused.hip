@@ -255,10 +255,12 @@ __device__ __forceinline__ Converted<V> convert_words(const FusedReluParty& p, c
     return r;
 }
 
-// Registers: 128, so that a wave fits beside the GEMM's on a SIMD; the operands of three rounds of three parties need 156
-// (held at 128 they are spilled; 512 workgroups are less than two waves per SIMD either way), those of the copying exchange 135.
+// Registers: 128 (two parties, prefix network of Kogge and Stone), which leaves the GEMM's wave its room on a SIMD; the
+// prefix tree needs 131 (held at 128 it spills four: 70 001 / 2 097 152 elements 14.4 / 312.7 us, 13.0 / 306.5 at 131), the copying
+// exchange 135 and 139, the operands of three rounds of three parties 156 (512 workgroups are less than two waves per SIMD
+// either way).
 template <int NP, int V, int TOPO, bool COPY>
-__global__ __launch_bounds__(NP * kWave, (NP == 3 || COPY) && V == 2 ? 3 : 4) void k_relu_fused(FusedRelu q)
+__global__ __launch_bounds__(NP * kWave, (NP == 3 || COPY || TOPO) && V == 2 ? 3 : 4) void k_relu_fused(FusedRelu q)
 {
     const int party = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int lane = threadIdx.x % kWave;
