@@ -394,8 +394,18 @@ struct ReluWs {
     u64 *G[2], *P[2]; u8* p63[2];
     u64 *sendL[2], *recvL[2], *gsel[2];     // packed levels only
     u64* box; size_t box_bytes;             // all of it: the buffers of the one-launch chain
-    size_t bytes; bool ok;
+    size_t bytes; bool ok;                  // bytes: what the queries return; ok: there is room for the call, launch by launch at least
 };
+
+// Most elements of a call whose exchange by copies is part of the one launch (relu_run).
+constexpr size_t kCopyInLaunchMaxN = (size_t)1 << 18;
+void fill_room(ReluWs& r, const WsAlloc& w, u8* base, size_t cap, size_t n, size_t box, size_t copy_box)
+{
+    const size_t least = w.off > box ? w.off : box;
+    r.box = reinterpret_cast<u64*>(base); r.box_bytes = cap;
+    r.ok = w.ok && cap >= least;
+    r.bytes = n <= kCopyInLaunchMaxN && copy_box > least ? copy_box : least;
+}
 
 ReluWs carve_relu(u8* base, size_t cap, size_t n)
 {
@@ -406,9 +416,7 @@ ReluWs carve_relu(u8* base, size_t cap, size_t n)
         r.sendb[i] = w.take<u8>(n); r.recvb[i] = w.take<u8>(n);
         r.G[i] = w.take<u64>(n); r.P[i] = w.take<u64>(n); r.p63[i] = w.take<u8>(n);
     }
-    r.box = reinterpret_cast<u64*>(base); r.box_bytes = cap;
-    const size_t box = relu_fused_box_bytes(2, n);
-    r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
+    fill_room(r, w, base, cap, n, relu_fused_box_bytes(2, n), relu_fused_box_bytes(2, n, true));
     return r;
 }
 
@@ -423,9 +431,7 @@ ReluWs carve_relu_msb(u8* base, size_t cap, size_t n, const MsbGeom& g)
         r.sendL[i] = w.take<u64>(g.words_level_blocks); r.recvL[i] = w.take<u64>(g.words_level_blocks);
         r.gsel[i] = w.take<u64>(g.words_gsel);
     }
-    r.box = reinterpret_cast<u64*>(base); r.box_bytes = cap;
-    const size_t box = relu_fused_msb_box_bytes(2, n);
-    r.bytes = w.off > box ? w.off : box; r.ok = w.ok && cap >= r.bytes;
+    fill_room(r, w, base, cap, n, relu_fused_msb_box_bytes(2, n), relu_fused_msb_box_bytes(2, n, true));
     return r;
 }
 
@@ -580,7 +586,6 @@ PackedTriples packed_triples(const MsbGeom& g)
 // they do: 8 192 elements 89 us a call, 65 536 90, 131 072 110, 262 144 165 (half of it still launches), and as one launch
 // 28, 27, 28 (all of it the host) and 50 us; sign-only 89-93 us, 28.  Beyond, the copies are most of the call, and
 // stay launches of their own, which the caller of MPC_EXCHANGE_COPY can tile and place on the wire stream.
-constexpr size_t kCopyInLaunchMaxN = (size_t)1 << 18;
 int relu_run(mpc_ctx* c, ReluParty (&pp)[2], u64* box, size_t box_bytes, size_t n, int n_chunks, const MsbGeom* geom = nullptr)
 {
     const bool in_order = one_queue(c);   // in-order queue: no events needed
@@ -892,7 +897,7 @@ int maxpool_entry(mpc_ctx* c, mpc_cshare x, const mpc_relu_material* mat1, const
 // Its rounds exchange and carry state through a fixed array in the code object
 // instead of the caller's workspace.  Layout and size are those carve_relu gives
 // for kStaticMaxN elements: per party 2 x [4][n] words (sent / received), 2 x n
-// bytes, G, P (n words each), n bytes (the one-launch chain needs a third of that).
+// bytes, G, P (n words each), n bytes: 10.4 MiB, of which the one-launch chain with copies takes 8.
 constexpr size_t kStaticMaxN = 65536;
 constexpr size_t static_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 constexpr size_t kStaticBytes =

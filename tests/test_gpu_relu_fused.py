@@ -55,9 +55,9 @@ def test_one_launch_relu(mpc, lane, n, adder):
     equal(mpc, sa, want.s_arith, "sign arithmetic share")
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 4097, 131072, 131073, 131072 + 128 + 65, 524288 + 3])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 4097, 65536, 65537, 65536 + 256 + 65, 131072, 131073, 131072 + 128 + 65, 524288 + 3])
 def test_one_launch_sign_only_relu(mpc, lane, n):
-    """The packed chain changes from one to two elements per lane at 131 072 | 131 073; beyond it the last n mod 128
+    """The packed chain changes from one to four elements per lane at 65 536 | 65 537; beyond it the last n mod 256
     elements run one per lane."""
     print(f"one-launch sign-only relu n={n}", flush=True)
     rng = np.random.default_rng(n)
@@ -122,11 +122,10 @@ def test_one_launch_maxpool(mpc, lane, shape, parties, chain):
 
 @pytest.mark.parametrize("chain", ["kogge-stone", "tree", "packed"])
 @pytest.mark.parametrize("queues", ["one", "three"])
-@pytest.mark.parametrize("n", [1, 33, 63, 64, 65, 65536, 65537, 131072 + 129, 262144, 262145])
+@pytest.mark.parametrize("n", [1, 33, 63, 64, 65, 100, 4097, 65536, 65537, 131072 + 129, 262144, 262145])
 def test_copies_inside_the_launch(mpc, n, queues, chain):
-    """Exchange by copies, the default: up to 2^18 elements the rounds and their copies are one launch, beyond it (and where
-    the queried workspace has no room for the buffers, n = 1) launches of their own.  On a workspace of exactly the queried
-    size between guard areas."""
+    """Exchange by copies, the default: up to 2^18 elements the rounds and their copies are one launch, beyond it launches of
+    their own.  On a workspace of exactly the queried size between guard areas."""
     from ctypes import c_void_p
     import torch
     print(f"copying relu n={n} {queues} {chain}", flush=True)
@@ -141,6 +140,10 @@ def test_copies_inside_the_launch(mpc, n, queues, chain):
     if packed:
         md = ln.pack_material(md)
     nbytes = (mpc.lib().mpc_relu_msb_workspace_bytes if packed else mpc.lib().mpc_relu_workspace_bytes)(n)
+    if n <= 1 << 18:         # room for the one launch: four buffers a workgroup, four rows of its lanes' words (packed: two of whole words)
+        per_lane = 1 if n <= 65536 else 4 if packed else 2
+        tiles = n // 256 + (n % 256 + 63) // 64 if packed and per_lane == 4 else (n + 64 * per_lane - 1) // (64 * per_lane)
+        assert nbytes >= min(tiles, 1024) * 4 * (2 if packed else 4) * 64 * per_lane * 8
     guard = 4096
     buf = torch.full((nbytes + 2 * guard + 256,), 0xA5, dtype=torch.uint8, device="cuda:0")
     at = guard + (-(buf.data_ptr() + guard)) % 256

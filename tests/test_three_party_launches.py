@@ -2,49 +2,18 @@
 runtime (fake_hip.cpp) that records the launched kernels.  Either one launch of the form with few tiles holds all parties,
 or two launches hold two and one: whatever another thread sets mpc_set_gemm_small_tile to meanwhile, every call returns
 MPC_OK and no other kernel is given three parties."""
-import ctypes
-import json
-import os
-import subprocess
-import sys
-
 import pytest
 
-HERE = os.path.dirname(os.path.abspath(__file__))
+import fake_hip
 
-# The library is used through ctypes alone: a process that has loaded the real runtime's users first would not do.
-CLIENT = r'''
-import ctypes, json, sys
-from ctypes import c_int, c_size_t, c_void_p
-fake = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
-lib = ctypes.CDLL(sys.argv[2])
-
-class Share3(ctypes.Structure):
-    _fields_ = [("p", c_void_p * 3)]
-
+PRODUCT = r'''
+assert lib.mpc_ctx_set_exchange(ctx, 1) == 0
 lib.mpc_matmul3_workspace_bytes.restype = c_size_t
 lib.mpc_matmul3_workspace_bytes.argtypes = [c_int] * 4
-lib.mpc_ctx_set_workspace.argtypes = [c_void_p, c_void_p, c_size_t]
-lib.mpc_ctx_set_exchange.argtypes = [c_void_p, c_int]
 lib.mpc_beaver_matmul3.argtypes = [c_void_p] + [Share3] * 6 + [c_int] * 4 + [c_void_p, c_int]
-fake.fake_launches.restype = c_size_t
-text = ctypes.create_string_buffer(1 << 16)
-
-def launches():
-    fake.fake_launches(text, len(text))
-    return text.value.decode().split()
-
-ctx = c_void_p()
-assert lib.mpc_ctx_create_single_queue(ctypes.byref(ctx), 0, 16) == 0
-assert lib.mpc_ctx_set_exchange(ctx, 1) == 0
-at = 1 << 40
-def array(nbytes):
-    global at
-    a, at = at, at + (nbytes + 4095) // 4096 * 4096
-    return a
 
 def product(M, K, N):
-    """A call's arguments, every array at a place of its own; nothing reads them."""
+    """A call's arguments."""
     ws = lib.mpc_matmul3_workspace_bytes(M, K, N, 1)
     assert ws and lib.mpc_ctx_set_workspace(ctx, array(ws), ws) == 0
     return [Share3((c_void_p * 3)(*[array(8 * n) for _ in range(3)])) for n in (M * K, K * N, M * K, K * N, M * N, M * N)]
@@ -52,26 +21,13 @@ def product(M, K, N):
 def call(shares, M, K, N):
     rc = lib.mpc_beaver_matmul3(ctx, *shares, M, K, N, 1, None, 0)
     return rc, [n for n in launches() if "gemm" in n]
-
-result = {}
 '''
 
 
 @pytest.fixture(scope="module")
 def run(tmp_path_factory):
-    from paper_2209_13643_amd import mpc
-    if not os.path.exists(mpc.LIB_PATH):
-        import __graft_entry__
-        __graft_entry__.build()
     d = tmp_path_factory.mktemp("fake")
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-pthread", os.path.join(HERE, "fake_hip.cpp"), "-o", str(d / "fake_hip.so")])
-
-    def client(body):
-        out = subprocess.run([sys.executable, "-c", CLIENT + body + "\nprint(json.dumps(result))", str(d / "fake_hip.so"), mpc.LIB_PATH],
-                             capture_output=True, text=True, timeout=120)
-        assert out.returncode == 0, out.stderr[-2000:]
-        return json.loads(out.stdout.splitlines()[-1])
-    return client
+    return lambda body: fake_hip.run(d, PRODUCT + body)
 
 
 def one_launch(names):
