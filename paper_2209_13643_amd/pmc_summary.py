@@ -64,7 +64,8 @@ def is_relu(name):
 def relu_calls(rows):
     """KiB per secure-ReLU call by chain and exchange: a call is a maximal run of stage and wire dispatches (the
     conv call's kernels separate the runs; the chunks of a call follow each other), the chain shows in the stage
-    kernels' name, the exchange in their last template argument.  The one-launch kernels exchange by remote store."""
+    kernels' name, the exchange in their last template argument: true is remote store in a stage kernel, copies inside
+    the launch in a one-launch kernel."""
     out = collections.defaultdict(list)
     run = []
     for r in list(rows) + [(0, "end", 0, 0.0)]:
@@ -75,7 +76,7 @@ def relu_calls(rows):
             stages = [q[1] for q in run if "stage<" in q[1] or "fused" in q[1]]
             if stages:
                 chain = "sign-only" if any("msb" in q for q in stages) else "whole words"
-                put = any("fused" in q or q.rstrip(">").endswith("true") for q in stages)
+                put = any(("fused" in q) != q.rstrip(">").endswith("true") for q in stages)
                 out[(chain, "remote store" if put else "copy")].append(sum(q[3] for q in run))
             run = []
     return {k: sum(v) / len(v) for k, v in out.items()}
@@ -92,8 +93,8 @@ def gemm_launches(rows):
     for r in rows:
         if is_relu(r[1]):
             prologue = []
-        elif r[1].startswith("k_limb_gemm"):
-            if r[2] == biggest and prologue:
+        elif r[1].startswith(("k_limb_gemm", "k_sliced_gemm", "k_few_rows_gemm")):       # a call's GEMM, whichever, ends its prologue
+            if r[1].startswith("k_limb_gemm") and r[2] == biggest and prologue:
                 mixed = [g for n, g in prologue if n.startswith("k_recode_mixed")]
                 rows_only = not mixed and any(n.startswith(("k_open_recode", "k_recode_rows")) for n, _ in prologue)
                 if mixed or rows_only:
