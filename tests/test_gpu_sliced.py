@@ -44,7 +44,8 @@ def same(mpc, lane, got, want, what):
 @pytest.mark.parametrize("M,K,N,batch", [
     (1, 1, 1, None), (31, 17, 33, None), (32, 64, 32, None), (33, 128, 31, None), (64, 250, 70, None), (65, 512, 129, None),
     (40, 1008, 20, None), (40, 1024, 33, None), (40, 1025, 20, None), (500, 40, 256, None), (513, 40, 256, None), (40, 48, 36, 32),
-    (2, 300, 100, 3), (5, 4100, 33, None), (65, 2500, 40, None), (20, 1300, 24, 3), (2, 12000, 130, None), (100, 1100, 1000, None),
+    (2, 300, 100, 3), (5, 4100, 33, None), (65, 2500, 40, None), (20, 1300, 24, 3), (2, 12000, 130, None), (100, 1100, 1000, None), (70, 100, 500, 3),
+    (300, 100, 70, 3),
 ])
 def test_products(mpc, lane, M, K, N, batch):
     print(f"sliced {M}x{K}x{N} batch {batch}", flush=True)
