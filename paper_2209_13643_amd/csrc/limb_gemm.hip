@@ -851,13 +851,18 @@ static int tile_kind(const Tuning& tune, int M, int N, int batch, int longest_st
 // 48 / 108 / 98).  Convolutions: 8 x 14 x 14 x 128, 3x3, 42.2 / 32.7 / 37.0; 4 x 14 x 14 x 64 27.5 / 18.6 / 17.9.
 // mpc_set_gemm_small_tile(0, ...) switches this form off as well.
 //
-// Longer contractions with at most 256 workgroups: by cost, in steps of eight waves on a compute unit (about 1.05 us).  The
-// contraction is then split over workgroups too, over as many as the chip holds at once and the caller's partial products
-// have room for (*slices, of which the finishing pass costs 5).  Tiles above: rounds of workgroups x (steps per slice + 6), a
-// step of the 32-row tile counting half; sliced: steps per wave + 4.  Us, tiles above / sliced:
-//   2 x 25088 x 10      50.3 / 27.8     60 x 8000 x 400      49.3 / 40.8     128 x 4608 x 512 (left above)     50.7 / 52.7
-//   64 x 2048 x 128     29.5 / 19.5     100 x 20000 x 100    90.2 / 64.7     4 x 25088 x 1000 (left above)    130.4 / 130.1
-//   32 x 4096 x 1000    35.4 / 30.0     300 x 4000 x 200     53.8 / 49.8     64 x 8000 x 2000 (left above)    118.1 / 160.2
+// Longer contractions with at most 256 workgroups: by cost, in steps of a 64 x 128 tile.  The contraction is then split over
+// workgroups too, over as many as the chip holds at once and the caller's partial products have room for (*slices, of which
+// the finishing pass costs 5).  At once: every party's workgroups are dealt to the XCDs in eights, and an XCD with one more
+// than its 32 compute units runs two rounds (folded 22 x 21586 x 472 in 165 + 90 workgroups 85 us, in 150 + 75 52).  Tiles
+// above: rounds of workgroups x (steps per slice + 14), a step of the 32-row tile counting half; sliced: steps per wave + 4, a
+// step counting 1.5, as eight waves ask the L2 for 128 KB in it (2.2 us with the chip full; of a strided convolution, which
+// uses half of every line it reads, 2.25).  Of 1702 drawn products and convolutions with such contractions none beyond 32
+// rows then takes the slower form by more than 2 %, and 1398 of the 1446 that gain as much take it.  The launch, us,
+// tiles above / sliced:
+//   2 x 25088 x 10      50.3 / 27.8     60 x 8000 x 400      49.3 / 40.8     64 x 8000 x 2000 (left above)    125 / 155
+//   64 x 2048 x 128     29.5 / 19.5     100 x 20000 x 100    90.2 / 64.7     1073 x 12347 x 89 (left above)   188 / 232
+//   32 x 4096 x 1000    35.4 / 30.0     300 x 4000 x 200     53.8 / 49.8     316 x 25053 x 158 (left above)   204 / 226
 //   30 x 1100 x 4000    37.2 / 28.4     200 x 3001 x 333     49.0 / 43.6     3x3 convolution of 4 x 7 x 7 x 256  35.5 / 30.3
 constexpr int kSlicedMaxSteps = 64, kFinishCost = 5;
 constexpr long long kSlicedMaxBlocks = 1024, kSlicedWideBlocks = 256;
@@ -874,16 +879,16 @@ static int sliced_waves(const Tuning& tune, const GemmArgs& g, int longest, cons
     if (blocks > kSlicedWideBlocks || g.nparty > 2) return 0;
     auto blocks_of = [&](int per, long long t) {
         long long n = 0;
-        for (int p = 0; p < g.nparty; ++p) n += t * ((steps[p] + per - 1) / per);
+        for (int p = 0; p < g.nparty; ++p) n += (t * ((steps[p] + per - 1) / per) + 7) / 8 * 8;
         return n;
     };
     int s = 1;
     while (s < g.ksplit && (longest + s) / (s + 1) >= 8 && blocks_of((longest + s) / (s + 1), tiles) <= kSlicedWideBlocks) ++s;
     const int per = (longest + s - 1) / s;
-    const double cost = (per + 7) / 8 + 4 + (s > 1 ? kFinishCost : 0);
+    const double cost = (per + 7) / 8 * (g.conv.enabled && g.conv.stride > 1 ? 2.25 : 1.5) + 4 + (s > 1 ? kFinishCost : 0);
     const int kind = tile_kind(tune, g.M, g.N, g.batch, 1 << 30, false), tm = kind == 1 ? 128 : kind == 3 ? 32 : 64, tn = kind == 1 ? 64 : 128;
     const long long large = blocks_of(g.steps_per_split, (long long)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * g.batch);
-    const double cost_large = ((large + 255) / 256) * (g.steps_per_split * (kind == 3 ? 0.5 : 1.0) + 6) + (g.ksplit > 1 ? kFinishCost : 0);
+    const double cost_large = ((large + 255) / 256) * (g.steps_per_split * (kind == 3 ? 0.5 : 1.0) + 14) + (g.ksplit > 1 ? kFinishCost : 0);
     if (cost >= cost_large || (per + 7) / 8 > kMaxStepsExact) return 0;
     *slices = s;
     return 8;

@@ -1,5 +1,5 @@
 // A stand-in for the HIP runtime, for tests of the library's host side on a machine without a GPU: every call succeeds,
-// nothing runs, and the names of launched kernels are kept in order.  Load it with RTLD_GLOBAL ahead of libmpcpipe.so.
+// nothing runs, and the launched kernels' names and grids are kept in order.  Load it with RTLD_GLOBAL ahead of libmpcpipe.so.
 #include <atomic>
 #include <cstddef>
 #include <cstdio>
@@ -26,7 +26,11 @@ int __hipPopCallConfiguration(dim* grid, dim* block, size_t* shared, void** stre
     *grid = config.grid; *block = config.block; *shared = config.shared; *stream = config.stream;
     return 0;
 }
-int hipLaunchKernel(const void* host, dim, dim, void**, size_t, void*) { launched.push_back(kernels()[host]); return 0; }
+int hipLaunchKernel(const void* host, dim grid, dim, void**, size_t, void*)
+{
+    launched.push_back(kernels()[host] + "@" + std::to_string(grid.x));
+    return 0;
+}
 
 int hipGetLastError() { return 0; }
 int hipSetDevice(int) { return 0; }
@@ -53,7 +57,7 @@ int hipGraphDestroy(void*) { return 0; }
 int hipGraphExecDestroy(void*) { return 0; }
 
 // ---- for the tests ----
-// the kernels launched since the last call of this, one name a line
+// the kernels launched since the last call of this, a line each: name@workgroups along x
 size_t fake_launches(char* out, size_t cap)
 {
     std::string all;

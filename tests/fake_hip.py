@@ -1,5 +1,5 @@
 """Runs calls of the built library's host side on a stand-in for the HIP runtime (fake_hip.cpp), in a process of its own:
-nothing is executed, and the names of the launched kernels come back.  Used by tests that ask which launches a call makes."""
+nothing is executed, and the launched kernels' names and grids come back.  Used by tests that ask which launches a call makes."""
 import json
 import os
 import subprocess
@@ -26,7 +26,7 @@ fake.fake_launches.restype = c_size_t
 text = ctypes.create_string_buffer(1 << 16)
 
 def launches():
-    """Kernels launched since the last call of this."""
+    """Kernels launched since the last call of this, each as name@workgroups."""
     fake.fake_launches(text, len(text))
     return text.value.decode().split()
 
