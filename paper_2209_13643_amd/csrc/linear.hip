@@ -96,12 +96,24 @@ struct LinearWs {
     size_t bytes; bool ok;
 };
 
-LinearWs carve(u8* base, size_t cap, const LinearShape& s, bool folded = false)
+// Receive buffers with which every tile of a one-launch opening has a workgroup of its own, up to as many as are resident.
+// Operands of less than a tile, or of ragged ones, have fewer words than their tiles, and the arrays of the masked words
+// alone would leave the tiles of such a call to run one after the other (1 x 64 x 10: five tiles in one workgroup, 17 us).
+size_t open_room(const LinearShape& s, int parties)
+{
+    if (s.im2colT) return 0;
+    const size_t most = open_most_blocks(parties);
+    const size_t tiles = open_most_tiles(s.rowsL, s.KB_L, s.batch) + open_most_tiles(s.N, s.KB, s.batch);
+    return (tiles < most ? tiles : most) * open_box_bytes(parties);
+}
+
+LinearWs layout(u8* base, size_t cap, const LinearShape& s, bool folded, size_t room)
 {
     WsAlloc w(base, cap);
     LinearWs r{};
     for (int i = 0; i < 2; ++i) { r.se[i] = w.take<u64>(s.nx); r.re[i] = w.take<u64>(s.nx); }
     for (int i = 0; i < 2; ++i) { r.sf[i] = w.take<u64>(s.nw); r.rf[i] = w.take<u64>(s.nw); }
+    if (w.off < room) w.take<u8>(room - w.off);
     const size_t lp = 8 * s.L_plane * s.batch, rp = 8 * s.R_plane * s.batch;
     r.pl_e = w.take<u8>(lp); r.pl_a[0] = w.take<u8>(lp); r.pl_a[1] = w.take<u8>(lp);
     r.pr_f = w.take<u8>(rp); r.pr_b[0] = w.take<u8>(rp); r.pr_b[1] = w.take<u8>(rp);
@@ -111,6 +123,13 @@ LinearWs carve(u8* base, size_t cap, const LinearShape& s, bool folded = false)
     r.partial = r.ksplit > 1 ? w.take<u64>((size_t)r.ksplit * 2 * s.batch * s.M * s.N) : nullptr;
     r.bytes = w.off; r.ok = w.ok;
     return r;
+}
+
+// The queries return the size with open_room; without it a workspace is enough as well.
+LinearWs carve(u8* base, size_t cap, const LinearShape& s, bool folded = false)
+{
+    const LinearWs r = layout(base, cap, s, folded, open_room(s, 2));
+    return r.ok || !base ? r : layout(base, cap, s, folded, 0);
 }
 
 RecodeArgs recode_left(const LinearShape& s, const u64* src, const u64* src2, u8* dst)
@@ -536,13 +555,14 @@ struct LinearWs3 {
     size_t bytes; bool ok;
 };
 
-LinearWs3 carve3(u8* base, size_t cap, const LinearShape& s)
+LinearWs3 layout3(u8* base, size_t cap, const LinearShape& s, size_t room)
 {
     WsAlloc w(base, cap);
     LinearWs3 r{};
     for (int i = 0; i < 3; ++i) { r.se[i] = w.take<u64>(s.nx); r.re[i][0] = w.take<u64>(s.nx); r.re[i][1] = w.take<u64>(s.nx); }
     for (int i = 0; i < 3; ++i) { r.sf[i] = w.take<u64>(s.nw); r.rf[i][0] = w.take<u64>(s.nw); r.rf[i][1] = w.take<u64>(s.nw); }
     r.e_pub = w.take<u64>(s.nx); r.f_pub = w.take<u64>(s.nw);
+    if (w.off < room) w.take<u8>(room - w.off);
     const size_t lp = 8 * s.L_plane * s.batch, rp = 8 * s.R_plane * s.batch;
     r.pl_e = w.take<u8>(lp); for (int i = 0; i < 3; ++i) r.pl_a[i] = w.take<u8>(lp);
     r.pr_f = w.take<u8>(rp); for (int i = 0; i < 3; ++i) r.pr_b[i] = w.take<u8>(rp);
@@ -550,6 +570,12 @@ LinearWs3 carve3(u8* base, size_t cap, const LinearShape& s)
     r.g.partial = r.g.ksplit > 1 ? w.take<u64>((size_t)r.g.ksplit * 2 * s.batch * s.M * s.N) : nullptr;
     r.bytes = w.off; r.ok = w.ok;
     return r;
+}
+
+LinearWs3 carve3(u8* base, size_t cap, const LinearShape& s)
+{
+    const LinearWs3 r = layout3(base, cap, s, open_room(s, 3));
+    return r.ok || !base ? r : layout3(base, cap, s, 0);
 }
 
 // Alg. 1 / Eq. 3 with three parties, everything on the lane's first stream:

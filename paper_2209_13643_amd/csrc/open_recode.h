@@ -21,6 +21,9 @@ struct OpenSet {
 constexpr int kMaxOpenSets = 2;
 // bytes of receive buffers a workgroup has; the launch needs those of one, and uses as many as it is given
 constexpr size_t open_box_bytes(int parties) { return parties == 2 ? 16384 : 24576; }
+// tiles of an operand of so many plane rows and k blocks at most, whichever way it is stored, and workgroups of a launch at most
+size_t open_most_tiles(int plane_rows, int KB_total, int batch);
+size_t open_most_blocks(int parties);
 // several taps only with contiguous rows
 inline bool can_open(const OpenSet& s) { return s.row_stride == 1 || (s.k_stride == 1 && s.ntaps == 1); }
 int launch_open_recode(mpc_ctx* c, hipStream_t st, int parties, OpenPlanes planes, const OpenSet* sets, int count, u8* box, size_t box_bytes);

@@ -248,6 +248,18 @@ void launch(hipStream_t st, const OpenBatch& g, size_t box_bytes)
 
 }  // namespace
 
+size_t open_most_tiles(int plane_rows, int KB_total, int batch)
+{
+    const size_t rows = (size_t)plane_rows, kbt = (size_t)tile_blocks(KB_total), high = (size_t)tile_rows((int)kbt);
+    const size_t by_rows = (rows + high - 1) / high * ((KB_total + kbt - 1) / kbt), by_columns = (rows + kPartyThreads - 1) / kPartyThreads * KB_total;
+    return (by_rows > by_columns ? by_rows : by_columns) * batch;
+}
+size_t open_most_blocks(int parties)
+{
+    const unsigned plain = max_blocks(parties, OpenPlanes::kMasks), other = max_blocks(parties, parties == 2 ? OpenPlanes::kFolded : OpenPlanes::kOpened);
+    return plain > other ? plain : other;
+}
+
 int launch_open_recode(mpc_ctx* c, hipStream_t st, int parties, OpenPlanes planes, const OpenSet* sets, int count, u8* box, size_t box_bytes)
 {
     if (parties < 2 || parties > 3 || count < 1 || count > kMaxOpenSets || !box || box_bytes < open_box_bytes(parties)) return MPC_EINVAL;

@@ -1,0 +1,71 @@
+"""The launch that opens a linear layer's operands under the exchange by remote store, on the CPU: the built library's host
+side on a stand-in for the HIP runtime."""
+import pytest
+
+import fake_hip
+
+CALLS = r'''
+for q in ("mpc_matmul_workspace_bytes", "mpc_matmul3_workspace_bytes"):
+    getattr(lib, q).restype = c_size_t; getattr(lib, q).argtypes = [c_int] * 4
+lib.mpc_beaver_matmul.argtypes = [c_void_p] + [Share] * 6 + [c_int] * 4 + [c_void_p, c_int, c_int]
+lib.mpc_beaver_matmul3.argtypes = [c_void_p] + [Share3] * 6 + [c_int] * 4 + [c_void_p, c_int]
+lib.mpc_conv2d_grad_x_workspace_bytes.restype = c_size_t; lib.mpc_conv2d_grad_x_workspace_bytes.argtypes = [c_int] * 9
+lib.mpc_conv2d_grad_x.argtypes = [c_void_p] + [Share] * 6 + [c_int] * 9 + [c_void_p, c_int, c_int]
+assert lib.mpc_ctx_set_exchange(ctx, 1) == 0
+big = array(1 << 38)
+share = lambda: Share((c_void_p * 2)(big, big + (1 << 37)))
+share3 = lambda: Share3((c_void_p * 3)(big, big + (1 << 36), big + (1 << 37)))
+
+def query(parties, *s):
+    return (lib.mpc_matmul_workspace_bytes if parties == 2 else lib.mpc_matmul3_workspace_bytes)(*s)
+
+def product(parties, ws, *s, f_public=None):
+    """rc, launches, workgroups of the opening launch (0: none)"""
+    assert lib.mpc_ctx_set_workspace(ctx, array(ws), ws) == 0
+    if parties == 2: rc = lib.mpc_beaver_matmul(ctx, *[share() for _ in range(6)], *s, f_public, 1, 1)
+    else:            rc = lib.mpc_beaver_matmul3(ctx, *[share3() for _ in range(6)], *s, f_public, 0)
+    names = launches()
+    opening = [n for n in names if "k_open_recode" in n]
+    assert len(opening) <= 1
+    return rc, names, int(opening[0].split("@")[1]) if opening else 0
+'''
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    d = tmp_path_factory.mktemp("fake")
+    return lambda body: fake_hip.run(d, CALLS + body)
+
+
+def tiles(M, K, N, batch):
+    """128 rows of one, 64 of two or 32 of four k blocks of the left operand, one k block by 128 columns of the right one."""
+    up = lambda a, b: -(-a // b)
+    kb = up(K, 16) + up(K, 16) % 2
+    wide = kb if kb <= 2 else 4
+    return batch * (up(M, 128 // wide) * up(kb, wide) + up(N, 128) * kb)
+
+
+@pytest.mark.parametrize("parties", [2, 3])
+def test_every_tile_of_a_small_call_has_a_workgroup(run, parties):
+    """On a workspace of exactly the queried size; and the smallest workspace that a call accepts has no room for that."""
+    shapes = [(1, 64, 10, 1), (1, 1, 2, 1), (13, 22, 8, 21), (2, 5, 58, 1), (11, 5, 297, 3), (2, 63, 455, 5), (3, 300, 130, 1)]
+    r = run(f'''
+for s in {shapes}:
+    full, low = query({parties}, *s), 0
+    high = full
+    while high - low > 256:
+        mid = (low + high) // 512 * 256
+        rc, _, _ = product({parties}, mid, *s)
+        assert rc in (0, -2), rc
+        if rc == 0: high = mid
+        else: low = mid
+    result[str(s)] = product({parties}, full, *s), product({parties}, high, *s), full, high
+''')
+    less = 0
+    for s in shapes:
+        (rc, _, blocks), (rc_low, _, blocks_low), full, low = r[str(s)]
+        assert rc == 0 and rc_low == 0
+        assert blocks == tiles(*s), (s, blocks)
+        assert blocks_low <= blocks and low <= full
+        less += blocks_low < blocks
+    assert less >= 4
