@@ -256,6 +256,8 @@ int check_shape(const LinearShape& s)
     return MPC_OK;
 }
 
+constexpr size_t kOpenAloneMinWords = (size_t)1 << 20;
+
 // The whole secure linear layer.  See mpc_beaver_matmul in the public header.
 int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
                   mpc_cshare a, mpc_cshare b, mpc_cshare cc, mpc_share z,
@@ -334,13 +336,21 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
         // Plain calls with the exchange by remote store open what they open in one launch, planes of the masks with it.
         // (A filter read in reverse tap order, or operands of less than half a tile, take the steps below.)
         const bool one_launch = put && !folded && box_bytes >= open_box_bytes(2) && !(two_phase && have_f);
+        const bool open_right = one_launch && !have_f && !s.wflip;
+        // Where right planes are recoded in a launch of their own all the same (f public, a filter in reverse tap order), the
+        // left operand opens ahead of it only if it is large: up to 2^20 words the steps below, whose one launch recodes
+        // everything, are the faster ones.  Device time of calls with f public, opening launch / steps below, us:
+        // 3 x 6 x 6 13.2 / 9.6, 22 x 52 x 216 (55 products) 28.3 / 23.9, 659 x 407 x 1017 59.9 / 54.8, 3x3 convolution of
+        // 32 x 2 x 2 x 512 70.2 / 65.0, 1x1 input gradient of 25 x 29 x 29 x 35 56.1 / 47.3; 1467 x 1038 x 291 110.8 / 116.8,
+        // 898 x 2641 x 208 116.3 / 126.6, 3x3 of 32 x 56 x 56 x 64 506.7 / 561.9.
+        const bool recode_left_too = !skip_right && !open_right && s.nx <= kOpenAloneMinWords;
         OpenSet opens[2]; int n_open = 0;
         bool left_done = false, right_done = false;
-        if (one_launch && !skip_left && !x_public && !s.im2colT) {
+        if (one_launch && !skip_left && !x_public && !s.im2colT && !recode_left_too) {
             opens[n_open++] = open_set(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_e, nullptr, w.pl_a[0], w.pl_a[1]);
             left_done = true;
         }
-        if (one_launch && !have_f && !s.wflip) {
+        if (open_right) {
             opens[n_open++] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_f, nullptr, w.pr_b[0], w.pr_b[1], true);
             right_done = true;
         }

@@ -69,3 +69,37 @@ for s in {shapes}:
         assert blocks_low <= blocks and low <= full
         less += blocks_low < blocks
     assert less >= 4
+
+
+def test_left_operand_with_a_public_right_one(run):
+    """f public: the right planes are recoded in a launch of their own, and up to 2^20 words the left ones with them, behind
+    the masking launch; a larger left operand opens in one launch ahead of it."""
+    r = run('''
+f = array(1 << 30)
+for s in ((3, 6, 6, 1), (22, 52, 216, 55), (1024, 1024, 64, 1), (1024, 1025, 64, 1), (1467, 1038, 291, 1)):
+    result[str(s)] = product(2, query(2, *s), *s, f_public=f)
+    result[str(s) + " both"] = product(2, query(2, *s), *s)
+''')
+    for s in ((3, 6, 6, 1), (22, 52, 216, 55), (1024, 1024, 64, 1), (1024, 1025, 64, 1), (1467, 1038, 291, 1)):
+        M, K, _, batch = s
+        (rc, names, blocks), (rc_both, names_both, blocks_both) = r[str(s)], r[str(s) + " both"]
+        assert rc == 0 and rc_both == 0
+        assert (blocks > 0) == (M * K * batch > 1 << 20), (s, names)
+        assert sum("k_sub_multi" in n for n in names) == (blocks == 0) and sum("k_recode" in n for n in names) == 1, names
+        assert blocks_both > 0 and not any("k_sub_multi" in n or "k_recode" in n for n in names_both)
+
+
+def test_input_gradient_with_a_secret_filter(run):
+    """The filter is read in reverse tap order and recoded in a launch of its own: the same."""
+    r = run('''
+for B in (2, 65):
+    g = (B, 16, 16, 32, 64, 3, 3, 1, 1)
+    ws = lib.mpc_conv2d_grad_x_workspace_bytes(*g)
+    assert lib.mpc_ctx_set_workspace(ctx, array(ws), ws) == 0
+    rc = lib.mpc_conv2d_grad_x(ctx, *[share() for _ in range(6)], *g, None, 1, 1)
+    result[B] = rc, launches()
+''')
+    for B in (2, 65):
+        rc, names = r[str(B)]
+        assert rc == 0
+        assert any("k_open_recode" in n for n in names) == (B * 16 * 16 * 64 > 1 << 20), names
