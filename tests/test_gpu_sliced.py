@@ -86,6 +86,4 @@ def test_one_and_three_parties(mpc, lane, M, K, N):
     x, y, a, b = (synth.rand_words(rng, s) for s in ((M, K), (K, N), (M, K), (K, N)))
     sh = {k: synth.share_additive3(rng, v) for k, v in (("x", x), ("y", y), ("a", a), ("b", b), ("c", oracle.ring_matmul(a, b)))}
     z = lane.beaver_matmul3(*(dev(mpc, sh[k]) for k in ("x", "y", "a", "b", "c")))
-    lane.sync()
-    total = sum(mpc.to_host(t).astype(np.uint64) for t in z)
-    assert np.array_equal(total.reshape(M, N), oracle.ring_matmul(x, y))
+    same(mpc, lane, z, oracle.beaver_matmul3(*(sh[k] for k in ("x", "y", "a", "b", "c"))), "three parties")
