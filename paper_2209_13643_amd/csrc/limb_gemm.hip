@@ -348,7 +348,8 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g)
     // epilogue.  Issuing them from inside the last steps hides their latency (4 % on
     // 64-deep contractions) but keeps 64 more registers live across the main loop; the
     // kernel stays below 128 vector registers instead, so that a wave of a streaming
-    // kernel from another lane (secure ReLU: at most 128) fits beside it on the same SIMD
+    // kernel from another lane fits beside it on the same SIMD (512 registers in all: 136 are
+    // left; which of the one-launch kernels keep to that stands at their launch bounds)
     // and fills the issue slots the MFMAs leave free: 7-13 % on the inter-batch pipeline.
     const bool partial = g.ksplit > 1;      // raw partial products go to the workspace; a second kernel finishes
     const u64* addend = (P.addend && !partial) ? P.addend + (size_t)bidx * g.out_bstride : nullptr;

@@ -6,17 +6,18 @@
 // depend on each other, so no wave ever waits for another workgroup.  Between rounds (G, P) stay in registers, and a
 // receive buffer holds one round of one workgroup's elements, so what streams from HBM is the input, the offline
 // material and the output, each once: 690 bytes per element of both parties instead of the 2498 that one launch per
-// round moves.  2 097 152 elements: 0.95 ms as ten launches, 0.307 ms here (4.7 TB/s of compulsory bytes).
+// round moves.  2 097 152 elements: 0.95 ms as ten launches, 0.307-0.311 ms here (4.7 TB/s of compulsory bytes; two boxes).
 //
 // What bounds it is memory plus the exchange through the L2: a build that exchanges through LDS takes 0.255 ms (5.7 TB/s,
 // more than a large copy reaches), and the number of resident workgroups no longer matters (768 / 1024 / 2048: 0.305 /
 // 0.307 / 0.315 ms).  The order of the loads (issue_point below) keeps the rounds from waiting for memory: with the next
-// level's triples asked for ahead of the received words, and those loaded one after the other, the call took 0.342 ms, and
-// a workgroup began each tile with nothing in flight.  The receive
-// buffers have to stay in the L2: with a grid of 2048 workgroups and two buffers per party (33 MB) they were written
+// level's triples asked for ahead of the received words, and those loaded one after the other, the call took 0.342 and
+// 0.328 ms on the same two boxes, and a workgroup began each tile with nothing in flight.  The receive
+// buffers should stay in the L2: with a grid of 2048 workgroups and two buffers per party (33 MB) they were written
 // back to memory (0.64 GB per call) and the call took 5 % longer; with one buffer and a second barrier per round, and 1024
 // workgroups, they are 8 MB, and four lanes converting at once still fit (batch-128 VGG16 on four lanes: 11.7 ms with
-// two buffers, 11.2 ms with one).  The material is read once, hence the non-temporal loads (10 % at the same size).
+// two buffers, 11.2 ms with one).  The sign-only chain gives some of that up (msb_v below).  The material is read once, hence
+// the non-temporal loads (10 % at the same size).
 #include "common.h"
 #include "msb_pack.h"
 #include "relu_steps.h"
@@ -255,10 +256,11 @@ __device__ __forceinline__ Converted<V> convert_words(const FusedReluParty& p, c
     return r;
 }
 
-// Registers: 128 (two parties, prefix network of Kogge and Stone), which leaves the GEMM's wave its room on a SIMD; the
+// Registers: a GEMM wave leaves 136 of a SIMD's.  128 here (two parties, prefix network of Kogge and Stone); the
 // prefix tree needs 131 (held at 128 it spills four: 70 001 / 2 097 152 elements 14.4 / 312.7 us, 13.0 / 306.5 at 131), the copying
 // exchange 135 and 139, the operands of three rounds of three parties 156 (512 workgroups are less than two waves per SIMD
-// either way).
+// either way).  Max-pool of whole words: 136, with the prefix tree 141, three parties 159.  What is wider waits for a unit
+// without a GEMM wave.
 template <int NP, int V, int TOPO, bool COPY>
 __global__ __launch_bounds__(NP * kWave, (NP == 3 || COPY || TOPO) && V == 2 ? 3 : 4) void k_relu_fused(FusedRelu q)
 {
@@ -466,8 +468,10 @@ __device__ __forceinline__ unsigned msb_tiles(const FusedReluParty& p, const Pac
 
 // tiles 0 .. wide-1: 64 V elements each, V per lane; the others 64 elements, one per lane (the last one ragged).  Two
 // parties: four per lane, the rounds and the vector work of the deeper levels shared by twice the elements of two per lane
-// (2 097 152 elements 150 -> 135 us; VGG16 of 32 images on one lane 2.31 -> 2.25 ms, on four lanes, where the 168 registers no
-// longer fit beside the GEMM's, 0.7 % more).  Three parties: two per lane (four 2 % slower).
+// (2 097 152 elements 150 -> 135 us on one box, 143 -> 137 on another; VGG16 of 32 images on one lane 2.31 -> 2.25 ms, on four
+// lanes, where the 168 registers no longer fit beside the GEMM's, 0.7 % more).  A launch writes 121 MiB, of which 32 are
+// results, with two per lane 47: the buffers are 8 MB either way, but rows of four words a lane leave the L2 more often.  Three
+// parties: two per lane (four 2 % slower).
 constexpr int msb_v(int parties) { return parties == 2 ? 4 : 2; }
 constexpr size_t msb_box(int v) { return 2 * kWave * (size_t)v; }      // words: two rows of whole words, or four of level 0
 template <int NP, bool COPY>
@@ -556,8 +560,8 @@ __global__ __launch_bounds__(NP * kWave, PACKED ? 4 : 3) void k_maxpool_fused(Fu
 
 // Workgroups of a launch, [parties - 2]: as many as their receive buffers fit the L2 of their XCD (a three-party
 // workgroup has six of them).  Whole words, 2 097 152 elements: two parties 512 / 1024 / 2048 workgroups 0.315 / 0.307 /
-// 0.315 ms; three parties 320 / 384 workgroups 0.23 / 0.11 ms slower than 512, which take 0.59 ms (2.12 ms as eleven
-// launches).
+// 0.315 ms; three parties 384 / 512 / 640 / 768 / 1024 workgroups 0.707 / 0.592 / 0.680 / 0.624 / 0.639 ms (2.12 ms as eleven
+// launches), 300 000 elements 111 / 95 / 102 / 100 / 104 us.
 // Sign-only: two parties 768 / 1024 / 1280 workgroups 0.144 / 0.141 / 0.145 ms; three parties 768 .. 2048 workgroups level
 // (0.99 ms as eleven launches).
 constexpr unsigned kBlocks[2] = { 1024, 512 }, kMsbBlocks[2] = { 1024, 1536 }, kMsbPoolBlocks[2] = { 2048, 1536 };

@@ -70,7 +70,8 @@ template <int NP, int W> struct Received {
 // The receive buffers of a workgroup, one per ordered pair of parties: party i's buffer s holds what party
 // (i + 1 + s) mod NP sent last.  `box_words` words each.
 // COPY (two parties): a party stores its words into a send buffer of its own, and after the barrier the peer's wave moves
-// them into its receive buffer, using each word as it passes; two buffers per party.
+// them into its receive buffer, using each word as it passes; two buffers per party.  The receive buffer is not read back:
+// its stores are the exchange that the protocol asks for, one more word through the L2 per word sent.
 template <int NP, bool COPY = false>
 struct Wire {
     static_assert(!COPY || NP == 2, "the copying exchange is written for two parties");
