@@ -163,9 +163,12 @@ int mpc_graph_destroy(mpc_graph* graph);
  *   into the peer's receive buffer (what a peer-to-peer store would be between
  *   two devices).  Linear layers: masking, exchange and opening of a call's
  *   operands are one launch where they are stored as they are read (not the
- *   activations of a filter gradient), else the next step starts when the
- *   masking kernel has ended.  Secure ReLU, three-party rescale, max-pool, element-wise products and the backward calls
- *   built on them: all rounds run in one launch; a round ends when the waves of
+ *   activations of a filter gradient, nor up to 2^20 words of activations
+ *   where the right planes are recoded in the call: f_public, a filter read in
+ *   reverse), else the next step starts when the masking kernel has ended.
+ *   Secure ReLU, three-party rescale, max-pool, element-wise products and the
+ *   backward calls built on them: all rounds run in one launch; a round ends
+ *   when the waves of
  *   all parties that hold the same elements have stored their words, and
  *   n_chunks has nothing to cut.  A call whose output overlaps one of its inputs
  *   (other than element for element) runs launch by launch with the copy
@@ -252,8 +255,9 @@ int mpc_conv2d(mpc_ctx* ctx, mpc_cshare x, mpc_cshare w,
  * resident wave per SIMD hides.  Launches whose parties contract different lengths (the folded calls) also take
  * that tile at any contraction length once the output has 768 such tiles.  Outputs of at most 32 rows take it only where
  * they have at most 64 columns, else a tile of 32 x 128.  Contractions of at most 64 K steps with at most 1024 tiles of
- * 32 x 32 (both parties) run with the waves of a workgroup sharing one such tile's contraction.  max_steps = 0 switches
- * that and the small tile off.  MPC_EINVAL for max_steps < 0 or min_tiles < 1. */
+ * 32 x 32 (all parties of the launch together, one, two or three) run with the waves of a workgroup sharing one such tile's
+ * contraction; longer ones of one or two parties with at most 256 of them do where an estimate of both forms' time says so.
+ * max_steps = 0 switches that, at any length, and the small tile off.  MPC_EINVAL for max_steps < 0 or min_tiles < 1. */
 int mpc_set_gemm_small_tile(int max_steps, int min_tiles);
 
 /* Measurement aid for the roofline of the ring GEMM (no step of the protocol): the int8 matrix-core rate the

@@ -307,8 +307,8 @@ __global__ __launch_bounds__(kThreads) void k_recode_im2col_t(Im2colTBatch bt)
 // The same planes for a 3x3 filter of stride 1 and padding 1, whose output pixels are the input's: one thread fills the
 // three units of a filter row (dx = 0, 1, 2) of one (dy, ci), which read the same 16 pixels moved by one: 18 loads instead
 // of 48, at indices Cin words apart (pixel p of the flattened batch reads p + (dy - 1) W + dx - 1; a neighbour inside the
-// image row is the neighbour in the run).  Fourteen launches of a VGG16 training step 418 -> 331 us, the step of 32 images
-// 7.35 -> 7.25 ms.
+// image row is the neighbour in the run).  Fourteen launches of a VGG16 training step of 32 images
+// 418 -> 331 us in all.
 __global__ __launch_bounds__(kThreads) void k_recode_im2col3_t(Im2colTBatch bt)
 {
     const Im2colTArgs& a = bt.a[blockIdx.z];

@@ -591,7 +591,7 @@ LinearWs3 carve3(u8* base, size_t cap, const LinearShape& s)
 // Alg. 1 / Eq. 3 with three parties, everything on the lane's first stream:
 // mask, broadcast to both peers, open e and f, recode, then the two-segment
 // contraction [e | a_i] x [b_i (+ f for party 0) ; f] for parties 0 and 1 in
-// one launch and for party 2 in a second one.
+// one launch and for party 2 in a second one (few tiles: all in one).
 int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 y,
                    mpc_cshare3 a, mpc_cshare3 b, mpc_cshare3 cc, mpc_share3 z, const u64* f_public, size_t ws_off = 0,
                    const u8* prep_right = nullptr, const u8* prep_left = nullptr)
@@ -640,47 +640,46 @@ int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 
             MPC_TRY(launch_recode_multi(c, st, rr, 4));
         }
     } else {
-    // Alg. 1: every party masks its shares ...
-    SubSeg sub[6]; int ns = 0;
-    for (int i = 0; i < 3; ++i) sub[ns++] = SubSeg{ x.p[i], a.p[i], w.se[i], s.nx, 0, nullptr };
-    for (int i = 0; i < 3 && !have_f; ++i) sub[ns++] = SubSeg{ y.p[i], b.p[i], w.sf[i], s.nw, 0, nullptr };
-    MPC_TRY(launch_sub_multi(c, st, sub, ns));
-    // ... and broadcasts them: party i receives from party i+1 and party i+2
-    CopySeg cp[6];
-    for (int i = 0; i < 3; ++i)
-        for (int k = 0; k < 2; ++k)
-            cp[2 * i + k] = CopySeg{ (const u8*)w.se[(i + 1 + k) % 3], (u8*)w.re[i][k], s.nx * sizeof(u64), 0 };
-    MPC_TRY(launch_copy_multi(c, st, cp, 6));
-    if (!have_f) {
+        // Alg. 1: every party masks its shares ...
+        SubSeg sub[6]; int ns = 0;
+        for (int i = 0; i < 3; ++i) sub[ns++] = SubSeg{ x.p[i], a.p[i], w.se[i], s.nx, 0, nullptr };
+        for (int i = 0; i < 3 && !have_f; ++i) sub[ns++] = SubSeg{ y.p[i], b.p[i], w.sf[i], s.nw, 0, nullptr };
+        MPC_TRY(launch_sub_multi(c, st, sub, ns));
+        // ... and broadcasts them: party i receives from party i+1 and party i+2
+        CopySeg cp[6];
         for (int i = 0; i < 3; ++i)
             for (int k = 0; k < 2; ++k)
-                cp[2 * i + k] = CopySeg{ (const u8*)w.sf[(i + 1 + k) % 3], (u8*)w.rf[i][k], s.nw * sizeof(u64), 0 };
+                cp[2 * i + k] = CopySeg{ (const u8*)w.se[(i + 1 + k) % 3], (u8*)w.re[i][k], s.nx * sizeof(u64), 0 };
         MPC_TRY(launch_copy_multi(c, st, cp, 6));
-    }
-    // Delta and epsilon (all parties hold the same three words; formed once, from party 0's buffers)
-    MPC_TRY(launch_sum3(c, st, w.se[0], w.re[0][0], w.re[0][1], w.e_pub, s.nx));
-    const u64* f = f_public;
-    if (!have_f) { MPC_TRY(launch_sum3(c, st, w.sf[0], w.rf[0][0], w.rf[0][1], w.f_pub, s.nw)); f = w.f_pub; }
-
-    // digit planes
-    {
-        if (!skip_left) {
-            const u64* src[3] = { a.p[0], a.p[1], a.p[2] };
-            const u64* none[3] = { nullptr, nullptr, nullptr };
-            u8* dst[3] = { w.pl_a[0], w.pl_a[1], w.pl_a[2] };
-            MPC_TRY(launch_left(c, st, s, 3, src, none, dst));
+        if (!have_f) {
+            for (int i = 0; i < 3; ++i)
+                for (int k = 0; k < 2; ++k)
+                    cp[2 * i + k] = CopySeg{ (const u8*)w.sf[(i + 1 + k) % 3], (u8*)w.rf[i][k], s.nw * sizeof(u64), 0 };
+            MPC_TRY(launch_copy_multi(c, st, cp, 6));
         }
-        MPC_TRY(launch_left1(c, st, s, w.e_pub, nullptr, w.pl_e));
-        if (!skip_right) {
-            RecodeArgs rr[4];
-            rr[0] = recode_right(s, b.p[1], nullptr, nullptr, w.pr_b[1]);
-            rr[1] = recode_right(s, b.p[2], nullptr, nullptr, w.pr_b[2]);
-            rr[2] = recode_right(s, f, nullptr, nullptr, w.pr_f);
-            rr[3] = recode_right(s, b.p[0], f, nullptr, w.pr_b[0]);
-            MPC_TRY(launch_recode_multi(c, st, rr, 4));
-        }
-    }
+        // Delta and epsilon (all parties hold the same three words; formed once, from party 0's buffers)
+        MPC_TRY(launch_sum3(c, st, w.se[0], w.re[0][0], w.re[0][1], w.e_pub, s.nx));
+        const u64* f = f_public;
+        if (!have_f) { MPC_TRY(launch_sum3(c, st, w.sf[0], w.rf[0][0], w.rf[0][1], w.f_pub, s.nw)); f = w.f_pub; }
 
+        // digit planes
+        {
+            if (!skip_left) {
+                const u64* src[3] = { a.p[0], a.p[1], a.p[2] };
+                const u64* none[3] = { nullptr, nullptr, nullptr };
+                u8* dst[3] = { w.pl_a[0], w.pl_a[1], w.pl_a[2] };
+                MPC_TRY(launch_left(c, st, s, 3, src, none, dst));
+            }
+            MPC_TRY(launch_left1(c, st, s, w.e_pub, nullptr, w.pl_e));
+            if (!skip_right) {
+                RecodeArgs rr[4];
+                rr[0] = recode_right(s, b.p[1], nullptr, nullptr, w.pr_b[1]);
+                rr[1] = recode_right(s, b.p[2], nullptr, nullptr, w.pr_b[2]);
+                rr[2] = recode_right(s, f, nullptr, nullptr, w.pr_f);
+                rr[3] = recode_right(s, b.p[0], f, nullptr, w.pr_b[0]);
+                MPC_TRY(launch_recode_multi(c, st, rr, 4));
+            }
+        }
     }
 
     GemmArgs g{};

@@ -5,9 +5,10 @@
 // every share and mask is read once and every plane written once, six traversals of the operand, and the receive buffers
 // stay in the L2.  As three launches (mask and send, open and recode, recode) there were eleven; 32 x 56 x 56 x 64
 // words took 104 us in all, here 77 (4.0 TB/s).  Calls, same box, three launches / one: per-head Q K^T 342 / 305 us, A V 636 / 465,
-// 1x1 convolution of 64 to 256 channels 362 / 334, 3x3 of 128 channels 233 / 222, 8 products of 64 x 64 x 64 27.4 / 19.0.
+// 1x1 convolution of 64 to 256 channels 362 / 334, 3x3 of 128 channels 233 / 222 (on another box, with all else that changed
+// meanwhile, 328 / 296, 346 / 313 and 221 / 218: the last is bound by its GEMM), 8 products of 64 x 64 x 64 27.4 / 19.0.
 // Plain calls write the planes of the masks from the same pass, seven traversals instead of twelve (left) and seventeen
-// (right operand): VGG16 training step of 32 images 7.61 / 7.51 ms.
+// (right operand).
 // Three parties: an operand's masks, broadcast, sum and recoding were four launches and 84 us for 64 x 16 x 16 x 128 words,
 // 47 here.
 // Non-temporal loads lose (3x3: 235 us): the operand was often written just before and is in the last-level cache.
@@ -29,8 +30,9 @@ constexpr int tile_rows(int KBT) { return 128 / KBT; }
 constexpr int block_pitch(int KBT) { return tile_rows(KBT) * 4 + 64 / KBT; }
 constexpr int kTileWords = 8 * (512 + 64);
 int tile_blocks(int KB_total) { return KB_total > 2 ? 4 : KB_total; }
-// Workgroups of a launch, as many as are resident at once: two parties three to a compute unit (167 registers; held at 128
+// Workgroups of a launch, as many as are resident at once: two parties three to a compute unit (168 registers; held at 128
 // for a fourth they are spilled, and the 3x3 convolution takes 228 us), two in plain calls (228); three parties two and one.
+// None fits beside a GEMM wave's 376 on a SIMD: another lane's opening waits for the GEMM's units.
 // 512 / 768 / 1024 workgroups of folded calls: level within 1-2 %.
 constexpr unsigned max_blocks(int parties, OpenPlanes planes)
 {
