@@ -334,7 +334,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             return nar.end();
         }
         // Plain calls with the exchange by remote store open what they open in one launch, planes of the masks with it.
-        // (A filter read in reverse tap order, or operands of less than half a tile, take the steps below.)
+        // (A filter read in reverse tap order, and a workspace without one receive buffer, take the steps below.)
         const bool one_launch = put && !folded && box_bytes >= open_box_bytes(2) && !(two_phase && have_f);
         const bool open_right = one_launch && !have_f && !s.wflip;
         // Where right planes are recoded in a launch of their own all the same (f public, a filter in reverse tap order), the
@@ -624,8 +624,8 @@ int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 
     const int pi = prof_begin(c, MPC_PROF_LINEAR, st);
 
     // Exchange by remote store: what opens, opens in one launch (open_recode.hip), with the planes of the masks that are not
-    // prepared.  (Not where the planes are a transposed im2col, a filter is read in reverse tap order, or there is less than
-    // half a tile.)
+    // prepared.  (Not where the planes are a transposed im2col, a filter is read in reverse tap order, or the workspace has no
+    // receive buffer.)
     const size_t box_bytes = (size_t)(w.pl_e - reinterpret_cast<u8*>(w.se[0]));
     const bool open_right = !have_f;
     if (c->exchange_put && box_bytes >= open_box_bytes(3) && !s.im2colT && !(open_right && s.wflip)) {
