@@ -876,6 +876,12 @@ static int sliced_waves(const Tuning& tune, const GemmArgs& g, int longest, cons
     // a lane's offset inside a plane is 32 bits wide
     if ((g.conv.enabled ? (g.conv.npix + 1) * g.conv.CB : (long long)longest * KS * g.rows_L) * 16 >= (1ll << 31)) return 0;
     if ((long long)longest * KS * g.N * 16 >= (1ll << 31)) return 0;
+    // Few rows and a handful of steps: the 32 x 128 tiles in one round, where this form has two (two workgroups of four waves to
+    // a compute unit).  The launch, us, those tiles / four waves: 57 products of 8 x 8 x 240 9.6 / 12.2, 21 of 1 x 21 x 595
+    // 9.5 / 11.9, 102 of 12 x 66 x 111 (6 steps) 13.0 / 14.8; from 8 steps on this form is level or ahead (21 of 28 x 97 x 432
+    // 0.88-0.93 of the tiles' time).
+    if (g.nparty <= 2 && g.M <= 32 && g.N > 64 && longest <= 6 && blocks > 2 * kSlicedWideBlocks &&
+        (long long)((g.N + 127) / 128) * g.batch * g.nparty <= 256) return 0;
     if (longest <= kSlicedMaxSteps) return blocks <= kSlicedWideBlocks ? 8 : 4;
     if (blocks > kSlicedWideBlocks || g.nparty > 2) return 0;
     auto blocks_of = [&](int per, long long t) {

@@ -17,10 +17,10 @@ assert lib.mpc_ctx_set_exchange(ctx, 1) == 0
 big = array(1 << 38)
 share = lambda: Share((c_void_p * 2)(big, big + (1 << 37)))
 
-def product(M, K, N, flags=1):
-    ws = lib.mpc_matmul_workspace_bytes(M, K, N, 1)
+def product(M, K, N, batch=1, flags=1):
+    ws = lib.mpc_matmul_workspace_bytes(M, K, N, batch)
     assert lib.mpc_ctx_set_workspace(ctx, array(ws), ws) == 0
-    assert lib.mpc_beaver_matmul_prepared(ctx, share(), share(), share(), share(), big, big, M, K, N, 1, 1, flags) == 0
+    assert lib.mpc_beaver_matmul_prepared(ctx, share(), share(), share(), share(), big, big, M, K, N, batch, 1, flags) == 0
     return [n for n in launches() if "gemm" in n]
 
 def convolution(B, HW, Cin, Cout, k, stride):
@@ -54,6 +54,21 @@ result["conv"] = convolution(34, 6, 368, 276, 3, 2)
 ''')
     for what, names in r.items():
         assert not sliced(names), (what, names)
+
+
+def test_few_rows_and_few_steps(run):
+    """More than 512 tiles of 32 x 32 of both parties and at most 6 steps: the 32 x 128 tiles, unless they need a second round
+    or are half empty."""
+    tiles = ((8, 8, 240, 57), (1, 21, 595, 21), (12, 66, 111, 102))
+    shared = ((8, 8, 240, 30), (8, 150, 240, 57), (8, 8, 64, 200), (8, 8, 129, 100), (40, 8, 240, 30), (33, 8, 140, 50))
+    r = run(f'''
+for s in {tiles + shared}:
+    result[str(s)] = product(*s)
+''')
+    for s in tiles:
+        assert not sliced(r[str(s)]), s
+    for s in shared:
+        assert sliced(r[str(s)]), (s, r[str(s)])
 
 
 def test_long_contractions_shared(run):
