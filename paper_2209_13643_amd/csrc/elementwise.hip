@@ -672,7 +672,13 @@ int launch_recode_im2col_t(mpc_ctx* c, hipStream_t st, const Im2colTArgs* sets, 
     Im2colTBatch bt{};
     for (int i = 0; i < count; ++i) bt.a[i] = sets[i];
     const Im2colTArgs& s = sets[0];          // the sets of a launch have one geometry
-    const bool rows_of_three = s.KH == 3 && s.KW == 3 && s.stride == 1 && s.pad == 1 && (long long)s.B * s.H * s.W + 2ll * s.W + 32 < (1ll << 31);
+    // Three units a thread: its wave stores Cin units side by side, which fill a cache line from 8 channels on.  With fewer the
+    // lines are written in parts, which the caches make up for while the planes are small; filter gradients, us, one unit a
+    // thread / three: 8 x 32 x 32 x 1 36.2 / 37.6, 32 x 32 x 32 x 3 58.4 / 57.8, 8 x 112 x 112 x 3 114 / 124, 8 x 224 x 224 x 3 461 / 538,
+    // 32 x 64 x 64 x 4 141 / 142, 8 x 224 x 224 x 4 508 / 538, 8 x 224 x 224 x 8 622 / 613.
+    const long long npix = (long long)s.B * s.H * s.W;
+    const bool rows_of_three = s.KH == 3 && s.KW == 3 && s.stride == 1 && s.pad == 1 && npix + 2ll * s.W + 32 < (1ll << 31) &&
+                               (s.Cin >= 8 || (s.Cin > 1 && npix <= 16384ll * s.Cin));
     const size_t items = (size_t)s.KB_total * s.KH * s.Cin * (rows_of_three ? 1 : s.KW);
     if (rows_of_three) hipLaunchKernelGGL(k_recode_im2col3_t, dim3(grid_for(items), 1, count), dim3(kThreads), 0, st, bt);
     else               hipLaunchKernelGGL(k_recode_im2col_t, dim3(grid_for(items), 1, count), dim3(kThreads), 0, st, bt);

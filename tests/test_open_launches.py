@@ -1,5 +1,5 @@
-"""The launch that opens a linear layer's operands under the exchange by remote store, on the CPU: the built library's host
-side on a stand-in for the HIP runtime."""
+"""The launches that open and recode a linear layer's operands under the exchange by remote store, on the CPU: the built
+library's host side on a stand-in for the HIP runtime."""
 import pytest
 
 import fake_hip
@@ -103,3 +103,21 @@ for B in (2, 65):
         rc, names = r[str(B)]
         assert rc == 0
         assert any("k_open_recode" in n for n in names) == (B * 16 * 16 * 64 > 1 << 20), names
+
+
+def test_im2col_of_few_channels(run):
+    """Filter gradients of 3x3 filters: three units a thread from 8 channels on, with two to seven while the planes are small."""
+    r = run('''
+lib.mpc_conv2d_grad_w_workspace_bytes.restype = c_size_t; lib.mpc_conv2d_grad_w_workspace_bytes.argtypes = [c_int] * 9
+lib.mpc_conv2d_grad_w.argtypes = [c_void_p] + [Share] * 6 + [c_int] * 9 + [c_void_p, c_int, c_int]
+for B, HW, Cin in ((8, 32, 1), (32, 32, 2), (33, 32, 2), (32, 32, 3), (8, 112, 3), (8, 224, 7), (8, 224, 8), (1, 4, 200)):
+    g = (B, HW, HW, Cin, 16, 3, 3, 1, 1)
+    ws = lib.mpc_conv2d_grad_w_workspace_bytes(*g)
+    assert lib.mpc_ctx_set_workspace(ctx, array(ws), ws) == 0
+    rc = lib.mpc_conv2d_grad_w(ctx, *[share() for _ in range(6)], *g, None, 1, 1)
+    names = launches()
+    result["%d %d %d" % (B, HW, Cin)] = rc, sum("k_recode_im2col3_t" in n for n in names), sum("k_recode_im2col_t" in n for n in names)
+''')
+    three = {"8 32 1": 0, "32 32 2": 1, "33 32 2": 0, "32 32 3": 1, "8 112 3": 0, "8 224 7": 0, "8 224 8": 1, "1 4 200": 1}
+    for k, (rc, with_three, with_one) in r.items():
+        assert rc == 0 and (with_three, with_one) == (three[k], 1 - three[k]), (k, rc, with_three, with_one)
