@@ -101,9 +101,8 @@ struct LinearWs {
 // alone would leave the tiles of such a call to run one after the other (1 x 64 x 10: five tiles in one workgroup, 17 us).
 size_t open_room(const LinearShape& s, int parties)
 {
-    if (s.im2colT) return 0;
     const size_t most = open_most_blocks(parties);
-    const size_t tiles = open_most_tiles(s.rowsL, s.KB_L, s.batch) + open_most_tiles(s.N, s.KB, s.batch);
+    const size_t tiles = (s.im2colT ? 0 : open_most_tiles(s.rowsL, s.KB_L, s.batch)) + open_most_tiles(s.N, s.KB, s.batch);
     return (tiles < most ? tiles : most) * open_box_bytes(parties);
 }
 

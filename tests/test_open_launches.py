@@ -121,3 +121,20 @@ for B, HW, Cin in ((8, 32, 1), (32, 32, 2), (33, 32, 2), (32, 32, 3), (8, 112, 3
     three = {"8 32 1": 0, "32 32 2": 1, "33 32 2": 0, "32 32 3": 1, "8 112 3": 0, "8 224 7": 0, "8 224 8": 1, "1 4 200": 1}
     for k, (rc, with_three, with_one) in r.items():
         assert rc == 0 and (with_three, with_one) == (three[k], 1 - three[k]), (k, rc, with_three, with_one)
+
+
+def test_every_tile_of_a_filter_gradients_right_operand_has_a_workgroup(run):
+    """The output gradient alone opens in the launch: [B Ho Wo][Cout] words, a k block of 16 pixels a tile."""
+    r = run('''
+lib.mpc_conv2d_grad_w_workspace_bytes.restype = c_size_t; lib.mpc_conv2d_grad_w_workspace_bytes.argtypes = [c_int] * 9
+lib.mpc_conv2d_grad_w.argtypes = [c_void_p] + [Share] * 6 + [c_int] * 9 + [c_void_p, c_int, c_int]
+for HW, Cin in ((32, 1), (24, 2), (10, 1)):
+    g = (1, HW, HW, Cin, 8, 3, 3, 1, 1)
+    ws = lib.mpc_conv2d_grad_w_workspace_bytes(*g)
+    assert lib.mpc_ctx_set_workspace(ctx, array(ws), ws) == 0
+    assert lib.mpc_conv2d_grad_w(ctx, *[share() for _ in range(6)], *g, None, 1, 1) == 0
+    result[HW] = [int(n.split("@")[1]) for n in launches() if "k_open_recode" in n]
+''')
+    for HW, blocks in r.items():
+        kb = -(-int(HW) ** 2 // 16)
+        assert blocks == [kb + kb % 2], (HW, blocks)
