@@ -204,8 +204,13 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g)
     const long long krowR = (long long)g.N * 16;
 
     // ---- per-lane constant byte offsets
-    // conv: pixel index of filter tap (0,0), biased so that it is never negative
-    const int bias = CONV ? g.conv.pad * g.conv.W + g.conv.pad : 0;
+    // conv: pixel index of filter tap (0,0), biased so that it is never negative, nor the zero row's distance from any tap's
+    // base (a filter higher than the whole batch: 5x5 on three images of 1 x 1; the last tap here is the one past the end)
+    int bias = CONV ? g.conv.pad * g.conv.W + g.conv.pad : 0;
+    if (CONV && g.conv.npix < (long long)g.conv.KH * g.conv.W + g.conv.KW) {
+        const int need = g.conv.KH * g.conv.W + g.conv.KW - (int)g.conv.npix;
+        bias = bias > need ? bias : need;
+    }
     unsigned voffL[C::RCM];
     unsigned long long lvalid[C::RCM];      // conv: bit per filter tap that hits the image
 #pragma unroll

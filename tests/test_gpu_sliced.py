@@ -64,6 +64,7 @@ def test_products(mpc, lane, M, K, N, batch):
 @pytest.mark.parametrize("B,H,W,Cin,Cout,k,pad,stride", [
     (1, 4, 4, 3, 20, 3, 1, 1), (2, 5, 7, 17, 33, 3, 1, 1), (1, 9, 9, 40, 64, 3, 0, 2), (2, 6, 6, 33, 40, 1, 0, 2), (3, 4, 4, 48, 96, 3, 1, 1),
     (1, 6, 5, 16, 32, 5, 2, 1), (8, 12, 12, 20, 130, 3, 1, 1), (2, 4, 4, 200, 40, 3, 1, 1), (1, 5, 5, 500, 33, 3, 1, 2),
+    (3, 1, 1, 17, 1, 5, 2, 2), (1, 1, 5, 40, 33, 3, 1, 1), (1, 1, 1, 33, 20, 3, 1, 1), (2, 1, 1, 20, 70, 7, 3, 1), (1, 2, 1, 5, 9, 7, 3, 1), (1, 3, 2, 18, 40, 7, 3, 2),
 ])
 def test_convolutions(mpc, lane, B, H, W, Cin, Cout, k, pad, stride):
     print(f"sliced conv {B}x{H}x{W}x{Cin}->{Cout} k{k} s{stride}", flush=True)
