@@ -316,12 +316,12 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
         g.nparty = 2;
         // receive buffers of the one-launch opening: the parts of the workspace ahead of the planes
         const size_t box_bytes = (size_t)(w.pl_e - reinterpret_cast<u8*>(w.se[0]));
-        if (folded && put && !s.im2colT && box_bytes >= open_box_bytes(2)) {
+        OpenSet open[2] = { open_set(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_a[0], w.pl_e), OpenSet{} };
+        if (right_online) open[1] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_b[0], w.pr_f);
+        if (folded && put && !s.im2colT && box_bytes >= open_box_bytes(2) && open_pays(2, OpenPlanes::kFolded, open, right_online ? 2 : 1)) {
             // Folded call with the exchange by remote store, in one launch (open_recode.hip): both parties mask and send
             // e_i = x_i - a_i, then party 0 recodes a_0 + e = x_0 + e_1 and party 1 the opened e.  A product of two
             // activations opens f in the same launch: f_i = y_i - b_i, b_0 + f = y_0 + f_1, f.
-            OpenSet open[2] = { open_set(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_a[0], w.pl_e), OpenSet{} };
-            if (right_online) open[1] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_b[0], w.pr_f);
             MPC_TRY(launch_open_recode(c, P0, 2, OpenPlanes::kFolded, open, right_online ? 2 : 1, reinterpret_cast<u8*>(w.se[0]), box_bytes));
             g.nseg = 2;
             g.seg[0][0] = make_seg(s, w.pl_a[0], w.pr_b[0]); g.seg[0][1] = GemmSeg{};
@@ -333,7 +333,8 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             return nar.end();
         }
         // Plain calls with the exchange by remote store open what they open in one launch, planes of the masks with it.
-        // (A filter read in reverse tap order, and a workspace without one receive buffer, take the steps below.)
+        // (A filter read in reverse tap order, a workspace without one receive buffer, and operands that fill few of
+        // their tiles take the steps below.)
         const bool one_launch = put && !folded && box_bytes >= open_box_bytes(2) && !(two_phase && have_f);
         const bool open_right = one_launch && !have_f && !s.wflip;
         // Where right planes are recoded in a launch of their own all the same (f public, a filter in reverse tap order), the
@@ -353,6 +354,7 @@ int beaver_linear(mpc_ctx* c, const LinearShape& s, mpc_cshare x, mpc_cshare y,
             opens[n_open++] = open_set(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_f, nullptr, w.pr_b[0], w.pr_b[1], true);
             right_done = true;
         }
+        if (n_open && !open_pays(2, OpenPlanes::kMasks, opens, n_open)) { n_open = 0; left_done = right_done = false; }
         if (n_open) MPC_TRY(launch_open_recode(c, P0, 2, OpenPlanes::kMasks, opens, n_open, reinterpret_cast<u8*>(w.se[0]), box_bytes));
         if ((size_t)n_chunks > s.nx) n_chunks = (int)s.nx;
         bool f_pending = !have_f && !right_done;             // the weight mask rides with the first launch issued
@@ -623,16 +625,16 @@ int beaver_linear3(mpc_ctx* c, const LinearShape& s, mpc_cshare3 x, mpc_cshare3 
     const int pi = prof_begin(c, MPC_PROF_LINEAR, st);
 
     // Exchange by remote store: what opens, opens in one launch (open_recode.hip), with the planes of the masks that are not
-    // prepared.  (Not where the planes are a transposed im2col, a filter is read in reverse tap order, or the workspace has no
-    // receive buffer.)
+    // prepared.  (Not where the planes are a transposed im2col, a filter is read in reverse tap order, the workspace has no
+    // receive buffer, or the operands fill few of their tiles.)
     const size_t box_bytes = (size_t)(w.pl_e - reinterpret_cast<u8*>(w.se[0]));
     const bool open_right = !have_f;
-    if (c->exchange_put && box_bytes >= open_box_bytes(3) && !s.im2colT && !(open_right && s.wflip)) {
-        const bool masks = !skip_left || open_right;
-        OpenSet open[2] = { open_set3(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_e, skip_left ? nullptr : w.pl_a), OpenSet{} };
-        if (open_right) open[1] = open_set3(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_f, w.pr_b, true);
-        MPC_TRY(launch_open_recode(c, st, 3, masks ? OpenPlanes::kMasks : OpenPlanes::kOpened, open, open_right ? 2 : 1,
-                                   reinterpret_cast<u8*>(w.se[0]), box_bytes));
+    const OpenPlanes planes = !skip_left || open_right ? OpenPlanes::kMasks : OpenPlanes::kOpened;
+    OpenSet open[2] = { open_set3(recode_left(s, nullptr, nullptr, nullptr), x, a, w.pl_e, skip_left ? nullptr : w.pl_a), OpenSet{} };
+    if (open_right) open[1] = open_set3(recode_right(s, nullptr, nullptr, nullptr, nullptr), y, b, w.pr_f, w.pr_b, true);
+    if (c->exchange_put && box_bytes >= open_box_bytes(3) && !s.im2colT && !(open_right && s.wflip) &&
+        open_pays(3, planes, open, open_right ? 2 : 1)) {
+        MPC_TRY(launch_open_recode(c, st, 3, planes, open, open_right ? 2 : 1, reinterpret_cast<u8*>(w.se[0]), box_bytes));
         if (!skip_right && f_public) {
             RecodeArgs rr[4] = { recode_right(s, b.p[1], nullptr, nullptr, w.pr_b[1]), recode_right(s, b.p[2], nullptr, nullptr, w.pr_b[2]),
                                  recode_right(s, f_public, nullptr, nullptr, w.pr_f), recode_right(s, b.p[0], f_public, nullptr, w.pr_b[0]) };

@@ -26,4 +26,6 @@ size_t open_most_tiles(int plane_rows, int KB_total, int batch);
 size_t open_most_blocks(int parties);
 // several taps only with contiguous rows
 inline bool can_open(const OpenSet& s) { return s.row_stride == 1 || (s.k_stride == 1 && s.ntaps == 1); }
+// whether the launch pays for these operands (their tiles may hold few words)
+bool open_pays(int parties, OpenPlanes planes, const OpenSet* sets, int count);
 int launch_open_recode(mpc_ctx* c, hipStream_t st, int parties, OpenPlanes planes, const OpenSet* sets, int count, u8* box, size_t box_bytes);

@@ -248,7 +248,39 @@ void launch(hipStream_t st, const OpenBatch& g, size_t box_bytes)
     hipLaunchKernelGGL((k_open_recode<NP, PLANES>), dim3((unsigned)blocks), dim3(NP * kPartyThreads), 0, st, g);
 }
 
+// tiles of a set; fills kbt, gx and gy
+unsigned long long lay_tiles(OpenSet& s)
+{
+    s.kbt = s.k_stride == 1 && s.ntaps == 1 ? tile_blocks(s.KB_total) : 0;
+    const int high = s.kbt ? tile_rows(s.kbt) : kPartyThreads, wide = s.kbt ? s.kbt : 1;
+    s.gx = (unsigned)((s.plane_rows + high - 1) / high);
+    s.gy = (unsigned)((s.KB_total + wide - 1) / wide);
+    return (unsigned long long)s.gx * s.gy * s.batch;
+}
+
 }  // namespace
+
+// A tile takes its time however few of its 2048 words there are, and a launch with more tiles than workgroups takes them in
+// rounds, where the kernels it replaces have threads for the words that exist.  Two parties lose with long operands of few
+// contiguous rows ([K][N] with few columns, [K][M] with few rows); tiles across k of narrow operands stay ahead (3x3
+// convolutions of 1 to 3 channels 0.94-0.96 of the other kernels' time).  Three parties lose with either, in plain calls, whose
+// other launches are more, only after many rounds.  Calls, us, this launch / separate kernels: 3 x 20000 x 4 twice 49.3 / 36.2,
+// the same transposed 62.2 / 31.6, folded 47.6 / 34.7, 17 x 3000 x 8 sixteen times 53.8 / 43.4; three parties, prepared, 3000 x 2 x 40
+// sixteen times 65.5 / 54.0, plain 71.8 / 74.0, 3 x 3000 x 4 sixteen times 95.4 / 63.0.  From a sixth of the words on they are level.
+bool open_pays(int parties, OpenPlanes planes, const OpenSet* sets, int count)
+{
+    unsigned long long tiles = 0, words = 0, col_tiles = 0, col_words = 0;
+    for (int i = 0; i < count; ++i) {
+        OpenSet s = sets[i];
+        const unsigned long long t = lay_tiles(s), w = (unsigned long long)s.rows * s.K * s.ntaps * s.batch;
+        tiles += t; words += w;
+        if (!s.kbt) { col_tiles += t; col_words += w; }
+    }
+    const unsigned blocks = max_blocks(parties, planes);
+    if (tiles <= blocks) return true;
+    if (parties == 2) return col_tiles * 2 < tiles || col_words * 6 >= col_tiles * 2048;
+    return words * 6 >= tiles * 2048 || (planes == OpenPlanes::kMasks && tiles <= 8ull * blocks);
+}
 
 size_t open_most_tiles(int plane_rows, int KB_total, int batch)
 {
@@ -273,12 +305,8 @@ int launch_open_recode(mpc_ctx* c, hipStream_t st, int parties, OpenPlanes plane
         s = sets[i];
         if (s.rows < 1 || s.K < 1 || s.batch < 1 || s.plane_rows < s.rows || (long long)s.KB_total * 16 < s.K) return MPC_EINVAL;
         if (!can_open(s) || s.ntaps < 1 || s.KB_tap < 1) return MPC_EINVAL;
-        s.kbt = s.k_stride == 1 && s.ntaps == 1 ? tile_blocks(s.KB_total) : 0;
-        const int high = s.kbt ? tile_rows(s.kbt) : kPartyThreads, wide = s.kbt ? s.kbt : 1;
-        s.gx = (unsigned)((s.plane_rows + high - 1) / high);
-        s.gy = (unsigned)((s.KB_total + wide - 1) / wide);
         s.first = (unsigned)tiles;
-        tiles += (unsigned long long)s.gx * s.gy * s.batch;
+        tiles += lay_tiles(s);
         if (tiles >= (1ull << 31)) return MPC_EINVAL;
     }
     g.count = count; g.tiles = (unsigned)tiles; g.box = box;

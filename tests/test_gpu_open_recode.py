@@ -53,6 +53,7 @@ def same(mpc, lane, got, want, what):
     (16, 65, 40, None), (17, 64, 33, None), (31, 66, 129, None), (32, 128, 16, None), (33, 130, 128, None), (49, 63, 20, None),
     (64, 32, 65, None), (65, 17, 63, None), (129, 33, 5, None), (128, 16, 64, None), (130, 15, 50, None), (300, 3, 200, None),
     (2, 2000, 30, None), (20, 70, 24, 5), (3, 200, 129, 4), (24640, 64, 1, None), (5, 7, 1500, 3),
+    (3, 9000, 4, None), (17, 3000, 8, 5), (3, 13000, 7, None),
 ])
 def test_products(mpc, lane, M, K, N, batch):
     """Both operands opened by the call, and the left one alone; folded, and plain with the masks' planes."""
@@ -106,7 +107,7 @@ def test_convolutions(mpc, lane, B, H, W, Cin, Cout, k):
     same(mpc, lane, lane.conv2d(x, w, a, b, c, k // 2, 1), oracle_conv(d, 16), "conv, plain")      # opens the filter too
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 700, 40), (17, 64, 33), (33, 130, 128), (65, 17, 63), (129, 33, 70), (300, 3, 200), (64, 1300, 40), (1000, 300, 5)])
+@pytest.mark.parametrize("M,K,N", [(1, 700, 40), (17, 64, 33), (33, 130, 128), (65, 17, 63), (129, 33, 70), (300, 3, 200), (64, 1300, 40), (1000, 300, 5), (70000, 1, 3), (3, 40000, 4)])
 def test_three_parties(mpc, lane, M, K, N):
     """Masks' planes of all parties (plain), the opened words alone (prepared), the weight mask opened ahead."""
     import oracle

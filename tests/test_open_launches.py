@@ -138,3 +138,19 @@ for HW, Cin in ((32, 1), (24, 2), (10, 1)):
     for HW, blocks in r.items():
         kb = -(-int(HW) ** 2 // 16)
         assert blocks == [kb + kb % 2], (HW, blocks)
+
+
+def test_operands_that_fill_few_of_their_tiles(run):
+    """With more tiles than workgroups: long operands of few contiguous rows are opened by the separate kernels, others in one
+    launch; three parties plain only after many rounds."""
+    two = {(3, 9000, 4, 1): False, (3, 8000, 4, 1): False, (17, 3000, 8, 16): False, (3, 9000, 40, 1): True, (3, 4000, 4, 1): True,
+           (3000, 2, 40, 16): True, (300, 3000, 300, 1): True}
+    three = {(3, 40000, 4, 1): False, (3, 9000, 4, 1): True, (3000, 2, 40, 16): True, (3, 300, 4, 1): True}
+    r = run(f'''
+for s in {list(two)}: result["2 " + str(s)] = product(2, query(2, *s), *s)
+for s in {list(three)}: result["3 " + str(s)] = product(3, query(3, *s), *s)
+''')
+    for n, cases in (("2 ", two), ("3 ", three)):
+        for s, one in cases.items():
+            rc, names, blocks = r[n + str(s)]
+            assert rc == 0 and (blocks > 0) == one, (n, s, names)
