@@ -165,7 +165,7 @@ int mpc_graph_destroy(mpc_graph* graph);
  *   operands are one launch where they are stored as they are read (not the
  *   activations of a filter gradient, nor up to 2^20 words of activations
  *   where the right planes are recoded in the call: f_public, a filter read in
- *   reverse), else the next step starts when the masking kernel has ended.
+ *   reverse; nor long operands of few contiguous rows), else the next step starts when the masking kernel has ended.
  *   Secure ReLU, three-party rescale, max-pool, element-wise products and the
  *   backward calls built on them: all rounds run in one launch; a round ends
  *   when the waves of
@@ -256,7 +256,7 @@ int mpc_conv2d(mpc_ctx* ctx, mpc_cshare x, mpc_cshare w,
  * that tile at any contraction length once the output has 768 such tiles.  Outputs of at most 32 rows take it only where
  * they have at most 64 columns, else a tile of 32 x 128.  Contractions of at most 64 K steps with at most 1024 tiles of
  * 32 x 32 (all parties of the launch together, one, two or three) run with the waves of a workgroup sharing one such tile's
- * contraction; longer ones of one or two parties with at most 256 of them do where an estimate of both forms' time says so.
+ * contraction (not a handful of steps of at most 32 rows with more than 512 of them); longer ones of one or two parties with at most 256 of them do where an estimate of both forms' time says so.
  * max_steps = 0 switches that, at any length, and the small tile off.  MPC_EINVAL for max_steps < 0 or min_tiles < 1. */
 int mpc_set_gemm_small_tile(int max_steps, int min_tiles);
 
